@@ -119,10 +119,9 @@ struct Workspace {
     // five-read baseline: evaluation tables (53 bytes per tile)
     uint8_t *d_naive = nullptr;
     uint64_t naive_cap = 0;
-    // whole-field decodes: chunk offsets of the pre-pass and its outcome word
+    // whole-field decodes: group totals and chunk offsets of the pre-pass
     unsigned long long *d_offs = nullptr;
     uint64_t offs_cap = 0;
-    uint32_t *d_go = nullptr;
 };
 
 std::mutex g_mu;
@@ -151,7 +150,6 @@ Workspace *get_workspace(hipStream_t s, fsz_status *st)
                 ok(hipMalloc(&ws->d_stats, sizeof(fsz_stats))) &&
                 ok(hipMalloc(&ws->d_partials, sizeof(StatsPartial) * kStatsMaxBlocks)) &&
                 ok(hipMalloc(&ws->b_ticket, sizeof(unsigned long long))) &&
-                ok(hipMalloc(&ws->d_go, sizeof(uint32_t))) &&
                 ok(hipMemset(ws->d_ticket, 0, sizeof(unsigned long long))) &&
                 ok(hipMemset(ws->b_ticket, 0, sizeof(unsigned long long))) &&
                 ok(hipMemset(ws->d_final, 0, sizeof(fsz_result))) &&
@@ -312,10 +310,10 @@ fsz_status enqueue_decompress(Workspace *ws, const void *d_cmp, uint64_t cmp_siz
         e = launch_decompress_prezero(a, aligned(d_out, 16), ws->stream);
     } else if (tuning().dec_prescan && tuning().staged_decompress && n >= tuning().dec_lookback_below) {
         // chunk offsets from the rate header first (chunks of 32 or 64 tiles)
-        if (!grow(&ws->d_offs, &ws->offs_cap, std::max<uint64_t>(ceil_div(a.ntiles, 32), 1), ws->stream))
+        if (!grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + std::max<uint64_t>(ceil_div(a.ntiles, 32), 1),
+                  ws->stream))
             return FSZ_ERR_DEVICE;
-        e = launch_decompress_prescan(a, ws->d_offs, ws->d_go, aligned(d_out, 16), n < tuning().dec_direct_below,
-                                      ws->stream);
+        e = launch_decompress_prescan(a, ws->d_offs, aligned(d_out, 16), n < tuning().dec_direct_below, ws->stream);
     } else {
         e = launch_decompress(a, aligned(d_out, 16), tuning().staged_decompress, ws->stream);
     }
@@ -398,10 +396,8 @@ fsz_status enqueue_decompress_config(Workspace *ws, const void *d_cmp, uint64_t 
     hipError_t e;
     if (prescan) {
         // chunk offsets from the rate header first, as for the default format
-        if (!grow(&ws->d_offs, &ws->offs_cap, a.nchunks, ws->stream)) return FSZ_ERR_DEVICE;
-        a.offsets = ws->d_offs;
-        a.go = ws->d_go;
-        e = launch_decompress_cfg_prescan(a, block, tile_blocks, aligned(d_out, 16), ws->stream);
+        if (!grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + a.nchunks, ws->stream)) return FSZ_ERR_DEVICE;
+        e = launch_decompress_cfg_prescan(a, ws->d_offs, block, tile_blocks, aligned(d_out, 16), ws->stream);
     } else {
         e = launch_decompress_cfg(a, block, tile_blocks, aligned(d_out, 16), ws->stream);
     }

@@ -91,10 +91,12 @@ struct DecompressArgs {
     uint64_t tile_begin, tile_end, elem_begin, elem_end;
     const unsigned long long *range_base;
     uint32_t cfg_flags;  // tile-configuration decoders: the header flags bits 2-4 required
-    // Whole-field decodes with the offsets pre-pass: each chunk's byte offset
-    // after data0 (written by the pre-pass), and its outcome (FSZ_OK: decode).
+    // Whole-field decodes with the offsets pre-pass, which writes them: the
+    // bytes of each group of 2^group_shift chunks (bit 63: a reserved rate-byte
+    // bit) and each chunk's byte offset inside its group.
+    const unsigned long long *groups;
     const unsigned long long *offsets;
-    const uint32_t *go;
+    uint32_t group_shift;
     uint32_t epoch, flag_epoch;
     unsigned long long *flags;
     unsigned long long *ticket;  // zero between launches (self-resetting)
@@ -164,11 +166,12 @@ hipError_t launch_compress(const CompressArgs &a, bool in_aligned16, bool staged
 hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bool in_aligned16, hipStream_t s);
 hipError_t launch_decompress(const DecompressArgs &a, bool out_aligned16, bool staged, hipStream_t s);
 // Whole-field decompression with the chunk offsets computed first from the
-// rate header (no lookback in the decoder): offsets has room for one word per
-// chunk of 32 tiles, go for one status word.  direct: one chunk of 32 tiles
+// rate header (no lookback in the decoder): words has room for kMaxGroupWords
+// words and one per chunk of 32 tiles.  direct: one chunk of 32 tiles
 // per workgroup instead of the persistent grid over chunks of 64 tiles.
-hipError_t launch_decompress_prescan(const DecompressArgs &a, unsigned long long *offsets, uint32_t *go,
-                                     bool out_aligned16, bool direct, hipStream_t s);
+constexpr uint64_t kMaxGroupWords = 512;
+hipError_t launch_decompress_prescan(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
+                                     bool direct, hipStream_t s);
 // Pre-zeroed decompression (Sec. III-A): a fill of out[0, n) with +0.0, then
 // the decoder that skips waves whose tiles are all zero.
 hipError_t launch_decompress_prezero(const DecompressArgs &a, bool out_aligned16, hipStream_t s);
@@ -181,10 +184,10 @@ hipError_t launch_compress_cfg(const CompressArgs &a, int block, int tile_blocks
 hipError_t launch_decompress_cfg(const DecompressArgs &a, int block, int tile_blocks, bool out_aligned16,
                                  hipStream_t s);
 // The same decode with chunk offsets from a pre-pass over the rate header
-// (a.nchunks and a.offsets: one per chunk of kCfgDecChunkSegs segments; a.go:
-// its outcome).
-hipError_t launch_decompress_cfg_prescan(const DecompressArgs &a, int block, int tile_blocks, bool out_aligned16,
-                                         hipStream_t s);
+// (a.nchunks counts chunks of kCfgDecChunkSegs segments; words has room for
+// kMaxGroupWords words and one per chunk).
+hipError_t launch_decompress_cfg_prescan(const DecompressArgs &a, unsigned long long *words, int block,
+                                         int tile_blocks, bool out_aligned16, hipStream_t s);
 constexpr int kCfgWaves = 16;
 constexpr int kCfgChunkSegs = kCfgWaves * 64;
 constexpr int kCfgPipeChunkSegs = 8 * 64;  // the pipelined configuration compressor's chunk

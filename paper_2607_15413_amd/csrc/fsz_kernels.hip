@@ -1707,13 +1707,52 @@ struct DecChunk {
     int order2, cent;
 };
 
+// Slots rotate from chunk to chunk.  The decoders with the offsets pre-pass pass
+// one barrier per chunk, so a wave may be one chunk ahead of another and three
+// slots are in use; the lookback decoders pass several and use two.
 template <int W>
 struct DecompressShared {
-    uint32_t wave_total[2][W];
+    uint32_t wave_total[3][W];
+    unsigned long long group_base[3];
     int bad[2];
     unsigned long long base;
     unsigned long long ticket[2];  // alternating broadcast slots
 };
+
+// Running sum over the groups of the offsets pre-pass (dec_groups_kernel), kept
+// by one wave: bytes of groups [0, next) and whether one of them holds a
+// reserved rate-byte bit.
+constexpr unsigned long long kGroupBad = 1ull << 63;
+struct GroupCursor {
+    uint64_t next = 0, sum = 0;
+    bool bad = false;
+};
+
+// Moves the cursor up to group g; the whole wave runs it (64 groups per load).
+__device__ __forceinline__ void groups_advance(const unsigned long long *groups, uint64_t g, GroupCursor &c)
+{
+    for (; c.next < g; c.next += 64) {
+        const uint64_t k = c.next + __lane_id();
+        const unsigned long long v = k < g ? groups[k] : 0ull;
+        c.sum += wave_sum_u64(v & ~kGroupBad);
+        c.bad = c.bad || __ballot(v >> 63) != 0;
+    }
+    c.next = g;
+}
+
+// Run by one whole wave with the cursor at the last chunk's group: the call's
+// outcome.  The stream is sound if no rate byte has a reserved bit, the sizes
+// add up to the header's total and the rate header's padding (at most 15
+// bytes, one lane each) is zero.
+__device__ __forceinline__ void finish_decode(const DecompressArgs &a, const GroupCursor &c, uint64_t end,
+                                              uint64_t total)
+{
+    const uint64_t k = kHeaderBytes + a.nblocks + __lane_id();
+    const bool padbad = __ballot(__lane_id() < 16 && k < a.data0 && a.cmp[k < a.data0 ? k : 0] != 0) != 0;
+    const bool bad = c.bad || padbad || (a.ntiles && (a.groups[c.next] >> 63) != 0) || a.data0 + end != total;
+    if (__lane_id() == 0)
+        write_final(a.final, total, bad ? (uint32_t)FSZ_ERR_CORRUPT : (uint32_t)FSZ_OK, a.epoch);
+}
 
 // Decompression steps 1-2 (Sec. III-A): rate bytes and tile metadata ->
 // block and tile sizes -> this chunk's aggregate, published at once so that
@@ -1736,11 +1775,12 @@ __device__ __forceinline__ uint32_t dec_rate_byte(const DecompressArgs &a, uint6
 }
 
 // rb: the lane's rate byte from dec_rate_byte (loaded ahead by the caller).
-// PRESCAN: the offsets pre-pass has checked the rate bytes and placed every
-// chunk; the chunk's offset is read instead of publishing its aggregate.
+// PRESCAN: the offsets pre-pass has summed the groups of chunks and placed
+// every chunk inside its group; wave 0 brings its group cursor up to the
+// chunk's group instead of publishing an aggregate.
 template <int W, bool RANGE = false, bool PRESCAN = false>
 __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t chunk, uint32_t rb, int slot,
-                                              DecompressShared<W> &sh)
+                                              DecompressShared<W> &sh, GroupCursor &gc)
 {
     const int tid = threadIdx.x;
     const int w = tid >> 6;
@@ -1766,9 +1806,13 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
     d.blk_off = d.tile_excl + group_excl_scan(S, j) + 4u * d.cent;
     d.base = 0;
     if (PRESCAN) {
-        d.base = a.offsets[__builtin_amdgcn_readfirstlane((uint32_t)chunk)];
+        if (w == 0) {
+            groups_advance(a.groups, chunk >> a.group_shift, gc);
+            if (lane == 0) sh.group_base[slot] = gc.sum + a.offsets[chunk];
+        }
         if (lane == 0) sh.wave_total[slot][w] = d.wave_total;
         lds_barrier();
+        d.base = sh.group_base[slot];
         return d;
     }
     const bool wave_bad = __ballot(bad) != 0;
@@ -1802,7 +1846,7 @@ struct DecPlace {
 
 template <int W, bool RANGE = false, bool PREZERO = false, bool PRESCAN = false>
 __device__ __forceinline__ DecPlace dec_place(const DecompressArgs &a, const DecChunk &d, int slot, uint64_t total,
-                                              DecompressShared<W> &sh)
+                                              DecompressShared<W> &sh, const GroupCursor &gc)
 {
     const int tid = threadIdx.x;
     const int w = tid >> 6;
@@ -1814,11 +1858,12 @@ __device__ __forceinline__ DecPlace dec_place(const DecompressArgs &a, const Dec
         if (k < w) wave_base += sh.wave_total[slot][k];
         chunk_total += sh.wave_total[slot][k];
     }
-    if (PRESCAN) {  // placed and checked by the pre-pass
+    if (PRESCAN) {  // placed by the pre-pass
         DecPlace p;
         p.tile0 = d.chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
         p.wave_data = a.cmp + a.data0 + d.base + wave_base;
-        p.live = p.tile0 < a.ntiles;
+        p.live = a.data0 + d.base + chunk_total <= total && p.tile0 < a.ntiles;
+        if (w == 0 && d.chunk == a.nchunks - 1) finish_decode(a, gc, d.base + chunk_total, total);
         if (PREZERO && p.live) {
             const uint64_t gblock = (p.tile0 + (lane >> 3)) * kBlocksPerTile + j;
             p.live = __ballot(gblock < a.nblocks && (d.r != 0 || d.cent != 0)) != 0;
@@ -2034,9 +2079,7 @@ __global__ __launch_bounds__(W * 64) void decompress_kernel(DecompressArgs a)
     uint64_t total;
     bool indep;
     const int hst = dec_header(a, E, total, indep);
-    if (PRESCAN) {  // the pre-pass checked the stream and reported its outcome
-        if (*a.go != FSZ_OK) return;
-    } else if (hst != FSZ_OK) {
+    if (hst != FSZ_OK) {
         if (tid == 0 && blockIdx.x == 0) write_final(a.final, 0, hst, a.epoch);
         return;
     }
@@ -2050,18 +2093,20 @@ __global__ __launch_bounds__(W * 64) void decompress_kernel(DecompressArgs a)
     uint64_t cur = PRESCAN ? (uint64_t)blockIdx.x : next_ticket(a.ticket, takes, sh, tslot);
     if (cur >= a.nchunks) return;
     int slot = 0;
-    DecChunk dc = dec_sizes<W, RANGE, PRESCAN>(a, cur, dec_rate_byte<W, RANGE>(a, cur), slot, sh);
+    GroupCursor gc;
+    DecChunk dc = dec_sizes<W, RANGE, PRESCAN>(a, cur, dec_rate_byte<W, RANGE>(a, cur), slot, sh, gc);
     for (;;) {
         const uint64_t nxt = PRESCAN ? cur + gridDim.x : next_ticket(a.ticket, takes, sh, tslot);
+        const int nslot = PRESCAN ? (slot == 2 ? 0 : slot + 1) : slot ^ 1;
         DecChunk dn;
         if (nxt < a.nchunks)
-            dn = dec_sizes<W, RANGE, PRESCAN>(a, nxt, dec_rate_byte<W, RANGE>(a, nxt), slot ^ 1, sh);
-        const DecPlace pl = dec_place<W, RANGE, PREZERO, PRESCAN>(a, dc, slot, total, sh);
+            dn = dec_sizes<W, RANGE, PRESCAN>(a, nxt, dec_rate_byte<W, RANGE>(a, nxt), nslot, sh, gc);
+        const DecPlace pl = dec_place<W, RANGE, PREZERO, PRESCAN>(a, dc, slot, total, sh, gc);
         if (pl.live) dec_decode<ALIGNED, STAGED, W, RANGE>(a, dc, pl, E, indep, st);
         if (nxt >= a.nchunks) break;
         dc = dn;
         cur = nxt;
-        slot ^= 1;
+        slot = nslot;
     }
 }
 
@@ -2071,125 +2116,126 @@ __global__ __launch_bounds__(W * 64) void decompress_kernel(DecompressArgs a)
 // (decompression steps 1-2, Sec. III-A), so one small launch computes them
 // before the decoder starts, and the decoder reads its chunk's offset instead
 // of waiting on a lookback.
+//
+// The pre-pass has no order between workgroups either: each takes one group of
+// kGroupTiles << m consecutive tiles, writes the offset of each of its chunks
+// inside the group and the group's total, and ends.  The decoder adds up the
+// totals of the groups before its own, 64 per load; m is the least that keeps
+// them at kMaxGroups (8 loads for the last chunk of any field).  What bounds
+// it is one round trip for the rate bytes and the launch itself: 512^3 takes
+// 4.9 us, where workgroups in ticket order with a decoupled lookback
+// over their totals took 9.4 us (25 M elements: 4.7 against 8.0 us).
+constexpr int kGroupThreads = 256;
+constexpr int kGroupTilesPerThread = 4;
+constexpr int kGroupTiles = kGroupThreads * kGroupTilesPerThread;
+constexpr uint64_t kMaxGroups = kMaxGroupWords;
 
-// The offsets pre-pass, in one pass: workgroups of 1024 threads, each thread
-// 4 consecutive tiles, taken in ticket order.  A workgroup adds up its tiles'
-// sizes, publishes its total in the flag words and takes its exclusive prefix
-// by the decoupled lookback, then writes the offsets of its chunks (TPC tiles
-// each, so no chunk straddles two threads or workgroups).  Reserved rate-byte
-// bits ride on the flags' error bit; the workgroup holding the last tiles
-// checks the header's total and the padding and reports the outcome.
-constexpr int kScanThreads = 1024;
-constexpr int kScanTilesPerThread = 4;
-constexpr int kScanTiles = kScanThreads * kScanTilesPerThread;
+// Four rate bytes: sum of r + (r > 0) over them, added to acc (a block of rate
+// r > 0 is one sign word and r planes long).
+__device__ __forceinline__ uint32_t rate_units(uint32_t w, uint32_t acc)
+{
+    const uint32_t x = w & 0x1F1F1F1Fu;
+    const uint32_t nz = ((x + 0x1F1F1F1Fu) >> 5) & 0x01010101u;
+    return (uint32_t)__builtin_popcount(nz) + __builtin_amdgcn_sad_u8(x, 0u, acc);
+}
 
 // TPC tiles per decoder chunk; T blocks per tile of HB 32-element segments
 // each (the default format: 8 and 1; the tile configurations: the stream's).
+// The rate header lies inside the buffer (checked by the host), so any bytes
+// may be read before the decoder has looked at the stream header.
 template <int TPC, int T = kBlocksPerTile, int HB = 1>
-__global__ __launch_bounds__(kScanThreads) void dec_offsets_single_kernel(DecompressArgs a, unsigned long long *offs,
-                                                                          uint32_t *go, uint64_t ngroups)
+__global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArgs a, unsigned long long *offs,
+                                                                   unsigned long long *groups, uint32_t passes)
 {
     static_assert(T == 4 || T == 8 || T == 16, "a tile's rate bytes are 1, 2 or 4 words");
-    static_assert(TPC % kScanTilesPerThread == 0, "a chunk starts at a thread's first tile");
-    __shared__ uint32_t wsum[kScanThreads / 64];
-    __shared__ unsigned long long gbase;
-    __shared__ unsigned long long tk;
-    __shared__ int gbad;
+    static_assert(TPC % kGroupTilesPerThread == 0, "a chunk starts at a thread's first tile");
+    constexpr int kWavesG = kGroupThreads / 64;
+    constexpr int kWords = kGroupTilesPerThread * T / 4;
+    __shared__ uint32_t wsum[2][kWavesG];
+    __shared__ uint32_t wbad[kWavesG];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
+    if (a.data0 > a.cmp_size) return;  // the decoder reports it
+    uint64_t run = 0;
+    uint32_t bad = 0;
+    for (uint32_t p = 0; p < passes; p++) {
+        const uint64_t tile0 =
+            (((uint64_t)blockIdx.x * passes + p) * kGroupThreads + (uint64_t)tid) * kGroupTilesPerThread;
+        uint32_t units = 0, cents = 0;
+        const g_u32 *rp = (const g_u32 *)(a.cmp + kHeaderBytes + tile0 * T);
+        if ((tile0 + kGroupTilesPerThread) * T <= a.nblocks) {
+            uint32_t rw[kWords];
+#pragma unroll
+            for (int q = 0; q < kWords; q++) rw[q] = rp[q];
+#pragma unroll
+            for (int q = 0; q < kWords; q++) {
+                const bool head = q % (T / 4) == 0;
+                bad |= rw[q] & (head ? 0xE0E0E020u : 0xE0E0E0E0u);
+                units = rate_units(rw[q], units);
+                if (head) cents += (rw[q] >> 6) & 1u;
+            }
+        } else if (tile0 * T < a.nblocks) {  // the field's last blocks, byte by byte
+            const uint64_t left = a.nblocks - tile0 * T;
+            for (uint32_t k = 0; k < (uint32_t)left; k++) {
+                const uint32_t rb = ((const g_u8 *)rp)[k];
+                const bool head = k % T == 0;
+                bad |= rb & (head ? 0x20u : 0xE0u);
+                units = rate_units(rb & 0xFFu, units);
+                if (head) cents += (rb >> 6) & 1u;
+            }
+        }
+        const uint32_t z = 4u * HB * units + 4u * cents;
+        const uint32_t incl = (uint32_t)wave_incl_scan((int)z);
+        if (lane == 63) wsum[p & 1][w] = incl;
+        lds_barrier();
+        uint32_t wave_base = 0, ptotal = 0;
+#pragma unroll
+        for (int k = 0; k < kWavesG; k++) {
+            if (k < w) wave_base += wsum[p & 1][k];
+            ptotal += wsum[p & 1][k];
+        }
+        if (tile0 < a.ntiles && (tile0 % TPC) == 0) offs[tile0 / TPC] = run + wave_base + incl - z;
+        run += ptotal;
+    }
+    const bool wave_bad = __ballot(bad != 0) != 0;
+    if (lane == 0) wbad[w] = wave_bad ? 1u : 0u;
+    lds_barrier();
     if (tid == 0) {
-        tk = take_ticket(a.ticket, ngroups);
-        gbad = 0;
-    }
-    __syncthreads();
-    const uint64_t g = tk;
-    float E;
-    uint64_t total;
-    bool indep;
-    const int hst = dec_header(a, E, total, indep);
-    if (hst != FSZ_OK) {
-        if (tid == 0 && g == 0) {
-            *go = (uint32_t)hst;
-            write_final(a.final, 0, hst, a.epoch);
-        }
-        return;
-    }
-    // the rate bytes of a tile lie inside the (zero-padded) rate header, which
-    // the header check placed inside the buffer
-    const uint64_t tile0 = (g * kScanThreads + tid) * kScanTilesPerThread;
-    uint32_t z = 0, bad = 0;
+        uint32_t any = 0;
 #pragma unroll
-    for (int i = 0; i < kScanTilesPerThread; i++) {
-        const uint64_t tile = tile0 + i;
-        if (tile < a.ntiles) {
-            const uint32_t *p = reinterpret_cast<const uint32_t *>(a.cmp + kHeaderBytes + tile * T);
-            uint32_t rw[T / 4];
-#pragma unroll
-            for (int q = 0; q < T / 4; q++) rw[q] = p[q];
-            const uint64_t nb64 = a.nblocks - tile * T;
-            const uint32_t nb = nb64 < (uint64_t)T ? (uint32_t)nb64 : (uint32_t)T;
-#pragma unroll
-            for (uint32_t b = 0; b < (uint32_t)T; b++) {
-                const uint32_t rb = (rw[b >> 2] >> (8 * (b & 3))) & 0xFFu;
-                if (b < nb) {
-                    bad |= b == 0 ? (rb & 0x20u) : (rb & 0xE0u);
-                    z += HB * block_bytes(rb & 31u) + ((b == 0 && (rb & 0x40u)) ? 4u : 0u);
-                }
-            }
-        }
+        for (int k = 0; k < kWavesG; k++) any |= wbad[k];
+        groups[blockIdx.x] = run | (any ? kGroupBad : 0ull);
+        if (a.ntiles == 0) offs[0] = 0;
     }
-    const uint32_t incl = (uint32_t)wave_incl_scan((int)z);
-    if (lane == 63) wsum[w] = incl;
-    if (__ballot(bad != 0) != 0 && lane == 0) gbad = 1;
-    __syncthreads();
-    uint32_t wave_base = 0, gtotal = 0;
-#pragma unroll
-    for (int k = 0; k < kScanThreads / 64; k++) {
-        if (k < w) wave_base += wsum[k];
-        gtotal += wsum[k];
-    }
-    if (w == 0) {
-        bool padbad = false;
-        if (g == ngroups - 1) {  // the rate header's zero padding: at most 15 bytes, one lane each
-            const uint64_t k = kHeaderBytes + a.nblocks + (uint64_t)lane;
-            padbad = __ballot(lane < 16 && k < a.data0 && a.cmp[k] != 0) != 0;
-        }
-        if (lane == 0) publish_aggregate(a.flags, g, a.flag_epoch, gtotal, gbad != 0);
-        const Prefix pre = lookback_wait(a.flags, g, a.flag_epoch, gtotal, gbad != 0);
-        if (lane == 0) {
-            gbase = pre.excl;
-            if (g == ngroups - 1) {  // pre.err: a reserved bit in any group (or a lookback that gave up)
-                const bool ok = !pre.err && !padbad && a.data0 + pre.excl + gtotal == total;
-                const uint32_t st = ok ? (uint32_t)FSZ_OK : (uint32_t)FSZ_ERR_CORRUPT;
-                *go = st;
-                write_final(a.final, total, st, a.epoch);
-            }
-        }
-    }
-    __syncthreads();
-    if (tile0 < a.ntiles && (tile0 % TPC) == 0) offs[tile0 / TPC] = gbase + wave_base + incl - z;
-    if (a.ntiles == 0 && tid == 0) offs[0] = 0;
 }
 
 // Whole-field decoder for the offsets pre-pass, one chunk of 8*W tiles per
 // workgroup and no ticket: with every chunk's offset known there is no order
 // to keep, and the hardware dispatcher keeps the CUs busy.  Used for fields
-// too small to give a persistent grid several chunks per workgroup.
+// too small to give a persistent grid several chunks per workgroup.  The size
+// pass needs nothing of the stream header but the room for the rate bytes, so
+// its loads go out before the header's have come back.
 template <bool ALIGNED, int W>
 __global__ __launch_bounds__(W * 64) void decompress_direct_kernel(DecompressArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
     __shared__ DecompressShared<W> sh;
-    if (*a.go != FSZ_OK) return;  // the pre-pass checked the stream and reported its outcome
+    const uint64_t chunk = blockIdx.x;
+    uint32_t *st = stage + (threadIdx.x >> 6) * kStageWaveDwords;
+    GroupCursor gc;
+    DecChunk dc;
+    const bool room = a.data0 <= a.cmp_size;
+    if (room) dc = dec_sizes<W, false, true>(a, chunk, dec_rate_byte<W>(a, chunk), 0, sh, gc);
     float E;
     uint64_t total;
     bool indep;
-    dec_header(a, E, total, indep);
-    const uint64_t chunk = blockIdx.x;
-    uint32_t *st = stage + (threadIdx.x >> 6) * kStageWaveDwords;
-    const DecChunk dc = dec_sizes<W, false, true>(a, chunk, dec_rate_byte<W>(a, chunk), 0, sh);
-    const DecPlace pl = dec_place<W, false, false, true>(a, dc, 0, total, sh);
+    const int hst = dec_header(a, E, total, indep);
+    if (!room || hst != FSZ_OK) {
+        if (threadIdx.x == 0 && chunk == 0) write_final(a.final, 0, hst, a.epoch);
+        return;
+    }
+    const DecPlace pl = dec_place<W, false, false, true>(a, dc, 0, total, sh, gc);
     if (pl.live) dec_decode<ALIGNED, true, W>(a, dc, pl, E, indep, st);
 }
 
@@ -2426,8 +2472,9 @@ __global__ __launch_bounds__(W * 64) void batch_kernel(BatchArgs b)
             if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, hst, a.epoch);
             return;
         }
-        const DecChunk dc = dec_sizes<W>(a, chunk, dec_rate_byte<W>(a, chunk), 0, sh.d);
-        const DecPlace pl = dec_place<W>(a, dc, 0, total, sh.d);
+        GroupCursor gc;
+        const DecChunk dc = dec_sizes<W>(a, chunk, dec_rate_byte<W>(a, chunk), 0, sh.d, gc);
+        const DecPlace pl = dec_place<W>(a, dc, 0, total, sh.d, gc);
         if (pl.live) dec_decode<ALIGNED, true, W>(a, dc, pl, E, indep, st);
     }
 }
@@ -2449,6 +2496,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(4))) voi
     const uint64_t takes = b.total_chunks + gridDim.x;
     int tslot = 0;
     uint64_t t = next_ticket(b.ticket, takes, sh, tslot);
+    GroupCursor gc;     // unused by the lookback form
     bool have = false;  // dc holds the size pass of item t (slot `slot`)
     DecChunk dc;
     int slot = 0;
@@ -2465,7 +2513,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(4))) voi
             if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, hst, a.epoch);
             have = false;
         } else {
-            if (!have) dc = dec_sizes<W>(a, chunk, dec_rate_byte<W>(a, chunk), slot, sh);
+            if (!have) dc = dec_sizes<W>(a, chunk, dec_rate_byte<W>(a, chunk), slot, sh, gc);
             bool next_have = false;
             DecChunk dn;
             if (nxt < b.total_chunks) {
@@ -2476,11 +2524,11 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(4))) voi
                 uint64_t total2;
                 bool indep2;
                 if (dec_header(a2, E2, total2, indep2) == FSZ_OK) {
-                    dn = dec_sizes<W>(a2, chunk2, dec_rate_byte<W>(a2, chunk2), slot ^ 1, sh);
+                    dn = dec_sizes<W>(a2, chunk2, dec_rate_byte<W>(a2, chunk2), slot ^ 1, sh, gc);
                     next_have = true;
                 }
             }
-            const DecPlace pl = dec_place<W>(a, dc, slot, total, sh);
+            const DecPlace pl = dec_place<W>(a, dc, slot, total, sh, gc);
             if (pl.live) dec_decode<ALIGNED, true, W>(a, dc, pl, E, indep, st);
             if (next_have) {
                 dc = dn;
@@ -3176,8 +3224,7 @@ __global__ __launch_bounds__(kCfgWaves * 64) void compress_cfg_kernel(CompressAr
 // which small fields need, and several workgroups per CU to hide the lookback
 // and the tile loads; 16 in the lookback form of fields above 2^21 elements,
 // whose chain the larger chunks halve twice).  PRESCAN: the chunk offsets come from
-// dec_offsets_single_kernel<64 WV / L, L / HB, HB> (which also checked the
-// stream and reported its outcome): chunk = workgroup, no lookback.
+// dec_groups_kernel<64 WV / L, L / HB, HB>: chunk = workgroup, no lookback.
 template <bool ALIGNED, int HB, int L, bool PRESCAN = false, int WV = kCfgDecWaves>
 __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs a)
 {
@@ -3203,13 +3250,12 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
     const uint64_t total = (uint64_t)hw[7] << 32 | hw[6];
     if (hst == FSZ_OK && (!__builtin_isfinite(E) || !(E > 0.0f) || total > a.cmp_size || total < a.data0))
         hst = FSZ_ERR_CORRUPT;
-    if (PRESCAN) {
-        if (*a.go != FSZ_OK) return;
-    } else if (hst != FSZ_OK) {
+    if (hst != FSZ_OK) {
         if (tid == 0 && blockIdx.x == 0) write_final(a.final, 0, hst, a.epoch);
         return;
     }
     int tslot = 0;
+    GroupCursor gc;
     const uint64_t chunk = PRESCAN ? (uint64_t)blockIdx.x : next_ticket(a.ticket, a.nchunks, sh, tslot);
     if (chunk >= a.nchunks) return;
 
@@ -3238,6 +3284,10 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
         sh.wave_total[0][w] = wave_total;
         sh.wave_total[1][w] = wave_bad ? 1u : 0u;
     }
+    if (PRESCAN && w == 0) {
+        groups_advance(a.groups, chunk >> a.group_shift, gc);
+        if (lane == 0) sh.base = gc.sum + a.offsets[chunk];
+    }
     lds_barrier();
     uint32_t chunk_total = 0, wave_base = 0;
     bool any_bad = false;
@@ -3249,7 +3299,8 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
     }
     uint64_t base;
     if (PRESCAN) {
-        base = a.offsets[chunk];
+        base = sh.base;
+        if (w == 0 && chunk == a.nchunks - 1) finish_decode(a, gc, base + chunk_total, total);
     } else {
         if (tid == 0) publish_aggregate(a.flags, chunk, a.flag_epoch, chunk_total, any_bad);
         if (w == 0) {
@@ -3399,30 +3450,44 @@ static hipError_t launch_decompress_w(const DecompressArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_decompress_prescan(const DecompressArgs &a, unsigned long long *offsets, uint32_t *go,
-                                     bool out_aligned16, bool direct, hipStream_t s)
+// Rounds of kGroupTiles tiles per group of the offsets pre-pass: the least power
+// of two that leaves at most kMaxGroups groups.
+static uint32_t group_passes(uint64_t ntiles)
+{
+    uint32_t p = 1;
+    while (ceil_div(ntiles, (uint64_t)kGroupTiles * p) > kMaxGroups) p *= 2;
+    return p;
+}
+
+// Enqueues the offsets pre-pass for chunks of TPC tiles and names its results
+// in a: `words` holds kMaxGroups group totals, then an offset per chunk.
+template <int TPC, int T = kBlocksPerTile, int HB = 1>
+static hipError_t launch_dec_groups(DecompressArgs &a, unsigned long long *words, hipStream_t s)
+{
+    const uint32_t passes = group_passes(a.ntiles);
+    const uint64_t ngroups = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kGroupTiles * passes) : 1;
+    a.groups = words;
+    a.offsets = words + kMaxGroups;
+    a.group_shift = (uint32_t)__builtin_ctz(kGroupTiles / TPC * passes);
+    hipLaunchKernelGGL((dec_groups_kernel<TPC, T, HB>), dim3((unsigned)ngroups), dim3(kGroupThreads), 0, s, a,
+                       words + kMaxGroups, words, passes);
+    return hipGetLastError();
+}
+
+hipError_t launch_decompress_prescan(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
+                                     bool direct, hipStream_t s)
 {
     // chunks of 8 tiles per wave: 8 waves (persistent grid) or 4 (one chunk per workgroup)
-    const int W = direct ? 4 : 8;
     DecompressArgs p = a;
-    p.offsets = offsets;
-    p.go = go;
-    const uint64_t nchunks = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kTilesPerWave * W) : 1;
-    const uint64_t ngroups = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kScanTiles) : 1;
-    if (direct)
-        hipLaunchKernelGGL(dec_offsets_single_kernel<kTilesPerWave * 4>, dim3((unsigned)ngroups), dim3(kScanThreads), 0,
-                           s, p, offsets, go, ngroups);
-    else
-        hipLaunchKernelGGL(dec_offsets_single_kernel<kTilesPerWave * 8>, dim3((unsigned)ngroups), dim3(kScanThreads), 0,
-                           s, p, offsets, go, ngroups);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = direct ? launch_dec_groups<kTilesPerWave * 4>(p, words, s)
+                                : launch_dec_groups<kTilesPerWave * 8>(p, words, s);
     if (e != hipSuccess) return e;
     if (direct) {
-        p.nchunks = nchunks;
+        p.nchunks = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kTilesPerWave * 4) : 1;
         if (out_aligned16)
-            hipLaunchKernelGGL((decompress_direct_kernel<true, 4>), dim3((unsigned)nchunks), dim3(256), 0, s, p);
+            hipLaunchKernelGGL((decompress_direct_kernel<true, 4>), dim3((unsigned)p.nchunks), dim3(256), 0, s, p);
         else
-            hipLaunchKernelGGL((decompress_direct_kernel<false, 4>), dim3((unsigned)nchunks), dim3(256), 0, s, p);
+            hipLaunchKernelGGL((decompress_direct_kernel<false, 4>), dim3((unsigned)p.nchunks), dim3(256), 0, s, p);
         return hipGetLastError();
     }
     return out_aligned16 ? launch_decompress_w<true, true, 8, false, false, true>(p, s)
@@ -3669,39 +3734,36 @@ hipError_t launch_decompress_cfg(const DecompressArgs &a, int block, int tile_bl
 // Offsets pre-pass (chunks of kCfgDecChunkSegs segments = kCfgDecChunkSegs / L
 // tiles), then one chunk per workgroup without lookback.
 template <bool ALIGNED, int HB, int L>
-static hipError_t launch_decompress_cfg_prescan_t(const DecompressArgs &a, hipStream_t s)
+static hipError_t launch_decompress_cfg_prescan_t(const DecompressArgs &a, unsigned long long *words, hipStream_t s)
 {
-    const uint64_t ngroups = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kScanTiles) : 1;
-    hipLaunchKernelGGL((dec_offsets_single_kernel<kCfgDecChunkSegs / L, L / HB, HB>), dim3((unsigned)ngroups),
-                       dim3(kScanThreads), 0, s, a, const_cast<unsigned long long *>(a.offsets),
-                       const_cast<uint32_t *>(a.go), ngroups);
-    const hipError_t e = hipGetLastError();
+    DecompressArgs p = a;
+    const hipError_t e = launch_dec_groups<kCfgDecChunkSegs / L, L / HB, HB>(p, words, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decompress_cfg_kernel<ALIGNED, HB, L, true>), dim3((unsigned)a.nchunks),
-                       dim3(kCfgDecWaves * 64), 0, s, a);
+                       dim3(kCfgDecWaves * 64), 0, s, p);
     return hipGetLastError();
 }
 
 template <bool ALIGNED>
-static hipError_t launch_decompress_cfg_prescan_a(const DecompressArgs &a, int block, int tile_blocks,
-                                                  hipStream_t s)
+static hipError_t launch_decompress_cfg_prescan_a(const DecompressArgs &a, unsigned long long *words, int block,
+                                                  int tile_blocks, hipStream_t s)
 {
     switch (block * 100 + tile_blocks) {
-    case 3204: return launch_decompress_cfg_prescan_t<ALIGNED, 1, 4>(a, s);
-    case 3208: return launch_decompress_cfg_prescan_t<ALIGNED, 1, 8>(a, s);
-    case 3216: return launch_decompress_cfg_prescan_t<ALIGNED, 1, 16>(a, s);
-    case 6404: return launch_decompress_cfg_prescan_t<ALIGNED, 2, 8>(a, s);
-    case 6408: return launch_decompress_cfg_prescan_t<ALIGNED, 2, 16>(a, s);
-    case 6416: return launch_decompress_cfg_prescan_t<ALIGNED, 2, 32>(a, s);
+    case 3204: return launch_decompress_cfg_prescan_t<ALIGNED, 1, 4>(a, words, s);
+    case 3208: return launch_decompress_cfg_prescan_t<ALIGNED, 1, 8>(a, words, s);
+    case 3216: return launch_decompress_cfg_prescan_t<ALIGNED, 1, 16>(a, words, s);
+    case 6404: return launch_decompress_cfg_prescan_t<ALIGNED, 2, 8>(a, words, s);
+    case 6408: return launch_decompress_cfg_prescan_t<ALIGNED, 2, 16>(a, words, s);
+    case 6416: return launch_decompress_cfg_prescan_t<ALIGNED, 2, 32>(a, words, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_decompress_cfg_prescan(const DecompressArgs &a, int block, int tile_blocks, bool out_aligned16,
-                                         hipStream_t s)
+hipError_t launch_decompress_cfg_prescan(const DecompressArgs &a, unsigned long long *words, int block,
+                                         int tile_blocks, bool out_aligned16, hipStream_t s)
 {
-    return out_aligned16 ? launch_decompress_cfg_prescan_a<true>(a, block, tile_blocks, s)
-                         : launch_decompress_cfg_prescan_a<false>(a, block, tile_blocks, s);
+    return out_aligned16 ? launch_decompress_cfg_prescan_a<true>(a, words, block, tile_blocks, s)
+                         : launch_decompress_cfg_prescan_a<false>(a, words, block, tile_blocks, s);
 }
 
 constexpr size_t kLdsPerCu = 160 * 1024;

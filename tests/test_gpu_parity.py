@@ -570,3 +570,27 @@ def test_decoder_regimes_and_corrupt_streams():
             assert st == fsz.FSZ_ERR_CORRUPT
     finally:
         oracle.set_threads(old)
+
+
+@pytest.mark.parametrize("n", [1 << 23, (1 << 23) + 1, (1 << 23) + 1024 * 256 - 31, (1 << 26) + 3 * 1024 * 256,
+                               (1 << 27) + 5])
+def test_offsets_pre_pass_group_edges(n):
+    """The offsets pre-pass sums groups of 1024 tiles (2048 above 2^27
+    elements): whole groups, one tile or a few elements over, one block short,
+    and a reserved rate bit in the first and the last group, which must reach
+    the result although no other chunk of its group sees it."""
+    x = workloads.sparse_field(n, 6, spacing=500)
+    old = oracle.set_threads(8)
+    try:
+        s = oracle.compress(x, oracle.REL, 1e-4)
+        announce(f"group edges n={n}")
+        st, y = gpu_decompress(s, n)
+        assert st == fsz.FSZ_OK
+        assert np.array_equal(y.view(np.uint32), oracle.decompress(s, n).view(np.uint32))
+        for block in (9, (n + 31) // 32 - 1):
+            bad = bytearray(s)
+            bad[32 + block] |= 0x20
+            announce(f"group edges n={n}: reserved bit in block {block}")
+            assert gpu_decompress(bytes(bad), n)[0] == fsz.FSZ_ERR_CORRUPT
+    finally:
+        oracle.set_threads(old)
