@@ -24,7 +24,6 @@ const Tuning &tuning()
         Tuning v;
         if (const char *e = std::getenv("FSZ_STAGED")) {  // letters: c = compress, d = decompress
             v.staged_compress = std::strchr(e, 'c') != nullptr;
-            v.staged_decompress = std::strchr(e, 'd') != nullptr;
             v.staged_compress_loads = std::strchr(e, 'l') != nullptr;
         }
         if (const char *e = std::getenv("FSZ_PIPE")) v.pipe_compress = std::atoi(e) != 0;
@@ -32,14 +31,8 @@ const Tuning &tuning()
             const int k = std::atoi(e);
             if (k == 1 || k == 2 || k == 4 || k == 7 || k == 8 || k == 9) v.pipe_waves = k;  // 7, 9: + 1 control wave
         }
-        if (const char *e = std::getenv("FSZ_DEC_WAVES")) {
-            const int k = std::atoi(e);
-            if (k == 4 || k == 8 || k == 16) v.dec_waves = k;
-        }
         if (const char *e = std::getenv("FSZ_PREZERO_CR")) v.prezero_min_cr = std::atof(e);
-        if (const char *e = std::getenv("FSZ_DEC_PRESCAN")) v.dec_prescan = std::atoi(e) != 0;
         if (const char *e = std::getenv("FSZ_DEC_WIDE_ABOVE")) v.dec_wide_above = std::strtoull(e, nullptr, 10);
-        if (const char *e = std::getenv("FSZ_DEC_LOOKBACK_BELOW")) v.dec_lookback_below = std::strtoull(e, nullptr, 10);
         if (const char *e = std::getenv("FSZ_CFG_DEC_LOOKBACK_BELOW"))
             v.cfg_dec_lookback_below = std::strtoull(e, nullptr, 10);
         if (const char *e = std::getenv("FSZ_DEC_DIRECT_BELOW")) v.dec_direct_below = std::strtoull(e, nullptr, 10);
@@ -114,12 +107,10 @@ struct Workspace {
     fsz_stats *b_stats = nullptr;
     uint64_t b_stats_cap = 0;
     unsigned long long *b_ticket = nullptr;
-    // random-access decode: the range's base offset, then the reduction partials
-    unsigned long long *d_range = nullptr;
     // five-read baseline: evaluation tables (53 bytes per tile)
     uint8_t *d_naive = nullptr;
     uint64_t naive_cap = 0;
-    // whole-field decodes: group totals and chunk offsets of the pre-pass
+    // decodes: group totals and chunk offsets of the pre-pass
     unsigned long long *d_offs = nullptr;
     uint64_t offs_cap = 0;
 };
@@ -243,6 +234,14 @@ fsz_status enqueue_compress(Workspace *ws, const float *d_in, uint64_t n, int mo
 template <typename T>
 bool grow(T **p, uint64_t *cap, uint64_t want, hipStream_t s);
 
+// Room for the offsets pre-pass of a decode, if it has one.
+bool ensure_words(Workspace *ws, const DecompressArgs &a, bool prezero)
+{
+    if (!prezero && decode_by_prefix(a.tile_begin, a.tile_end)) return true;
+    return grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + ceil_div(a.tile_end, (uint64_t)kTilesPerChunk) + 1,
+                ws->stream);
+}
+
 // The five-read baseline (Sec. V-C, Fig. 6): the same stream as
 // enqueue_compress, from four evaluation passes and one encode pass.
 fsz_status enqueue_compress_naive(Workspace *ws, const float *d_in, uint64_t n, int mode, double value,
@@ -293,30 +292,16 @@ fsz_status enqueue_decompress(Workspace *ws, const void *d_cmp, uint64_t cmp_siz
     a.n = n;
     a.ntiles = ceil_div(n, kTile);
     a.nblocks = ceil_div(n, kBlock);
-    a.nchunks = a.ntiles ? ceil_div(a.ntiles, kTilesPerChunk) : 1;
     a.data0 = kHeaderBytes + pad16(a.nblocks);
     a.tile_begin = 0;
     a.tile_end = a.ntiles;
     a.elem_begin = 0;
     a.elem_end = n;
-    a.range_base = nullptr;
-    if (!ensure_flags(ws, std::max<uint64_t>(a.nchunks, ceil_div(a.ntiles, kTilesPerWave)))) return FSZ_ERR_DEVICE;
+    if (!ensure_words(ws, a, prezero)) return FSZ_ERR_DEVICE;
     if (!next_epoch(ws, &a.epoch, &a.flag_epoch)) return FSZ_ERR_DEVICE;
-    a.flags = ws->d_flags;
-    a.ticket = ws->d_ticket;
     a.final = d_final;
-    hipError_t e;
-    if (prezero) {
-        e = launch_decompress_prezero(a, aligned(d_out, 16), ws->stream);
-    } else if (tuning().dec_prescan && tuning().staged_decompress && n >= tuning().dec_lookback_below) {
-        // chunk offsets from the rate header first (chunks of 32 or 64 tiles)
-        if (!grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + std::max<uint64_t>(ceil_div(a.ntiles, 32), 1),
-                  ws->stream))
-            return FSZ_ERR_DEVICE;
-        e = launch_decompress_prescan(a, ws->d_offs, aligned(d_out, 16), n < tuning().dec_direct_below, ws->stream);
-    } else {
-        e = launch_decompress(a, aligned(d_out, 16), tuning().staged_decompress, ws->stream);
-    }
+    const hipError_t e = prezero ? launch_decompress_prezero(a, ws->d_offs, aligned(d_out, 16), ws->stream)
+                                 : launch_decompress(a, ws->d_offs, aligned(d_out, 16), false, ws->stream);
     if (!ok(e)) return FSZ_ERR_DEVICE;
     *epoch_out = a.epoch;
     return FSZ_OK;
@@ -378,7 +363,7 @@ fsz_status enqueue_decompress_config(Workspace *ws, const void *d_cmp, uint64_t 
     a.n = n;
     a.ntiles = ceil_div(n, (uint64_t)block * tile_blocks);
     a.nblocks = ceil_div(n, (uint64_t)block);
-    const bool prescan = tuning().dec_prescan && n >= tuning().cfg_dec_lookback_below;
+    const bool prescan = n >= tuning().cfg_dec_lookback_below;
     const uint64_t chunk_segs = 64ull * (uint64_t)(prescan ? kCfgDecWaves : cfg_dec_lookback_waves(n));
     a.nchunks = n ? ceil_div(ceil_div(n, kBlock), chunk_segs) : 1;
     a.data0 = kHeaderBytes + pad16(a.nblocks);
@@ -386,7 +371,6 @@ fsz_status enqueue_decompress_config(Workspace *ws, const void *d_cmp, uint64_t 
     a.tile_end = a.ntiles;
     a.elem_begin = 0;
     a.elem_end = n;
-    a.range_base = nullptr;
     a.cfg_flags = cfg_flag_bits(block, tile_blocks);
     if (!ensure_flags(ws, a.nchunks)) return FSZ_ERR_DEVICE;
     if (!next_epoch(ws, &a.epoch, &a.flag_epoch)) return FSZ_ERR_DEVICE;
@@ -422,20 +406,12 @@ fsz_status enqueue_decompress_range(Workspace *ws, const void *d_cmp, uint64_t c
     a.tile_end = end > begin ? ceil_div(end, kTile) : a.tile_begin;
     a.elem_begin = begin;
     a.elem_end = end;
-    const uint64_t tiles = a.tile_end - a.tile_begin;
-    a.nchunks = tiles ? ceil_div(tiles, kTilesPerChunk) : 1;
-    if (!ws->d_range && !ok(hipMalloc(&ws->d_range, (1 + kStatsMaxBlocks) * sizeof(unsigned long long))))
-        return FSZ_ERR_DEVICE;
-    if (!ok(launch_range_base(a, ws->d_range, ws->d_range + 1, ws->stream))) return FSZ_ERR_DEVICE;
-    a.range_base = ws->d_range;
-    if (!ensure_flags(ws, std::max<uint64_t>(a.nchunks, ceil_div(tiles, kTilesPerWave)))) return FSZ_ERR_DEVICE;
+    if (!ensure_words(ws, a, false)) return FSZ_ERR_DEVICE;
     if (!next_epoch(ws, &a.epoch, &a.flag_epoch)) return FSZ_ERR_DEVICE;
-    a.flags = ws->d_flags;
-    a.ticket = ws->d_ticket;
     a.final = d_final;
     // 16-byte stores need the field's element 0 (d_out - begin) 16-byte aligned
     const bool al16 = ((reinterpret_cast<uintptr_t>(d_out) - 4 * (uintptr_t)begin) & 15u) == 0;
-    if (!ok(launch_decompress(a, al16, tuning().staged_decompress, ws->stream))) return FSZ_ERR_DEVICE;
+    if (!ok(launch_decompress(a, ws->d_offs, al16, true, ws->stream))) return FSZ_ERR_DEVICE;
     return FSZ_OK;
 }
 

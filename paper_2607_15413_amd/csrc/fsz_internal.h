@@ -84,14 +84,14 @@ struct DecompressArgs {
     uint64_t cmp_size;
     float *out;  // element elem_begin of the field
     uint64_t n, ntiles, nblocks, nchunks, data0;
-    // Decoded range: tiles [tile_begin, tile_end) (chunks count from
-    // tile_begin), elements [elem_begin, elem_end) written.  range_base: the
-    // byte offset of tile_begin's data after data0 (device; null = 0 for a
-    // whole-field decode, which also checks the stream's total and padding).
+    // Decoded range: tiles [tile_begin, tile_end), elements [elem_begin,
+    // elem_end) written (a whole field: all of them; the stream's total and
+    // padding are then checked too).  The launch fills in the chunks that hold
+    // them, [chunk_begin, nchunks).
     uint64_t tile_begin, tile_end, elem_begin, elem_end;
-    const unsigned long long *range_base;
+    uint64_t chunk_begin;
     uint32_t cfg_flags;  // tile-configuration decoders: the header flags bits 2-4 required
-    // Whole-field decodes with the offsets pre-pass, which writes them: the
+    // Decodes with the offsets pre-pass, which writes them: the
     // bytes of each group of 2^group_shift chunks (bit 63: a reserved rate-byte
     // bit) and each chunk's byte offset inside its group.
     const unsigned long long *groups;
@@ -164,17 +164,20 @@ hipError_t launch_compress(const CompressArgs &a, bool in_aligned16, bool staged
 // The five-read baseline: four evaluation launches, then the encode launch
 // (a.nchunks counts chunks of kTilesPerChunk tiles).
 hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bool in_aligned16, hipStream_t s);
-hipError_t launch_decompress(const DecompressArgs &a, bool out_aligned16, bool staged, hipStream_t s);
-// Whole-field decompression with the chunk offsets computed first from the
-// rate header (no lookback in the decoder): words has room for kMaxGroupWords
-// words and one per chunk of 32 tiles.  direct: one chunk of 32 tiles
-// per workgroup instead of the persistent grid over chunks of 64 tiles.
+// Decompression of a.tile_begin .. a.tile_end (range: of a part of the field).
+// One launch whose workgroups add up the rate bytes before their chunk
+// themselves while those are few (decode_by_prefix); otherwise the offsets
+// pre-pass and a decoder, one chunk of 32 tiles per workgroup or, from
+// dec_direct_below elements, a persistent grid over chunks of 64.  words
+// (pre-pass only): kMaxGroupWords words and one per chunk of 32 tiles up to
+// tile_end.
 constexpr uint64_t kMaxGroupWords = 512;
-hipError_t launch_decompress_prescan(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
-                                     bool direct, hipStream_t s);
-// Pre-zeroed decompression (Sec. III-A): a fill of out[0, n) with +0.0, then
-// the decoder that skips waves whose tiles are all zero.
-hipError_t launch_decompress_prezero(const DecompressArgs &a, bool out_aligned16, hipStream_t s);
+hipError_t launch_decompress(const DecompressArgs &a, unsigned long long *words, bool out_aligned16, bool range,
+                             hipStream_t s);
+// Pre-zeroed decompression (Sec. III-A): a fill of out[0, n) with +0.0, the
+// offsets pre-pass, then the decoder that skips waves whose tiles are all zero.
+hipError_t launch_decompress_prezero(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
+                                     hipStream_t s);
 // Tile configurations (Sec. VI-C): one chunk of kCfgWaves x 64 32-element segments per
 // workgroup (a.nchunks counts those; for the decoder kCfgDecWaves x 64), block in {32, 64},
 // tile_blocks in {4, 8, 16}.  A
@@ -205,10 +208,6 @@ inline bool cfg_supported(int block, int tile_blocks)
 {
     return (block == 32 || block == 64) && (tile_blocks == 4 || tile_blocks == 8 || tile_blocks == 16);
 }
-// Byte offset of tile_begin's data: a reduction of the block sizes before it
-// over the rate header into *range_base (partials: kStatsMaxBlocks words).
-hipError_t launch_range_base(const DecompressArgs &a, unsigned long long *range_base, unsigned long long *partials,
-                             hipStream_t s);
 // Range pass + flag clear, per-job stats, then the batched kernel.
 // Compress-only batches with 16-byte aligned inputs run a persistent
 // pipelined kernel, decompress-only batches a persistent decoder, mixed
@@ -236,41 +235,46 @@ fsz_status check_decompress_args(const void *d_cmp, size_t cmp_size, const float
 bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t segs);
 
 // Launch tuning knobs, process-wide, read once from the environment:
-// FSZ_STAGED (letters c / d / l: stage compress output / decompress output /
-// compress input through LDS), FSZ_PIPE (0: no pipelined persistent
+// FSZ_STAGED (letters c / l: stage compress output / compress input through
+// LDS), FSZ_PIPE (0: no pipelined persistent
 // compression for 16-byte aligned inputs), FSZ_PIPE_WAVES (its waves per
-// workgroup: 1, 2, 4 or 8), FSZ_DEC_WAVES (waves per workgroup of the
-// default format's whole-field lookback decoder: 4, 8 or 16, for every size),
-// FSZ_DEC_WIDE_ABOVE (16-wave chunks above this many decoded elements, else 8,
-// for that decoder without FSZ_DEC_WAVES and for random access; for the tile
-// configurations' lookback form 16, else 4),
-// FSZ_DEC_LOOKBACK_BELOW and FSZ_CFG_DEC_LOOKBACK_BELOW (whole-field decodes of
-// the default format / the tile configurations below this many elements use
+// workgroup: 1, 2, 4 or 8), FSZ_DEC_WIDE_ABOVE (the tile configurations'
+// lookback decoder: 16-wave chunks above this many elements, else 4),
+// FSZ_CFG_DEC_LOOKBACK_BELOW (decodes of
+// the tile configurations below this many elements use
 // the lookback decoder, larger ones the offsets pre-pass), FSZ_DEC_DIRECT_BELOW
 // (pre-pass decodes below this size: one chunk per workgroup), FSZ_GRID_FACTOR
 // (persistent workgroups per CU slot,
 // default 1) and FSZ_PREZERO_CR (whole-field decodes of streams above this
-// compression ratio, judged from the buffer size, use the pre-zeroed decoder)
-// and FSZ_DEC_PRESCAN (0: whole-field decodes find chunk offsets by lookback
-// instead of the offsets pre-pass).
+// compression ratio, judged from the buffer size, use the pre-zeroed decoder).
 struct Tuning {
     bool staged_compress = true;
-    bool staged_decompress = true;
     bool staged_compress_loads = true;
     bool pipe_compress = true;  // persistent compression with asynchronous LDS prefetch
     int pipe_waves = 9;         // pipelined compression: data waves per workgroup (1, 2, 4, 8), or 9 / 7:
                                 // 8 / 7 data waves and a control wave (compress_ctrl_kernel)
-    int dec_waves = 0;          // waves per workgroup of the lookback decoder (4, 8, 16; 0: by size)
-    uint64_t dec_wide_above = 1ull << 21;  // by size: 16 waves above this many decoded elements, else 8
-                                           // (tile configurations: 16, else 4)
+    uint64_t dec_wide_above = 1ull << 21;  // tile configurations, lookback form: 16 waves above, else 4
     int grid_factor = 1;
     double prezero_min_cr = 0.0;  // whole-field decodes pre-zero above this CR (0: never)
-    bool dec_prescan = true;      // whole-field decodes take chunk offsets from a pre-pass (no lookback)
-    uint64_t dec_lookback_below = 1ull << 23;      // ... except fields below this many elements (one launch)
-    uint64_t cfg_dec_lookback_below = 1ull << 23;  // the same for the tile configurations
+    uint64_t cfg_dec_lookback_below = 1ull << 23;  // tile configurations: lookback below, pre-pass from here
     uint64_t dec_direct_below = 1ull << 26;    // pre-pass decodes below this size: one chunk per workgroup
 };
 const Tuning &tuning();
+
+// Whether a decode of tiles [t0, t1) needs no offsets pre-pass: every workgroup
+// reads the rate bytes before its chunk (8 per tile) itself.  That costs each
+// of them a pass over at most kPrefixBytes and all of them together the reads
+// summed here (for chunks of 64 tiles), against about 3.5 us for the pre-pass
+// launch.  Whole fields, GRF at REL 1e-3, prefix / pre-pass in us per call: 2^20
+// 6.4 / 8.7, 2^21 7.4 / 9.1, 2^22 9.0 / 9.9 (16.8 MB summed), 6.3 M 12.6 / 11.6
+// (38 MB), 2^23 14.7 / 12.3; a range of 2^20 elements at 2^22 8.6 / 9.4 (9 MB),
+// one of 1.7 M at 7.6 M 12.8 / 11.6 (27 MB).
+constexpr uint64_t kPrefixBytes = 1ull << 18;
+inline bool decode_by_prefix(uint64_t t0, uint64_t t1)
+{
+    const uint64_t chunks = ceil_div(t1 - t0, 64);
+    return t1 * kBlocksPerTile <= kPrefixBytes && chunks * (t0 + t1) / 2 * kBlocksPerTile <= (18ull << 20);
+}
 
 // Waves per workgroup of the configuration decoder's lookback form for an
 // n-element field (the pre-pass form always takes kCfgDecWaves).

@@ -136,6 +136,8 @@ typedef __attribute__((address_space(1))) uint8_t g_u8;
 typedef __attribute__((address_space(1))) uint32_t g_u32;
 typedef __attribute__((address_space(1))) float g_f32;
 typedef __attribute__((address_space(1))) u32x4 g_u32x4;
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+typedef __attribute__((address_space(1))) u32x4_a4 g_u32x4_a4;  // 16 bytes at a 4-byte aligned address
 
 // Store of nw dwords from a wave's LDS staging area to global memory at a
 // 4-byte aligned address g, by the whole wave: 4-byte stores up to the first
@@ -1699,6 +1701,15 @@ __global__ __launch_bounds__(W * 64) void compress_pipe2_kernel(CompressArgs a)
 
 // ------------------------------------------------------------------ decompress
 
+// Four rate bytes: sum of r + (r > 0) over them, added to acc (a block of rate
+// r > 0 is one sign word and r planes long).
+__device__ __forceinline__ uint32_t rate_units(uint32_t w, uint32_t acc)
+{
+    const uint32_t x = w & 0x1F1F1F1Fu;
+    const uint32_t nz = ((x + 0x1F1F1F1Fu) >> 5) & 0x01010101u;
+    return (uint32_t)__builtin_popcount(nz) + __builtin_amdgcn_sad_u8(x, 0u, acc);
+}
+
 // Per-lane state of one chunk between the size pass and the decode pass.
 struct DecChunk {
     uint64_t chunk;
@@ -1707,12 +1718,23 @@ struct DecChunk {
     int order2, cent;
 };
 
-// Slots rotate from chunk to chunk.  The decoders with the offsets pre-pass pass
-// one barrier per chunk, so a wave may be one chunk ahead of another and three
-// slots are in use; the lookback decoders pass several and use two.
+// How a decoder's workgroup learns its chunk's byte offset.
+enum DecOffsets {
+    kByLookback,  // decoupled lookback over the chunks' aggregates (batches)
+    kByGroups,    // group totals and in-group offsets from dec_groups_kernel, chunk after chunk
+    kByGroupsOnce,  // the same for a workgroup's only chunk
+    kByPrefix     // its own sum over the rate bytes before the chunk
+};
+
+// Slots rotate from chunk to chunk.  The persistent decoder with the offsets
+// pre-pass passes one barrier per chunk, so a wave may be one chunk ahead of
+// another and three slots are in use; the lookback decoders pass several and
+// use two.
 template <int W>
 struct DecompressShared {
     uint32_t wave_total[3][W];
+    unsigned long long wave_prefix[W];  // kByPrefix, kByGroupsOnce: the waves' shares of the sum, and
+    uint32_t wave_bad[W];               // whether they saw a reserved rate-byte bit
     unsigned long long group_base[3];
     int bad[2];
     unsigned long long base;
@@ -1740,45 +1762,96 @@ __device__ __forceinline__ void groups_advance(const unsigned long long *groups,
     c.next = g;
 }
 
-// Run by one whole wave with the cursor at the last chunk's group: the call's
-// outcome.  The stream is sound if no rate byte has a reserved bit, the sizes
-// add up to the header's total and the rate header's padding (at most 15
-// bytes, one lane each) is zero.
-__device__ __forceinline__ void finish_decode(const DecompressArgs &a, const GroupCursor &c, uint64_t end,
-                                              uint64_t total)
+// Run by one whole wave that knows of every rate byte up to the last decoded
+// tile: the call's outcome.  The stream is sound if none of them has a reserved
+// bit and, for a whole field, the sizes add up to the header's total and the
+// rate header's padding (at most 15 bytes, one lane each) is zero; for a range,
+// if its data ends inside the stream.
+template <bool RANGE>
+__device__ __forceinline__ void finish_decode(const DecompressArgs &a, bool bad, uint64_t end, uint64_t total)
 {
-    const uint64_t k = kHeaderBytes + a.nblocks + __lane_id();
-    const bool padbad = __ballot(__lane_id() < 16 && k < a.data0 && a.cmp[k < a.data0 ? k : 0] != 0) != 0;
-    const bool bad = c.bad || padbad || (a.ntiles && (a.groups[c.next] >> 63) != 0) || a.data0 + end != total;
+    if (RANGE) {
+        bad = bad || a.data0 + end > total;
+    } else {
+        const uint64_t k = kHeaderBytes + a.nblocks + __lane_id();
+        const bool pad = __lane_id() < 16 && k < a.data0;
+        bad = bad || a.data0 + end != total || __ballot(a.cmp[pad ? k : 0] != 0 && pad) != 0;
+    }
     if (__lane_id() == 0)
         write_final(a.final, total, bad ? (uint32_t)FSZ_ERR_CORRUPT : (uint32_t)FSZ_OK, a.epoch);
 }
 
 // Decompression steps 1-2 (Sec. III-A): rate bytes and tile metadata ->
-// block and tile sizes -> this chunk's aggregate, published at once so that
-// successors' lookbacks rarely wait.
+// block and tile sizes, and the chunk's offset (kByLookback: the chunk's
+// aggregate, published at once so that successors' lookbacks rarely wait).
 // RANGE: decode the tiles [a.tile_begin, a.tile_end) only (random access);
-// otherwise the whole field (the range fields are not read).
-// The lane's rate byte of `chunk` (0 past the end or outside a range).
-template <int W, bool RANGE = false>
+// otherwise the whole field (the range fields are not read).  Chunks count
+// from the field's first tile, but from tile_begin with kByPrefix.
+template <int W, bool RANGE, int OFF>
+__device__ __forceinline__ uint64_t dec_chunk_tile0(const DecompressArgs &a, uint64_t chunk)
+{
+    return (RANGE && OFF == kByPrefix ? a.tile_begin : 0) + chunk * (kTilesPerWave * W);
+}
+
+// The lane's rate byte of `chunk` (0 past the end of the field or the range).
+template <int W, bool RANGE, int OFF>
 __device__ __forceinline__ uint32_t dec_rate_byte(const DecompressArgs &a, uint64_t chunk)
 {
     const int tid = threadIdx.x;
-    const int w = tid >> 6;
     const int lane = tid & 63;
-    const uint64_t tile =
-        (RANGE ? a.tile_begin : 0) + chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave + (lane >> 3);
+    const uint64_t tile = dec_chunk_tile0<W, RANGE, OFF>(a, chunk) + (uint64_t)(tid >> 3);
     const bool tile_ok = tile < (RANGE ? a.tile_end : a.ntiles);
     const uint64_t gblock = tile * kBlocksPerTile + (lane & 7);
     const bool blk_ok = (RANGE ? tile_ok : true) && gblock < a.nblocks;
     return blk_ok ? ((const g_u8 *)a.cmp)[kHeaderBytes + gblock] : 0u;
 }
 
+// Bytes of the tiles before `tile0` that this thread's share of the rate
+// header adds up to (16 bytes, i.e. two tiles, per load; all of them whole
+// tiles), and whether a reserved bit is set in it.
+template <int THREADS>
+__device__ __forceinline__ uint32_t dec_prefix_share(const DecompressArgs &a, uint64_t tile0, uint32_t &bad)
+{
+    const g_u32 *p = (const g_u32 *)(a.cmp + kHeaderBytes);
+    const uint32_t n16 = (uint32_t)(tile0 / 2);
+    uint32_t units = 0, cents = 0;
+    auto take = [&](uint32_t w, bool head) {
+        bad |= w & (head ? 0xE0E0E020u : 0xE0E0E0E0u);
+        units = rate_units(w, units);
+        if (head) cents += (w >> 6) & 1u;
+    };
+    auto take4 = [&](const u32x4 &v) {
+        take(v.x, true);
+        take(v.y, false);
+        take(v.z, true);
+        take(v.w, false);
+    };
+    uint32_t i = threadIdx.x;
+    for (; i + 3 * THREADS < n16; i += 4 * THREADS) {
+        const u32x4 v0 = *(const g_u32x4_a4 *)(p + 4 * (uint64_t)i);
+        const u32x4 v1 = *(const g_u32x4_a4 *)(p + 4 * (uint64_t)(i + THREADS));
+        const u32x4 v2 = *(const g_u32x4_a4 *)(p + 4 * (uint64_t)(i + 2 * THREADS));
+        const u32x4 v3 = *(const g_u32x4_a4 *)(p + 4 * (uint64_t)(i + 3 * THREADS));
+        take4(v0);
+        take4(v1);
+        take4(v2);
+        take4(v3);
+    }
+    for (; i < n16; i += THREADS) take4(u32x4(*(const g_u32x4_a4 *)(p + 4 * (uint64_t)i)));
+    if ((tile0 & 1) && threadIdx.x == 0) {  // the odd tile
+        take(p[4 * (uint64_t)n16], true);
+        take(p[4 * (uint64_t)n16 + 1], false);
+    }
+    return 4u * units + 4u * cents;
+}
+
 // rb: the lane's rate byte from dec_rate_byte (loaded ahead by the caller).
-// PRESCAN: the offsets pre-pass has summed the groups of chunks and placed
+// kByGroups: the offsets pre-pass has summed the groups of chunks and placed
 // every chunk inside its group; wave 0 brings its group cursor up to the
-// chunk's group instead of publishing an aggregate.
-template <int W, bool RANGE = false, bool PRESCAN = false>
+// chunk's group.  kByGroupsOnce: the group totals before the chunk's are read
+// by all threads at once.  kByPrefix: every thread adds up its share of the rate bytes
+// before the chunk.
+template <int W, bool RANGE, int OFF>
 __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t chunk, uint32_t rb, int slot,
                                               DecompressShared<W> &sh, GroupCursor &gc)
 {
@@ -1786,8 +1859,7 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
     const int w = tid >> 6;
     const int lane = tid & 63;
     const int j = lane & 7;
-    const uint64_t tile =
-        (RANGE ? a.tile_begin : 0) + chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave + (lane >> 3);
+    const uint64_t tile = dec_chunk_tile0<W, RANGE, OFF>(a, chunk) + (uint64_t)(tid >> 3);
     const bool tile_ok = tile < (RANGE ? a.tile_end : a.ntiles);
     const uint64_t gblock = tile * kBlocksPerTile + j;
     const bool blk_ok = (RANGE ? tile_ok : true) && gblock < a.nblocks;
@@ -1805,7 +1877,7 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
     d.wave_total = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
     d.blk_off = d.tile_excl + group_excl_scan(S, j) + 4u * d.cent;
     d.base = 0;
-    if (PRESCAN) {
+    if (OFF == kByGroups) {
         if (w == 0) {
             groups_advance(a.groups, chunk >> a.group_shift, gc);
             if (lane == 0) sh.group_base[slot] = gc.sum + a.offsets[chunk];
@@ -1813,6 +1885,41 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
         if (lane == 0) sh.wave_total[slot][w] = d.wave_total;
         lds_barrier();
         d.base = sh.group_base[slot];
+        return d;
+    }
+    if constexpr (OFF == kByPrefix || OFF == kByGroupsOnce) {
+        bool seen;
+        unsigned long long psum;
+        if (OFF == kByPrefix) {
+            uint32_t pbad = 0;
+            const uint32_t share = dec_prefix_share<W * 64>(a, dec_chunk_tile0<W, RANGE, OFF>(a, chunk), pbad);
+            psum = (uint32_t)__builtin_amdgcn_readlane(wave_incl_scan((int)share), 63);
+            seen = bad || pbad != 0;
+        } else {
+            const uint32_t g = (uint32_t)(chunk >> a.group_shift);
+            unsigned long long v = 0, flags = 0;
+            for (uint32_t k = tid; k < g; k += W * 64) {
+                const unsigned long long t = a.groups[k];
+                v += t & ~kGroupBad;
+                flags |= t;
+            }
+            psum = wave_sum_u64(v);
+            seen = (flags & kGroupBad) != 0;
+            d.base = a.offsets[chunk];
+            gc.next = g;
+        }
+        const bool wave_bad = __ballot(seen) != 0;
+        if (lane == 0) {
+            sh.wave_prefix[w] = psum;
+            sh.wave_total[slot][w] = d.wave_total;
+            sh.wave_bad[w] = wave_bad ? 1u : 0u;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            d.base += sh.wave_prefix[k];
+            gc.bad = gc.bad || sh.wave_bad[k] != 0;
+        }
         return d;
     }
     const bool wave_bad = __ballot(bad) != 0;
@@ -1830,10 +1937,10 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
     return d;
 }
 
-// Decompression step 3 (Sec. III-A): the chunk's byte offset from the
-// lookback (wave 0; the workgroup waits at one barrier), then where the
-// wave's share of the chunk's data starts.  The workgroup owning the last
-// chunk reports the outcome.  live: the wave has blocks to decode.
+// Decompression step 3 (Sec. III-A): where the wave's share of the chunk's data
+// starts (kByLookback: the chunk's offset from the lookback of wave 0; the
+// workgroup waits at one barrier).  The workgroup owning the last chunk
+// reports the outcome.  live: the wave has blocks to decode, inside the stream.
 // PREZERO: the output was cleared to +0.0 before the launch (Sec. III-A, for
 // highly compressible streams); a wave whose blocks all have rate 0 and whose
 // tiles are all uncentred decodes to q = 0, i.e. +0.0 everywhere, and is not
@@ -1844,7 +1951,7 @@ struct DecPlace {
     bool live;
 };
 
-template <int W, bool RANGE = false, bool PREZERO = false, bool PRESCAN = false>
+template <int W, bool RANGE, bool PREZERO, int OFF>
 __device__ __forceinline__ DecPlace dec_place(const DecompressArgs &a, const DecChunk &d, int slot, uint64_t total,
                                               DecompressShared<W> &sh, const GroupCursor &gc)
 {
@@ -1858,42 +1965,26 @@ __device__ __forceinline__ DecPlace dec_place(const DecompressArgs &a, const Dec
         if (k < w) wave_base += sh.wave_total[slot][k];
         chunk_total += sh.wave_total[slot][k];
     }
-    if (PRESCAN) {  // placed by the pre-pass
-        DecPlace p;
-        p.tile0 = d.chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
-        p.wave_data = a.cmp + a.data0 + d.base + wave_base;
-        p.live = a.data0 + d.base + chunk_total <= total && p.tile0 < a.ntiles;
-        if (w == 0 && d.chunk == a.nchunks - 1) finish_decode(a, gc, d.base + chunk_total, total);
-        if (PREZERO && p.live) {
-            const uint64_t gblock = (p.tile0 + (lane >> 3)) * kBlocksPerTile + j;
-            p.live = __ballot(gblock < a.nblocks && (d.r != 0 || d.cent != 0)) != 0;
+    uint64_t base = d.base;
+    bool bad = false;
+    if (OFF == kByLookback) {
+        bad = sh.bad[slot] != 0;
+        if (w == 0) {
+            const Prefix pre = lookback_wait(a.flags, d.chunk, a.flag_epoch, chunk_total, bad);
+            if (lane == 0) sh.base = pre.excl;
+            if (d.chunk == a.nchunks - 1) finish_decode<RANGE>(a, pre.err, pre.excl + chunk_total, total);
         }
-        return p;
+        lds_barrier();
+        base = sh.base;
+    } else if (w == 0 && d.chunk == a.nchunks - 1) {
+        const bool seen = gc.bad || ((OFF == kByGroups || OFF == kByGroupsOnce) && (a.groups[gc.next] & kGroupBad) != 0);
+        finish_decode<RANGE>(a, seen, base + chunk_total, total);
     }
-    const bool bad = sh.bad[slot] != 0;
-    const uint64_t base0 = RANGE ? *a.range_base : 0;  // data of tiles before the range
-    if (w == 0) {
-        const Prefix pre = lookback_wait(a.flags, d.chunk, a.flag_epoch, chunk_total, bad);
-        if (lane == 0) {
-            sh.base = base0 + pre.excl;
-            if (d.chunk == a.nchunks - 1) {
-                bool ok;
-                if (RANGE) {  // a range: its data lies inside the stream
-                    ok = !pre.err && a.data0 + base0 + pre.excl + chunk_total <= total;
-                } else {  // the whole field: the sizes add up to the stream's total, padding is zero
-                    ok = !pre.err && a.data0 + pre.excl + chunk_total == total;
-                    for (uint64_t k = kHeaderBytes + a.nblocks; ok && k < a.data0; k++) ok = a.cmp[k] == 0;
-                }
-                write_final(a.final, total, ok ? (uint32_t)FSZ_OK : (uint32_t)FSZ_ERR_CORRUPT, a.epoch);
-            }
-        }
-    }
-    lds_barrier();
-    const uint64_t base = sh.base;
     DecPlace p;
-    p.tile0 = (RANGE ? a.tile_begin : 0) + d.chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
+    p.tile0 = dec_chunk_tile0<W, RANGE, OFF>(a, d.chunk) + (uint64_t)w * kTilesPerWave;
     p.wave_data = a.cmp + a.data0 + base + wave_base;
-    p.live = !(bad || a.data0 + base + chunk_total > total || p.tile0 >= (RANGE ? a.tile_end : a.ntiles));
+    p.live = !bad && a.data0 + base + chunk_total <= total && p.tile0 < (RANGE ? a.tile_end : a.ntiles) &&
+             (!RANGE || p.tile0 + kTilesPerWave > a.tile_begin);
     if (PREZERO && p.live) {
         const uint64_t gblock = (p.tile0 + (lane >> 3)) * kBlocksPerTile + j;
         p.live = __ballot(gblock < a.nblocks && (d.r != 0 || d.cent != 0)) != 0;
@@ -1904,7 +1995,7 @@ __device__ __forceinline__ DecPlace dec_place(const DecompressArgs &a, const Dec
 // Decompression steps 4-5 of a live wave: bit-unshuffle, inverse cross-block
 // prediction (one inclusive scan for LZ1, two for LZ2, plus the tile mean),
 // x' = (float)q * E.
-template <bool ALIGNED, bool STAGED, int W, bool RANGE = false>
+template <bool ALIGNED, int W, bool RANGE>
 __device__ __forceinline__ void dec_decode(const DecompressArgs &a, const DecChunk &d, const DecPlace &p, float E,
                                            bool indep, uint32_t *st)
 {
@@ -1985,25 +2076,9 @@ __device__ __forceinline__ void dec_decode(const DecompressArgs &a, const DecChu
         }
     }
 
-    const uint64_t eblk = gblock * kBlock;
-    const int cnt = eblk >= a.n ? 0 : (a.n - eblk >= kBlock ? kBlock : (int)(a.n - eblk));
     // element e of the field goes to out[e - eb], for eb <= e < ee
     g_f32 *out = (g_f32 *)a.out;
     const uint64_t eb = RANGE ? a.elem_begin : 0, ee = RANGE ? a.elem_end : a.n;
-    if (!STAGED) {  // lane-per-block stores, 8 x 16 B per lane
-        if (ALIGNED && cnt == 32 && eblk >= eb && eblk + 32 <= ee) {
-            g_u32x4 *p = (g_u32x4 *)(out + (eblk - eb));
-#pragma unroll
-            for (int k = 0; k < 8; k++)
-                p[k] = u32x4{__float_as_uint(xo[4 * k]), __float_as_uint(xo[4 * k + 1]), __float_as_uint(xo[4 * k + 2]),
-                             __float_as_uint(xo[4 * k + 3])};
-        } else {
-#pragma unroll
-            for (int i = 0; i < 32; i++)
-                if (i < cnt && eblk + i >= eb && eblk + i < ee) out[eblk + i - eb] = xo[i];
-        }
-        return;
-    }
     // ---- write back through LDS with coalesced stores
 #pragma unroll
     for (int k = 0; k < 8; k++)
@@ -2063,17 +2138,18 @@ __device__ __forceinline__ int dec_header(const DecompressArgs &a, float &E, uin
     return FSZ_OK;
 }
 
-// Persistent decompression kernel: the size pass of the next chunk (which
-// publishes its aggregate) runs before the decode of the current one.
-// W waves per workgroup; a chunk is 8 tiles per wave (a.nchunks counts chunks
-// of that size).
-template <bool ALIGNED, bool STAGED, int W, bool RANGE = false, bool PREZERO = false, bool PRESCAN = false>
+// Persistent decompression kernel for the offsets pre-pass: the size pass of
+// the next chunk runs before the decode of the current one.  W waves per
+// workgroup; a chunk is 8 tiles per wave; chunks [a.chunk_begin, a.nchunks).
+// With every chunk's offset known no workgroup waits on another, and a static
+// schedule (chunk = workgroup + k * grid) needs no ticket.
+template <bool ALIGNED, int W, bool RANGE, bool PREZERO>
 __global__ __launch_bounds__(W * 64) void decompress_kernel(DecompressArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t stage[STAGED ? W * kStageWaveDwords : 4];
+    __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
     __shared__ DecompressShared<W> sh;
     const int tid = threadIdx.x;
-    uint32_t *st = stage + (STAGED ? (tid >> 6) * kStageWaveDwords : 0);
+    uint32_t *st = stage + (tid >> 6) * kStageWaveDwords;
 
     float E;
     uint64_t total;
@@ -2083,26 +2159,19 @@ __global__ __launch_bounds__(W * 64) void decompress_kernel(DecompressArgs a)
         if (tid == 0 && blockIdx.x == 0) write_final(a.final, 0, hst, a.epoch);
         return;
     }
-
-    // Chunks come from the ticket counter, in increasing order over the
-    // running workgroups, so that lookbacks only wait on running chunks.  With
-    // offsets from the pre-pass no workgroup waits on another, and a static
-    // schedule (chunk = workgroup + k * grid) saves the ticket's round trip.
-    int tslot = 0;
-    const uint64_t takes = a.nchunks + gridDim.x;
-    uint64_t cur = PRESCAN ? (uint64_t)blockIdx.x : next_ticket(a.ticket, takes, sh, tslot);
+    uint64_t cur = a.chunk_begin + blockIdx.x;
     if (cur >= a.nchunks) return;
     int slot = 0;
     GroupCursor gc;
-    DecChunk dc = dec_sizes<W, RANGE, PRESCAN>(a, cur, dec_rate_byte<W, RANGE>(a, cur), slot, sh, gc);
+    DecChunk dc = dec_sizes<W, RANGE, kByGroups>(a, cur, dec_rate_byte<W, RANGE, kByGroups>(a, cur), slot, sh, gc);
     for (;;) {
-        const uint64_t nxt = PRESCAN ? cur + gridDim.x : next_ticket(a.ticket, takes, sh, tslot);
-        const int nslot = PRESCAN ? (slot == 2 ? 0 : slot + 1) : slot ^ 1;
+        const uint64_t nxt = cur + gridDim.x;
+        const int nslot = slot == 2 ? 0 : slot + 1;
         DecChunk dn;
         if (nxt < a.nchunks)
-            dn = dec_sizes<W, RANGE, PRESCAN>(a, nxt, dec_rate_byte<W, RANGE>(a, nxt), nslot, sh, gc);
-        const DecPlace pl = dec_place<W, RANGE, PREZERO, PRESCAN>(a, dc, slot, total, sh, gc);
-        if (pl.live) dec_decode<ALIGNED, STAGED, W, RANGE>(a, dc, pl, E, indep, st);
+            dn = dec_sizes<W, RANGE, kByGroups>(a, nxt, dec_rate_byte<W, RANGE, kByGroups>(a, nxt), nslot, sh, gc);
+        const DecPlace pl = dec_place<W, RANGE, PREZERO, kByGroups>(a, dc, slot, total, sh, gc);
+        if (pl.live) dec_decode<ALIGNED, W, RANGE>(a, dc, pl, E, indep, st);
         if (nxt >= a.nchunks) break;
         dc = dn;
         cur = nxt;
@@ -2130,15 +2199,6 @@ constexpr int kGroupTilesPerThread = 4;
 constexpr int kGroupTiles = kGroupThreads * kGroupTilesPerThread;
 constexpr uint64_t kMaxGroups = kMaxGroupWords;
 
-// Four rate bytes: sum of r + (r > 0) over them, added to acc (a block of rate
-// r > 0 is one sign word and r planes long).
-__device__ __forceinline__ uint32_t rate_units(uint32_t w, uint32_t acc)
-{
-    const uint32_t x = w & 0x1F1F1F1Fu;
-    const uint32_t nz = ((x + 0x1F1F1F1Fu) >> 5) & 0x01010101u;
-    return (uint32_t)__builtin_popcount(nz) + __builtin_amdgcn_sad_u8(x, 0u, acc);
-}
-
 // TPC tiles per decoder chunk; T blocks per tile of HB 32-element segments
 // each (the default format: 8 and 1; the tile configurations: the stream's).
 // The rate header lies inside the buffer (checked by the host), so any bytes
@@ -2157,6 +2217,7 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
     const int lane = tid & 63;
     const int w = tid >> 6;
     if (a.data0 > a.cmp_size) return;  // the decoder reports it
+    const uint64_t nb = a.tile_end < a.ntiles ? a.tile_end * T : a.nblocks;  // blocks of the tiles up to tile_end
     uint64_t run = 0;
     uint32_t bad = 0;
     for (uint32_t p = 0; p < passes; p++) {
@@ -2164,7 +2225,7 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
             (((uint64_t)blockIdx.x * passes + p) * kGroupThreads + (uint64_t)tid) * kGroupTilesPerThread;
         uint32_t units = 0, cents = 0;
         const g_u32 *rp = (const g_u32 *)(a.cmp + kHeaderBytes + tile0 * T);
-        if ((tile0 + kGroupTilesPerThread) * T <= a.nblocks) {
+        if ((tile0 + kGroupTilesPerThread) * T <= nb) {
             uint32_t rw[kWords];
 #pragma unroll
             for (int q = 0; q < kWords; q++) rw[q] = rp[q];
@@ -2175,8 +2236,8 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
                 units = rate_units(rw[q], units);
                 if (head) cents += (rw[q] >> 6) & 1u;
             }
-        } else if (tile0 * T < a.nblocks) {  // the field's last blocks, byte by byte
-            const uint64_t left = a.nblocks - tile0 * T;
+        } else if (tile0 * T < nb) {  // the last blocks, byte by byte
+            const uint64_t left = nb - tile0 * T;
             for (uint32_t k = 0; k < (uint32_t)left; k++) {
                 const uint32_t rb = ((const g_u8 *)rp)[k];
                 const bool head = k % T == 0;
@@ -2195,7 +2256,7 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
             if (k < w) wave_base += wsum[p & 1][k];
             ptotal += wsum[p & 1][k];
         }
-        if (tile0 < a.ntiles && (tile0 % TPC) == 0) offs[tile0 / TPC] = run + wave_base + incl - z;
+        if (tile0 < a.tile_end && (tile0 % TPC) == 0) offs[tile0 / TPC] = run + wave_base + incl - z;
         run += ptotal;
     }
     const bool wave_bad = __ballot(bad != 0) != 0;
@@ -2206,95 +2267,44 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
 #pragma unroll
         for (int k = 0; k < kWavesG; k++) any |= wbad[k];
         groups[blockIdx.x] = run | (any ? kGroupBad : 0ull);
-        if (a.ntiles == 0) offs[0] = 0;
+        if (a.tile_end == 0) offs[0] = 0;
     }
 }
 
-// Whole-field decoder for the offsets pre-pass, one chunk of 8*W tiles per
-// workgroup and no ticket: with every chunk's offset known there is no order
-// to keep, and the hardware dispatcher keeps the CUs busy.  Used for fields
-// too small to give a persistent grid several chunks per workgroup.  The size
-// pass needs nothing of the stream header but the room for the rate bytes, so
-// its loads go out before the header's have come back.
-template <bool ALIGNED, int W>
+// One chunk of 8*W tiles per workgroup and no order to keep: the hardware
+// dispatcher keeps the CUs busy.
+// kByGroupsOnce: the decoder behind the offsets pre-pass for fields too small to
+// give the persistent grid several chunks per workgroup.
+// kByPrefix: the only launch of a small decode.  Every workgroup adds up all
+// rate bytes before its chunk itself (at most kPrefixBytes, read from the L2
+// after the first workgroups; 8 VALU operations per 4 bytes), so nothing is
+// passed between workgroups: two dependent round trips to memory (rate bytes,
+// then the data words) where the ticket, the aggregate's two barriers and the
+// lookback of the earlier form were five (2^20 sinusoid 7.5 -> 6.1 us per call,
+// 2^16 6.6 -> 4.8, a range of 300 elements at 10^6 13.8 -> 6.5).
+// The size pass needs nothing of the stream header but the room for the rate
+// bytes, so its loads go out before the header's have come back.
+template <bool ALIGNED, int W, bool RANGE, int OFF>
 __global__ __launch_bounds__(W * 64) void decompress_direct_kernel(DecompressArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
     __shared__ DecompressShared<W> sh;
-    const uint64_t chunk = blockIdx.x;
+    const uint64_t chunk = a.chunk_begin + blockIdx.x;
     uint32_t *st = stage + (threadIdx.x >> 6) * kStageWaveDwords;
     GroupCursor gc;
     DecChunk dc;
     const bool room = a.data0 <= a.cmp_size;
-    if (room) dc = dec_sizes<W, false, true>(a, chunk, dec_rate_byte<W>(a, chunk), 0, sh, gc);
+    if (room) dc = dec_sizes<W, RANGE, OFF>(a, chunk, dec_rate_byte<W, RANGE, OFF>(a, chunk), 0, sh, gc);
     float E;
     uint64_t total;
     bool indep;
     const int hst = dec_header(a, E, total, indep);
     if (!room || hst != FSZ_OK) {
-        if (threadIdx.x == 0 && chunk == 0) write_final(a.final, 0, hst, a.epoch);
+        if (threadIdx.x == 0 && blockIdx.x == 0) write_final(a.final, 0, hst, a.epoch);
         return;
     }
-    const DecPlace pl = dec_place<W, false, false, true>(a, dc, 0, total, sh, gc);
-    if (pl.live) dec_decode<ALIGNED, true, W>(a, dc, pl, E, indep, st);
-}
-
-// ------------------------------------------------------------------ random-access decode
-
-// Byte offset of a range's first tile, from the rate header alone (the block
-// sizes of decompression step 2, Sec. III-A): each workgroup sums the sizes of
-// a grid-stride share of the blocks before tile_begin; a reserved rate-byte
-// bit sets bit 63 of the partial.
-__global__ __launch_bounds__(kStatsThreads) void range_partial_kernel(DecompressArgs a, unsigned long long *partials)
-{
-    const uint64_t nb = a.tile_begin * kBlocksPerTile;  // every tile before the last is whole
-    unsigned long long sum = 0;
-    uint32_t bad = 0;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += stride) {
-        if (kHeaderBytes + b >= a.cmp_size) {  // a stream shorter than its rate header
-            bad = 1;
-            break;
-        }
-        const uint32_t rb = a.cmp[kHeaderBytes + b];
-        const bool head = (b & (kBlocksPerTile - 1)) == 0;
-        bad |= head ? (rb & 0x20u) : (rb & 0xE0u);
-        sum += block_bytes(rb & 31u) + ((head && (rb & 0x40u)) ? 4u : 0u);
-    }
-    sum = wave_sum_u64(sum);
-    const bool wbad = __ballot(bad != 0) != 0;
-    __shared__ unsigned long long wsum[kStatsThreads / 64];
-    __shared__ uint32_t wflag[kStatsThreads / 64];
-    if ((threadIdx.x & 63) == 0) {
-        wsum[threadIdx.x >> 6] = sum;
-        wflag[threadIdx.x >> 6] = wbad ? 1u : 0u;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        uint32_t f = 0;
-        for (int k = 0; k < kStatsThreads / 64; k++) {
-            t += wsum[k];
-            f |= wflag[k];
-        }
-        partials[blockIdx.x] = t | ((unsigned long long)f << 63);
-    }
-}
-
-// Folds the partials into *out; a reserved bit anywhere makes the offset
-// 2^62, past any stream, so the decode reports a corrupt stream.
-__global__ __launch_bounds__(64) void range_final_kernel(const unsigned long long *partials, unsigned nparts,
-                                                         unsigned long long *out)
-{
-    unsigned long long t = 0;
-    bool bad = false;
-    for (unsigned i = threadIdx.x; i < nparts; i += 64) {
-        t += partials[i] & ~(1ull << 63);
-        bad = bad || (partials[i] >> 63) != 0;
-    }
-    t = wave_sum_u64(t);
-    bad = __ballot(bad) != 0;
-    if (threadIdx.x == 0) *out = bad ? (1ull << 62) : t;
+    const DecPlace pl = dec_place<W, RANGE, false, OFF>(a, dc, 0, total, sh, gc);
+    if (pl.live) dec_decode<ALIGNED, W, RANGE>(a, dc, pl, E, indep, st);
 }
 
 // ------------------------------------------------------------------ batched form
@@ -2426,7 +2436,6 @@ __device__ __forceinline__ DecompressArgs batch_decompress_args(const BatchArgs 
     a.tile_end = J.ntiles;
     a.elem_begin = 0;
     a.elem_end = J.n;
-    a.range_base = nullptr;
     a.cfg_flags = 0;
     a.epoch = b.epoch;
     a.flag_epoch = 1;
@@ -2473,9 +2482,9 @@ __global__ __launch_bounds__(W * 64) void batch_kernel(BatchArgs b)
             return;
         }
         GroupCursor gc;
-        const DecChunk dc = dec_sizes<W>(a, chunk, dec_rate_byte<W>(a, chunk), 0, sh.d, gc);
-        const DecPlace pl = dec_place<W>(a, dc, 0, total, sh.d, gc);
-        if (pl.live) dec_decode<ALIGNED, true, W>(a, dc, pl, E, indep, st);
+        const DecChunk dc = dec_sizes<W, false, kByLookback>(a, chunk, dec_rate_byte<W, false, kByLookback>(a, chunk), 0, sh.d, gc);
+        const DecPlace pl = dec_place<W, false, false, kByLookback>(a, dc, 0, total, sh.d, gc);
+        if (pl.live) dec_decode<ALIGNED, W, false>(a, dc, pl, E, indep, st);
     }
 }
 
@@ -2513,7 +2522,9 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(4))) voi
             if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, hst, a.epoch);
             have = false;
         } else {
-            if (!have) dc = dec_sizes<W>(a, chunk, dec_rate_byte<W>(a, chunk), slot, sh, gc);
+            if (!have)
+                dc = dec_sizes<W, false, kByLookback>(a, chunk, dec_rate_byte<W, false, kByLookback>(a, chunk), slot, sh,
+                                                      gc);
             bool next_have = false;
             DecChunk dn;
             if (nxt < b.total_chunks) {
@@ -2524,12 +2535,13 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(4))) voi
                 uint64_t total2;
                 bool indep2;
                 if (dec_header(a2, E2, total2, indep2) == FSZ_OK) {
-                    dn = dec_sizes<W>(a2, chunk2, dec_rate_byte<W>(a2, chunk2), slot ^ 1, sh, gc);
+                    dn = dec_sizes<W, false, kByLookback>(a2, chunk2, dec_rate_byte<W, false, kByLookback>(a2, chunk2),
+                                                      slot ^ 1, sh, gc);
                     next_have = true;
                 }
             }
-            const DecPlace pl = dec_place<W>(a, dc, slot, total, sh, gc);
-            if (pl.live) dec_decode<ALIGNED, true, W>(a, dc, pl, E, indep, st);
+            const DecPlace pl = dec_place<W, false, false, kByLookback>(a, dc, slot, total, sh, gc);
+            if (pl.live) dec_decode<ALIGNED, W, false>(a, dc, pl, E, indep, st);
             if (next_have) {
                 dc = dn;
                 slot ^= 1;
@@ -3300,7 +3312,8 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
     uint64_t base;
     if (PRESCAN) {
         base = sh.base;
-        if (w == 0 && chunk == a.nchunks - 1) finish_decode(a, gc, base + chunk_total, total);
+        if (w == 0 && chunk == a.nchunks - 1) 
+            finish_decode<false>(a, gc.bad || (a.groups[gc.next] & kGroupBad) != 0, base + chunk_total, total);
     } else {
         if (tid == 0) publish_aggregate(a.flags, chunk, a.flag_epoch, chunk_total, any_bad);
         if (w == 0) {
@@ -3435,21 +3448,6 @@ static hipError_t launch_compress_t(const CompressArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-template <bool ALIGNED, bool STAGED, int W, bool RANGE = false, bool PREZERO = false, bool PRESCAN = false>
-static hipError_t launch_decompress_w(const DecompressArgs &a, hipStream_t s)
-{
-    // the arguments count chunks of kTilesPerChunk tiles
-    DecompressArgs p = a;
-    const uint64_t tiles = p.tile_end - p.tile_begin;
-    p.nchunks = tiles ? ceil_div(tiles, (uint64_t)kTilesPerWave * W) : 1;
-    static const unsigned cap =
-        persistent_grid(decompress_kernel<ALIGNED, STAGED, W, RANGE, PREZERO, PRESCAN>, ~0ull, W * 64);
-    const unsigned grid = (unsigned)(p.nchunks < cap ? p.nchunks : cap);
-    hipLaunchKernelGGL((decompress_kernel<ALIGNED, STAGED, W, RANGE, PREZERO, PRESCAN>), dim3(grid), dim3(W * 64), 0,
-                       s, p);
-    return hipGetLastError();
-}
-
 // Rounds of kGroupTiles tiles per group of the offsets pre-pass: the least power
 // of two that leaves at most kMaxGroups groups.
 static uint32_t group_passes(uint64_t ntiles)
@@ -3464,8 +3462,8 @@ static uint32_t group_passes(uint64_t ntiles)
 template <int TPC, int T = kBlocksPerTile, int HB = 1>
 static hipError_t launch_dec_groups(DecompressArgs &a, unsigned long long *words, hipStream_t s)
 {
-    const uint32_t passes = group_passes(a.ntiles);
-    const uint64_t ngroups = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kGroupTiles * passes) : 1;
+    const uint32_t passes = group_passes(a.tile_end);
+    const uint64_t ngroups = a.tile_end ? ceil_div(a.tile_end, (uint64_t)kGroupTiles * passes) : 1;
     a.groups = words;
     a.offsets = words + kMaxGroups;
     a.group_shift = (uint32_t)__builtin_ctz(kGroupTiles / TPC * passes);
@@ -3474,24 +3472,67 @@ static hipError_t launch_dec_groups(DecompressArgs &a, unsigned long long *words
     return hipGetLastError();
 }
 
-hipError_t launch_decompress_prescan(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
-                                     bool direct, hipStream_t s)
+template <bool ALIGNED, bool RANGE, bool PREZERO>
+static hipError_t launch_decompress_persistent(const DecompressArgs &a, hipStream_t s)
 {
-    // chunks of 8 tiles per wave: 8 waves (persistent grid) or 4 (one chunk per workgroup)
+    static const unsigned cap = persistent_grid(decompress_kernel<ALIGNED, 8, RANGE, PREZERO>, ~0ull, 512);
+    const uint64_t chunks = a.nchunks - a.chunk_begin;
+    hipLaunchKernelGGL((decompress_kernel<ALIGNED, 8, RANGE, PREZERO>), dim3((unsigned)(chunks < cap ? chunks : cap)),
+                       dim3(512), 0, s, a);
+    return hipGetLastError();
+}
+
+// Chunks of tpc tiles that hold the decoded tiles, counted from the field's
+// first tile or from the first decoded one.  An empty decode still has one, to
+// report the outcome: the one that ends where its data would start.
+static void chunk_span(DecompressArgs &a, uint64_t tpc, bool from_begin)
+{
+    const uint64_t t0 = from_begin ? 0 : a.tile_begin;
+    const uint64_t t1 = from_begin ? a.tile_end - a.tile_begin : a.tile_end;
+    a.chunk_begin = (t1 > t0 ? t0 : t1 ? t1 - 1 : 0) / tpc;
+    a.nchunks = t1 > t0 ? ceil_div(t1, tpc) : a.chunk_begin + 1;
+}
+
+template <bool ALIGNED, int W, bool RANGE, int OFF>
+static hipError_t launch_decompress_direct(const DecompressArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL((decompress_direct_kernel<ALIGNED, W, RANGE, OFF>), dim3((unsigned)(a.nchunks - a.chunk_begin)),
+                       dim3(W * 64), 0, s, a);
+    return hipGetLastError();
+}
+
+template <bool ALIGNED, bool RANGE>
+static hipError_t launch_decompress_t(const DecompressArgs &a, unsigned long long *words, bool prezero, hipStream_t s)
+{
     DecompressArgs p = a;
+    const uint64_t tiles = a.tile_end - a.tile_begin;
+    if (!prezero && decode_by_prefix(a.tile_begin, a.tile_end)) {
+        // chunks of 4 waves spread small decodes wider; from 2^21 elements
+        // on 8 waves halve the reads of the rate bytes (2^21 GRF 7.4 against
+        // 7.9 us, 2^22 9.9 against 9.0)
+        const bool wide = tiles * kTile > (1ull << 21);
+        chunk_span(p, (uint64_t)kTilesPerWave * (wide ? 8 : 4), true);
+        return wide ? launch_decompress_direct<ALIGNED, 8, RANGE, kByPrefix>(p, s)
+                    : launch_decompress_direct<ALIGNED, 4, RANGE, kByPrefix>(p, s);
+    }
+    const bool direct = !prezero && tiles * kTile < tuning().dec_direct_below;
     const hipError_t e = direct ? launch_dec_groups<kTilesPerWave * 4>(p, words, s)
                                 : launch_dec_groups<kTilesPerWave * 8>(p, words, s);
     if (e != hipSuccess) return e;
-    if (direct) {
-        p.nchunks = a.ntiles ? ceil_div(a.ntiles, (uint64_t)kTilesPerWave * 4) : 1;
-        if (out_aligned16)
-            hipLaunchKernelGGL((decompress_direct_kernel<true, 4>), dim3((unsigned)p.nchunks), dim3(256), 0, s, p);
-        else
-            hipLaunchKernelGGL((decompress_direct_kernel<false, 4>), dim3((unsigned)p.nchunks), dim3(256), 0, s, p);
-        return hipGetLastError();
-    }
-    return out_aligned16 ? launch_decompress_w<true, true, 8, false, false, true>(p, s)
-                         : launch_decompress_w<false, true, 8, false, false, true>(p, s);
+    chunk_span(p, (uint64_t)kTilesPerWave * (direct ? 4 : 8), false);
+    if (direct) return launch_decompress_direct<ALIGNED, 4, RANGE, kByGroupsOnce>(p, s);
+    if (!RANGE && prezero) return launch_decompress_persistent<ALIGNED, false, true>(p, s);
+    return launch_decompress_persistent<ALIGNED, RANGE, false>(p, s);
+}
+
+hipError_t launch_decompress(const DecompressArgs &a, unsigned long long *words, bool out_aligned16, bool range,
+                             hipStream_t s)
+{
+    if (range)
+        return out_aligned16 ? launch_decompress_t<true, true>(a, words, false, s)
+                             : launch_decompress_t<false, true>(a, words, false, s);
+    return out_aligned16 ? launch_decompress_t<true, false>(a, words, false, s)
+                         : launch_decompress_t<false, false>(a, words, false, s);
 }
 
 // +0.0 into out[0, n): 16-byte nontemporal stores from the first 16-byte
@@ -3510,7 +3551,8 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float *out, uint64_t n)
     if (t < n - tail) out[tail + t] = 0.0f;
 }
 
-hipError_t launch_decompress_prezero(const DecompressArgs &a, bool out_aligned16, hipStream_t s)
+hipError_t launch_decompress_prezero(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
+                                     hipStream_t s)
 {
     if (a.n) {
         const uint64_t want = ceil_div(a.n, 4ull * 256);
@@ -3519,23 +3561,8 @@ hipError_t launch_decompress_prezero(const DecompressArgs &a, bool out_aligned16
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return out_aligned16 ? launch_decompress_w<true, true, 8, false, true>(a, s)
-                         : launch_decompress_w<false, true, 8, false, true>(a, s);
-}
-
-// Waves per workgroup: FSZ_DEC_WAVES if set, else by the elements to decode:
-// 8 (64-tile chunks) for up to dec_wide_above, 16 above it, where the shorter
-// lookback chain of the larger chunks pays for their coarser spread.
-template <bool ALIGNED, bool STAGED>
-static hipError_t launch_decompress_t(const DecompressArgs &a, hipStream_t s)
-{
-    const uint64_t elems = (a.tile_end - a.tile_begin) * kTile;
-    const int w = tuning().dec_waves ? tuning().dec_waves : (elems > tuning().dec_wide_above ? 16 : 8);
-    switch (w) {
-    case 16: return launch_decompress_w<ALIGNED, STAGED, 16>(a, s);
-    case 8: return launch_decompress_w<ALIGNED, STAGED, 8>(a, s);
-    default: return launch_decompress_w<ALIGNED, STAGED, 4>(a, s);
-    }
+    return out_aligned16 ? launch_decompress_t<true, false>(a, words, true, s)
+                         : launch_decompress_t<false, false>(a, words, true, s);
 }
 
 hipError_t launch_compress(const CompressArgs &a, bool in_aligned16, bool staged, hipStream_t s)
@@ -3624,31 +3651,6 @@ hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bo
     else
         hipLaunchKernelGGL(naive_encode_kernel<false>, dim3(grid), dim3(kThreads), 0, s, a, t);
     return hipGetLastError();
-}
-
-hipError_t launch_range_base(const DecompressArgs &a, unsigned long long *range_base, unsigned long long *partials,
-                             hipStream_t s)
-{
-    const uint64_t nb = a.tile_begin * kBlocksPerTile;
-    const uint64_t want = ceil_div(nb, (uint64_t)kStatsThreads * 16);
-    const unsigned grid = (unsigned)(want < 1 ? 1 : (want > kStatsMaxBlocks ? kStatsMaxBlocks : want));
-    hipLaunchKernelGGL(range_partial_kernel, dim3(grid), dim3(kStatsThreads), 0, s, a, partials);
-    hipLaunchKernelGGL(range_final_kernel, dim3(1), dim3(64), 0, s, partials, grid, range_base);
-    return hipGetLastError();
-}
-
-hipError_t launch_decompress(const DecompressArgs &a, bool out_aligned16, bool staged, hipStream_t s)
-{
-    if (a.range_base) {  // random access: the staged decoder with range bookkeeping, 16 waves for long ranges
-        if ((a.tile_end - a.tile_begin) * kTile > tuning().dec_wide_above)
-            return out_aligned16 ? launch_decompress_w<true, true, 16, true>(a, s)
-                                 : launch_decompress_w<false, true, 16, true>(a, s);
-        return out_aligned16 ? launch_decompress_w<true, true, 8, true>(a, s)
-                             : launch_decompress_w<false, true, 8, true>(a, s);
-    }
-    if (out_aligned16)
-        return staged ? launch_decompress_t<true, true>(a, s) : launch_decompress_t<true, false>(a, s);
-    return staged ? launch_decompress_t<false, true>(a, s) : launch_decompress_t<false, false>(a, s);
 }
 
 // Tile configurations (Sec. VI-C): (B, T) -> (HB, L) = (B / 32, T B / 32).

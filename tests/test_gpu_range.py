@@ -174,3 +174,38 @@ def test_range_short_or_mismatched_stream_rejected():
     announce("range decode with a mismatched n")
     st, _ = gpu_decompress_range(s, n + 7, 20_000, 30_000)
     assert st == fsz.FSZ_ERR_SIZE_MISMATCH
+
+
+CHUNK4 = 32 * 256  # elements per workgroup of 4 waves
+_N = (1 << 24) + 77
+
+
+@pytest.mark.parametrize("begin,end", [
+    (0, 1 << 21), (0, (1 << 21) + 1), (0, 1 << 22), (0, (1 << 22) + 3 * 8192),     # 4 / 8 waves, prefix / pre-pass
+    ((1 << 23) - 300, 1 << 23), ((1 << 23) - 300, (1 << 23) + 1),                  # the prefix's largest rate header
+    (1 << 22, 1 << 22), (3 << 22, 3 << 22), ((3 << 22) + 5, (3 << 22) + 5),        # empty: prefix, pre-pass
+    ((3 << 22) - 1, (3 << 22) + 2 * CHUNK4), (1 << 23, (1 << 23) + 5 * CHUNK4),    # chunk and group edges
+    (256 * 1024 * 40, 256 * 1024 * 41), (256 * 1024 * 40 - 1, _N), (_N - 1, _N)])
+def test_range_offsets_at_edges(begin, end):
+    """Where the base offset of a range comes from (its workgroups' own sums, or
+    the offsets pre-pass over groups of 1024 tiles): decoded bits, a reserved
+    rate bit in the last tile before the range's end (reported) and in the
+    tile after it (not read)."""
+    old = oracle.set_threads(8)
+    try:
+        x = workloads.sparse_field(_N, 9, spacing=300)
+        s = oracle.compress(x, oracle.REL, 1e-3)
+        full = oracle.decompress(s, _N)
+    finally:
+        oracle.set_threads(old)
+    announce(f"range offsets [{begin}, {end})")
+    st, y = gpu_decompress_range(s, _N, begin, end)
+    assert st == fsz.FSZ_OK
+    assert np.array_equal(y.view(np.uint32), full[begin:end].view(np.uint32))
+    tile_end = -(-end // 256) if end > begin else begin // 256
+    for tile, want in ((tile_end - 1, fsz.FSZ_ERR_CORRUPT), (tile_end, fsz.FSZ_OK)):
+        if 0 <= tile < -(-_N // 256):
+            bad = bytearray(s)
+            bad[32 + 8 * tile] |= 0x20
+            announce(f"range offsets [{begin}, {end}): reserved bit in tile {tile}")
+            assert gpu_decompress_range(bytes(bad), _N, begin, end)[0] == want
