@@ -1073,11 +1073,9 @@ def main():
         dec_time += dec_ms[k]
 
     dominant = "compress" if comp_time >= dec_time else "decompress"
-    # kernel names as rocprofv3 reports them (torch allocations are 16-byte aligned)
+    # kernel names as rocprofv3 reports them
     waves = os.environ.get("FSZ_PIPE_WAVES", "9")
-    if os.environ.get("FSZ_PIPE", "1") == "0":
-        comp_kernel = "compress_kernel"
-    elif waves in ("7", "9"):
+    if waves in ("7", "9"):
         comp_kernel = "compress_ctrl_kernel"
     else:
         comp_kernel = "compress_pipe2_kernel"

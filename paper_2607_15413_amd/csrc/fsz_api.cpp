@@ -22,11 +22,6 @@ const Tuning &tuning()
 {
     static const Tuning t = [] {
         Tuning v;
-        if (const char *e = std::getenv("FSZ_STAGED")) {  // letters: c = compress, d = decompress
-            v.staged_compress = std::strchr(e, 'c') != nullptr;
-            v.staged_compress_loads = std::strchr(e, 'l') != nullptr;
-        }
-        if (const char *e = std::getenv("FSZ_PIPE")) v.pipe_compress = std::atoi(e) != 0;
         if (const char *e = std::getenv("FSZ_PIPE_WAVES")) {
             const int k = std::atoi(e);
             if (k == 1 || k == 2 || k == 4 || k == 7 || k == 8 || k == 9) v.pipe_waves = k;  // 7, 9: + 1 control wave
@@ -226,7 +221,7 @@ fsz_status enqueue_compress(Workspace *ws, const float *d_in, uint64_t n, int mo
     a.flags = ws->d_flags;
     a.ticket = ws->d_ticket;
     a.final = d_final;
-    if (!ok(launch_compress(a, aligned(d_in, 16), tuning().staged_compress, ws->stream))) return FSZ_ERR_DEVICE;
+    if (!ok(launch_compress(a, ws->stream))) return FSZ_ERR_DEVICE;
     *epoch_out = a.epoch;
     return FSZ_OK;
 }
@@ -316,7 +311,7 @@ bool auto_prezero(uint64_t n, uint64_t cmp_size)
 }
 
 // Tile configurations (Sec. VI-C, Table V): the generic lane-per-segment
-// kernels, one chunk of kCfgChunkSegs 32-element segments per workgroup
+// kernels, compression in chunks of kCfgPipeChunkSegs 32-element segments
 // (decoder: 64 x kCfgDecWaves, or 64 x kCfgDecWideWaves in the lookback form
 // of fields above dec_wide_above elements).
 fsz_status enqueue_compress_config(Workspace *ws, const float *d_in, uint64_t n, int mode, double value,
@@ -333,7 +328,7 @@ fsz_status enqueue_compress_config(Workspace *ws, const float *d_in, uint64_t n,
     a.n = n;
     a.ntiles = ceil_div(n, (uint64_t)block * tile_blocks);
     a.nblocks = ceil_div(n, (uint64_t)block);
-    a.nchunks = n ? ceil_div(ceil_div(n, kBlock), kCfgChunkSegs) : 1;
+    a.nchunks = n ? ceil_div(ceil_div(n, kBlock), kCfgPipeChunkSegs) : 1;
     a.data0 = kHeaderBytes + pad16(a.nblocks);
     a.out = static_cast<uint8_t *>(d_out);
     a.capacity = cap;
@@ -342,14 +337,12 @@ fsz_status enqueue_compress_config(Workspace *ws, const float *d_in, uint64_t n,
     a.mode = mode;
     a.features = kFeaturesAll;
     a.cfg_flags = cfg_flag_bits(block, tile_blocks);
-    // flags for the generic kernel's chunks or the pipelined one's (smaller)
-    if (!ensure_flags(ws, std::max<uint64_t>(a.nchunks, ceil_div(ceil_div(n, kBlock), kCfgPipeChunkSegs))))
-        return FSZ_ERR_DEVICE;
+    if (!ensure_flags(ws, a.nchunks)) return FSZ_ERR_DEVICE;
     if (!next_epoch(ws, &a.epoch, &a.flag_epoch)) return FSZ_ERR_DEVICE;
     a.flags = ws->d_flags;
     a.ticket = ws->d_ticket;
     a.final = d_final;
-    if (!ok(launch_compress_cfg(a, block, tile_blocks, aligned(d_in, 16), ws->stream))) return FSZ_ERR_DEVICE;
+    if (!ok(launch_compress_cfg(a, block, tile_blocks, ws->stream))) return FSZ_ERR_DEVICE;
     return FSZ_OK;
 }
 

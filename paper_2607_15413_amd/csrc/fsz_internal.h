@@ -158,9 +158,7 @@ struct BatchShape {
 
 // Kernel launchers (fsz_kernels.hip).
 hipError_t launch_stats(const StatsArgs &a, hipStream_t s);
-// staged = write outputs through an LDS staging buffer with coalesced stores
-// instead of lane-per-block stores.
-hipError_t launch_compress(const CompressArgs &a, bool in_aligned16, bool staged, hipStream_t s);
+hipError_t launch_compress(const CompressArgs &a, hipStream_t s);
 // The five-read baseline: four evaluation launches, then the encode launch
 // (a.nchunks counts chunks of kTilesPerChunk tiles).
 hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bool in_aligned16, hipStream_t s);
@@ -178,12 +176,11 @@ hipError_t launch_decompress(const DecompressArgs &a, unsigned long long *words,
 // offsets pre-pass, then the decoder that skips waves whose tiles are all zero.
 hipError_t launch_decompress_prezero(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
                                      hipStream_t s);
-// Tile configurations (Sec. VI-C): one chunk of kCfgWaves x 64 32-element segments per
-// workgroup (a.nchunks counts those; for the decoder kCfgDecWaves x 64), block in {32, 64},
-// tile_blocks in {4, 8, 16}.  A
-// 16-byte aligned input runs the pipelined compressor instead, whose chunks of
-// kCfgPipeChunkSegs segments the launch counts itself (the flags must cover them).
-hipError_t launch_compress_cfg(const CompressArgs &a, int block, int tile_blocks, bool in_aligned16, hipStream_t s);
+// Tile configurations (Sec. VI-C), block in {32, 64}, tile_blocks in {4, 8, 16}:
+// the pipelined compressor, whose chunks of kCfgPipeChunkSegs segments the
+// launch counts itself (the flags must cover them), and a decoder with one
+// chunk of kCfgDecWaves x 64 segments per workgroup (a.nchunks counts those).
+hipError_t launch_compress_cfg(const CompressArgs &a, int block, int tile_blocks, hipStream_t s);
 hipError_t launch_decompress_cfg(const DecompressArgs &a, int block, int tile_blocks, bool out_aligned16,
                                  hipStream_t s);
 // The same decode with chunk offsets from a pre-pass over the rate header
@@ -191,8 +188,6 @@ hipError_t launch_decompress_cfg(const DecompressArgs &a, int block, int tile_bl
 // kMaxGroupWords words and one per chunk).
 hipError_t launch_decompress_cfg_prescan(const DecompressArgs &a, unsigned long long *words, int block,
                                          int tile_blocks, bool out_aligned16, hipStream_t s);
-constexpr int kCfgWaves = 16;
-constexpr int kCfgChunkSegs = kCfgWaves * 64;
 constexpr int kCfgPipeChunkSegs = 8 * 64;  // the pipelined configuration compressor's chunk
 // the configuration decoder: workgroups of 4 waves, one chunk of 4 x 64 segments each
 // (the lookback form of fields above dec_wide_above elements: 16 waves)
@@ -209,8 +204,7 @@ inline bool cfg_supported(int block, int tile_blocks)
     return (block == 32 || block == 64) && (tile_blocks == 4 || tile_blocks == 8 || tile_blocks == 16);
 }
 // Range pass + flag clear, per-job stats, then the batched kernel.
-// Compress-only batches with 16-byte aligned inputs run a persistent
-// pipelined kernel, decompress-only batches a persistent decoder, mixed
+// Compress-only batches run a persistent pipelined kernel, decompress-only batches a persistent decoder, mixed
 // batches one work item per workgroup.
 hipError_t launch_batch(const BatchArgs &b, bool aligned16, bool any_compress, bool any_decompress,
                         const BatchShape &shape, hipStream_t s);
@@ -235,10 +229,8 @@ fsz_status check_decompress_args(const void *d_cmp, size_t cmp_size, const float
 bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t segs);
 
 // Launch tuning knobs, process-wide, read once from the environment:
-// FSZ_STAGED (letters c / l: stage compress output / compress input through
-// LDS), FSZ_PIPE (0: no pipelined persistent
-// compression for 16-byte aligned inputs), FSZ_PIPE_WAVES (its waves per
-// workgroup: 1, 2, 4 or 8), FSZ_DEC_WIDE_ABOVE (the tile configurations'
+// FSZ_PIPE_WAVES (the compressor's waves per
+// workgroup: 1, 2, 4 or 8, or 7 / 9 with a control wave), FSZ_DEC_WIDE_ABOVE (the tile configurations'
 // lookback decoder: 16-wave chunks above this many elements, else 4),
 // FSZ_CFG_DEC_LOOKBACK_BELOW (decodes of
 // the tile configurations below this many elements use
@@ -248,9 +240,6 @@ bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t 
 // default 1) and FSZ_PREZERO_CR (whole-field decodes of streams above this
 // compression ratio, judged from the buffer size, use the pre-zeroed decoder).
 struct Tuning {
-    bool staged_compress = true;
-    bool staged_compress_loads = true;
-    bool pipe_compress = true;  // persistent compression with asynchronous LDS prefetch
     int pipe_waves = 9;         // pipelined compression: data waves per workgroup (1, 2, 4, 8), or 9 / 7:
                                 // 8 / 7 data waves and a control wave (compress_ctrl_kernel)
     uint64_t dec_wide_above = 1ull << 21;  // tile configurations, lookback form: 16 waves above, else 4

@@ -490,28 +490,6 @@ __device__ Prefix lookback_wait(unsigned long long *flags, uint64_t chunk, uint3
 
 // ------------------------------------------------------------------ staging
 
-// Lane-per-block loads straight from HBM: lane L reads its block's 128
-// contiguous bytes (8 x 16 B); the wave's 8 loads cover 64 whole blocks.
-// Elements at or beyond n read as +0.
-template <bool ALIGNED>
-__device__ __forceinline__ void load_block(const float *__restrict__ x, uint64_t eblk, int cnt, float (&v)[32])
-{
-    if (ALIGNED && cnt == 32) {
-        const f4 *p = reinterpret_cast<const f4 *>(x + eblk);
-#pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const f4 f = __builtin_nontemporal_load(p + k);
-            v[4 * k + 0] = f.x;
-            v[4 * k + 1] = f.y;
-            v[4 * k + 2] = f.z;
-            v[4 * k + 3] = f.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 32; i++) v[i] = i < cnt ? x[eblk + i] : 0.0f;
-    }
-}
-
 // Coalesced loads of the wave's 8 tiles (2048 floats from element e0, 16 B
 // per lane per instruction), handed to the lane-per-block layout through LDS
 // (rows padded to 36 dwords so that neither side has bank conflicts).
@@ -614,34 +592,39 @@ struct RangeAcc {
     }
 };
 
+// Elements from x to its first 16-byte boundary.
+__device__ __forceinline__ uint32_t align_head(const void *x)
+{
+    return ((16u - ((uint32_t)(uintptr_t)x & 15u)) & 15u) >> 2;
+}
+
 // Value-range pass, part 1: one partial (min, max, max|x|, non-finite) per
 // workgroup over a grid-stride slice of x (four 16-byte loads in flight per
-// thread).
-template <bool ALIGNED>
+// thread; the elements before the first and after the last 16-byte boundary
+// one per thread).  Bound by the read: 512^3 at 5.8 TB/s.
 __global__ __launch_bounds__(kStatsThreads) void stats_partial_kernel(StatsArgs a)
 {
     RangeAcc acc;
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t nthreads = (uint64_t)gridDim.x * blockDim.x;
-    if (ALIGNED) {
-        const uint64_t nvec = a.n / 4;
-        const f4 *x4 = reinterpret_cast<const f4 *>(a.x);
-        uint64_t i = tid;
-        for (; i + 3 * nthreads < nvec; i += 4 * nthreads) {
-            const f4 f0 = __builtin_nontemporal_load(x4 + i);
-            const f4 f1 = __builtin_nontemporal_load(x4 + i + nthreads);
-            const f4 f2 = __builtin_nontemporal_load(x4 + i + 2 * nthreads);
-            const f4 f3 = __builtin_nontemporal_load(x4 + i + 3 * nthreads);
-            acc.take4(f0);
-            acc.take4(f1);
-            acc.take4(f2);
-            acc.take4(f3);
-        }
-        for (; i < nvec; i += nthreads) acc.take4(x4[i]);
-        for (uint64_t k = nvec * 4 + tid; k < a.n; k += nthreads) acc.take(a.x[k]);
-    } else {
-        for (uint64_t k = tid; k < a.n; k += nthreads) acc.take(a.x[k]);
+    const uint64_t head = min((uint64_t)align_head(a.x), a.n);
+    const uint64_t nvec = (a.n - head) / 4;
+    const f4 *x4 = reinterpret_cast<const f4 *>(a.x + head);
+    uint64_t i = tid;
+    for (; i + 3 * nthreads < nvec; i += 4 * nthreads) {
+        const f4 f0 = __builtin_nontemporal_load(x4 + i);
+        const f4 f1 = __builtin_nontemporal_load(x4 + i + nthreads);
+        const f4 f2 = __builtin_nontemporal_load(x4 + i + 2 * nthreads);
+        const f4 f3 = __builtin_nontemporal_load(x4 + i + 3 * nthreads);
+        acc.take4(f0);
+        acc.take4(f1);
+        acc.take4(f2);
+        acc.take4(f3);
     }
+    for (; i < nvec; i += nthreads) acc.take4(x4[i]);
+    const uint64_t tail = head + 4 * nvec;  // at most 3 elements on either side, and >= 256 threads
+    if (tid < head) acc.take(a.x[tid]);
+    if (tid < a.n - tail) acc.take(a.x[tail + tid]);
     const StatsPartial p = acc.reduce();
     if (threadIdx.x == 0) a.partials[blockIdx.x] = p;
 }
@@ -989,8 +972,8 @@ __device__ __forceinline__ void finish_stream(const CompressArgs &a, const Resol
 
 // Steps 4-5 of one chunk whose rate pass is done: wait for the chunk's output
 // offset (decoupled lookback, Sec. IV-D), then the sign / bit-plane encoding
-// (Sec. IV-C) straight to the output.  B holds the LZ1 residuals.
-template <bool STAGED, int W, bool FEAT = false>
+// (Sec. IV-C) through the wave's LDS staging area.  B holds the LZ1 residuals.
+template <int W>
 __device__ __forceinline__ void compress_encode(const CompressArgs &a, const Resolved &R, const ChunkState &cs,
                                                 int (&B)[32], int slot, CompressShared<W> &sh, uint32_t *st)
 {
@@ -1017,17 +1000,12 @@ __device__ __forceinline__ void compress_encode(const CompressArgs &a, const Res
     if (a.data0 + base + chunk_total > a.capacity || tile0 >= a.ntiles) return;
 
     uint8_t *wave_out = a.out + a.data0 + base + wave_base;
-    if (cs.vm != 0 && j == 0 && cs.cent) {
-        if (STAGED)
-            st[cs.tile_excl >> 2] = (uint32_t)cs.mu;
-        else
-            *reinterpret_cast<uint32_t *>(wave_out + cs.tile_excl) = (uint32_t)cs.mu;
-    }
-    block_codes(B, cs.carry_l1, FEAT ? (cs.first ? 0 : 1) : j, cs.order2, cs.cent, cs.mu);
+    if (cs.vm != 0 && j == 0 && cs.cent) st[cs.tile_excl >> 2] = (uint32_t)cs.mu;
+    block_codes(B, cs.carry_l1, j, cs.order2, cs.cent, cs.mu);
     // valid slots in stored bit order (element i at bit i ^ 7)
     const uint32_t keep = __builtin_bswap32(__builtin_bitreverse32(cs.vm));
     const uint32_t nwords = cs.r ? cs.r + 1 : 0;  // sign word + r planes
-    uint32_t *words = STAGED ? st + (cs.blk_off >> 2) : reinterpret_cast<uint32_t *>(wave_out + cs.blk_off);
+    uint32_t *words = st + (cs.blk_off >> 2);
     for (uint32_t g = 0; __ballot(8 * g < nwords) != 0; g++) {
         uint32_t Rg[8];
 #pragma unroll
@@ -1039,11 +1017,10 @@ __device__ __forceinline__ void compress_encode(const CompressArgs &a, const Res
         for (int p = 0; p < 8; p++)
             if (8 * g + p < nwords) words[8 * g + p] = Rg[p] & keep;
     }
-    if (STAGED) {  // coalesced copy of the wave's contiguous output
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        wave_store_staged(reinterpret_cast<uint32_t *>(wave_out), st, cs.wave_total >> 2, lane);
-    }
+    // coalesced copy of the wave's contiguous output
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wave_store_staged(reinterpret_cast<uint32_t *>(wave_out), st, cs.wave_total >> 2, lane);
 }
 
 // Thread 0 takes the next ticket and broadcasts it.  Consecutive calls use
@@ -1061,7 +1038,7 @@ __device__ __forceinline__ uint64_t next_ticket(unsigned long long *ticket, uint
 
 // One chunk of a compression (Sec. III-A steps 1-5) by a workgroup of W
 // waves: bound resolution, coalesced load, rate pass, lookback, encode.
-template <bool ALIGNED, bool LOAD_STAGED, bool STORE_STAGED, int W, bool FEAT = false>
+template <bool ALIGNED, int W>
 __device__ __forceinline__ void compress_chunk(const CompressArgs &a, uint64_t chunk, CompressShared<W> &sh,
                                                uint32_t *st)
 {
@@ -1077,41 +1054,17 @@ __device__ __forceinline__ void compress_chunk(const CompressArgs &a, uint64_t c
     int x[32];
     {
         float f[32];
-        if (LOAD_STAGED) {
-            if (tile0 < a.ntiles) {
-                load_blocks_staged<ALIGNED>(a.x, a.n, tile0 * kTile, st, lane, f);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 32; i++) f[i] = 0.0f;
-            }
+        if (tile0 < a.ntiles) {
+            load_blocks_staged<ALIGNED>(a.x, a.n, tile0 * kTile, st, lane, f);
         } else {
-            const uint64_t eblk = (tile0 + (lane >> 3)) * kTile + (uint64_t)(lane & 7) * kBlock;
-            const int cnt = eblk >= a.n ? 0 : (a.n - eblk >= kBlock ? kBlock : (int)(a.n - eblk));
-            load_block<ALIGNED>(a.x, eblk, cnt, f);
+#pragma unroll
+            for (int i = 0; i < 32; i++) f[i] = 0.0f;
         }
 #pragma unroll
         for (int i = 0; i < 32; i++) x[i] = __float_as_int(f[i]);
     }
-    const ChunkState cs = compress_rates<W, false, FEAT>(a, R, chunk, x, 0, sh);
-    compress_encode<STORE_STAGED, W, FEAT>(a, R, cs, x, 0, sh, st);
-}
-
-// Compression kernel: one chunk per workgroup, chunk ids from the ticket
-// counter, so the lookback only waits on chunks that are already running.
-// The kernel is kept small in registers so that many chunks are in flight per
-// CU: chunks waiting in the lookback leave the CU to the others.
-template <bool ALIGNED, bool LOAD_STAGED, bool STORE_STAGED, bool FEAT = false>
-__global__ __launch_bounds__(kThreads) void compress_kernel(CompressArgs a)
-{
-    __shared__ CompressShared<kWaves> sh;
-    __shared__ __attribute__((aligned(16))) uint32_t
-        stage[(LOAD_STAGED || STORE_STAGED) ? kWaves * kStageWaveDwords : 4];
-    const int w = threadIdx.x >> 6;
-    uint32_t *st = stage + ((LOAD_STAGED || STORE_STAGED) ? w * kStageWaveDwords : 0);
-    int tslot = 0;
-    const uint64_t chunk = next_ticket(a.ticket, a.nchunks, sh, tslot);
-    if (chunk >= a.nchunks) return;  // inconsistent ticket counter: never index past the flags
-    compress_chunk<ALIGNED, LOAD_STAGED, STORE_STAGED, kWaves, FEAT>(a, chunk, sh, st);
+    const ChunkState cs = compress_rates<W>(a, R, chunk, x, 0, sh);
+    compress_encode<W>(a, R, cs, x, 0, sh, st);
 }
 
 // ------------------------------------------------------------------ naive five-read baseline
@@ -1313,12 +1266,12 @@ __global__ __launch_bounds__(kThreads) void naive_encode_kernel(CompressArgs a, 
         for (int i = 0; i < 32; i++) x[i] = __float_as_int(f[i]);
     }
     const ChunkState cs = naive_select(a, R, t, chunk, x, sh);
-    compress_encode<true, kWaves>(a, R, cs, x, 0, sh, st);
+    compress_encode<kWaves>(a, R, cs, x, 0, sh, st);
 }
 
 // ------------------------------------------------------------------ pipelined compress
 //
-// Persistent form of the compression kernel for 16-byte aligned inputs: each
+// Persistent compression kernel: each
 // workgroup keeps the next chunk's input in flight while it works on the
 // current ones, through asynchronous global->LDS copies that hold no
 // registers.  The LDS image of a wave's 8 tiles is unpadded and rotated:
@@ -1345,6 +1298,23 @@ __device__ __forceinline__ void chunk_copy_async(const float *__restrict__ x, ui
     }
 }
 
+// Same image from an input off the 16-byte grid, 4 bytes per lane: instruction
+// k brings blocks 2k and 2k + 1 (a lane's dword d = 64 k + lane is element d & 3
+// of the piece at slot d >> 2).  Four times the instructions, and lines that
+// straddle are fetched by two of them, but the pipeline hides it: 2^27 elements
+// at offset 1 265 us per call with the range pass, 248 aligned (the kernel with
+// one chunk per workgroup that such inputs had before: 673); 3.1 M 21.4 (32.1).
+__device__ __forceinline__ void chunk_copy_async4(const float *__restrict__ x, uint64_t e0, uint32_t *wbuf, int lane)
+{
+    const int half = lane >> 5;
+#pragma unroll
+    for (int k = 0; k < 32; k++) {
+        const int m = (((lane >> 2) & 7) - 2 * k - half) & 7;
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(x + e0 + 64 * k + 32 * half + 4 * m + (lane & 3)),
+                                         (lds_void *)(wbuf + 64 * k), 4, 0, kCachePolicyNT);
+    }
+}
+
 // Same image, loaded synchronously; elements at or beyond n read as +0.
 __device__ __forceinline__ void chunk_copy_sync(const float *__restrict__ x, uint64_t n, uint64_t e0, uint32_t *wbuf,
                                                 int lane)
@@ -1368,9 +1338,12 @@ template <int W>
 __device__ __forceinline__ void chunk_fetch(const CompressArgs &a, uint64_t chunk, uint32_t *wbuf, int w, int lane)
 {
     const uint64_t e0 = (chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave) * kTile;
-    if (e0 + kTilesPerWave * kTile <= a.n)
-        chunk_copy_async(a.x, e0, wbuf, lane);
-    else
+    if (e0 + kTilesPerWave * kTile <= a.n) {
+        if (((uintptr_t)a.x & 15u) == 0)  // the same for every chunk of a field
+            chunk_copy_async(a.x, e0, wbuf, lane);
+        else
+            chunk_copy_async4(a.x, e0, wbuf, lane);
+    } else
         chunk_copy_sync(a.x, a.n, e0, wbuf, lane);
 }
 
@@ -2326,7 +2299,6 @@ __device__ __forceinline__ uint32_t find_job(const uint64_t *end, uint32_t njobs
 // Batched range pass: workgroup s reduces segment s (kSegElems elements of
 // one compress job) into partials[s]; every workgroup also clears a slice of
 // the batch's chunk flags for the kernel that follows.
-template <bool ALIGNED>
 __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
 {
     for (uint64_t i = (uint64_t)blockIdx.x * kStatsThreads + threadIdx.x; i < b.nflags;
@@ -2343,40 +2315,40 @@ __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
         const uint64_t e1 = J.n - e0 < (uint64_t)kSegElems ? J.n : e0 + kSegElems;
         RangeAcc acc;
         const int tid = threadIdx.x;
-        if (ALIGNED) {  // 16-byte loads, four in flight per thread; a ragged segment's last 0-3 elements singly
-            const g_f4 *x4 = (const g_f4 *)(x + e0);
-            const uint32_t nv = (uint32_t)((e1 - e0) / 4);
-            if (nv == kSegElems / 4) {
+        // 16-byte loads, four in flight per thread; the elements before the
+        // segment's first and after its last 16-byte boundary singly
+        const uint32_t head = (uint32_t)min((uint64_t)align_head((const void *)J.src), e1 - e0);
+        const g_f4 *x4 = (const g_f4 *)(x + e0 + head);
+        const uint32_t nv = (uint32_t)((e1 - e0 - head) / 4);
+        if (nv == kSegElems / 4) {
 #pragma unroll 2
-                for (int k = 0; k < kSegElems / (4 * kStatsThreads); k += 4) {
-                    const f4 f0 = __builtin_nontemporal_load(x4 + (k + 0) * kStatsThreads + tid);
-                    const f4 f1 = __builtin_nontemporal_load(x4 + (k + 1) * kStatsThreads + tid);
-                    const f4 f2 = __builtin_nontemporal_load(x4 + (k + 2) * kStatsThreads + tid);
-                    const f4 f3 = __builtin_nontemporal_load(x4 + (k + 3) * kStatsThreads + tid);
-                    acc.take4(f0);
-                    acc.take4(f1);
-                    acc.take4(f2);
-                    acc.take4(f3);
-                }
-            } else {
-                uint32_t k = tid;
-                for (; k + 3 * kStatsThreads < nv; k += 4 * kStatsThreads) {
-                    const f4 f0 = __builtin_nontemporal_load(x4 + k);
-                    const f4 f1 = __builtin_nontemporal_load(x4 + k + kStatsThreads);
-                    const f4 f2 = __builtin_nontemporal_load(x4 + k + 2 * kStatsThreads);
-                    const f4 f3 = __builtin_nontemporal_load(x4 + k + 3 * kStatsThreads);
-                    acc.take4(f0);
-                    acc.take4(f1);
-                    acc.take4(f2);
-                    acc.take4(f3);
-                }
-                for (; k < nv; k += kStatsThreads) acc.take4(f4(x4[k]));
-                const uint64_t t = e0 + 4ull * nv + tid;
-                if (t < e1) acc.take(x[t]);
+            for (int k = 0; k < kSegElems / (4 * kStatsThreads); k += 4) {
+                const f4 f0 = __builtin_nontemporal_load(x4 + (k + 0) * kStatsThreads + tid);
+                const f4 f1 = __builtin_nontemporal_load(x4 + (k + 1) * kStatsThreads + tid);
+                const f4 f2 = __builtin_nontemporal_load(x4 + (k + 2) * kStatsThreads + tid);
+                const f4 f3 = __builtin_nontemporal_load(x4 + (k + 3) * kStatsThreads + tid);
+                acc.take4(f0);
+                acc.take4(f1);
+                acc.take4(f2);
+                acc.take4(f3);
             }
         } else {
-            for (uint64_t i = e0 + tid; i < e1; i += kStatsThreads) acc.take(x[i]);
+            uint32_t k = tid;
+            for (; k + 3 * kStatsThreads < nv; k += 4 * kStatsThreads) {
+                const f4 f0 = __builtin_nontemporal_load(x4 + k);
+                const f4 f1 = __builtin_nontemporal_load(x4 + k + kStatsThreads);
+                const f4 f2 = __builtin_nontemporal_load(x4 + k + 2 * kStatsThreads);
+                const f4 f3 = __builtin_nontemporal_load(x4 + k + 3 * kStatsThreads);
+                acc.take4(f0);
+                acc.take4(f1);
+                acc.take4(f2);
+                acc.take4(f3);
+            }
+            for (; k < nv; k += kStatsThreads) acc.take4(f4(x4[k]));
         }
+        if ((uint32_t)tid < head) acc.take(x[e0 + tid]);
+        const uint64_t t = e0 + head + 4ull * nv + tid;
+        if (t < e1) acc.take(x[t]);
         const StatsPartial p = acc.reduce();
         if (tid == 0) b.partials[seg] = p;
         __syncthreads();  // the reduction's shared slots are reused by the next segment
@@ -2470,7 +2442,7 @@ __global__ __launch_bounds__(W * 64) void batch_kernel(BatchArgs b)
     const BatchJob &J = b.jobs[job];
     const uint64_t chunk = t - J.chunk_base;
     if (J.op == FSZ_OP_COMPRESS) {
-        compress_chunk<ALIGNED, true, true, W>(batch_compress_args(b, job, J), chunk, sh.c, st);
+        compress_chunk<ALIGNED, W>(batch_compress_args(b, job, J), chunk, sh.c, st);
     } else {
         const DecompressArgs a = batch_decompress_args(b, J);
         float E;
@@ -2558,17 +2530,14 @@ hipError_t launch_stats(const StatsArgs &a, hipStream_t s)
 {
     const uint64_t want = ceil_div(a.n, (uint64_t)kStatsThreads * 16);
     const unsigned grid = (unsigned)(want < 1 ? 1 : (want > kStatsMaxBlocks ? kStatsMaxBlocks : want));
-    if ((reinterpret_cast<uintptr_t>(a.x) & 15u) == 0)
-        hipLaunchKernelGGL(stats_partial_kernel<true>, dim3(grid), dim3(kStatsThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(stats_partial_kernel<false>, dim3(grid), dim3(kStatsThreads), 0, s, a);
+    hipLaunchKernelGGL(stats_partial_kernel, dim3(grid), dim3(kStatsThreads), 0, s, a);
     hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(kStatsThreads), 0, s, a, grid);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ batched pipelined compression
 //
-// Compress-only batches with 16-byte aligned inputs: the pipeline of
+// Compress-only batches: the pipeline of
 // compress_pipe2_kernel over the batch's work items.  Tickets are global item
 // ids in job order; every item in flight carries its job, whose arguments
 // (input, output, flag range, bound) come from the job table where they are
@@ -2818,12 +2787,10 @@ __global__ __launch_bounds__(W * 64) void batch_pipe_kernel(BatchArgs b)
 // runs over L lanes.  A 64-element block's words (sign map, planes) are 64
 // bits with element i at bit 63 - i, written most-significant byte first:
 // the stored words of its two halves side by side, so the lane of half h
-// writes its word k at byte 8k + 4h of the block.  One chunk of kCfgWaves
-// waves (decoder: kCfgDecWaves) per workgroup, chunk ids from the ticket
-// counter (as compress_kernel).
+// writes its word k at byte 8k + 4h of the block.  The decoder runs one chunk
+// of kCfgDecWaves waves per workgroup.
 
-// a wave's staging area: the padded input rows (64 x 36 dwords), reused for
-// its output (at most 64 x 128 B + 16 tile means = 2064 dwords)
+// a decoding wave's staging area: padded output rows (64 x 36 dwords)
 constexpr int kCfgStageDwords = 64 * kStageRowDwords;
 
 // Sum over aligned groups of L lanes, in every lane of the group.  For binary32
@@ -2850,8 +2817,7 @@ __device__ __forceinline__ uint32_t lane_run_incl_scan(uint32_t v, int pos, int 
     return v;
 }
 
-// Rate pass of one chunk of W waves in a tile configuration (the pipelined
-// counterpart of compress_cfg_kernel's first half, for TileCfg): tile mean,
+// Rate pass of one chunk of W waves in a tile configuration (for TileCfg): tile mean,
 // quantization, cross-block extrema, four-way evaluation and selection, and
 // the offsets of the lane's words inside its wave (blk_off, with the lane's
 // half h of a 64-element block at byte 4 h).  One workgroup barrier; wave 1
@@ -3058,178 +3024,6 @@ __global__ __launch_bounds__(9 * 64) void compress_cfg_pipe_kernel(CompressArgs 
                                                     stbuf + w * kPipeWaveDwords, w);
     else
         ctrl_run<8>(a, R, sh);
-}
-
-template <bool ALIGNED, int HB, int L>
-__global__ __launch_bounds__(kCfgWaves * 64) void compress_cfg_kernel(CompressArgs a)
-{
-    __shared__ CompressShared<kCfgWaves> sh;
-    __shared__ __attribute__((aligned(16))) uint32_t stage[kCfgWaves * kCfgStageDwords];
-    const int tid = threadIdx.x;
-    const int w = tid >> 6;
-    const int lane = tid & 63;
-    const int tl = lane % L;  // lane inside the tile
-    const int h = tl % HB;    // half of a 64-element block
-    uint32_t *st = stage + w * kCfgStageDwords;
-    int tslot = 0;
-    const uint64_t chunk = next_ticket(a.ticket, a.nchunks, sh, tslot);
-    if (chunk >= a.nchunks) return;  // inconsistent ticket counter: never index past the flags
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
-    if (R.status != FSZ_OK) {
-        if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, R.status, a.epoch);
-        return;
-    }
-    const uint64_t seg0 = (chunk * kCfgWaves + w) * 64;  // the wave's first segment
-    const uint64_t seg = seg0 + lane;
-    const uint64_t e0 = seg * 32;
-    const int cnt = e0 >= a.n ? 0 : (a.n - e0 >= 32 ? 32 : (int)(a.n - e0));
-    const bool tile_ok = seg / L < a.ntiles;
-    const bool full = (seg0 + 64) * 32 <= a.n;  // wave-uniform
-    const uint32_t vm = cnt >= 32 ? 0xFFFFFFFFu : ((1u << cnt) - 1u);
-    int x[32];
-    {
-        float f[32];
-        if (seg0 * 32 < a.n) {  // coalesced loads of the wave's 2048 elements through LDS
-            load_blocks_staged<ALIGNED>(a.x, a.n, seg0 * 32, st, lane, f);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 32; i++) f[i] = 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < 32; i++) x[i] = __float_as_int(f[i]);
-    }
-
-    // ---- tile mean: pairwise binary32 tree over the B T slots, times 1/(B T)
-    float s16[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) s16[i] = __int_as_float(x[2 * i]) + __int_as_float(x[2 * i + 1]);
-#pragma unroll
-    for (int i = 0; i < 8; i++) s16[i] = s16[2 * i] + s16[2 * i + 1];
-#pragma unroll
-    for (int i = 0; i < 4; i++) s16[i] = s16[2 * i] + s16[2 * i + 1];
-#pragma unroll
-    for (int i = 0; i < 2; i++) s16[i] = s16[2 * i] + s16[2 * i + 1];
-    const float ts = lane_group_sum<L>(s16[0] + s16[1]);
-    const float mean_q = (ts * (1.0f / (float)(32 * L))) * R.inv;
-    const bool centre_ok = __builtin_isfinite(mean_q);
-    const int mu = centre_ok ? (int)__builtin_rintf(mean_q) : 0;
-
-    // ---- quantize (biased), cross-block state from the previous lane of the tile
-#pragma unroll
-    for (int i = 0; i < 32; i++) x[i] = __float_as_int(__int_as_float(x[i]) * R.inv + kQMagic);
-    const int p31 = __shfl_up(x[31], 1);
-    const int p30 = __shfl_up(x[30], 1);
-    const bool first = tl == 0;  // the tile start: the prediction restarts
-    const int carry_b = first ? kQBias : p31;
-    const int carry_l1 = first ? 0 : p31 - p30;
-    uint32_t a1, a2;
-    int l2_1;
-    if (full)
-        block_extrema<true>(x, carry_b, carry_l1, first ? 0 : 1, vm, a1, a2, l2_1);
-    else
-        block_extrema<false>(x, carry_b, carry_l1, first ? 0 : 1, vm, a1, a2, l2_1);
-
-    // ---- four-way evaluation (Eq. (3)-(4)): block magnitude maxima per
-    // variant, the tile start re-rated per variant
-    uint32_t m0 = a1, m1 = a2, m2 = a1, m3 = a2;
-    if (first) {
-        const int q0 = x[0];  // d[0] = q[0] at a tile start
-        const int d1 = cnt >= 2 ? l2_1 : 0;  // q1 - 2 q0
-        const int c0 = q0 - mu;
-        const int c1 = cnt >= 2 ? l2_1 + mu : 0;
-        m0 = max(uabs(q0), a1);
-        m1 = max(max(uabs(q0), uabs(d1)), a2);
-        m2 = max(uabs(c0), a1);
-        m3 = max(max(uabs(c0), uabs(c1)), a2);
-    }
-    if (cnt == 0) m0 = m1 = m2 = m3 = 0;  // segments past the end of the field
-    if (HB == 2) {
-        m0 = max(m0, (uint32_t)__shfl_xor((int)m0, 1));
-        m1 = max(m1, (uint32_t)__shfl_xor((int)m1, 1));
-        m2 = max(m2, (uint32_t)__shfl_xor((int)m2, 1));
-        m3 = max(m3, (uint32_t)__shfl_xor((int)m3, 1));
-    }
-    const uint32_t r0 = bitlen(m0), r1 = bitlen(m1), r2 = bitlen(m2), r3 = bitlen(m3);
-    // block costs (B/8 bytes per word, sign map + r planes), counted once per block
-    const uint32_t Ca = lane_group_sum<L>(h == 0 ? (uint32_t)HB * block_bytes(r0) : 0u);
-    const uint32_t Cb = lane_group_sum<L>(h == 0 ? (uint32_t)HB * block_bytes(r1) : 0u);
-    const uint32_t Cc = lane_group_sum<L>(h == 0 ? (uint32_t)HB * block_bytes(r2) : 0u) + 4u;
-    const uint32_t Cd = lane_group_sum<L>(h == 0 ? (uint32_t)HB * block_bytes(r3) : 0u) + 4u;
-    int best = 0;
-    uint32_t C = Ca, r = r0;
-    if (Cb < C) {
-        best = 1;
-        C = Cb;
-        r = r1;
-    }
-    if (centre_ok) {
-        if (Cc < C) {
-            best = 2;
-            C = Cc;
-            r = r2;
-        }
-        if (Cd < C) {
-            best = 3;
-            C = Cd;
-            r = r3;
-        }
-    }
-    if (!tile_ok) {
-        best = 0;
-        C = 0;
-        r = 0;
-    }
-    const int order2 = best & 1, cent = best >> 1;
-    if (h == 0 && cnt > 0)  // the block's rate byte (Sec. III-A)
-        ((g_u8 *)a.out)[kHeaderBytes + seg / HB] = (uint8_t)(first ? (r | (uint32_t)order2 << 7 | (uint32_t)cent << 6) : r);
-
-    // ---- offsets: the lane's block inside the tile, the tile inside the wave
-    const uint32_t S = block_bytes(r);  // this lane's words: 4 (1 + r) bytes
-    const uint32_t pre = lane_run_incl_scan<L>(S, tl, L) - S;
-    const uint32_t blk_rel = 4u * (uint32_t)cent + pre - (uint32_t)h * S;
-    const int incl = wave_incl_scan(first ? (int)C : 0);
-    const uint32_t tile_excl = (uint32_t)incl - C;
-    const uint32_t wave_total = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
-    if (lane == 0) sh.wave_total[0][w] = wave_total;
-    lds_barrier();
-    uint32_t chunk_total = 0, wave_base = 0;
-#pragma unroll
-    for (int k = 0; k < kCfgWaves; k++) {
-        if (k < w) wave_base += sh.wave_total[0][k];
-        chunk_total += sh.wave_total[0][k];
-    }
-    if (tid == 0) publish_aggregate(a.flags, chunk, a.flag_epoch, chunk_total, false);
-    if (w == 0) {  // decoupled lookback (Sec. IV-D)
-        const Prefix pre_c = lookback_wait(a.flags, chunk, a.flag_epoch, chunk_total, false);
-        if (lane == 0) {
-            sh.base = pre_c.excl;
-            if (chunk == a.nchunks - 1) finish_stream(a, R, pre_c, chunk_total);
-        }
-    }
-    lds_barrier();
-    const uint64_t base = sh.base;
-    if (a.data0 + base + chunk_total > a.capacity || seg0 / L >= a.ntiles) return;
-
-    // ---- encode (Sec. IV-C) into the wave's staging area, then one copy
-    if (first && cent && tile_ok) st[tile_excl >> 2] = (uint32_t)mu;
-    block_codes(x, carry_l1, first ? 0 : 1, order2, cent, mu);
-    const uint32_t keep = __builtin_bswap32(__builtin_bitreverse32(vm));
-    const uint32_t nwords = r ? r + 1 : 0;
-    uint32_t *words = st + ((tile_excl + blk_rel) >> 2) + h;
-    for (uint32_t g = 0; __ballot(8 * g < nwords) != 0; g++) {
-        uint32_t Rg[8];
-#pragma unroll
-        for (int rho = 0; rho < 8; rho++)
-            Rg[rho] = pack_byte_g((uint32_t)x[7 - rho], (uint32_t)x[15 - rho], (uint32_t)x[23 - rho],
-                                  (uint32_t)x[31 - rho], g);
-        transpose8(Rg);
-#pragma unroll
-        for (int p = 0; p < 8; p++)
-            if (8 * g + p < nwords) words[HB * (8 * g + p)] = Rg[p] & keep;
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    wave_store_staged(reinterpret_cast<uint32_t *>(a.out + a.data0 + base + wave_base), st, wave_total >> 2, lane);
 }
 
 // WV waves per workgroup, chunks of 64 WV segments (4 waves: a wider grid,
@@ -3441,13 +3235,6 @@ static unsigned persistent_grid(K kernel, uint64_t nchunks, int threads = kThrea
     return (unsigned)(nchunks < g ? nchunks : g);
 }
 
-template <bool ALIGNED, bool LS, bool SS>
-static hipError_t launch_compress_t(const CompressArgs &a, hipStream_t s)
-{
-    hipLaunchKernelGGL((compress_kernel<ALIGNED, LS, SS>), dim3((unsigned)a.nchunks), dim3(kThreads), 0, s, a);
-    return hipGetLastError();
-}
-
 // Rounds of kGroupTiles tiles per group of the offsets pre-pass: the least power
 // of two that leaves at most kMaxGroups groups.
 static uint32_t group_passes(uint64_t ntiles)
@@ -3565,76 +3352,34 @@ hipError_t launch_decompress_prezero(const DecompressArgs &a, unsigned long long
                          : launch_decompress_t<false, false>(a, words, true, s);
 }
 
-hipError_t launch_compress(const CompressArgs &a, bool in_aligned16, bool staged, hipStream_t s)
+template <typename K>
+static hipError_t launch_pipe(K kernel, unsigned cap, int waves, const CompressArgs &a, int data_waves, hipStream_t s)
 {
-    if (a.features != kFeaturesAll) {  // the ablation's feature subsets: 8-wave pipeline or the plain kernel
-        if (in_aligned16) {
-            CompressArgs p = a;
-            p.nchunks = p.ntiles ? ceil_div(p.ntiles, (uint64_t)kTilesPerWave * 8) : 1;
-            static const unsigned cap = persistent_grid(compress_pipe2_kernel<8, true>, ~0ull, 512);
-            hipLaunchKernelGGL((compress_pipe2_kernel<8, true>), dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(512), 0, s, p);
-        } else {
-            hipLaunchKernelGGL((compress_kernel<false, true, true, true>), dim3((unsigned)a.nchunks), dim3(kThreads), 0,
-                               s, a);
-        }
-        return hipGetLastError();
+    // the pipeline's chunks are 8 tiles per data wave
+    CompressArgs p = a;
+    p.nchunks = p.ntiles ? ceil_div(p.ntiles, (uint64_t)kTilesPerWave * data_waves) : 1;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)), dim3(waves * 64), 0, s, p);
+    return hipGetLastError();
+}
+
+#define FSZ_LAUNCH_PIPE(K, WAVES, DATA)                                                \
+    {                                                                                  \
+        static const unsigned cap = persistent_grid(K, ~0ull, (WAVES) * 64);           \
+        return launch_pipe(K, cap, WAVES, a, DATA, s);                                 \
     }
-    if (in_aligned16 && tuning().pipe_compress) {
-        // the arguments count chunks of kTilesPerChunk tiles; the pipeline's
-        // chunks are 8 tiles per wave
-        CompressArgs p = a;
-        const int W = tuning().pipe_waves;
-        p.nchunks = p.ntiles ? ceil_div(p.ntiles, (uint64_t)kTilesPerWave * W) : 1;
-        if (W == 7) p.nchunks = p.ntiles ? ceil_div(p.ntiles, (uint64_t)kTilesPerWave * 7) : 1;
-        if (W == 9) p.nchunks = p.ntiles ? ceil_div(p.ntiles, (uint64_t)kTilesPerWave * 8) : 1;
-        switch (W) {
-        case 7: {  // 7 data waves + 1 control wave
-            static const unsigned cap = persistent_grid(compress_ctrl_kernel<7>, ~0ull, 512);
-            hipLaunchKernelGGL(compress_ctrl_kernel<7>, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(512), 0, s, p);
-            break;
-        }
-        case 9: {  // 8 data waves + 1 control wave
-            static const unsigned cap = persistent_grid(compress_ctrl_kernel<8>, ~0ull, 576);
-            hipLaunchKernelGGL(compress_ctrl_kernel<8>, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(576), 0, s, p);
-            break;
-        }
-        case 1: {
-            static const unsigned cap = persistent_grid(compress_pipe2_kernel<1>, ~0ull, 64);
-            hipLaunchKernelGGL(compress_pipe2_kernel<1>, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(64), 0, s, p);
-            break;
-        }
-        case 2: {
-            static const unsigned cap = persistent_grid(compress_pipe2_kernel<2>, ~0ull, 128);
-            hipLaunchKernelGGL(compress_pipe2_kernel<2>, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(128), 0, s, p);
-            break;
-        }
-        case 8: {
-            static const unsigned cap = persistent_grid(compress_pipe2_kernel<8>, ~0ull, 512);
-            hipLaunchKernelGGL(compress_pipe2_kernel<8>, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(512), 0, s, p);
-            break;
-        }
-        default: {
-            static const unsigned cap = persistent_grid(compress_pipe2_kernel<4>, ~0ull, 256);
-            hipLaunchKernelGGL(compress_pipe2_kernel<4>, dim3((unsigned)(p.nchunks < cap ? p.nchunks : cap)),
-                               dim3(256), 0, s, p);
-            break;
-        }
-        }
-        return hipGetLastError();
+
+hipError_t launch_compress(const CompressArgs &a, hipStream_t s)
+{
+    if (a.features != kFeaturesAll)  // the ablation's feature subsets
+        FSZ_LAUNCH_PIPE((compress_pipe2_kernel<8, true>), 8, 8)
+    switch (tuning().pipe_waves) {
+    case 7: FSZ_LAUNCH_PIPE(compress_ctrl_kernel<7>, 8, 7)  // 7 data waves + 1 control wave
+    case 1: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<1>, 1, 1)
+    case 2: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<2>, 2, 2)
+    case 4: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<4>, 4, 4)
+    case 8: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<8>, 8, 8)
+    default: FSZ_LAUNCH_PIPE(compress_ctrl_kernel<8>, 9, 8)  // 8 data waves + 1 control wave
     }
-    const bool ls = tuning().staged_compress_loads;
-    if (in_aligned16) {
-        if (ls) return staged ? launch_compress_t<true, true, true>(a, s) : launch_compress_t<true, true, false>(a, s);
-        return staged ? launch_compress_t<true, false, true>(a, s) : launch_compress_t<true, false, false>(a, s);
-    }
-    if (ls) return staged ? launch_compress_t<false, true, true>(a, s) : launch_compress_t<false, true, false>(a, s);
-    return staged ? launch_compress_t<false, false, true>(a, s) : launch_compress_t<false, false, false>(a, s);
 }
 
 hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bool in_aligned16, hipStream_t s)
@@ -3654,23 +3399,6 @@ hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bo
 }
 
 // Tile configurations (Sec. VI-C): (B, T) -> (HB, L) = (B / 32, T B / 32).
-template <bool ALIGNED>
-static hipError_t launch_compress_cfg_t(const CompressArgs &a, int block, int tile_blocks, hipStream_t s)
-{
-    const dim3 grid((unsigned)a.nchunks), threads(kCfgWaves * 64);
-    const int key = block * 100 + tile_blocks;
-    switch (key) {
-    case 3204: hipLaunchKernelGGL((compress_cfg_kernel<ALIGNED, 1, 4>), grid, threads, 0, s, a); break;
-    case 3208: hipLaunchKernelGGL((compress_cfg_kernel<ALIGNED, 1, 8>), grid, threads, 0, s, a); break;
-    case 3216: hipLaunchKernelGGL((compress_cfg_kernel<ALIGNED, 1, 16>), grid, threads, 0, s, a); break;
-    case 6404: hipLaunchKernelGGL((compress_cfg_kernel<ALIGNED, 2, 8>), grid, threads, 0, s, a); break;
-    case 6408: hipLaunchKernelGGL((compress_cfg_kernel<ALIGNED, 2, 16>), grid, threads, 0, s, a); break;
-    case 6416: hipLaunchKernelGGL((compress_cfg_kernel<ALIGNED, 2, 32>), grid, threads, 0, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 template <bool ALIGNED, int WV>
 static hipError_t launch_decompress_cfg_w(const DecompressArgs &a, int block, int tile_blocks, hipStream_t s)
 {
@@ -3697,7 +3425,7 @@ static hipError_t launch_decompress_cfg_t(const DecompressArgs &a, int block, in
                : launch_decompress_cfg_w<ALIGNED, kCfgDecWaves>(a, block, tile_blocks, s);
 }
 
-// Pipelined form (16-byte aligned input): persistent workgroups of 8 data
+// Persistent workgroups of 8 data
 // waves and a control wave, chunks of kCfgPipeChunkSegs segments.
 template <int HB, int L>
 static hipError_t launch_compress_cfg_pipe_t(const CompressArgs &a, hipStream_t s)
@@ -3708,22 +3436,19 @@ static hipError_t launch_compress_cfg_pipe_t(const CompressArgs &a, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_compress_cfg(const CompressArgs &a, int block, int tile_blocks, bool in_aligned16, hipStream_t s)
+hipError_t launch_compress_cfg(const CompressArgs &a, int block, int tile_blocks, hipStream_t s)
 {
-    if (in_aligned16) {
-        CompressArgs p = a;
-        p.nchunks = a.n ? ceil_div(ceil_div(a.n, (uint64_t)kBlock), (uint64_t)kCfgPipeChunkSegs) : 1;
-        switch (block * 100 + tile_blocks) {
-        case 3204: return launch_compress_cfg_pipe_t<1, 4>(p, s);
-        case 3208: return launch_compress_cfg_pipe_t<1, 8>(p, s);
-        case 3216: return launch_compress_cfg_pipe_t<1, 16>(p, s);
-        case 6404: return launch_compress_cfg_pipe_t<2, 8>(p, s);
-        case 6408: return launch_compress_cfg_pipe_t<2, 16>(p, s);
-        case 6416: return launch_compress_cfg_pipe_t<2, 32>(p, s);
-        default: return hipErrorInvalidValue;
-        }
+    CompressArgs p = a;
+    p.nchunks = a.n ? ceil_div(ceil_div(a.n, (uint64_t)kBlock), (uint64_t)kCfgPipeChunkSegs) : 1;
+    switch (block * 100 + tile_blocks) {
+    case 3204: return launch_compress_cfg_pipe_t<1, 4>(p, s);
+    case 3208: return launch_compress_cfg_pipe_t<1, 8>(p, s);
+    case 3216: return launch_compress_cfg_pipe_t<1, 16>(p, s);
+    case 6404: return launch_compress_cfg_pipe_t<2, 8>(p, s);
+    case 6408: return launch_compress_cfg_pipe_t<2, 16>(p, s);
+    case 6416: return launch_compress_cfg_pipe_t<2, 32>(p, s);
+    default: return hipErrorInvalidValue;
     }
-    return launch_compress_cfg_t<false>(a, block, tile_blocks, s);
 }
 
 hipError_t launch_decompress_cfg(const DecompressArgs &a, int block, int tile_blocks, bool out_aligned16,
@@ -3824,8 +3549,8 @@ static hipError_t launch_batch_t(const BatchArgs &b, bool any_compress, bool any
                                  hipStream_t s)
 {
     size_t pad = 0;
-    if (ALIGNED && any_compress && !any_decompress) {
-        // compression only, 16-byte aligned inputs: the persistent pipeline,
+    if (any_compress && !any_decompress) {
+        // compression only: the persistent pipeline,
         // one workgroup per CU at most (its LDS); a cap of 1 needs no pad
         return b.njobs <= kPipeLdsJobs ? launch_batch_pipe<W, true>(b, groups, s)
                                        : launch_batch_pipe<W, false>(b, groups, s);
@@ -3872,10 +3597,7 @@ hipError_t launch_batch(const BatchArgs &b, bool aligned16, bool any_compress, b
     const uint64_t clear = ceil_div(b.nflags, kStatsThreads);
     if (grid < clear) grid = clear < kStatsMaxBlocks ? clear : kStatsMaxBlocks;
     if (grid < 1) grid = 1;
-    if (aligned16)
-        hipLaunchKernelGGL(batch_stats_kernel<true>, dim3((unsigned)grid), dim3(kStatsThreads), 0, s, b);
-    else
-        hipLaunchKernelGGL(batch_stats_kernel<false>, dim3((unsigned)grid), dim3(kStatsThreads), 0, s, b);
+    hipLaunchKernelGGL(batch_stats_kernel, dim3((unsigned)grid), dim3(kStatsThreads), 0, s, b);
     if (any_compress)
         hipLaunchKernelGGL(batch_stats_final_kernel, dim3(b.njobs), dim3(kStatsThreads), 0, s, b);
     hipError_t e = hipGetLastError();
@@ -3979,8 +3701,7 @@ fsz_status compress_noalloc(const float *d_in, uint64_t n, int mode, double valu
         d_stats = stats;
     }
     a.stats = d_stats;
-    const bool al16 = (reinterpret_cast<uintptr_t>(d_in) & 15u) == 0;
-    if (launch_compress(a, al16, tuning().staged_compress, s) != hipSuccess) return FSZ_ERR_DEVICE;
+    if (launch_compress(a, s) != hipSuccess) return FSZ_ERR_DEVICE;
     return FSZ_OK;
 }
 

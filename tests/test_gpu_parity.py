@@ -594,3 +594,31 @@ def test_offsets_pre_pass_group_edges(n):
             assert gpu_decompress(bytes(bad), n)[0] == fsz.FSZ_ERR_CORRUPT
     finally:
         oracle.set_threads(old)
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 1023, 1 << 15, (1 << 15) + 3, 1 << 20])
+def test_range_pass_off_the_16_byte_grid(n, offset):
+    """The value-range pass reads 16 bytes at a time between a field's first
+    and last 16-byte boundary and the elements outside them singly: the
+    extreme value at each end and next to each boundary must count (single
+    call and batch)."""
+    for at in sorted({k % n for k in (0, 4 - offset - 1, 4 - offset, n - 1, n - 2, n - 4, (1 << 15) - 1)}):
+        x = np.full(n + offset + 4, 1e9, np.float32)  # larger values lie outside the field
+        x[offset:offset + n] = np.linspace(-1.0, 1.0, n)
+        x[offset + at] = -40.0
+        xd = torch.from_numpy(x).to(_dev())
+        announce(f"range pass n={n} offset={offset} extreme at {at}")
+        stats = torch.zeros(4, dtype=torch.float32, device=_dev())
+        assert fsz.fsz_field_stats(xd.data_ptr() + 4 * offset, n, stats.data_ptr(), _stream()) == fsz.FSZ_OK
+        field = x[offset:offset + n]
+        want = [field.min(), field.max(), np.abs(field).max()]
+        assert stats.cpu().numpy()[:3].tolist() == want
+        if n > 1:  # one value alone is a constant field
+            ref = oracle.compress(field, oracle.REL, 1e-2)
+            out = torch.zeros(fsz.fsz_compressed_bound(n), dtype=torch.uint8, device=_dev())
+            res = torch.zeros(2, dtype=torch.int64, device=_dev())
+            job = fsz.compress_job(xd.data_ptr() + 4 * offset, n, fsz.FSZ_REL, 1e-2, out.data_ptr(), out.numel(),
+                                   res.data_ptr())
+            assert fsz.fsz_batch_async([job], None, _stream()) == fsz.FSZ_OK
+            assert out[:len(ref)].cpu().numpy().tobytes() == ref
