@@ -272,15 +272,14 @@ fsz_status fsz_decompress_config_async(const void *d_cmp, size_t cmp_size, float
  *
  * Every job produces exactly the bytes (compress) or floats (decompress)
  * that the plain call with the same arguments produces; only the launch
- * differs.  A batch runs as three kernels on the stream: a segmented
- * value-range pass over all compress jobs, a per-job fold of that pass, and
- * one kernel that takes (job, chunk) work items from a single ticket counter
- * in job order, each chunk following Sec. III-A steps 1-5 (compress) or
- * decompression steps 1-5, with one decoupled-lookback chain (Sec. IV-D) per
- * job.  That kernel is a persistent pipeline (the single-field kernels'
- * prefetch and overlap, across job boundaries) when every job compresses
- * from a 16-byte aligned input or every job decompresses, and one work item
- * per workgroup otherwise.
+ * differs.  A batch runs as two or three kernels on the stream: a segmented
+ * value-range pass over all compress jobs together with the chunk offsets of
+ * all decompress jobs (from their rate headers); the decompress jobs
+ * (decompression steps 1-5), one work item (job, chunk) per workgroup, with a
+ * per-job fold of the range pass; and the compress jobs (Sec. III-A steps
+ * 1-5), whose kernel takes work items from a single ticket counter in job
+ * order with one decoupled-lookback chain (Sec. IV-D) per job, in the
+ * single-field kernel's persistent pipeline across job boundaries.
  *
  * Jobs of one batch must not write memory that another job of the same batch
  * reads or writes.  Per-job errors (non-finite input, bound too small,
@@ -332,7 +331,7 @@ fsz_status fsz_autotune(const fsz_job *jobs, size_t njobs, int reps, void *strea
 
 /* A plan is a fixed batch captured once in a HIP graph: its job table,
  * flags and range-pass scratch live in plan-owned device memory, and
- * fsz_plan_launch replays the graph (three kernel nodes, no host work per
+ * fsz_plan_launch replays the graph (kernel nodes only, no host work per
  * replay).  Buffers named by the jobs must stay valid for the plan's life.
  * Launches of one plan are ordered only if they share a stream; a plan must
  * not run concurrently with itself.  tuning NULL = as fsz_batch_async. */

@@ -102,6 +102,8 @@ struct Workspace {
     fsz_stats *b_stats = nullptr;
     uint64_t b_stats_cap = 0;
     unsigned long long *b_ticket = nullptr;
+    unsigned long long *b_words = nullptr;  // decompress jobs: group totals, chunk offsets
+    uint64_t b_words_cap = 0;
     // five-read baseline: evaluation tables (53 bytes per tile)
     uint8_t *d_naive = nullptr;
     uint64_t naive_cap = 0;
@@ -411,34 +413,44 @@ fsz_status enqueue_decompress_range(Workspace *ws, const void *d_cmp, uint64_t c
 
 // ------------------------------------------------------------------ batched form
 
-// Device-side layout of a batch for one launch shape.
-struct BatchLayout {
+// Device-side layout of a batch for one launch shape: the jobs of one kind, and
+// both kinds (k[FSZ_OP_COMPRESS], k[FSZ_OP_DECOMPRESS]) one after the other.
+struct KindLayout {
     std::vector<BatchJob> jobs;
     std::vector<uint64_t> chunk_end, seg_end;
-    uint64_t total_chunks = 0, total_segs = 0, total_elems = 0;
-    bool aligned16 = true, any_compress = false, any_decompress = false;
-    size_t desc_bytes() const { return jobs.size() * (sizeof(BatchJob) + 2 * sizeof(uint64_t)); }
-    void pack(void *dst) const
+    uint64_t total_chunks = 0, total_segs = 0;
+    size_t bytes() const { return jobs.size() * (sizeof(BatchJob) + 2 * sizeof(uint64_t)); }
+    char *pack(char *p) const
     {
-        char *p = static_cast<char *>(dst);
-        std::memcpy(p, jobs.data(), jobs.size() * sizeof(BatchJob));
-        p += jobs.size() * sizeof(BatchJob);
-        std::memcpy(p, chunk_end.data(), jobs.size() * sizeof(uint64_t));
-        p += jobs.size() * sizeof(uint64_t);
-        std::memcpy(p, seg_end.data(), jobs.size() * sizeof(uint64_t));
+        const size_t nj = jobs.size();
+        if (nj == 0) return p;
+        std::memcpy(p, jobs.data(), nj * sizeof(BatchJob));
+        p += nj * sizeof(BatchJob);
+        std::memcpy(p, chunk_end.data(), nj * sizeof(uint64_t));
+        p += nj * sizeof(uint64_t);
+        std::memcpy(p, seg_end.data(), nj * sizeof(uint64_t));
+        return p + nj * sizeof(uint64_t);
     }
+};
+struct BatchLayout {
+    KindLayout k[2];
+    bool aligned_out = true;  // every decompress output is 16-byte aligned
+    int waves = 4;
+    size_t desc_bytes() const { return k[0].bytes() + k[1].bytes(); }
+    void pack(void *dst) const { (void)k[1].pack(k[0].pack(static_cast<char *>(dst))); }
+    uint64_t flag_words() const { return k[FSZ_OP_COMPRESS].total_chunks * kFlagStride; }
+    // the decompress jobs' group totals and chunk offsets
+    uint64_t dec_words() const { return k[FSZ_OP_DECOMPRESS].total_segs + k[FSZ_OP_DECOMPRESS].total_chunks; }
 };
 
 // Validates every job (nothing is enqueued unless all pass) and lays out
-// global chunk and range-pass segment ranges in job order.
+// global chunk and segment (or tile group) ranges of each kind in job order.
 fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayout *L)
 {
     if (njobs > 0 && !jobs) return FSZ_ERR_INVALID_ARG;
     if (njobs >= (1u << 31)) return FSZ_ERR_INVALID_ARG;
     const uint64_t tiles_per_chunk = (uint64_t)kTilesPerWave * (uint64_t)waves;
-    L->jobs.resize(njobs);
-    L->chunk_end.resize(njobs);
-    L->seg_end.resize(njobs);
+    L->waves = waves;
     for (size_t k = 0; k < njobs; k++) {
         const fsz_job &j = jobs[k];
         if (!j.d_result) return FSZ_ERR_INVALID_ARG;
@@ -465,25 +477,27 @@ fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayou
         J.dst_capacity = j.op == FSZ_OP_COMPRESS ? j.dst_capacity : 0;
         J.value = j.value;
         J.final = j.d_result;
-        J.chunk_base = L->total_chunks;
-        L->total_chunks += J.nchunks;
-        J.seg_base = L->total_segs;
-        J.nsegs = j.op == FSZ_OP_COMPRESS ? ceil_div(j.n, kSegElems) : 0;
-        L->total_segs += J.nsegs;
-        L->total_elems += j.n;
-        L->chunk_end[k] = L->total_chunks;
-        L->seg_end[k] = L->total_segs;
+        KindLayout &K = L->k[j.op];
+        J.chunk_base = K.total_chunks;
+        K.total_chunks += J.nchunks;
+        J.seg_base = K.total_segs;
         if (j.op == FSZ_OP_COMPRESS) {
-            L->any_compress = true;
-            L->aligned16 = L->aligned16 && aligned(j.d_src, 16);
+            J.nsegs = ceil_div(j.n, kSegElems);
         } else {
-            L->any_decompress = true;
-            L->aligned16 = L->aligned16 && aligned(j.d_dst, 16);
+            J.group_passes = group_passes(J.ntiles);
+            const uint64_t tiles = (uint64_t)kGroupTiles * J.group_passes;
+            J.nsegs = J.ntiles ? ceil_div(J.ntiles, tiles) : 1;
+            J.group_shift = (uint32_t)__builtin_ctzll(tiles / tiles_per_chunk);
+            L->aligned_out = L->aligned_out && aligned(j.d_dst, 16);
         }
-        L->jobs[k] = J;
+        K.total_segs += J.nsegs;
+        K.chunk_end.push_back(K.total_chunks);
+        K.seg_end.push_back(K.total_segs);
+        K.jobs.push_back(J);
     }
     // one work item per workgroup: grid x times workgroup size must fit 32 bits
-    if (L->total_chunks * (uint64_t)(waves * 64) >= (1ull << 32) || L->total_segs * kStatsThreads >= (1ull << 32))
+    if ((L->k[0].total_chunks + L->k[1].total_chunks) * (uint64_t)(waves * 64) >= (1ull << 32) ||
+        (L->k[0].total_segs + L->k[1].total_segs) * kStatsThreads >= (1ull << 32))
         return FSZ_ERR_INVALID_ARG;
     return FSZ_OK;
 }
@@ -612,23 +626,35 @@ fsz_status resolve_tuning(const fsz_job *jobs, size_t njobs, const fsz_tuning *t
 }
 
 BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigned long long *flags,
-                     unsigned long long *ticket, fsz_stats *stats, StatsPartial *partials)
+                     unsigned long long *ticket, fsz_stats *stats, StatsPartial *partials, unsigned long long *words)
 {
     BatchArgs b{};
-    const size_t nj = L.jobs.size();
+    const KindLayout &C = L.k[FSZ_OP_COMPRESS], &D = L.k[FSZ_OP_DECOMPRESS];
+    auto table = [](char *p, const KindLayout &K, const BatchJob **jobs, const uint64_t **chunk_end,
+                    const uint64_t **seg_end) {
+        const size_t nj = K.jobs.size();
+        *jobs = reinterpret_cast<const BatchJob *>(p);
+        *chunk_end = reinterpret_cast<const uint64_t *>(p + nj * sizeof(BatchJob));
+        *seg_end = reinterpret_cast<const uint64_t *>(p + nj * (sizeof(BatchJob) + sizeof(uint64_t)));
+    };
     char *p = static_cast<char *>(d_desc);
-    b.jobs = reinterpret_cast<const BatchJob *>(p);
-    b.chunk_end = reinterpret_cast<const uint64_t *>(p + nj * sizeof(BatchJob));
-    b.seg_end = reinterpret_cast<const uint64_t *>(p + nj * (sizeof(BatchJob) + sizeof(uint64_t)));
-    b.njobs = (uint32_t)nj;
+    table(p, C, &b.jobs, &b.chunk_end, &b.seg_end);
+    table(p + C.bytes(), D, &b.dec.jobs, &b.dec.chunk_end, &b.dec.group_end);
+    b.njobs = (uint32_t)C.jobs.size();
     b.epoch = epoch;
-    b.total_chunks = L.total_chunks;
-    b.total_segs = L.total_segs;
-    b.nflags = L.total_chunks * kFlagStride;  // words
+    b.total_chunks = C.total_chunks;
+    b.total_segs = C.total_segs;
+    b.nflags = L.flag_words();
     b.flags = flags;
     b.ticket = ticket;
     b.stats = stats;
     b.partials = partials;
+    b.dec.njobs = (uint32_t)D.jobs.size();
+    b.dec.tpc_log2 = (uint32_t)__builtin_ctz((unsigned)(kTilesPerWave * L.waves));
+    b.dec.total_chunks = D.total_chunks;
+    b.dec.total_groups = D.total_segs;
+    b.dec.groups = words;
+    b.dec.offsets = words + D.total_segs;
     return b;
 }
 
@@ -655,9 +681,10 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
     BatchLayout L;
     fsz_status st = layout_batch(jobs, njobs, shape.waves, &L);
     if (st != FSZ_OK || njobs == 0) return st;
-    if (!grow(&ws->b_flags, &ws->b_flags_cap, L.total_chunks * kFlagStride, ws->stream) ||
-        !grow(&ws->b_partials, &ws->b_partials_cap, std::max<uint64_t>(L.total_segs, 1), ws->stream) ||
-        !grow(&ws->b_stats, &ws->b_stats_cap, njobs, ws->stream))
+    if (!grow(&ws->b_flags, &ws->b_flags_cap, L.flag_words(), ws->stream) ||
+        !grow(&ws->b_partials, &ws->b_partials_cap, L.k[FSZ_OP_COMPRESS].total_segs, ws->stream) ||
+        !grow(&ws->b_stats, &ws->b_stats_cap, njobs, ws->stream) ||
+        !grow(&ws->b_words, &ws->b_words_cap, L.dec_words(), ws->stream))
         return FSZ_ERR_DEVICE;
     DescSlot &slot = ws->ring[ws->ring_next++ % ws->ring.size()];
     if (slot.used && !ok(hipEventSynchronize(slot.ev))) return FSZ_ERR_DEVICE;
@@ -666,8 +693,9 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
     L.pack(slot.h);
     if (!ok(hipMemcpyAsync(slot.d, slot.h, bytes, hipMemcpyHostToDevice, ws->stream))) return FSZ_ERR_DEVICE;
     if (++ws->call == 0) ++ws->call;
-    const BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_stats, ws->b_partials);
-    if (!ok(launch_batch(b, L.aligned16, L.any_compress, L.any_decompress, shape, ws->stream))) return FSZ_ERR_DEVICE;
+    const BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_stats, ws->b_partials,
+                                   ws->b_words);
+    if (!ok(launch_batch(b, L.aligned_out, shape, ws->stream))) return FSZ_ERR_DEVICE;
     if (!ok(hipEventRecord(slot.ev, ws->stream))) return FSZ_ERR_DEVICE;
     slot.used = true;
     return FSZ_OK;
@@ -685,7 +713,8 @@ bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t 
     std::lock_guard<std::mutex> g(ws->mu);
     if (!grow(&ws->b_flags, &ws->b_flags_cap, std::max<uint64_t>(chunks, 1) * kFlagStride, ws->stream) ||
         !grow(&ws->b_partials, &ws->b_partials_cap, std::max<uint64_t>(segs, 1), ws->stream) ||
-        !grow(&ws->b_stats, &ws->b_stats_cap, std::max<uint64_t>(jobs, 1), ws->stream))
+        !grow(&ws->b_stats, &ws->b_stats_cap, std::max<uint64_t>(jobs, 1), ws->stream) ||
+        !grow(&ws->b_words, &ws->b_words_cap, chunks + segs, ws->stream))  // a tile group holds several segments
         return false;
     const size_t bytes = jobs * (sizeof(BatchJob) + 2 * sizeof(uint64_t));
     for (auto &slot : ws->ring) {
@@ -707,6 +736,7 @@ struct fsz_plan {
     unsigned long long *d_ticket = nullptr;
     StatsPartial *d_partials = nullptr;
     fsz_stats *d_stats = nullptr;
+    unsigned long long *d_words = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
@@ -723,6 +753,7 @@ void free_plan(fsz_plan *p)
     (void)hipFree(p->d_ticket);
     (void)hipFree(p->d_partials);
     (void)hipFree(p->d_stats);
+    (void)hipFree(p->d_words);
     delete p;
 }
 
@@ -1013,20 +1044,22 @@ fsz_status fsz_plan_create(const fsz_job *jobs, size_t njobs, const fsz_tuning *
         L.pack(host.data());
         hipStream_t cs = nullptr;
         good = ok(hipMalloc(&p->d_desc, host.size())) &&
-               ok(hipMalloc(&p->d_flags, std::max<uint64_t>(L.total_chunks, 1) * kFlagStride * sizeof(unsigned long long))) &&
+               ok(hipMalloc(&p->d_flags, std::max<uint64_t>(L.flag_words(), 1) * sizeof(unsigned long long))) &&
+               ok(hipMalloc(&p->d_words, std::max<uint64_t>(L.dec_words(), 1) * sizeof(unsigned long long))) &&
                ok(hipMalloc(&p->d_ticket, sizeof(unsigned long long))) &&
-               ok(hipMalloc(&p->d_partials, std::max<uint64_t>(L.total_segs, 1) * sizeof(StatsPartial))) &&
+               ok(hipMalloc(&p->d_partials,
+                            std::max<uint64_t>(L.k[FSZ_OP_COMPRESS].total_segs, 1) * sizeof(StatsPartial))) &&
                ok(hipMalloc(&p->d_stats, njobs * sizeof(fsz_stats))) &&
                ok(hipMemcpy(p->d_desc, host.data(), host.size(), hipMemcpyHostToDevice)) &&
                ok(hipMemset(p->d_ticket, 0, sizeof(unsigned long long))) && ok(hipDeviceSynchronize()) &&
                ok(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
         if (good) {
             const BatchArgs b = batch_args(L, p->d_desc, g_plan_ids++, p->d_flags, p->d_ticket, p->d_stats,
-                                           p->d_partials);
+                                           p->d_partials, p->d_words);
             good = ok(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
             if (good) {
                 const bool launched =
-                    ok(launch_batch(b, L.aligned16, L.any_compress, L.any_decompress, to_shape(t), cs));
+                    ok(launch_batch(b, L.aligned_out, to_shape(t), cs));
                 const bool ended = ok(hipStreamEndCapture(cs, &p->graph));
                 good = launched && ended && ok(hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0));
             }

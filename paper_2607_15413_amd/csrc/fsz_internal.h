@@ -113,14 +113,31 @@ struct NaiveTables {
     uint8_t *centre_ok;  // ntiles: the mean is finite
 };
 
+// ---- offsets pre-pass of the decoders: geometry of its groups
+
+constexpr int kGroupThreads = 256;
+constexpr int kGroupTilesPerThread = 4;
+constexpr int kGroupTiles = kGroupThreads * kGroupTilesPerThread;
+constexpr uint64_t kMaxGroupWords = 512;
+// Rounds of kGroupTiles tiles per group: the least power of two that leaves at
+// most kMaxGroupWords groups.
+inline uint32_t group_passes(uint64_t ntiles)
+{
+    uint32_t p = 1;
+    while (ceil_div(ntiles, (uint64_t)kGroupTiles * p) > kMaxGroupWords) p *= 2;
+    return p;
+}
+
 // ---- batched form: one launch over many jobs (compress or decompress)
 
 constexpr int kSegElems = 32768;  // elements per workgroup of the batched range pass
 
 // One job of a batch, as the kernels read it (built by the host, uploaded to
-// device memory once per batch).  Chunks of job j are global chunks
-// [chunk_base, chunk_base + nchunks); its range-pass segments are
-// [seg_base, seg_base + nsegs) (compress only).
+// device memory once per batch).  The compress jobs come first, then the
+// decompress jobs, each in the caller's order and with counts of their own.
+// Chunks of job j are items [chunk_base, chunk_base + nchunks) of its kind;
+// its range-pass segments (compress) or tile groups (decompress) are
+// [seg_base, seg_base + nsegs).
 struct BatchJob {
     uint32_t op;  // FSZ_OP_COMPRESS or FSZ_OP_DECOMPRESS
     int32_t mode;
@@ -132,11 +149,12 @@ struct BatchJob {
     double value;
     fsz_result *final;
     uint64_t chunk_base, seg_base, nsegs;
-    uint64_t pad;
+    uint32_t group_passes, group_shift;  // decompress: rounds of kGroupTiles per group, log2 of its chunks
 };
 static_assert(sizeof(BatchJob) == 128, "BatchJob layout");
 
 struct BatchArgs {
+    // compress jobs
     const BatchJob *jobs;
     const uint64_t *chunk_end;  // chunk_end[j] = chunk_base[j] + nchunks[j]
     const uint64_t *seg_end;    // seg_end[j] = seg_base[j] + nsegs[j]
@@ -147,6 +165,14 @@ struct BatchArgs {
     unsigned long long *ticket; // zero between launches (self-resetting)
     fsz_stats *stats;           // one per job
     StatsPartial *partials;     // one per segment
+    // decompress jobs
+    struct {
+        const BatchJob *jobs;
+        const uint64_t *chunk_end, *group_end;
+        uint32_t njobs, tpc_log2;         // log2 of the tiles per chunk
+        uint64_t total_chunks, total_groups;
+        unsigned long long *groups, *offsets;  // one word per group / per chunk
+    } dec;
 };
 
 // Launch shape of the batched kernel: waves per workgroup (a chunk is 8 tiles
@@ -169,7 +195,6 @@ hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bo
 // dec_direct_below elements, a persistent grid over chunks of 64.  words
 // (pre-pass only): kMaxGroupWords words and one per chunk of 32 tiles up to
 // tile_end.
-constexpr uint64_t kMaxGroupWords = 512;
 hipError_t launch_decompress(const DecompressArgs &a, unsigned long long *words, bool out_aligned16, bool range,
                              hipStream_t s);
 // Pre-zeroed decompression (Sec. III-A): a fill of out[0, n) with +0.0, the
@@ -203,11 +228,10 @@ inline bool cfg_supported(int block, int tile_blocks)
 {
     return (block == 32 || block == 64) && (tile_blocks == 4 || tile_blocks == 8 || tile_blocks == 16);
 }
-// Range pass + flag clear, per-job stats, then the batched kernel.
-// Compress-only batches run a persistent pipelined kernel, decompress-only batches a persistent decoder, mixed
-// batches one work item per workgroup.
-hipError_t launch_batch(const BatchArgs &b, bool aligned16, bool any_compress, bool any_decompress,
-                        const BatchShape &shape, hipStream_t s);
+// Range pass + flag clear + offsets pre-pass, then the decompress jobs (one
+// item per workgroup) with the per-job stats, then the compress jobs (a
+// persistent pipelined kernel).
+hipError_t launch_batch(const BatchArgs &b, bool aligned_out, const BatchShape &shape, hipStream_t s);
 bool batch_shape_supported(const BatchShape &shape);
 
 // Allocation-free compression: fsz_compress_async's work with every scratch

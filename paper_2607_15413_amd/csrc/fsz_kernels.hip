@@ -548,7 +548,8 @@ __device__ __forceinline__ void stats_combine(float &mn, float &mx, float &ma, u
     nf |= p.flags;
 }
 
-// block-wide reduction of (min, max, max|x|, non-finite); result in thread 0
+// block-wide reduction of (min, max, max|x|, non-finite); result in every thread
+template <int THREADS>
 __device__ StatsPartial stats_block_reduce(float mn, float mx, float ma, uint32_t nf)
 {
     for (int m = 32; m >= 1; m >>= 1) {
@@ -557,11 +558,11 @@ __device__ StatsPartial stats_block_reduce(float mn, float mx, float ma, uint32_
         ma = fmaxf(ma, __shfl_xor(ma, m));
         nf |= __shfl_xor(nf, m);
     }
-    __shared__ StatsPartial wsum[kStatsThreads / 64];
+    __shared__ StatsPartial wsum[THREADS / 64];
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = StatsPartial{mn, mx, ma, nf};
     __syncthreads();
     StatsPartial p = wsum[0];
-    for (int k = 1; k < kStatsThreads / 64; k++) stats_combine(p.xmin, p.xmax, p.maxabs, p.flags, wsum[k]);
+    for (int k = 1; k < THREADS / 64; k++) stats_combine(p.xmin, p.xmax, p.maxabs, p.flags, wsum[k]);
     return p;
 }
 
@@ -588,7 +589,7 @@ struct RangeAcc {
     __device__ __forceinline__ StatsPartial reduce() const
     {
         const uint32_t nf = ma >= 0x7F800000u ? 1u : 0u;
-        return stats_block_reduce(mn, mx, __uint_as_float(ma & 0x7FFFFFFFu), nf);
+        return stats_block_reduce<kStatsThreads>(mn, mx, __uint_as_float(ma & 0x7FFFFFFFu), nf);
     }
 };
 
@@ -635,7 +636,7 @@ __global__ __launch_bounds__(kStatsThreads) void stats_final_kernel(StatsArgs a,
     float mn = INFINITY, mx = -INFINITY, ma = 0.0f;
     uint32_t nf = 0;
     for (unsigned i = threadIdx.x; i < nparts; i += blockDim.x) stats_combine(mn, mx, ma, nf, a.partials[i]);
-    const StatsPartial p = stats_block_reduce(mn, mx, ma, nf);
+    const StatsPartial p = stats_block_reduce<kStatsThreads>(mn, mx, ma, nf);
     if (threadIdx.x == 0) *a.out = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
 }
 
@@ -1034,37 +1035,6 @@ __device__ __forceinline__ uint64_t next_ticket(unsigned long long *ticket, uint
     const uint64_t t = sh.ticket[slot];
     slot ^= 1;
     return t;
-}
-
-// One chunk of a compression (Sec. III-A steps 1-5) by a workgroup of W
-// waves: bound resolution, coalesced load, rate pass, lookback, encode.
-template <bool ALIGNED, int W>
-__device__ __forceinline__ void compress_chunk(const CompressArgs &a, uint64_t chunk, CompressShared<W> &sh,
-                                               uint32_t *st)
-{
-    const int tid = threadIdx.x;
-    const int w = tid >> 6;
-    const int lane = tid & 63;
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
-    if (R.status != FSZ_OK) {
-        if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, R.status, a.epoch);
-        return;
-    }
-    const uint64_t tile0 = chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
-    int x[32];
-    {
-        float f[32];
-        if (tile0 < a.ntiles) {
-            load_blocks_staged<ALIGNED>(a.x, a.n, tile0 * kTile, st, lane, f);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 32; i++) f[i] = 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < 32; i++) x[i] = __float_as_int(f[i]);
-    }
-    const ChunkState cs = compress_rates<W>(a, R, chunk, x, 0, sh);
-    compress_encode<W>(a, R, cs, x, 0, sh, st);
 }
 
 // ------------------------------------------------------------------ naive five-read baseline
@@ -1693,7 +1663,6 @@ struct DecChunk {
 
 // How a decoder's workgroup learns its chunk's byte offset.
 enum DecOffsets {
-    kByLookback,  // decoupled lookback over the chunks' aggregates (batches)
     kByGroups,    // group totals and in-group offsets from dec_groups_kernel, chunk after chunk
     kByGroupsOnce,  // the same for a workgroup's only chunk
     kByPrefix     // its own sum over the rate bytes before the chunk
@@ -1701,17 +1670,15 @@ enum DecOffsets {
 
 // Slots rotate from chunk to chunk.  The persistent decoder with the offsets
 // pre-pass passes one barrier per chunk, so a wave may be one chunk ahead of
-// another and three slots are in use; the lookback decoders pass several and
-// use two.
+// another and three slots are in use.
 template <int W>
 struct DecompressShared {
     uint32_t wave_total[3][W];
     unsigned long long wave_prefix[W];  // kByPrefix, kByGroupsOnce: the waves' shares of the sum, and
     uint32_t wave_bad[W];               // whether they saw a reserved rate-byte bit
     unsigned long long group_base[3];
-    int bad[2];
-    unsigned long long base;
-    unsigned long long ticket[2];  // alternating broadcast slots
+    unsigned long long base;       // tile configurations
+    unsigned long long ticket[2];  // (their lookback form: alternating broadcast slots)
 };
 
 // Running sum over the groups of the offsets pre-pass (dec_groups_kernel), kept
@@ -1755,8 +1722,7 @@ __device__ __forceinline__ void finish_decode(const DecompressArgs &a, bool bad,
 }
 
 // Decompression steps 1-2 (Sec. III-A): rate bytes and tile metadata ->
-// block and tile sizes, and the chunk's offset (kByLookback: the chunk's
-// aggregate, published at once so that successors' lookbacks rarely wait).
+// block and tile sizes, and the chunk's offset.
 // RANGE: decode the tiles [a.tile_begin, a.tile_end) only (random access);
 // otherwise the whole field (the range fields are not read).  Chunks count
 // from the field's first tile, but from tile_begin with kByPrefix.
@@ -1850,7 +1816,7 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
     d.wave_total = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
     d.blk_off = d.tile_excl + group_excl_scan(S, j) + 4u * d.cent;
     d.base = 0;
-    if (OFF == kByGroups) {
+    if constexpr (OFF == kByGroups) {
         if (w == 0) {
             groups_advance(a.groups, chunk >> a.group_shift, gc);
             if (lane == 0) sh.group_base[slot] = gc.sum + a.offsets[chunk];
@@ -1858,7 +1824,6 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
         if (lane == 0) sh.wave_total[slot][w] = d.wave_total;
         lds_barrier();
         d.base = sh.group_base[slot];
-        return d;
     }
     if constexpr (OFF == kByPrefix || OFF == kByGroupsOnce) {
         bool seen;
@@ -1893,27 +1858,12 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
             d.base += sh.wave_prefix[k];
             gc.bad = gc.bad || sh.wave_bad[k] != 0;
         }
-        return d;
     }
-    const bool wave_bad = __ballot(bad) != 0;
-    if (lane == 0) {
-        sh.wave_total[slot][w] = d.wave_total;
-        if (w == 0) sh.bad[slot] = 0;
-    }
-    lds_barrier();
-    if (lane == 0 && wave_bad) sh.bad[slot] = 1;
-    lds_barrier();
-    uint32_t chunk_total = 0;
-#pragma unroll
-    for (int k = 0; k < W; k++) chunk_total += sh.wave_total[slot][k];
-    if (tid == 0) publish_aggregate(a.flags, chunk, a.flag_epoch, chunk_total, sh.bad[slot] != 0);
     return d;
 }
 
 // Decompression step 3 (Sec. III-A): where the wave's share of the chunk's data
-// starts (kByLookback: the chunk's offset from the lookback of wave 0; the
-// workgroup waits at one barrier).  The workgroup owning the last chunk
-// reports the outcome.  live: the wave has blocks to decode, inside the stream.
+// starts.  The workgroup owning the last chunk reports the outcome.  live: the wave has blocks to decode, inside the stream.
 // PREZERO: the output was cleared to +0.0 before the launch (Sec. III-A, for
 // highly compressible streams); a wave whose blocks all have rate 0 and whose
 // tiles are all uncentred decodes to q = 0, i.e. +0.0 everywhere, and is not
@@ -1938,25 +1888,14 @@ __device__ __forceinline__ DecPlace dec_place(const DecompressArgs &a, const Dec
         if (k < w) wave_base += sh.wave_total[slot][k];
         chunk_total += sh.wave_total[slot][k];
     }
-    uint64_t base = d.base;
-    bool bad = false;
-    if (OFF == kByLookback) {
-        bad = sh.bad[slot] != 0;
-        if (w == 0) {
-            const Prefix pre = lookback_wait(a.flags, d.chunk, a.flag_epoch, chunk_total, bad);
-            if (lane == 0) sh.base = pre.excl;
-            if (d.chunk == a.nchunks - 1) finish_decode<RANGE>(a, pre.err, pre.excl + chunk_total, total);
-        }
-        lds_barrier();
-        base = sh.base;
-    } else if (w == 0 && d.chunk == a.nchunks - 1) {
-        const bool seen = gc.bad || ((OFF == kByGroups || OFF == kByGroupsOnce) && (a.groups[gc.next] & kGroupBad) != 0);
-        finish_decode<RANGE>(a, seen, base + chunk_total, total);
+    if (w == 0 && d.chunk == a.nchunks - 1) {
+        const bool seen = gc.bad || (OFF != kByPrefix && (a.groups[gc.next] & kGroupBad) != 0);
+        finish_decode<RANGE>(a, seen, d.base + chunk_total, total);
     }
     DecPlace p;
     p.tile0 = dec_chunk_tile0<W, RANGE, OFF>(a, d.chunk) + (uint64_t)w * kTilesPerWave;
-    p.wave_data = a.cmp + a.data0 + base + wave_base;
-    p.live = !bad && a.data0 + base + chunk_total <= total && p.tile0 < (RANGE ? a.tile_end : a.ntiles) &&
+    p.wave_data = a.cmp + a.data0 + d.base + wave_base;
+    p.live = a.data0 + d.base + chunk_total <= total && p.tile0 < (RANGE ? a.tile_end : a.ntiles) &&
              (!RANGE || p.tile0 + kTilesPerWave > a.tile_begin);
     if (PREZERO && p.live) {
         const uint64_t gblock = (p.tile0 + (lane >> 3)) * kBlocksPerTile + j;
@@ -2163,25 +2102,21 @@ __global__ __launch_bounds__(W * 64) void decompress_kernel(DecompressArgs a)
 // kGroupTiles << m consecutive tiles, writes the offset of each of its chunks
 // inside the group and the group's total, and ends.  The decoder adds up the
 // totals of the groups before its own, 64 per load; m is the least that keeps
-// them at kMaxGroups (8 loads for the last chunk of any field).  What bounds
+// them at kMaxGroupWords (8 loads for the last chunk of any field).  What bounds
 // it is one round trip for the rate bytes and the launch itself: 512^3 takes
 // 4.9 us, where workgroups in ticket order with a decoupled lookback
 // over their totals took 9.4 us (25 M elements: 4.7 against 8.0 us).
-constexpr int kGroupThreads = 256;
-constexpr int kGroupTilesPerThread = 4;
-constexpr int kGroupTiles = kGroupThreads * kGroupTilesPerThread;
-constexpr uint64_t kMaxGroups = kMaxGroupWords;
 
-// TPC tiles per decoder chunk; T blocks per tile of HB 32-element segments
-// each (the default format: 8 and 1; the tile configurations: the stream's).
-// The rate header lies inside the buffer (checked by the host), so any bytes
-// may be read before the decoder has looked at the stream header.
-template <int TPC, int T = kBlocksPerTile, int HB = 1>
-__global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArgs a, unsigned long long *offs,
-                                                                   unsigned long long *groups, uint32_t passes)
+// One group: tiles [group * passes * kGroupTiles, ...) below a.tile_end.
+// 2^tpc_log2 tiles per decoder chunk (at least a thread's tiles); T blocks per
+// tile of HB 32-element segments each (the default format: 8 and 1; the tile
+// configurations: the stream's).  The rate header is read where it lies inside
+// the buffer, before anything has looked at the stream header.
+template <int T, int HB>
+__device__ __forceinline__ void group_sums(const DecompressArgs &a, uint64_t group, uint32_t passes,
+                                           uint32_t tpc_log2, unsigned long long *offs, unsigned long long *groups)
 {
     static_assert(T == 4 || T == 8 || T == 16, "a tile's rate bytes are 1, 2 or 4 words");
-    static_assert(TPC % kGroupTilesPerThread == 0, "a chunk starts at a thread's first tile");
     constexpr int kWavesG = kGroupThreads / 64;
     constexpr int kWords = kGroupTilesPerThread * T / 4;
     __shared__ uint32_t wsum[2][kWavesG];
@@ -2195,7 +2130,7 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
     uint32_t bad = 0;
     for (uint32_t p = 0; p < passes; p++) {
         const uint64_t tile0 =
-            (((uint64_t)blockIdx.x * passes + p) * kGroupThreads + (uint64_t)tid) * kGroupTilesPerThread;
+            ((group * passes + p) * kGroupThreads + (uint64_t)tid) * kGroupTilesPerThread;
         uint32_t units = 0, cents = 0;
         const g_u32 *rp = (const g_u32 *)(a.cmp + kHeaderBytes + tile0 * T);
         if ((tile0 + kGroupTilesPerThread) * T <= nb) {
@@ -2229,7 +2164,7 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
             if (k < w) wave_base += wsum[p & 1][k];
             ptotal += wsum[p & 1][k];
         }
-        if (tile0 < a.tile_end && (tile0 % TPC) == 0) offs[tile0 / TPC] = run + wave_base + incl - z;
+        if (tile0 < a.tile_end && (tile0 & ((1u << tpc_log2) - 1u)) == 0) offs[tile0 >> tpc_log2] = run + wave_base + incl - z;
         run += ptotal;
     }
     const bool wave_bad = __ballot(bad != 0) != 0;
@@ -2239,9 +2174,17 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
         uint32_t any = 0;
 #pragma unroll
         for (int k = 0; k < kWavesG; k++) any |= wbad[k];
-        groups[blockIdx.x] = run | (any ? kGroupBad : 0ull);
+        groups[group] = run | (any ? kGroupBad : 0ull);
         if (a.tile_end == 0) offs[0] = 0;
     }
+}
+
+template <int T, int HB>
+__global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArgs a, unsigned long long *offs,
+                                                                   unsigned long long *groups, uint32_t passes,
+                                                                   uint32_t tpc_log2)
+{
+    group_sums<T, HB>(a, blockIdx.x, passes, tpc_log2, offs, groups);
 }
 
 // One chunk of 8*W tiles per workgroup and no order to keep: the hardware
@@ -2258,12 +2201,9 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
 // The size pass needs nothing of the stream header but the room for the rate
 // bytes, so its loads go out before the header's have come back.
 template <bool ALIGNED, int W, bool RANGE, int OFF>
-__global__ __launch_bounds__(W * 64) void decompress_direct_kernel(DecompressArgs a)
+__device__ __forceinline__ void decompress_one(const DecompressArgs &a, uint64_t chunk, DecompressShared<W> &sh,
+                                               uint32_t *st)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
-    __shared__ DecompressShared<W> sh;
-    const uint64_t chunk = a.chunk_begin + blockIdx.x;
-    uint32_t *st = stage + (threadIdx.x >> 6) * kStageWaveDwords;
     GroupCursor gc;
     DecChunk dc;
     const bool room = a.data0 <= a.cmp_size;
@@ -2273,11 +2213,20 @@ __global__ __launch_bounds__(W * 64) void decompress_direct_kernel(DecompressArg
     bool indep;
     const int hst = dec_header(a, E, total, indep);
     if (!room || hst != FSZ_OK) {
-        if (threadIdx.x == 0 && blockIdx.x == 0) write_final(a.final, 0, hst, a.epoch);
+        if (threadIdx.x == 0 && chunk == a.chunk_begin) write_final(a.final, 0, hst, a.epoch);
         return;
     }
     const DecPlace pl = dec_place<W, RANGE, false, OFF>(a, dc, 0, total, sh, gc);
     if (pl.live) dec_decode<ALIGNED, W, RANGE>(a, dc, pl, E, indep, st);
+}
+
+template <bool ALIGNED, int W, bool RANGE, int OFF>
+__global__ __launch_bounds__(W * 64) void decompress_direct_kernel(DecompressArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
+    __shared__ DecompressShared<W> sh;
+    decompress_one<ALIGNED, W, RANGE, OFF>(a, a.chunk_begin + blockIdx.x, sh,
+                                           stage + (threadIdx.x >> 6) * kStageWaveDwords);
 }
 
 // ------------------------------------------------------------------ batched form
@@ -2296,17 +2245,56 @@ __device__ __forceinline__ uint32_t find_job(const uint64_t *end, uint32_t njobs
     return njobs;
 }
 
-// Batched range pass: workgroup s reduces segment s (kSegElems elements of
-// one compress job) into partials[s]; every workgroup also clears a slice of
-// the batch's chunk flags for the kernel that follows.
+__device__ __forceinline__ DecompressArgs batch_decompress_args(const BatchArgs &b, const BatchJob &J)
+{
+    DecompressArgs a;
+    a.cmp = static_cast<const uint8_t *>(J.src);
+    a.cmp_size = J.src_size;
+    a.out = static_cast<float *>(J.dst);
+    a.n = J.n;
+    a.ntiles = J.ntiles;
+    a.nblocks = J.nblocks;
+    a.nchunks = J.nchunks;
+    a.data0 = J.data0;
+    a.tile_begin = 0;
+    a.tile_end = J.ntiles;
+    a.elem_begin = 0;
+    a.elem_end = J.n;
+    a.chunk_begin = 0;
+    a.cfg_flags = 0;
+    a.groups = b.dec.groups + J.seg_base;
+    a.offsets = b.dec.offsets + J.chunk_base;
+    a.group_shift = J.group_shift;
+    a.epoch = b.epoch;
+    a.flag_epoch = 0;
+    a.flags = nullptr;
+    a.ticket = nullptr;
+    a.final = J.final;
+    return a;
+}
+
+// Batched range pass and offsets pre-pass.  The first b.dec.total_groups
+// workgroups each sum one group of tiles of a decompress job (as
+// dec_groups_kernel).  The others reduce segments (kSegElems elements of one
+// compress job, a partial each) and clear the batch's chunk flags for the
+// kernel that follows.
 __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * kStatsThreads + threadIdx.x; i < b.nflags;
-         i += (uint64_t)gridDim.x * kStatsThreads)
-        b.flags[i] = 0;
+    static_assert(kStatsThreads == kGroupThreads, "both parts of the launch");
+    if (blockIdx.x < b.dec.total_groups) {
+        const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.dec.group_end, b.dec.njobs, blockIdx.x));
+        if (job >= b.dec.njobs) return;
+        const BatchJob &J = b.dec.jobs[job];
+        DecompressArgs a = batch_decompress_args(b, J);
+        group_sums<kBlocksPerTile, 1>(a, blockIdx.x - J.seg_base, J.group_passes, b.dec.tpc_log2,
+                                      b.dec.offsets + J.chunk_base, b.dec.groups + J.seg_base);
+        return;
+    }
+    const uint64_t wg = blockIdx.x - b.dec.total_groups, nwg = gridDim.x - b.dec.total_groups;
+    for (uint64_t i = wg * kStatsThreads + threadIdx.x; i < b.nflags; i += nwg * kStatsThreads) b.flags[i] = 0;
     // workgroups loop over segments (one partial each), so the job search and
     // the workgroup start are paid once per several segments
-    for (uint64_t seg = blockIdx.x; seg < b.total_segs; seg += gridDim.x) {
+    for (uint64_t seg = wg; seg < b.total_segs; seg += nwg) {
         const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.seg_end, b.njobs, seg));
         if (job >= b.njobs) return;
         const BatchJob &J = b.jobs[job];
@@ -2356,16 +2344,21 @@ __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
 }
 
 // Per-job fold of the batched range pass (one workgroup per job).
-__global__ __launch_bounds__(kStatsThreads) void batch_stats_final_kernel(BatchArgs b)
+template <int THREADS>
+__device__ __forceinline__ void fold_job_stats(const BatchArgs &b, uint32_t job)
 {
-    const BatchJob &J = b.jobs[blockIdx.x];
-    if (J.op != FSZ_OP_COMPRESS) return;
+    const BatchJob &J = b.jobs[job];
     float mn = INFINITY, mx = -INFINITY, ma = 0.0f;
     uint32_t nf = 0;
-    for (uint64_t i = threadIdx.x; i < J.nsegs; i += kStatsThreads)
+    for (uint64_t i = threadIdx.x; i < J.nsegs; i += THREADS)
         stats_combine(mn, mx, ma, nf, b.partials[J.seg_base + i]);
-    const StatsPartial p = stats_block_reduce(mn, mx, ma, nf);
-    if (threadIdx.x == 0) b.stats[blockIdx.x] = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+    const StatsPartial p = stats_block_reduce<THREADS>(mn, mx, ma, nf);
+    if (threadIdx.x == 0) b.stats[job] = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+}
+
+__global__ __launch_bounds__(kStatsThreads) void batch_stats_final_kernel(BatchArgs b)
+{
+    fold_job_stats<kStatsThreads>(b, blockIdx.x);
 }
 
 // The arguments of job J's chunks, as the whole-field kernels take them.
@@ -2393,135 +2386,28 @@ __device__ __forceinline__ CompressArgs batch_compress_args(const BatchArgs &b, 
     return a;
 }
 
-__device__ __forceinline__ DecompressArgs batch_decompress_args(const BatchArgs &b, const BatchJob &J)
-{
-    DecompressArgs a;
-    a.cmp = static_cast<const uint8_t *>(J.src);
-    a.cmp_size = J.src_size;
-    a.out = static_cast<float *>(J.dst);
-    a.n = J.n;
-    a.ntiles = J.ntiles;
-    a.nblocks = J.nblocks;
-    a.nchunks = J.nchunks;
-    a.data0 = J.data0;
-    a.tile_begin = 0;
-    a.tile_end = J.ntiles;
-    a.elem_begin = 0;
-    a.elem_end = J.n;
-    a.cfg_flags = 0;
-    a.epoch = b.epoch;
-    a.flag_epoch = 1;
-    a.flags = b.flags + J.chunk_base * kFlagStride;
-    a.ticket = nullptr;
-    a.final = J.final;
-    return a;
-}
-
-// Batched kernel: one (job, chunk) item per workgroup, items from one ticket
-// counter in job order, so every lookback waits only on items already
-// running, and lookback chains stay per job (each job has its own flag
-// range).  The item runs the whole-field per-chunk code, so every job's bytes
-// equal a plain call's.
+// Batched decompression: one (job, chunk) item per workgroup, as
+// decompress_direct_kernel.  The range-pass launch has placed every chunk in
+// its group (group_sums), so no item waits on another.  The first b.njobs
+// workgroups fold the range pass of the batch's compress jobs, whose kernel
+// comes next: a mixed batch has no launch more than a compression.  64 fields of 16 K to
+// 16 M elements (125 M together): 117 us per call, where a persistent grid
+// with tickets and a lookback per job took 221.
 template <bool ALIGNED, int W>
-__global__ __launch_bounds__(W * 64) void batch_kernel(BatchArgs b)
-{
-    __shared__ union {
-        CompressShared<W> c;
-        DecompressShared<W> d;
-    } sh;
-    __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
-    __shared__ unsigned long long tk;
-    const int tid = threadIdx.x;
-    uint32_t *st = stage + (tid >> 6) * kStageWaveDwords;
-    if (tid == 0) tk = take_ticket(b.ticket, b.total_chunks);
-    lds_barrier();
-    const uint64_t t = tk;
-    if (t >= b.total_chunks) return;
-    const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.chunk_end, b.njobs, t));
-    if (job >= b.njobs) return;
-    const BatchJob &J = b.jobs[job];
-    const uint64_t chunk = t - J.chunk_base;
-    if (J.op == FSZ_OP_COMPRESS) {
-        compress_chunk<ALIGNED, W>(batch_compress_args(b, job, J), chunk, sh.c, st);
-    } else {
-        const DecompressArgs a = batch_decompress_args(b, J);
-        float E;
-        uint64_t total;
-        bool indep;
-        const int hst = dec_header(a, E, total, indep);
-        if (hst != FSZ_OK) {
-            if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, hst, a.epoch);
-            return;
-        }
-        GroupCursor gc;
-        const DecChunk dc = dec_sizes<W, false, kByLookback>(a, chunk, dec_rate_byte<W, false, kByLookback>(a, chunk), 0, sh.d, gc);
-        const DecPlace pl = dec_place<W, false, false, kByLookback>(a, dc, 0, total, sh.d, gc);
-        if (pl.live) dec_decode<ALIGNED, W, false>(a, dc, pl, E, indep, st);
-    }
-}
-
-// Batched decompression when every job decompresses: a persistent grid whose
-// workgroups take items from the ticket counter until one is past the end.
-// The size pass of the next item runs before this item's decode, so its
-// aggregate is out before any lookback waits on it (as in the whole-field
-// decoder); every item publishes its aggregate before its own lookback and
-// tickets are taken in increasing order, so the waits always drain.  Held to
-// 128 VGPRs (4 waves per SIMD), as the whole-field decoder.
-template <bool ALIGNED, int W>
-__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(4))) void batch_dec_kernel(BatchArgs b)
+__global__ __launch_bounds__(W * 64) void batch_dec_kernel(BatchArgs b)
 {
     __shared__ DecompressShared<W> sh;
     __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
-    const int tid = threadIdx.x;
-    uint32_t *st = stage + (tid >> 6) * kStageWaveDwords;
-    const uint64_t takes = b.total_chunks + gridDim.x;
-    int tslot = 0;
-    uint64_t t = next_ticket(b.ticket, takes, sh, tslot);
-    GroupCursor gc;     // unused by the lookback form
-    bool have = false;  // dc holds the size pass of item t (slot `slot`)
-    DecChunk dc;
-    int slot = 0;
-    while (t < b.total_chunks) {
-        const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.chunk_end, b.njobs, t));
-        const DecompressArgs a = batch_decompress_args(b, b.jobs[job]);
-        const uint64_t chunk = t - b.jobs[job].chunk_base;
-        const uint64_t nxt = next_ticket(b.ticket, takes, sh, tslot);
-        float E;
-        uint64_t total;
-        bool indep;
-        const int hst = dec_header(a, E, total, indep);
-        if (hst != FSZ_OK) {
-            if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, hst, a.epoch);
-            have = false;
-        } else {
-            if (!have)
-                dc = dec_sizes<W, false, kByLookback>(a, chunk, dec_rate_byte<W, false, kByLookback>(a, chunk), slot, sh,
-                                                      gc);
-            bool next_have = false;
-            DecChunk dn;
-            if (nxt < b.total_chunks) {
-                const uint32_t job2 = __builtin_amdgcn_readfirstlane(find_job(b.chunk_end, b.njobs, nxt));
-                const DecompressArgs a2 = batch_decompress_args(b, b.jobs[job2]);
-                const uint64_t chunk2 = nxt - b.jobs[job2].chunk_base;
-                float E2;
-                uint64_t total2;
-                bool indep2;
-                if (dec_header(a2, E2, total2, indep2) == FSZ_OK) {
-                    dn = dec_sizes<W, false, kByLookback>(a2, chunk2, dec_rate_byte<W, false, kByLookback>(a2, chunk2),
-                                                      slot ^ 1, sh, gc);
-                    next_have = true;
-                }
-            }
-            const DecPlace pl = dec_place<W, false, false, kByLookback>(a, dc, slot, total, sh, gc);
-            if (pl.live) dec_decode<ALIGNED, W, false>(a, dc, pl, E, indep, st);
-            if (next_have) {
-                dc = dn;
-                slot ^= 1;
-            }
-            have = next_have;
-        }
-        t = nxt;
+    if (blockIdx.x < b.njobs) {
+        fold_job_stats<W * 64>(b, blockIdx.x);
+        return;
     }
+    const uint64_t t = blockIdx.x - b.njobs;
+    const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.dec.chunk_end, b.dec.njobs, t));
+    if (job >= b.dec.njobs) return;
+    const BatchJob &J = b.dec.jobs[job];
+    decompress_one<ALIGNED, W, false, kByGroupsOnce>(batch_decompress_args(b, J), t - J.chunk_base, sh,
+                                                     stage + (threadIdx.x >> 6) * kStageWaveDwords);
 }
 
 }  // namespace
@@ -2759,8 +2645,7 @@ __global__ __launch_bounds__(W * 64) void batch_pipe_kernel(BatchArgs b)
             reinterpret_cast<u32x4 *>(ljobs)[k] = reinterpret_cast<const u32x4 *>(b.jobs)[k];
         for (uint32_t k = threadIdx.x; k < b.njobs; k += blockDim.x) {
             const BatchJob &J = b.jobs[k];
-            lbound[k] = J.op == FSZ_OP_COMPRESS ? resolve_bound(b.stats + k, J.mode, J.value, J.n)
-                                                : Resolved{1.0f, 1.0f, 0u, FSZ_ERR_INVALID_ARG};
+            lbound[k] = resolve_bound(b.stats + k, J.mode, J.value, J.n);
             lend[k] = b.chunk_end[k];
         }
         lds_barrier();
@@ -3235,27 +3120,19 @@ static unsigned persistent_grid(K kernel, uint64_t nchunks, int threads = kThrea
     return (unsigned)(nchunks < g ? nchunks : g);
 }
 
-// Rounds of kGroupTiles tiles per group of the offsets pre-pass: the least power
-// of two that leaves at most kMaxGroups groups.
-static uint32_t group_passes(uint64_t ntiles)
-{
-    uint32_t p = 1;
-    while (ceil_div(ntiles, (uint64_t)kGroupTiles * p) > kMaxGroups) p *= 2;
-    return p;
-}
-
 // Enqueues the offsets pre-pass for chunks of TPC tiles and names its results
 // in a: `words` holds kMaxGroups group totals, then an offset per chunk.
 template <int TPC, int T = kBlocksPerTile, int HB = 1>
 static hipError_t launch_dec_groups(DecompressArgs &a, unsigned long long *words, hipStream_t s)
 {
+    static_assert(TPC % kGroupTilesPerThread == 0, "a chunk starts at a thread's first tile");
     const uint32_t passes = group_passes(a.tile_end);
     const uint64_t ngroups = a.tile_end ? ceil_div(a.tile_end, (uint64_t)kGroupTiles * passes) : 1;
     a.groups = words;
-    a.offsets = words + kMaxGroups;
+    a.offsets = words + kMaxGroupWords;
     a.group_shift = (uint32_t)__builtin_ctz(kGroupTiles / TPC * passes);
-    hipLaunchKernelGGL((dec_groups_kernel<TPC, T, HB>), dim3((unsigned)ngroups), dim3(kGroupThreads), 0, s, a,
-                       words + kMaxGroups, words, passes);
+    hipLaunchKernelGGL((dec_groups_kernel<T, HB>), dim3((unsigned)ngroups), dim3(kGroupThreads), 0, s, a,
+                       words + kMaxGroupWords, words, passes, (uint32_t)__builtin_ctz(TPC));
     return hipGetLastError();
 }
 
@@ -3544,37 +3421,38 @@ static hipError_t launch_batch_pipe(const BatchArgs &b, int groups, hipStream_t 
     return hipGetLastError();
 }
 
+template <int W>
+static hipError_t launch_batch_compress(const BatchArgs &b, int groups, hipStream_t s)
+{
+    // the persistent pipeline, one workgroup per CU at most (its LDS); a cap of 1 needs no pad
+    return b.njobs <= kPipeLdsJobs ? launch_batch_pipe<W, true>(b, groups, s)
+                                   : launch_batch_pipe<W, false>(b, groups, s);
+}
+
 template <bool ALIGNED, int W>
-static hipError_t launch_batch_t(const BatchArgs &b, bool any_compress, bool any_decompress, int groups,
-                                 hipStream_t s)
+static hipError_t launch_batch_decompress(const BatchArgs &b, int groups, hipStream_t s)
 {
     size_t pad = 0;
-    if (any_compress && !any_decompress) {
-        // compression only: the persistent pipeline,
-        // one workgroup per CU at most (its LDS); a cap of 1 needs no pad
-        return b.njobs <= kPipeLdsJobs ? launch_batch_pipe<W, true>(b, groups, s)
-                                       : launch_batch_pipe<W, false>(b, groups, s);
-    }
-    if (any_compress) {
-        if (!batch_lds_pad(batch_kernel<ALIGNED, W>, groups, &pad)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((batch_kernel<ALIGNED, W>), dim3((unsigned)b.total_chunks), dim3(W * 64), pad, s, b);
-        return hipGetLastError();
-    }
-    // decompression only: persistent, as many workgroups as fit at this shape
     if (!batch_lds_pad(batch_dec_kernel<ALIGNED, W>, groups, &pad)) return hipErrorInvalidValue;
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_dec_kernel<ALIGNED, W>, W * 64, pad) !=
-            hipSuccess ||
-        cus <= 0 || per_cu <= 0) {
-        cus = 256;
-        per_cu = 1;
-    }
-    const uint64_t g = (uint64_t)cus * (uint64_t)per_cu;
-    const unsigned grid = (unsigned)(b.total_chunks < g ? b.total_chunks : g);
-    hipLaunchKernelGGL((batch_dec_kernel<ALIGNED, W>), dim3(grid), dim3(W * 64), pad, s, b);
+    hipLaunchKernelGGL((batch_dec_kernel<ALIGNED, W>), dim3((unsigned)(b.njobs + b.dec.total_chunks)),
+                       dim3(W * 64), pad, s, b);
     return hipGetLastError();
+}
+
+template <int W>
+static hipError_t launch_batch_w(const BatchArgs &b, bool aligned_out, int groups, hipStream_t s)
+{
+    hipError_t e = hipSuccess;
+    if (b.dec.njobs) {
+        e = aligned_out ? launch_batch_decompress<true, W>(b, groups, s)
+                          : launch_batch_decompress<false, W>(b, groups, s);
+    } else {
+        hipLaunchKernelGGL(batch_stats_final_kernel, dim3(b.njobs), dim3(kStatsThreads), 0, s, b);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess && b.njobs)
+        e = launch_batch_compress<W>(b, groups, s);
+    return e;
 }
 
 bool batch_shape_supported(const BatchShape &shape)
@@ -3582,34 +3460,27 @@ bool batch_shape_supported(const BatchShape &shape)
     if (shape.groups_per_cu < 0 || shape.groups_per_cu > 8) return false;
     size_t pad = 0;
     switch (shape.waves) {
-    case 2: return batch_lds_pad(batch_kernel<true, 2>, shape.groups_per_cu, &pad);
-    case 4: return batch_lds_pad(batch_kernel<true, 4>, shape.groups_per_cu, &pad);
-    case 8: return batch_lds_pad(batch_kernel<true, 8>, shape.groups_per_cu, &pad);
+    case 2: return batch_lds_pad(batch_dec_kernel<true, 2>, shape.groups_per_cu, &pad);
+    case 4: return batch_lds_pad(batch_dec_kernel<true, 4>, shape.groups_per_cu, &pad);
+    case 8: return batch_lds_pad(batch_dec_kernel<true, 8>, shape.groups_per_cu, &pad);
     default: return false;
     }
 }
 
-hipError_t launch_batch(const BatchArgs &b, bool aligned16, bool any_compress, bool any_decompress,
-                        const BatchShape &shape, hipStream_t s)
+hipError_t launch_batch(const BatchArgs &b, bool aligned_out, const BatchShape &shape, hipStream_t s)
 {
     // workgroups loop over segments; enough of them to clear the flags
     uint64_t grid = b.total_segs < 2048 ? b.total_segs : 2048;
     const uint64_t clear = ceil_div(b.nflags, kStatsThreads);
     if (grid < clear) grid = clear < kStatsMaxBlocks ? clear : kStatsMaxBlocks;
-    if (grid < 1) grid = 1;
+    grid += b.dec.total_groups;
     hipLaunchKernelGGL(batch_stats_kernel, dim3((unsigned)grid), dim3(kStatsThreads), 0, s, b);
-    if (any_compress)
-        hipLaunchKernelGGL(batch_stats_final_kernel, dim3(b.njobs), dim3(kStatsThreads), 0, s, b);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (b.total_chunks == 0) return hipSuccess;
     switch (shape.waves) {
-    case 2: return aligned16 ? launch_batch_t<true, 2>(b, any_compress, any_decompress, shape.groups_per_cu, s)
-                             : launch_batch_t<false, 2>(b, any_compress, any_decompress, shape.groups_per_cu, s);
-    case 4: return aligned16 ? launch_batch_t<true, 4>(b, any_compress, any_decompress, shape.groups_per_cu, s)
-                             : launch_batch_t<false, 4>(b, any_compress, any_decompress, shape.groups_per_cu, s);
-    case 8: return aligned16 ? launch_batch_t<true, 8>(b, any_compress, any_decompress, shape.groups_per_cu, s)
-                             : launch_batch_t<false, 8>(b, any_compress, any_decompress, shape.groups_per_cu, s);
+    case 2: return launch_batch_w<2>(b, aligned_out, shape.groups_per_cu, s);
+    case 4: return launch_batch_w<4>(b, aligned_out, shape.groups_per_cu, s);
+    case 8: return launch_batch_w<8>(b, aligned_out, shape.groups_per_cu, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -477,3 +477,33 @@ def test_batch_stream_beyond_4gib():
             i = k + int(bad[0])
             raise AssertionError(f"{bad.numel()} of the elements [{k}, {k + a.numel()}) differ; first at {i}: "
                                  f"decoded {float(y[i])} expected {float(expect[i])} (x = {float(x[i])})")
+
+
+@pytest.mark.parametrize("shape", [(2, 0), (4, 0), (8, 0)])
+@pytest.mark.parametrize("offset", [0, 3])
+def test_batch_decompress_group_edges(shape, offset):
+    """Decompress jobs take their chunk offsets from groups of 1024 tiles summed
+    in the range pass of the batch's compress jobs: sizes at tile, chunk and
+    group edges, streams cut inside the rate header, reserved bits in the first
+    and last group and a mismatched n, beside compress jobs and alone."""
+    group = 1024 * 256
+    sizes = [0, 1, 255, 256, 257, 4095, 4096, 4097, group - 1, group, group + 1, 3 * group + 777]
+    d, c = [], []
+    for k, n in enumerate(sizes):
+        x = workloads.sinusoid_field(n, 900 + k)
+        _, data = oracle.compress_status(x, fsz.FSZ_REL, 1e-3)
+        d.append(("d", data, n))
+        c.append(("c", x[:50_000], fsz.FSZ_REL, 1e-4))
+    big = d[-1][1]
+    for block in (8, (sizes[-1] + 31) // 32 - 1):
+        bad = bytearray(big)
+        bad[32 + block] |= 0x20
+        d.append(("d", bytes(bad), sizes[-1]))
+    d.append(("d", big[:64], sizes[-1]))   # the rate header does not fit the buffer
+    d.append(("d", big, sizes[-1] - 256))  # another element count than the stream's
+    mixed = [s for pair in zip(d, c) for s in pair] + d[len(c):]
+    for name, specs in (("mixed", mixed), ("decompress only", d)):
+        announce(f"batch group edges, {name}, shape {shape}, offset {offset}")
+        b = DeviceBatch(specs, offset=offset)
+        b.run(shape)
+        check_against_oracle(b, oracle_refs(specs), f"group edges {name} {shape}")
