@@ -22,10 +22,6 @@ const Tuning &tuning()
 {
     static const Tuning t = [] {
         Tuning v;
-        if (const char *e = std::getenv("FSZ_PIPE_WAVES")) {
-            const int k = std::atoi(e);
-            if (k == 1 || k == 2 || k == 4 || k == 7 || k == 8 || k == 9) v.pipe_waves = k;  // 7, 9: + 1 control wave
-        }
         if (const char *e = std::getenv("FSZ_PREZERO_CR")) v.prezero_min_cr = std::atof(e);
         if (const char *e = std::getenv("FSZ_DEC_WIDE_ABOVE")) v.dec_wide_above = std::strtoull(e, nullptr, 10);
         if (const char *e = std::getenv("FSZ_CFG_DEC_LOOKBACK_BELOW"))

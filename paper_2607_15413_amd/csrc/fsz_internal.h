@@ -253,8 +253,7 @@ fsz_status check_decompress_args(const void *d_cmp, size_t cmp_size, const float
 bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t segs);
 
 // Launch tuning knobs, process-wide, read once from the environment:
-// FSZ_PIPE_WAVES (the compressor's waves per
-// workgroup: 1, 2, 4 or 8, or 7 / 9 with a control wave), FSZ_DEC_WIDE_ABOVE (the tile configurations'
+// FSZ_DEC_WIDE_ABOVE (the tile configurations'
 // lookback decoder: 16-wave chunks above this many elements, else 4),
 // FSZ_CFG_DEC_LOOKBACK_BELOW (decodes of
 // the tile configurations below this many elements use
@@ -264,8 +263,6 @@ bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t 
 // default 1) and FSZ_PREZERO_CR (whole-field decodes of streams above this
 // compression ratio, judged from the buffer size, use the pre-zeroed decoder).
 struct Tuning {
-    int pipe_waves = 9;         // pipelined compression: data waves per workgroup (1, 2, 4, 8), or 9 / 7:
-                                // 8 / 7 data waves and a control wave (compress_ctrl_kernel)
     uint64_t dec_wide_above = 1ull << 21;  // tile configurations, lookback form: 16 waves above, else 4
     int grid_factor = 1;
     double prezero_min_cr = 0.0;  // whole-field decodes pre-zero above this CR (0: never)

@@ -1251,7 +1251,13 @@ __global__ __launch_bounds__(kThreads) void naive_encode_kernel(CompressArgs a, 
 // conflicts.
 
 constexpr int kCachePolicyNT = 2;  // cache-policy operand of the LDS copies: nontemporal
-constexpr int kPipeWaveDwords = 2060;  // 8 tiles of input, or the wave's output (<= 8 x 1028 B) at a 16-byte phase
+// A wave's LDS: 8 tiles of input, and its output at a 16-byte phase.  The output
+// is at most 64 x 96 bytes: |q| <= 2^21 + 1 bounds every LZ1 residual by
+// 2^22 + 2, i.e. 23 bits and 4 + 4 x 23 bytes a block, LZ1 without centring may
+// always be selected, and a tile takes its cheapest variant (a 64-element
+// block: twice that for two lanes).
+constexpr int kPipeInDwords = 2048;
+constexpr int kPipeOutDwords = 64 * 24 + 4;
 typedef __attribute__((address_space(3))) void lds_void;
 
 // Input of the wave's 8 tiles (element e0 onward, all in bounds) -> LDS.
@@ -1591,12 +1597,19 @@ __device__ __forceinline__ void ctrl_run(const CompressArgs &a, const Resolved &
 
 // The pipelined compressor with WD data waves (8 tiles each per chunk) and
 // one control wave (ctrl_run).  a.nchunks must count chunks of 8 WD tiles.
+// One workgroup per CU; what bounds it are the data waves' latencies (its VALU
+// is busy half of the time, HBM at 60%), so the more waves the better: 11 data
+// waves and the control wave are three per SIMD, which 168 VGPRs allow, and
+// fill 154 of the 160 KB of LDS.  512^3 GRF, REL 1e-2 / 1e-3 / 1e-4, with the
+// range pass: 11 waves 228 / 236 / 247 us, 10 232 / 240 / 251, 9 239 / 246 /
+// 258, 8 242 / 250 / 259.  A field too small to give every workgroup two
+// chunks takes 8 (launch_compress).
 template <int WD>
 __global__ __launch_bounds__((WD + 1) * 64) void compress_ctrl_kernel(CompressArgs a)
 {
     __shared__ CompressShared<WD> sh;
-    __shared__ __attribute__((aligned(16))) uint32_t inbuf[WD * kPipeWaveDwords];
-    __shared__ __attribute__((aligned(16))) uint32_t stbuf[WD * kPipeWaveDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t inbuf[WD * kPipeInDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t stbuf[WD * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
     if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
@@ -1609,22 +1622,23 @@ __global__ __launch_bounds__((WD + 1) * 64) void compress_ctrl_kernel(CompressAr
         }
     }
     if (w < WD)
-        pipe2_run<false, WD, false>(a, R, sh, inbuf + w * kPipeWaveDwords, stbuf + w * kPipeWaveDwords, w);
+        pipe2_run<false, WD, false>(a, R, sh, inbuf + w * kPipeInDwords, stbuf + w * kPipeOutDwords, w);
     else
         ctrl_run<WD>(a, R, sh);
 }
 
-// W waves per workgroup; a chunk is 8 tiles per wave.  a.nchunks must count
-// chunks of that size.  FEAT: honour the feature switches in a.features.
-template <int W, bool FEAT = false>
+// The wave-0 form, for the feature switches (a.features).  W waves per
+// workgroup; a chunk is 8 tiles per wave.  a.nchunks must count chunks of that
+// size.
+template <int W>
 __global__ __launch_bounds__(W * 64) void compress_pipe2_kernel(CompressArgs a)
 {
     __shared__ CompressShared<W> sh;
-    __shared__ __attribute__((aligned(16))) uint32_t inbuf[W * kPipeWaveDwords];
-    __shared__ __attribute__((aligned(16))) uint32_t stbuf[W * kPipeWaveDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t inbuf[W * kPipeInDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t stbuf[W * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    uint32_t *qb = inbuf + w * kPipeWaveDwords;
-    uint32_t *pb = stbuf + w * kPipeWaveDwords;
+    uint32_t *qb = inbuf + w * kPipeInDwords;
+    uint32_t *pb = stbuf + w * kPipeOutDwords;
 
     const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
     if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
@@ -1637,9 +1651,9 @@ __global__ __launch_bounds__(W * 64) void compress_pipe2_kernel(CompressArgs a)
         }
     }
     if (w == 0)
-        pipe2_run<true, W, FEAT>(a, R, sh, qb, pb, w);
-    else if (W > 1)
-        pipe2_run<false, W, FEAT>(a, R, sh, qb, pb, w);
+        pipe2_run<true, W, true>(a, R, sh, qb, pb, w);
+    else
+        pipe2_run<false, W, true>(a, R, sh, qb, pb, w);
 }
 
 // ------------------------------------------------------------------ decompress
@@ -2632,11 +2646,11 @@ __global__ __launch_bounds__(W * 64) void batch_pipe_kernel(BatchArgs b)
 {
     __shared__ CompressShared<W> sh;
     __shared__ uint32_t s_job;
-    __shared__ __attribute__((aligned(16))) uint32_t inbuf[W * kPipeWaveDwords];
-    __shared__ __attribute__((aligned(16))) uint32_t stbuf[W * kPipeWaveDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t inbuf[W * kPipeInDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t stbuf[W * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    uint32_t *qb = inbuf + w * kPipeWaveDwords;
-    uint32_t *pb = stbuf + w * kPipeWaveDwords;
+    uint32_t *qb = inbuf + w * kPipeInDwords;
+    uint32_t *pb = stbuf + w * kPipeOutDwords;
     if (LDSJOBS) {
         __shared__ __attribute__((aligned(16))) BatchJob ljobs[kPipeLdsJobs];
         __shared__ Resolved lbound[kPipeLdsJobs];
@@ -2884,15 +2898,13 @@ struct TileCfg {
 // Pipelined compressor of a tile configuration: compress_ctrl_kernel's
 // pipeline (8 data waves, one control wave, persistent workgroups, chunks of
 // 8 x 64 segments from the ticket counter) over the configuration's tiles.
-// The input must be 16-byte aligned; a.nchunks counts chunks of
-// kCfgPipeChunkSegs segments.  A wave's output (rates <= 24: at most 64 x 100
-// B of words and 16 tile means) fits its staging area.
+// a.nchunks counts chunks of kCfgPipeChunkSegs segments.
 template <int HB, int L>
 __global__ __launch_bounds__(9 * 64) void compress_cfg_pipe_kernel(CompressArgs a)
 {
     __shared__ CompressShared<8> sh;
-    __shared__ __attribute__((aligned(16))) uint32_t inbuf[8 * kPipeWaveDwords];
-    __shared__ __attribute__((aligned(16))) uint32_t stbuf[8 * kPipeWaveDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t inbuf[8 * kPipeInDwords];
+    __shared__ __attribute__((aligned(16))) uint32_t stbuf[8 * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
     if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
@@ -2905,8 +2917,8 @@ __global__ __launch_bounds__(9 * 64) void compress_cfg_pipe_kernel(CompressArgs 
         }
     }
     if (w < 8)
-        pipe2_run<false, 8, false, TileCfg<HB, L>>(a, R, sh, inbuf + w * kPipeWaveDwords,
-                                                    stbuf + w * kPipeWaveDwords, w);
+        pipe2_run<false, 8, false, TileCfg<HB, L>>(a, R, sh, inbuf + w * kPipeInDwords,
+                                                    stbuf + w * kPipeOutDwords, w);
     else
         ctrl_run<8>(a, R, sh);
 }
@@ -3248,15 +3260,12 @@ static hipError_t launch_pipe(K kernel, unsigned cap, int waves, const CompressA
 hipError_t launch_compress(const CompressArgs &a, hipStream_t s)
 {
     if (a.features != kFeaturesAll)  // the ablation's feature subsets
-        FSZ_LAUNCH_PIPE((compress_pipe2_kernel<8, true>), 8, 8)
-    switch (tuning().pipe_waves) {
-    case 7: FSZ_LAUNCH_PIPE(compress_ctrl_kernel<7>, 8, 7)  // 7 data waves + 1 control wave
-    case 1: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<1>, 1, 1)
-    case 2: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<2>, 2, 2)
-    case 4: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<4>, 4, 4)
-    case 8: FSZ_LAUNCH_PIPE(compress_pipe2_kernel<8>, 8, 8)
-    default: FSZ_LAUNCH_PIPE(compress_ctrl_kernel<8>, 9, 8)  // 8 data waves + 1 control wave
-    }
+        FSZ_LAUNCH_PIPE(compress_pipe2_kernel<8>, 8, 8)
+    // 11 data waves and a control wave; 8 where the smaller workgroup's start
+    // and the finer spread count for more (2^20 GRF 14.8 against 16.0 us, 2^22
+    // 22.3 / 22.7, 6 M 26.5 / 26.9, 2^23 30.9 / 30.3, 2^25 76.9 / 74.5)
+    if (a.n >= (1ull << 23)) FSZ_LAUNCH_PIPE(compress_ctrl_kernel<11>, 12, 11)
+    FSZ_LAUNCH_PIPE(compress_ctrl_kernel<8>, 9, 8)
 }
 
 hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bool in_aligned16, hipStream_t s)

@@ -622,3 +622,26 @@ def test_range_pass_off_the_16_byte_grid(n, offset):
                                    res.data_ptr())
             assert fsz.fsz_batch_async([job], None, _stream()) == fsz.FSZ_OK
             assert out[:len(ref)].cpu().numpy().tobytes() == ref
+
+
+@pytest.mark.parametrize("n", [40_000, (1 << 23) - 1, (1 << 23) + 11 * 2048 * 3 + 5])
+def test_largest_output_of_a_wave(n):
+    """Alternating extremes at the smallest bound: LZ1 residuals of 2^22, 23 bit
+    planes in every block, 96 bytes per block, which is all that a compressing
+    wave's staging area holds; with 8 data waves and, from 2^23 elements, 11,
+    on and off the 16-byte grid."""
+    x = np.full(n, np.float32(1.0) - np.float32(2.0 ** -24), np.float32)
+    x[1::2] *= -1.0
+    x[::4096] = 0.25  # the rates vary a little
+    eb = 8.0 * 2.0 ** -24
+    old = oracle.set_threads(8)
+    try:
+        ref = oracle.compress(x, oracle.ABS, eb)
+    finally:
+        oracle.set_threads(old)
+    rates = np.frombuffer(ref, np.uint8)[32:32 + (n + 31) // 32] & 31
+    assert np.mean(rates == 23) > 0.9
+    for off in (0, 2):
+        announce(f"largest wave output n={n} offset {off}")
+        st, got = gpu_compress(x, fsz.FSZ_ABS, eb, in_offset=off)
+        assert st == fsz.FSZ_OK and got == ref, first_diff(got, ref)
