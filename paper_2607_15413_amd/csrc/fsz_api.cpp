@@ -195,12 +195,12 @@ fsz_status enqueue_compress(Workspace *ws, const float *d_in, uint64_t n, int mo
                             const fsz_stats *d_stats, void *d_out, uint64_t cap, fsz_result *d_final,
                             uint32_t *epoch_out, uint32_t features = kFeaturesAll)
 {
+    CompressArgs a{};
     if (!d_stats) {
         StatsArgs sa{d_in, n, ws->d_stats, ws->d_partials};
-        if (!ok(launch_stats(sa, ws->stream))) return FSZ_ERR_DEVICE;
-        d_stats = ws->d_stats;
+        if (!ok(launch_stats_partials(sa, &a.nparts, ws->stream))) return FSZ_ERR_DEVICE;
+        a.partials = ws->d_partials;
     }
-    CompressArgs a{};
     a.x = d_in;
     a.n = n;
     a.ntiles = ceil_div(n, kTile);
@@ -316,12 +316,12 @@ fsz_status enqueue_compress_config(Workspace *ws, const float *d_in, uint64_t n,
                                    const fsz_stats *d_stats, int block, int tile_blocks, void *d_out, uint64_t cap,
                                    fsz_result *d_final)
 {
+    CompressArgs a{};
     if (!d_stats) {
         StatsArgs sa{d_in, n, ws->d_stats, ws->d_partials};
-        if (!ok(launch_stats(sa, ws->stream))) return FSZ_ERR_DEVICE;
-        d_stats = ws->d_stats;
+        if (!ok(launch_stats_partials(sa, &a.nparts, ws->stream))) return FSZ_ERR_DEVICE;
+        a.partials = ws->d_partials;
     }
-    CompressArgs a{};
     a.x = d_in;
     a.n = n;
     a.ntiles = ceil_div(n, (uint64_t)block * tile_blocks);

@@ -67,7 +67,9 @@ struct CompressArgs {
     uint64_t n, ntiles, nblocks, nchunks, data0;
     uint8_t *out;
     uint64_t capacity;
-    const fsz_stats *stats;
+    const fsz_stats *stats;        // the caller's, or
+    const StatsPartial *partials;  // of the call's own range pass (null: stats)
+    uint32_t nparts;
     double value;
     int mode;
     uint32_t features;    // FSZ_FEAT_* switches (kFeaturesAll = the full method)
@@ -184,6 +186,8 @@ struct BatchShape {
 
 // Kernel launchers (fsz_kernels.hip).
 hipError_t launch_stats(const StatsArgs &a, hipStream_t s);
+// Its first part alone, for kernels that fold the partials themselves.
+hipError_t launch_stats_partials(const StatsArgs &a, uint32_t *nparts, hipStream_t s);
 hipError_t launch_compress(const CompressArgs &a, hipStream_t s);
 // The five-read baseline: four evaluation launches, then the encode launch
 // (a.nchunks counts chunks of kTilesPerChunk tiles).

@@ -288,11 +288,10 @@ __device__ __forceinline__ double sub_toward_zero(double a, double b)
 
 // Error-bound resolution (Sec. V-A) with the binary32 step tightening:
 // E = the largest binary32 <= 2 (eb - 4 ulp(max|x|)), inv = 1/E.
-__device__ Resolved resolve_bound(const fsz_stats *stp, int mode, double value, uint64_t n)
+__device__ Resolved resolve_bound(const fsz_stats &s, int mode, double value, uint64_t n)
 {
     Resolved r{1.0f, 1.0f, 0u, FSZ_OK};
     if (n == 0) return r;
-    const fsz_stats s = *stp;
     if (s.flags & 1u) {
         r.status = FSZ_ERR_NONFINITE;
         return r;
@@ -630,14 +629,34 @@ __global__ __launch_bounds__(kStatsThreads) void stats_partial_kernel(StatsArgs 
     if (threadIdx.x == 0) a.partials[blockIdx.x] = p;
 }
 
-// Value-range pass, part 2: one workgroup folds the partials into *out.
-__global__ __launch_bounds__(kStatsThreads) void stats_final_kernel(StatsArgs a, unsigned nparts)
+// The range pass's partials folded by one workgroup.
+template <int THREADS>
+__device__ __forceinline__ fsz_stats fold_partials(const StatsPartial *parts, uint32_t nparts)
 {
     float mn = INFINITY, mx = -INFINITY, ma = 0.0f;
     uint32_t nf = 0;
-    for (unsigned i = threadIdx.x; i < nparts; i += blockDim.x) stats_combine(mn, mx, ma, nf, a.partials[i]);
-    const StatsPartial p = stats_block_reduce<kStatsThreads>(mn, mx, ma, nf);
-    if (threadIdx.x == 0) *a.out = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+    for (uint32_t i = threadIdx.x; i < nparts; i += THREADS) stats_combine(mn, mx, ma, nf, parts[i]);
+    const StatsPartial p = stats_block_reduce<THREADS>(mn, mx, ma, nf);
+    return fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+}
+
+// The call's bound, resolved by every workgroup of a compression: from the
+// caller's stats, or from the partials of the call's own range pass.  Folding
+// them here (at most 1024 x 16 bytes, two loads per thread) costs each workgroup
+// about a microsecond; a launch of its own between the two kernels took 4.6 us
+// on large fields and 2 us on small ones.
+template <int THREADS>
+__device__ __forceinline__ Resolved resolve_call(const CompressArgs &a)
+{
+    const fsz_stats s = a.partials ? fold_partials<THREADS>(a.partials, a.nparts) : *a.stats;
+    return resolve_bound(s, a.mode, a.value, a.n);
+}
+
+// Value-range pass, part 2: one workgroup folds the partials into *out.
+__global__ __launch_bounds__(kStatsThreads) void stats_final_kernel(StatsArgs a, unsigned nparts)
+{
+    const fsz_stats s = fold_partials<kStatsThreads>(a.partials, nparts);
+    if (threadIdx.x == 0) *a.out = s;
 }
 
 // ------------------------------------------------------------------ compress
@@ -1054,7 +1073,7 @@ __global__ __launch_bounds__(kThreads) void naive_eval_kernel(CompressArgs a, Na
     const int w = tid >> 6;
     const int lane = tid & 63;
     const int j = lane & 7;
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
+    const Resolved R = resolve_bound(*a.stats, a.mode, a.value, a.n);
     if (R.status != FSZ_OK) return;  // the encode pass reports the status
     const uint64_t tile0 = (uint64_t)blockIdx.x * kTilesPerChunk + (uint64_t)w * kTilesPerWave;
     if (tile0 >= a.ntiles) return;  // wave-uniform; the kernel has no workgroup barrier
@@ -1217,7 +1236,7 @@ __global__ __launch_bounds__(kThreads) void naive_encode_kernel(CompressArgs a, 
     int tslot = 0;
     const uint64_t chunk = next_ticket(a.ticket, a.nchunks, sh, tslot);
     if (chunk >= a.nchunks) return;
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
+    const Resolved R = resolve_bound(*a.stats, a.mode, a.value, a.n);
     if (R.status != FSZ_OK) {
         if (tid == 0 && chunk == a.nchunks - 1) write_final(a.final, 0, R.status, a.epoch);
         return;
@@ -1611,7 +1630,7 @@ __global__ __launch_bounds__((WD + 1) * 64) void compress_ctrl_kernel(CompressAr
     __shared__ __attribute__((aligned(16))) uint32_t inbuf[WD * kPipeInDwords];
     __shared__ __attribute__((aligned(16))) uint32_t stbuf[WD * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
+    const Resolved R = resolve_call<(WD + 1) * 64>(a);
     if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
         const uint64_t takes = a.nchunks + gridDim.x;
         int tslot = 0;
@@ -1640,7 +1659,7 @@ __global__ __launch_bounds__(W * 64) void compress_pipe2_kernel(CompressArgs a)
     uint32_t *qb = inbuf + w * kPipeInDwords;
     uint32_t *pb = stbuf + w * kPipeOutDwords;
 
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
+    const Resolved R = resolve_call<W * 64>(a);
     if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
         const uint64_t takes = a.nchunks + gridDim.x;
         int tslot = 0;
@@ -2426,12 +2445,20 @@ __global__ __launch_bounds__(W * 64) void batch_dec_kernel(BatchArgs b)
 
 }  // namespace
 
-hipError_t launch_stats(const StatsArgs &a, hipStream_t s)
+hipError_t launch_stats_partials(const StatsArgs &a, uint32_t *nparts, hipStream_t s)
 {
     const uint64_t want = ceil_div(a.n, (uint64_t)kStatsThreads * 16);
-    const unsigned grid = (unsigned)(want < 1 ? 1 : (want > kStatsMaxBlocks ? kStatsMaxBlocks : want));
-    hipLaunchKernelGGL(stats_partial_kernel, dim3(grid), dim3(kStatsThreads), 0, s, a);
-    hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(kStatsThreads), 0, s, a, grid);
+    *nparts = (uint32_t)(want < 1 ? 1 : (want > kStatsMaxBlocks ? kStatsMaxBlocks : want));
+    hipLaunchKernelGGL(stats_partial_kernel, dim3(*nparts), dim3(kStatsThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_stats(const StatsArgs &a, hipStream_t s)
+{
+    uint32_t nparts = 0;
+    const hipError_t e = launch_stats_partials(a, &nparts, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(kStatsThreads), 0, s, a, nparts);
     return hipGetLastError();
 }
 
@@ -2466,7 +2493,7 @@ struct JobView {
 __device__ __forceinline__ Resolved job_bound(const BatchArgs &b, const JobView &v, uint32_t job, const BatchJob &J)
 {
     if (v.bound) return v.bound[job];
-    return resolve_bound(b.stats + job, J.mode, J.value, J.n);
+    return resolve_bound(b.stats[job], J.mode, J.value, J.n);
 }
 
 __device__ __forceinline__ BItem batch_item(const BatchArgs &b, const JobView &v, uint64_t t, uint32_t job)
@@ -2659,7 +2686,7 @@ __global__ __launch_bounds__(W * 64) void batch_pipe_kernel(BatchArgs b)
             reinterpret_cast<u32x4 *>(ljobs)[k] = reinterpret_cast<const u32x4 *>(b.jobs)[k];
         for (uint32_t k = threadIdx.x; k < b.njobs; k += blockDim.x) {
             const BatchJob &J = b.jobs[k];
-            lbound[k] = resolve_bound(b.stats + k, J.mode, J.value, J.n);
+            lbound[k] = resolve_bound(b.stats[k], J.mode, J.value, J.n);
             lend[k] = b.chunk_end[k];
         }
         lds_barrier();
@@ -2906,7 +2933,7 @@ __global__ __launch_bounds__(9 * 64) void compress_cfg_pipe_kernel(CompressArgs 
     __shared__ __attribute__((aligned(16))) uint32_t inbuf[8 * kPipeInDwords];
     __shared__ __attribute__((aligned(16))) uint32_t stbuf[8 * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const Resolved R = resolve_bound(a.stats, a.mode, a.value, a.n);
+    const Resolved R = resolve_call<9 * 64>(a);
     if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
         const uint64_t takes = a.nchunks + gridDim.x;
         int tslot = 0;
@@ -3577,8 +3604,8 @@ fsz_status compress_noalloc(const float *d_in, uint64_t n, int mode, double valu
     if (hipGetLastError() != hipSuccess) return FSZ_ERR_DEVICE;
     if (!d_stats) {
         const StatsArgs sa{d_in, n, stats, partials};
-        if (launch_stats(sa, s) != hipSuccess) return FSZ_ERR_DEVICE;
-        d_stats = stats;
+        if (launch_stats_partials(sa, &a.nparts, s) != hipSuccess) return FSZ_ERR_DEVICE;
+        a.partials = partials;
     }
     a.stats = d_stats;
     if (launch_compress(a, s) != hipSuccess) return FSZ_ERR_DEVICE;
