@@ -162,6 +162,7 @@ struct BatchArgs {
     const uint64_t *seg_end;    // seg_end[j] = seg_base[j] + nsegs[j]
     uint32_t njobs;
     uint32_t epoch;             // result tag
+    uint32_t *h_done;           // pinned: the first kernel stores the epoch there (null: nobody waits)
     uint64_t total_chunks, total_segs, nflags;  // nflags: flag words (kFlagStride per chunk)
     unsigned long long *flags;  // cleared by the batch's range pass
     unsigned long long *ticket; // zero between launches (self-resetting)

@@ -2314,6 +2314,8 @@ __device__ __forceinline__ DecompressArgs batch_decompress_args(const BatchArgs 
 __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
 {
     static_assert(kStatsThreads == kGroupThreads, "both parts of the launch");
+    if (blockIdx.x == 0 && threadIdx.x == 0 && b.h_done)  // the job table's copy is done with its staging
+        __hip_atomic_store(b.h_done, b.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (blockIdx.x < b.dec.total_groups) {
         const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.dec.group_end, b.dec.njobs, blockIdx.x));
         if (job >= b.dec.njobs) return;

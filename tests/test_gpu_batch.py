@@ -507,3 +507,20 @@ def test_batch_decompress_group_edges(shape, offset):
         b = DeviceBatch(specs, offset=offset)
         b.run(shape)
         check_against_oracle(b, oracle_refs(specs), f"group edges {name} {shape}")
+
+
+@pytest.mark.parametrize("count", [1, 3, 40])
+def test_batches_back_to_back(count):
+    """Batches enqueued without a wait between them, more than there are
+    staging slots for their job tables: every one runs its own jobs."""
+    fields = small_fields(8, 21, hi=1 << 18)
+    specs = [[("c", f.data[k:], fsz.FSZ_REL, f.rel) for f in fields[k % 4:k % 4 + 3]] for k in range(count)]
+    batches = [DeviceBatch(s, offset=k % 4) for k, s in enumerate(specs)]
+    refs = [oracle_refs(s) for s in specs]
+    announce(f"{count} batches back to back")
+    torch.cuda.synchronize()
+    for b in batches:
+        assert fsz.fsz_batch_async(b.jobs, None, _stream()) == fsz.FSZ_OK
+    torch.cuda.synchronize()
+    for k, b in enumerate(batches):
+        check_against_oracle(b, refs[k], f"batch {k} of {count}")
