@@ -301,13 +301,14 @@ typedef struct {
     fsz_result *d_result; /* outcome of the job (device memory, caller-owned) */
 } fsz_job;
 
-/* Launch shape of the batched kernel.  waves_per_group in {2, 4, 8} (a
- * workgroup owns 8 tiles per wave); groups_per_cu caps resident workgroups
- * per CU through extra LDS (0 = no cap, else 1..8; a cap that the kernel's
- * own LDS or the device's per-workgroup LDS limit makes void or impossible
- * is rejected as FSZ_ERR_INVALID_ARG; the pipelined compress-only kernel,
- * whose own LDS already allows few workgroups per CU, treats such a cap as
- * no cap).  Neither changes any output byte. */
+/* Launch shape of the batched kernels.  waves_per_group in {2, 4, 8}: waves
+ * per workgroup of the decompress kernel (8 tiles per wave; the compress
+ * kernel's width follows the batch's size); groups_per_cu caps its resident
+ * workgroups per CU through extra LDS (0 = no cap, else 1..8; a cap that the
+ * kernel's own LDS or the device's per-workgroup LDS limit makes void or
+ * impossible is rejected as FSZ_ERR_INVALID_ARG; the compress kernel, which
+ * runs one workgroup per CU or few, has no cap).  Neither changes any output
+ * byte. */
 typedef struct {
     int waves_per_group;
     int groups_per_cu;

@@ -435,7 +435,8 @@ struct KindLayout {
 struct BatchLayout {
     KindLayout k[2];
     bool aligned_out = true;  // every decompress output is 16-byte aligned
-    int waves = 4;
+    int waves = 4;           // decompress: per workgroup; a chunk is 8 tiles per wave
+    int compress_waves = 8;  // compress: data waves per workgroup
     size_t desc_bytes() const { return k[0].bytes() + k[1].bytes(); }
     void pack(void *dst) const { (void)k[1].pack(k[0].pack(static_cast<char *>(dst))); }
     uint64_t flag_words() const { return k[FSZ_OP_COMPRESS].total_chunks * kFlagStride; }
@@ -443,14 +444,23 @@ struct BatchLayout {
     uint64_t dec_words() const { return k[FSZ_OP_DECOMPRESS].total_segs + k[FSZ_OP_DECOMPRESS].total_chunks; }
 };
 
+// Data waves per workgroup of the batched compressor, for the elements of all
+// its jobs: wide workgroups once there are enough items for the chip, narrow
+// ones where the spread counts (4 / 8 / 10 waves in us per call: 0.1 M elements
+// in 2 jobs 26 / 28 / 29, 3.0 M in 8 33.5 / 33.2 / 34, 7.0 M in 32 47 / 43 / 43,
+// 17 M in 16 - / 62 / 62, 125 M in 64 - / 266 / 252).
+int compress_batch_waves(uint64_t elems) { return elems >= (1ull << 23) ? 10 : elems >= (1ull << 21) ? 8 : 4; }
+
 // Validates every job (nothing is enqueued unless all pass) and lays out
 // global chunk and segment (or tile group) ranges of each kind in job order.
 fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayout *L)
 {
     if (njobs > 0 && !jobs) return FSZ_ERR_INVALID_ARG;
     if (njobs >= (1u << 31)) return FSZ_ERR_INVALID_ARG;
-    const uint64_t tiles_per_chunk = (uint64_t)kTilesPerWave * (uint64_t)waves;
     L->waves = waves;
+    uint64_t celems = 0;
+    for (size_t k = 0; k < njobs; k++) celems += jobs[k].op == FSZ_OP_COMPRESS ? jobs[k].n : 0;
+    L->compress_waves = compress_batch_waves(celems);
     for (size_t k = 0; k < njobs; k++) {
         const fsz_job &j = jobs[k];
         if (!j.d_result) return FSZ_ERR_INVALID_ARG;
@@ -469,6 +479,8 @@ fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayou
         J.n = j.n;
         J.ntiles = ceil_div(j.n, kTile);
         J.nblocks = ceil_div(j.n, kBlock);
+        const uint64_t tiles_per_chunk =
+            (uint64_t)kTilesPerWave * (uint64_t)(j.op == FSZ_OP_COMPRESS ? L->compress_waves : waves);
         J.nchunks = J.ntiles ? ceil_div(J.ntiles, tiles_per_chunk) : 1;
         J.data0 = kHeaderBytes + pad16(J.nblocks);
         J.src = j.d_src;
@@ -641,6 +653,7 @@ BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigne
     table(p, C, &b.jobs, &b.chunk_end, &b.seg_end);
     table(p + C.bytes(), D, &b.dec.jobs, &b.dec.chunk_end, &b.dec.group_end);
     b.njobs = (uint32_t)C.jobs.size();
+    b.waves = (uint32_t)L.compress_waves;
     b.epoch = epoch;
     b.total_chunks = C.total_chunks;
     b.total_segs = C.total_segs;

@@ -161,6 +161,7 @@ struct BatchArgs {
     const uint64_t *chunk_end;  // chunk_end[j] = chunk_base[j] + nchunks[j]
     const uint64_t *seg_end;    // seg_end[j] = seg_base[j] + nsegs[j]
     uint32_t njobs;
+    uint32_t waves;             // data waves per workgroup: a chunk is 8 tiles per wave
     uint32_t epoch;             // result tag
     uint32_t *h_done;           // pinned: the first kernel stores the epoch there (null: nobody waits)
     uint64_t total_chunks, total_segs, nflags;  // nflags: flag words (kFlagStride per chunk)

@@ -2396,31 +2396,6 @@ __global__ __launch_bounds__(kStatsThreads) void batch_stats_final_kernel(BatchA
     fold_job_stats<kStatsThreads>(b, blockIdx.x);
 }
 
-// The arguments of job J's chunks, as the whole-field kernels take them.
-__device__ __forceinline__ CompressArgs batch_compress_args(const BatchArgs &b, uint32_t job, const BatchJob &J)
-{
-    CompressArgs a;
-    a.x = static_cast<const float *>(J.src);
-    a.n = J.n;
-    a.ntiles = J.ntiles;
-    a.nblocks = J.nblocks;
-    a.nchunks = J.nchunks;
-    a.data0 = J.data0;
-    a.out = static_cast<uint8_t *>(J.dst);
-    a.capacity = J.dst_capacity;
-    a.stats = b.stats + job;
-    a.value = J.value;
-    a.mode = J.mode;
-    a.features = kFeaturesAll;
-    a.cfg_flags = 0;
-    a.epoch = b.epoch;
-    a.flag_epoch = 1;
-    a.flags = b.flags + J.chunk_base * kFlagStride;
-    a.ticket = nullptr;
-    a.final = J.final;
-    return a;
-}
-
 // Batched decompression: one (job, chunk) item per workgroup, as
 // decompress_direct_kernel.  The range-pass launch has placed every chunk in
 // its group (group_sums), so no item waits on another.  The first b.njobs
@@ -2466,8 +2441,8 @@ hipError_t launch_stats(const StatsArgs &a, hipStream_t s)
 
 // ------------------------------------------------------------------ batched pipelined compression
 //
-// Compress-only batches: the pipeline of
-// compress_pipe2_kernel over the batch's work items.  Tickets are global item
+// The compress jobs of a batch: the control-wave pipeline of
+// compress_ctrl_kernel over the batch's work items.  Tickets are global item
 // ids in job order; every item in flight carries its job, whose arguments
 // (input, output, flag range, bound) come from the job table where they are
 // needed, so one pipeline runs across job boundaries.  Items of a job whose
@@ -2486,40 +2461,85 @@ struct BItem {
 // items' arguments; larger batches read the job table and resolve per use.
 constexpr uint32_t kPipeLdsJobs = 96;
 
+// A job's fields are the same in every lane: taken out of LDS into scalar
+// registers, they leave the vector registers to the data.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v)
+{
+    return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
+}
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p)
+{
+    return reinterpret_cast<T *>(uniform((uint64_t)p));
+}
+
 struct JobView {
     const BatchJob *jobs;       // LDS copy or the global table
     const Resolved *bound;      // LDS (null: resolve from the job's stats)
     const uint64_t *chunk_end;  // LDS copy or the global table
 };
 
-__device__ __forceinline__ Resolved job_bound(const BatchArgs &b, const JobView &v, uint32_t job, const BatchJob &J)
+__device__ __forceinline__ Resolved job_bound(const BatchArgs &b, const JobView &v, uint32_t job)
 {
-    if (v.bound) return v.bound[job];
-    return resolve_bound(b.stats[job], J.mode, J.value, J.n);
+    Resolved r;
+    if (v.bound) {
+        r = v.bound[job];
+    } else {
+        const BatchJob &J = v.jobs[job];
+        r = resolve_bound(b.stats[job], J.mode, J.value, J.n);
+    }
+    return Resolved{__uint_as_float(uniform(__float_as_uint(r.E))), __uint_as_float(uniform(__float_as_uint(r.inv))),
+                    uniform(r.flags), (int)uniform((uint32_t)r.status)};
+}
+
+// The arguments of a job's chunks, as the whole-field kernels take them.
+__device__ __forceinline__ CompressArgs batch_compress_args(const BatchArgs &b, const JobView &v, uint32_t job)
+{
+    const BatchJob &J = v.jobs[job];
+    CompressArgs a;
+    a.x = static_cast<const float *>(uniform(J.src));
+    a.n = uniform(J.n);
+    a.ntiles = uniform(J.ntiles);
+    a.nblocks = uniform(J.nblocks);
+    a.nchunks = uniform(J.nchunks);
+    a.data0 = uniform(J.data0);
+    a.out = static_cast<uint8_t *>(uniform(J.dst));
+    a.capacity = uniform(J.dst_capacity);
+    a.stats = nullptr;
+    a.partials = nullptr;
+    a.nparts = 0;
+    a.value = J.value;
+    a.mode = J.mode;
+    a.features = kFeaturesAll;
+    a.cfg_flags = 0;
+    a.epoch = b.epoch;
+    a.flag_epoch = 1;
+    a.flags = b.flags + uniform(J.chunk_base) * kFlagStride;
+    a.ticket = nullptr;
+    a.final = uniform(J.final);
+    return a;
 }
 
 __device__ __forceinline__ BItem batch_item(const BatchArgs &b, const JobView &v, uint64_t t, uint32_t job)
 {
     BItem it;
-    it.t = t;
-    it.job = t < b.total_chunks && job < b.njobs ? job : b.njobs;
-    it.c = it.job < b.njobs ? t - v.jobs[it.job].chunk_base : 0;
+    it.t = uniform(t);
+    it.job = uniform(t < b.total_chunks && job < b.njobs ? job : b.njobs);
+    it.c = it.job < b.njobs ? it.t - uniform(v.jobs[it.job].chunk_base) : 0;
     return it;
 }
 
 __device__ __forceinline__ BItem batch_item_of(const BatchArgs &b, const JobView &v, uint64_t t)
 {
-    const uint32_t job = t < b.total_chunks ? __builtin_amdgcn_readfirstlane(find_job(v.chunk_end, b.njobs, t))
-                                            : b.njobs;
-    return batch_item(b, v, t, job);
+    return batch_item(b, v, t, t < b.total_chunks ? find_job(v.chunk_end, b.njobs, t) : b.njobs);
 }
 
 template <int W>
 __device__ __forceinline__ void batch_fetch(const BatchArgs &b, const JobView &v, const BItem &it, uint32_t *qb,
                                             int w, int lane)
 {
-    const BatchJob &J = v.jobs[it.job];
-    chunk_fetch<W>(batch_compress_args(b, it.job, J), it.c, qb, w, lane);
+    chunk_fetch<W>(batch_compress_args(b, v, it.job), it.c, qb, w, lane);
 }
 
 // Rate pass of item B (as compress_rates with DEFER), or an empty state and
@@ -2528,11 +2548,9 @@ template <int W>
 __device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const JobView &v, const BItem &it,
                                                   int (&x)[32], int slot, CompressShared<W> &sh)
 {
-    const BatchJob &J = v.jobs[it.job];
-    const CompressArgs a = batch_compress_args(b, it.job, J);
-    const Resolved R = job_bound(b, v, it.job, J);
+    const Resolved R = job_bound(b, v, it.job);
     if (R.status == FSZ_OK) {
-        ChunkState cs = compress_rates<W, true>(a, R, it.c, x, slot, sh);
+        ChunkState cs = compress_rates<W, true>(batch_compress_args(b, v, it.job), R, it.c, x, slot, sh);
         cs.chunk = it.c;
         return cs;
     }
@@ -2543,67 +2561,30 @@ __device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const JobV
     return cs;
 }
 
-// One step of the batched pipeline: as pipe2_step, with A, B, C and the new
-// item each in its own job.
-template <bool W0, int W>
-__device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobView &v, uint64_t takes,
-                                                 const BItem &iA, const ChunkState &ca, int (&xa)[32], int sa,
-                                                 const BItem &iB, int (&yb)[32], ChunkState &cb, const BItem &iC,
-                                                 uint32_t *qb, uint32_t *pb, CompressShared<W> &sh,
-                                                 uint32_t &s_job, int w)
+// A data wave's step of the batched pipeline: as pipe2_step, with A, B, C and
+// the new item each in its own job.
+template <int W>
+__device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobView &v, const BItem &iA,
+                                                 const ChunkState &ca, int (&xa)[32], int sa, const BItem &iB,
+                                                 int (&yb)[32], ChunkState &cb, const BItem &iC, uint32_t *qb,
+                                                 uint32_t *pb, CompressShared<W> &sh, const uint32_t &s_job, int w)
 {
     const uint64_t N = b.total_chunks;
     const int lane = threadIdx.x & 63;
     const int j = lane & 7;
-    const bool take = iC.t < N;
-    const BatchJob &JA = v.jobs[iA.job];
-    const CompressArgs aA = batch_compress_args(b, iA.job, JA);
-    const Resolved RA = job_bound(b, v, iA.job, JA);
-    const bool liveA = RA.status == FSZ_OK;
-    unsigned long long traw = 0;
-    Probe probe{};
-    if (W0) {
-        if (take && lane == 0) traw = atomicAdd(b.ticket, 1ull);
-        if (liveA) probe = lookback_probe(aA.flags, iA.c, aA.flag_epoch);
-    }
     if (iB.t < N) cb = batch_rates<W>(b, v, iB, yb, sa ^ 1, sh);
+    lds_barrier();  // the control wave has A's offset and the new ticket
+    const uint64_t base = sh.base;
+    const BItem iD = batch_item(b, v, sh.ticket[0], s_job);
 
-    // ---- lookback of A (wave 0), the new ticket and its job
     uint32_t chunk_total = 0, wave_base = 0;
 #pragma unroll
     for (int k = 0; k < W; k++) {
         if (k < w) wave_base += sh.wave_total[sa][k];
         chunk_total += sh.wave_total[sa][k];
     }
-    if (W0) {
-        // lookback first (as in the single-field pipeline), then the new
-        // ticket and its job, found in the LDS copy of the job ends
-        Prefix pre{0, false};
-        consume_probe(probe);
-        if (liveA) pre = lookback_wait(aA.flags, iA.c, aA.flag_epoch, chunk_total, false, true, probe);
-        const unsigned long long tk =
-            take ? ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(traw >> 32)) << 32) |
-                       (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)traw)
-                 : N;
-        const uint32_t jobD = tk < N ? find_job(v.chunk_end, b.njobs, tk) : b.njobs;
-        if (lane == 0) {
-            if (take && tk == takes - 1)
-                __hip_atomic_store(b.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh.base = pre.excl;
-            sh.ticket[0] = tk;
-            s_job = jobD;
-            if (iA.c == aA.nchunks - 1) {
-                if (liveA)
-                    finish_stream(aA, RA, pre, chunk_total);
-                else
-                    write_final(aA.final, 0, (uint32_t)RA.status, aA.epoch);
-            }
-        }
-    }
-    lds_barrier();
-    const uint64_t base = sh.base;
-    const BItem iD = batch_item(b, v, sh.ticket[0], s_job);
-
+    const CompressArgs aA = batch_compress_args(b, v, iA.job);
+    const bool liveA = job_bound(b, v, iA.job).status == FSZ_OK;
     const uint64_t tile0 = iA.c * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
     const bool ok = liveA && aA.data0 + base + chunk_total <= aA.capacity && tile0 < aA.ntiles;
     uint32_t *wave_out = reinterpret_cast<uint32_t *>(aA.out + aA.data0 + base + wave_base);
@@ -2626,9 +2607,9 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobVi
     return iD;
 }
 
-template <bool W0, int W>
+template <int W>
 __device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const JobView &v, CompressShared<W> &sh,
-                                               uint32_t &s_job, uint32_t *qb, uint32_t *pb, int w)
+                                               const uint32_t &s_job, uint32_t *qb, uint32_t *pb, int w)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t N = b.total_chunks;
@@ -2657,9 +2638,9 @@ __device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const JobView
     }
     // loop invariant: A rate-passed in x (slot 0), B read into y, C in flight
     for (;;) {
-        const BItem iD = batch_pipe_step<W0, W>(b, v, takes, iA, ca, x, 0, iB, y, cb, iC, qb, pb, sh, s_job, w);
+        const BItem iD = batch_pipe_step<W>(b, v, iA, ca, x, 0, iB, y, cb, iC, qb, pb, sh, s_job, w);
         if (iB.t >= N) return;
-        const BItem iE = batch_pipe_step<W0, W>(b, v, takes, iB, cb, y, 1, iC, x, ca, iD, qb, pb, sh, s_job, w);
+        const BItem iE = batch_pipe_step<W>(b, v, iB, cb, y, 1, iC, x, ca, iD, qb, pb, sh, s_job, w);
         if (iC.t >= N) return;
         iA = iC;
         iB = iD;
@@ -2667,11 +2648,69 @@ __device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const JobView
     }
 }
 
-// LDSJOBS (njobs <= kPipeLdsJobs): the job records, their resolved bounds
+// The control wave (as ctrl_run): tickets, their jobs, and the lookback of the
+// item rate-passed in the previous step.  Passes every barrier of the data
+// waves.
+template <int W>
+__device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const JobView &v, CompressShared<W> &sh,
+                                               uint32_t &s_job)
+{
+    const uint64_t N = b.total_chunks;
+    const uint64_t takes = N + gridDim.x;
+    const int lane = __lane_id();
+    __builtin_amdgcn_s_setprio(3);  // as ctrl_run
+    int tslot = 0;
+    BItem iA = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    if (iA.t >= N) return;
+    BItem iB = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    lds_barrier();  // the rate pass of A
+    BItem iC = batch_item(b, v, N, b.njobs);
+    if (iB.t < N) iC = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    for (int sa = 0;; sa ^= 1) {
+        const bool take = iC.t < N;
+        unsigned long long traw = 0;
+        if (take && lane == 0) traw = atomicAdd(b.ticket, 1ull);
+        uint32_t chunk_total = 0;
+#pragma unroll
+        for (int k = 0; k < W; k++) chunk_total += sh.wave_total[sa][k];  // A's, from the previous step
+        const CompressArgs aA = batch_compress_args(b, v, iA.job);
+        const Resolved RA = job_bound(b, v, iA.job);
+        Prefix pre{0, false};
+        if (RA.status == FSZ_OK) pre = lookback_wait(aA.flags, iA.c, aA.flag_epoch, chunk_total, false);
+        const unsigned long long tk = take ? uniform((uint64_t)traw) : N;
+        const uint32_t jobD = tk < N ? find_job(v.chunk_end, b.njobs, tk) : b.njobs;
+        if (iB.t < N) lds_barrier();  // the data waves' rate pass of B
+        if (lane == 0) {
+            if (take && tk == takes - 1)
+                __hip_atomic_store(b.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sh.base = pre.excl;
+            sh.ticket[0] = tk;
+            s_job = jobD;
+            if (iA.c == aA.nchunks - 1) {
+                if (RA.status == FSZ_OK)
+                    finish_stream(aA, RA, pre, chunk_total);
+                else
+                    write_final(aA.final, 0, (uint32_t)RA.status, aA.epoch);
+            }
+        }
+        lds_barrier();  // the offset and the ticket go out
+        if (iB.t >= N) return;
+        iA = iB;
+        iB = iC;
+        iC = batch_item(b, v, tk, jobD);
+    }
+}
+
+// W data waves (8 tiles each per item) and a control wave, one workgroup per
+// CU.  LDSJOBS (njobs <= kPipeLdsJobs): the job records, their resolved bounds
 // and chunk ends are copied to LDS at the start; the view's address space is
 // then fixed at compile time, so job fields are read with LDS instructions.
+// 10 data waves and the job records fill the LDS (the narrower forms:
+// compress_batch_waves).  64 fields of 125 M elements: 251 us per call with the
+// range pass, where groups of 4 waves whose wave 0 walked the lookback beside
+// its data took 309 and such groups of 8 waves 266.
 template <int W, bool LDSJOBS>
-__global__ __launch_bounds__(W * 64) void batch_pipe_kernel(BatchArgs b)
+__global__ __launch_bounds__((W + 1) * 64) void batch_pipe_kernel(BatchArgs b)
 {
     __shared__ CompressShared<W> sh;
     __shared__ uint32_t s_job;
@@ -2693,16 +2732,16 @@ __global__ __launch_bounds__(W * 64) void batch_pipe_kernel(BatchArgs b)
         }
         lds_barrier();
         const JobView v{ljobs, lbound, lend};
-        if (w == 0)
-            batch_pipe_run<true, W>(b, v, sh, s_job, qb, pb, w);
-        else if (W > 1)
-            batch_pipe_run<false, W>(b, v, sh, s_job, qb, pb, w);
+        if (w < W)
+            batch_pipe_run<W>(b, v, sh, s_job, qb, pb, w);
+        else
+            batch_ctrl_run<W>(b, v, sh, s_job);
     } else {
         const JobView v{b.jobs, nullptr, b.chunk_end};
-        if (w == 0)
-            batch_pipe_run<true, W>(b, v, sh, s_job, qb, pb, w);
-        else if (W > 1)
-            batch_pipe_run<false, W>(b, v, sh, s_job, qb, pb, w);
+        if (w < W)
+            batch_pipe_run<W>(b, v, sh, s_job, qb, pb, w);
+        else
+            batch_ctrl_run<W>(b, v, sh, s_job);
     }
 }
 
@@ -3435,36 +3474,20 @@ static bool batch_lds_pad(K kernel, int groups, size_t *pad)
 }
 
 template <int W, bool LDSJOBS>
-static hipError_t launch_batch_pipe(const BatchArgs &b, int groups, hipStream_t s)
+static hipError_t launch_batch_pipe(const BatchArgs &b, hipStream_t s)
 {
-    size_t pad = 0;
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_pipe_kernel<W, LDSJOBS>, W * 64, 0) !=
-            hipSuccess ||
-        cus <= 0 || per_cu <= 0) {
-        cus = 256;
-        per_cu = 1;
-    }
-    if (groups > 0 && groups < per_cu) {  // the cap is a hint: dropped where no pad can set it
-        if (batch_lds_pad(batch_pipe_kernel<W, LDSJOBS>, groups, &pad))
-            per_cu = groups;
-        else
-            pad = 0;
-    }
-    const uint64_t g = (uint64_t)cus * (uint64_t)per_cu;
-    const unsigned grid = (unsigned)(b.total_chunks < g ? b.total_chunks : g);
-    hipLaunchKernelGGL((batch_pipe_kernel<W, LDSJOBS>), dim3(grid), dim3(W * 64), pad, s, b);
+    static const unsigned cap = persistent_grid(batch_pipe_kernel<W, LDSJOBS>, ~0ull, (W + 1) * 64);
+    const unsigned grid = (unsigned)(b.total_chunks < cap ? b.total_chunks : cap);
+    hipLaunchKernelGGL((batch_pipe_kernel<W, LDSJOBS>), dim3(grid), dim3((W + 1) * 64), 0, s, b);
     return hipGetLastError();
 }
 
-template <int W>
-static hipError_t launch_batch_compress(const BatchArgs &b, int groups, hipStream_t s)
+static hipError_t launch_batch_compress(const BatchArgs &b, hipStream_t s)
 {
-    // the persistent pipeline, one workgroup per CU at most (its LDS); a cap of 1 needs no pad
-    return b.njobs <= kPipeLdsJobs ? launch_batch_pipe<W, true>(b, groups, s)
-                                   : launch_batch_pipe<W, false>(b, groups, s);
+    const bool lds = b.njobs <= kPipeLdsJobs;
+    if (b.waves == 10) return lds ? launch_batch_pipe<10, true>(b, s) : launch_batch_pipe<10, false>(b, s);
+    if (b.waves == 4) return lds ? launch_batch_pipe<4, true>(b, s) : launch_batch_pipe<4, false>(b, s);
+    return lds ? launch_batch_pipe<8, true>(b, s) : launch_batch_pipe<8, false>(b, s);
 }
 
 template <bool ALIGNED, int W>
@@ -3489,7 +3512,7 @@ static hipError_t launch_batch_w(const BatchArgs &b, bool aligned_out, int group
         e = hipGetLastError();
     }
     if (e == hipSuccess && b.njobs)
-        e = launch_batch_compress<W>(b, groups, s);
+        e = launch_batch_compress(b, s);
     return e;
 }
 

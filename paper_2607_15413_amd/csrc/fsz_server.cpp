@@ -385,7 +385,7 @@ fsz_status fsz_server_create(const fsz_server_config *cfg, fsz_server **server)
     // elements.
     const uint64_t jobs = (uint64_t)c.max_jobs_per_round;
     const uint64_t elems = c.hbm_budget / 4;
-    const uint64_t chunks = elems / ((uint64_t)kTile * kTilesPerWave * (uint64_t)c.tuning.waves_per_group) + jobs;
+    const uint64_t chunks = elems / ((uint64_t)kTile * kTilesPerWave * (uint64_t)std::min(c.tuning.waves_per_group, 4)) + jobs;
     const uint64_t segs = elems / kSegElems + jobs;
     for (auto &slot : s->slots) {
         if (!good) break;

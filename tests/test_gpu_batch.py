@@ -524,3 +524,25 @@ def test_batches_back_to_back(count):
     torch.cuda.synchronize()
     for k, b in enumerate(batches):
         check_against_oracle(b, refs[k], f"batch {k} of {count}")
+
+
+@pytest.mark.parametrize("total", [(1 << 21) - 1, 1 << 21, (1 << 23) - 1, 1 << 23])
+@pytest.mark.parametrize("njobs", [3, 97])
+def test_batch_compress_widths(total, njobs):
+    """The compressing workgroups of a batch are 4, 8 or 10 data waves wide by
+    its elements, with the job records in LDS up to 96 jobs: sizes on both
+    sides of each line, a job without a valid bound among the others."""
+    base = workloads.sinusoid_field(1 << 22, 77)
+    sizes = [int(s) for s in np.random.default_rng(total + njobs).multinomial(total - njobs, [1 / njobs] * njobs) + 1]
+    specs = [("c", base[k:k + n], fsz.FSZ_REL, (1e-2, 1e-3, 1e-4)[k % 3]) for k, n in enumerate(sizes)]
+    specs[1] = ("c", specs[1][1], fsz.FSZ_ABS, 1e-12)  # below 8 ulp
+    assert sum(s[1].size for s in specs) == total
+    announce(f"batch of {njobs} jobs, {total} elements")
+    old = oracle.set_threads(8)
+    try:
+        refs = oracle_refs(specs)
+    finally:
+        oracle.set_threads(old)
+    b = DeviceBatch(specs, offset=njobs % 2, out_offset=1)
+    b.run()
+    check_against_oracle(b, refs, f"{njobs} jobs, {total} elements")
