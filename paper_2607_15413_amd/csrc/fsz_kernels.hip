@@ -3329,10 +3329,13 @@ hipError_t launch_compress(const CompressArgs &a, hipStream_t s)
 {
     if (a.features != kFeaturesAll)  // the ablation's feature subsets
         FSZ_LAUNCH_PIPE(compress_pipe2_kernel<8>, 8, 8)
-    // 11 data waves and a control wave; 8 where the smaller workgroup's start
-    // and the finer spread count for more (2^20 GRF 14.8 against 16.0 us, 2^22
-    // 22.3 / 22.7, 6 M 26.5 / 26.9, 2^23 30.9 / 30.3, 2^25 76.9 / 74.5)
+    // 11 data waves and a control wave; fewer where the smaller workgroup's
+    // start and the finer spread count for more (4 / 8 / 11 data waves in us
+    // per call, range pass included: 2^14 9.8 / 10.5 / -, 2^18 10.8 / 12.1 / -,
+    // 2^20 13.3 / 13.6 / 16.0, 2^21 17.6 / 15.3 / -, 2^22 - / 22.3 / 22.7, 6 M
+    // - / 26.5 / 26.9, 2^23 - / 30.9 / 30.3, 2^25 - / 76.9 / 74.5)
     if (a.n >= (1ull << 23)) FSZ_LAUNCH_PIPE(compress_ctrl_kernel<11>, 12, 11)
+    if (a.n <= (1ull << 20)) FSZ_LAUNCH_PIPE(compress_ctrl_kernel<4>, 5, 4)
     FSZ_LAUNCH_PIPE(compress_ctrl_kernel<8>, 9, 8)
 }
 

@@ -645,3 +645,9 @@ def test_largest_output_of_a_wave(n):
         announce(f"largest wave output n={n} offset {off}")
         st, got = gpu_compress(x, fsz.FSZ_ABS, eb, in_offset=off)
         assert st == fsz.FSZ_OK and got == ref, first_diff(got, ref)
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 20) + 1])
+def test_compressor_width_edge(n):
+    """4 data waves per workgroup up to 2^20 elements, 8 above."""
+    check_round_trip("width edge", workloads.sinusoid_field(n, 3), fsz.FSZ_REL, 1e-4, in_offset=n & 1)
