@@ -23,6 +23,7 @@ constexpr int kTilesPerWave = 8;
 constexpr int kTilesPerChunk = kTilesPerWave * kWaves;
 constexpr int kStatsThreads = 256;
 constexpr int kStatsMaxBlocks = 1024;
+constexpr int kRangeMaxBlocks = 256;  // workgroups (and partials) of the single-field range pass
 
 // Per-lane LDS staging row: 32 floats + 4 dwords of padding (bank spread).
 constexpr int kStageRowDwords = 36;

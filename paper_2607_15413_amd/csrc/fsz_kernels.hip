@@ -585,10 +585,11 @@ struct RangeAcc {
         ma = max(max(ma, __float_as_uint(f.x) & m),
                  max(max(__float_as_uint(f.y) & m, __float_as_uint(f.z) & m), __float_as_uint(f.w) & m));
     }
+    template <int THREADS = kStatsThreads>
     __device__ __forceinline__ StatsPartial reduce() const
     {
         const uint32_t nf = ma >= 0x7F800000u ? 1u : 0u;
-        return stats_block_reduce<kStatsThreads>(mn, mx, __uint_as_float(ma & 0x7FFFFFFFu), nf);
+        return stats_block_reduce<THREADS>(mn, mx, __uint_as_float(ma & 0x7FFFFFFFu), nf);
     }
 };
 
@@ -599,33 +600,50 @@ __device__ __forceinline__ uint32_t align_head(const void *x)
 }
 
 // Value-range pass, part 1: one partial (min, max, max|x|, non-finite) per
-// workgroup over a grid-stride slice of x (four 16-byte loads in flight per
-// thread; the elements before the first and after the last 16-byte boundary
-// one per thread).  Bound by the read: 512^3 at 5.8 TB/s.
-__global__ __launch_bounds__(kStatsThreads) void stats_partial_kernel(StatsArgs a)
+// workgroup.  Bound by the read: in every round a workgroup takes one piece of
+// kRangeUnroll x THREADS consecutive 16-byte vectors, so that its loads
+// in flight lie side by side in memory, and one workgroup of 8 waves per CU is
+// enough to fill HBM (512^3: 78 us, 6.9 TB/s; a grid of 4 workgroups per CU
+// whose loads in flight lay a grid apart took 92 us, 5.8 TB/s) and leaves 256
+// partials to fold.  The last, partial round goes to all threads one vector at
+// a time, the elements before the first and after the last 16-byte boundary
+// singly.  KEEP: loads without the nontemporal hint, which leave the field in
+// the memory-side cache for the compressor's read.
+constexpr int kRangeUnroll = 4;
+template <int THREADS, bool KEEP>
+__global__ __launch_bounds__(THREADS) void stats_partial_kernel(StatsArgs a)
 {
+    auto load = [](const f4 *p) { return KEEP ? *p : __builtin_nontemporal_load(p); };
     RangeAcc acc;
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t nthreads = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t tid = (uint64_t)blockIdx.x * THREADS + threadIdx.x;
+    const uint64_t nthreads = (uint64_t)gridDim.x * THREADS;
     const uint64_t head = min((uint64_t)align_head(a.x), a.n);
     const uint64_t nvec = (a.n - head) / 4;
     const f4 *x4 = reinterpret_cast<const f4 *>(a.x + head);
-    uint64_t i = tid;
-    for (; i + 3 * nthreads < nvec; i += 4 * nthreads) {
-        const f4 f0 = __builtin_nontemporal_load(x4 + i);
-        const f4 f1 = __builtin_nontemporal_load(x4 + i + nthreads);
-        const f4 f2 = __builtin_nontemporal_load(x4 + i + 2 * nthreads);
-        const f4 f3 = __builtin_nontemporal_load(x4 + i + 3 * nthreads);
-        acc.take4(f0);
-        acc.take4(f1);
-        acc.take4(f2);
-        acc.take4(f3);
+    const uint64_t whole = nvec - nvec % (kRangeUnroll * nthreads);  // vectors of whole rounds
+    for (uint64_t i = (uint64_t)blockIdx.x * THREADS * kRangeUnroll + threadIdx.x; i < whole;
+         i += kRangeUnroll * nthreads) {
+        f4 f[kRangeUnroll];
+#pragma unroll
+        for (int u = 0; u < kRangeUnroll; u++) f[u] = load(x4 + i + u * THREADS);
+#pragma unroll
+        for (int u = 0; u < kRangeUnroll; u++) acc.take4(f[u]);
     }
-    for (; i < nvec; i += nthreads) acc.take4(x4[i]);
-    const uint64_t tail = head + 4 * nvec;  // at most 3 elements on either side, and >= 256 threads
+    if (whole < nvec) {
+        f4 f[kRangeUnroll];
+#pragma unroll
+        for (int u = 0; u < kRangeUnroll; u++) {
+            const uint64_t i = whole + tid + u * nthreads;
+            if (i < nvec) f[u] = load(x4 + i);
+        }
+#pragma unroll
+        for (int u = 0; u < kRangeUnroll; u++)
+            if (whole + tid + u * nthreads < nvec) acc.take4(f[u]);
+    }
+    const uint64_t tail = head + 4 * nvec;  // at most 3 elements on either side
     if (tid < head) acc.take(a.x[tid]);
     if (tid < a.n - tail) acc.take(a.x[tail + tid]);
-    const StatsPartial p = acc.reduce();
+    const StatsPartial p = acc.reduce<THREADS>();
     if (threadIdx.x == 0) a.partials[blockIdx.x] = p;
 }
 
@@ -642,7 +660,7 @@ __device__ __forceinline__ fsz_stats fold_partials(const StatsPartial *parts, ui
 
 // The call's bound, resolved by every workgroup of a compression: from the
 // caller's stats, or from the partials of the call's own range pass.  Folding
-// them here (at most 1024 x 16 bytes, two loads per thread) costs each workgroup
+// them here (at most 256 x 16 bytes) costs each workgroup
 // about a microsecond; a launch of its own between the two kernels took 4.6 us
 // on large fields and 2 us on small ones.
 template <int THREADS>
@@ -2424,9 +2442,24 @@ __global__ __launch_bounds__(W * 64) void batch_dec_kernel(BatchArgs b)
 
 hipError_t launch_stats_partials(const StatsArgs &a, uint32_t *nparts, hipStream_t s)
 {
-    const uint64_t want = ceil_div(a.n, (uint64_t)kStatsThreads * 16);
-    *nparts = (uint32_t)(want < 1 ? 1 : (want > kStatsMaxBlocks ? kStatsMaxBlocks : want));
-    hipLaunchKernelGGL(stats_partial_kernel, dim3(*nparts), dim3(kStatsThreads), 0, s, a);
+    // 512 threads from 2^21 elements on; below, 256 (and the same 16 elements
+    // per thread) reach more CUs (2^20 13.0 against 13.3 us per compression)
+    const bool small = a.n <= (1ull << 21);
+    const uint64_t want = ceil_div(a.n, (small ? 256ull : 512ull) * 16);
+    *nparts = (uint32_t)(want < 1 ? 1 : (want > kRangeMaxBlocks ? kRangeMaxBlocks : want));
+    // A field that fits half of the memory-side cache (256 MB) beside what the
+    // compressor writes is kept there: GRF at REL 1e-2 / 1e-4, us per compression
+    // kept / not: 2^23 26.6 / 26.7, 28.7 / 29.4; 2^24 43.3 / 44.1, 46.3 / 47.0; 2^25
+    // 66.7 / 68.4, 72.7 / 72.6; but 2^25.25 75.1 / 77.5, 89.1 / 82.5 and 2^26
+    // 116.3 / 116.2, 130.1 / 124.6, and below 2^23 it gains nothing (2^22
+    // 20.3 / 19.9, 21.6 / 21.0).
+    const bool keep = a.n >= (1ull << 23) && a.n <= (1ull << 25);
+    if (small)
+        hipLaunchKernelGGL((stats_partial_kernel<256, false>), dim3(*nparts), dim3(256), 0, s, a);
+    else if (keep)
+        hipLaunchKernelGGL((stats_partial_kernel<512, true>), dim3(*nparts), dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((stats_partial_kernel<512, false>), dim3(*nparts), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 

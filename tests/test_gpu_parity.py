@@ -651,3 +651,24 @@ def test_largest_output_of_a_wave(n):
 def test_compressor_width_edge(n):
     """4 data waves per workgroup up to 2^20 elements, 8 above."""
     check_round_trip("width edge", workloads.sinusoid_field(n, 3), fsz.FSZ_REL, 1e-4, in_offset=n & 1)
+
+
+@pytest.mark.parametrize("n", [(1 << 21) + k for k in (-1, 0, 1, 5)] + [3 * (1 << 21) - 3, (1 << 23) - 1, 1 << 23,
+                                                                        (1 << 25) + 2])
+def test_range_pass_rounds(n):
+    """The range pass reads whole rounds of pieces per workgroup and the rest one
+    vector per thread, in three forms by size: the extremes in the first and
+    last vector of a piece, of the whole rounds and of the field."""
+    xd = torch.linspace(-1.0, 1.0, n + 1, device=_dev())[1:]  # 4 bytes off the 16-byte grid
+    stats = torch.zeros(4, dtype=torch.float32, device=_dev())
+    piece = 4 * 4 * (256 if n <= 1 << 21 else 512)
+    whole = (n - 3) // (256 * piece) * 256 * piece + 3
+    for at in sorted({k for k in (0, 3, 2 + piece, 3 + piece, whole - 1, whole, n - 4, n - 1) if 0 <= k < n}):
+        keep = float(xd[at])
+        for v, k in ((-7.0, 0), (9.0, 1)):
+            xd[at] = v
+            announce(f"range pass n={n} extreme {v} at {at}")
+            assert fsz.fsz_field_stats(xd.data_ptr(), n, stats.data_ptr(), _stream()) == fsz.FSZ_OK
+            s = stats.tolist()
+            assert s[k] == v and s[2] == abs(v)
+        xd[at] = keep
