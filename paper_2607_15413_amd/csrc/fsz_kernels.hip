@@ -559,7 +559,7 @@ __device__ StatsPartial stats_block_reduce(float mn, float mx, float ma, uint32_
     }
     __shared__ StatsPartial wsum[THREADS / 64];
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = StatsPartial{mn, mx, ma, nf};
-    __syncthreads();
+    lds_barrier();
     StatsPartial p = wsum[0];
     for (int k = 1; k < THREADS / 64; k++) stats_combine(p.xmin, p.xmax, p.maxabs, p.flags, wsum[k]);
     return p;
@@ -656,18 +656,6 @@ __device__ __forceinline__ fsz_stats fold_partials(const StatsPartial *parts, ui
     for (uint32_t i = threadIdx.x; i < nparts; i += THREADS) stats_combine(mn, mx, ma, nf, parts[i]);
     const StatsPartial p = stats_block_reduce<THREADS>(mn, mx, ma, nf);
     return fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
-}
-
-// The call's bound, resolved by every workgroup of a compression: from the
-// caller's stats, or from the partials of the call's own range pass.  Folding
-// them here (at most 256 x 16 bytes) costs each workgroup
-// about a microsecond; a launch of its own between the two kernels took 4.6 us
-// on large fields and 2 us on small ones.
-template <int THREADS>
-__device__ __forceinline__ Resolved resolve_call(const CompressArgs &a)
-{
-    const fsz_stats s = a.partials ? fold_partials<THREADS>(a.partials, a.nparts) : *a.stats;
-    return resolve_bound(s, a.mode, a.value, a.n);
 }
 
 // Value-range pass, part 2: one workgroup folds the partials into *out.
@@ -1530,18 +1518,50 @@ __device__ __forceinline__ uint64_t pipe2_step(const CompressArgs &a, const Reso
     return D;
 }
 
-// The whole pipeline of one wave (W0: wave 0's role), from the first ticket on.
+// The start of a compressing workgroup: the first ticket A, the copy of its
+// chunk under way, and the call's bound R, from the caller's stats or folded by
+// every workgroup from the partials of the call's own range pass (at most one
+// per thread; a launch of its own for that took 4.6 us on large fields and 2 us
+// on small ones).  The partials' loads go out first, so neither the ticket's
+// round trip nor the chunk's copy waits on them.  False: no chunk is left, or
+// the bound does not resolve (the tickets are then handed out without data
+// work, and the last chunk's taker reports).
+template <int THREADS, int W>
+__device__ __forceinline__ bool pipe_start(const CompressArgs &a, CompressShared<W> &sh, uint32_t *qb, int w,
+                                           Resolved &R, uint64_t &A, int &tslot)
+{
+    static_assert(THREADS >= kRangeMaxBlocks, "one partial per thread");
+    const uint64_t N = a.nchunks;
+    const uint64_t takes = N + gridDim.x;
+    StatsPartial part{INFINITY, -INFINITY, 0.0f, 0u};
+    if (a.partials && threadIdx.x < a.nparts) part = a.partials[threadIdx.x];
+    tslot = 0;
+    A = next_ticket(a.ticket, takes, sh, tslot);
+    if (A >= N) return false;
+    if (w < W) chunk_fetch<W>(a, A, qb, w, threadIdx.x & 63);
+    fsz_stats s;
+    if (a.partials) {
+        const StatsPartial p = stats_block_reduce<THREADS>(part.xmin, part.xmax, part.maxabs, part.flags);
+        s = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+    } else {
+        s = *a.stats;
+    }
+    R = resolve_bound(s, a.mode, a.value, a.n);
+    if (R.status == FSZ_OK) return true;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the copy into LDS has landed
+    for (uint64_t t = A; t < N; t = next_ticket(a.ticket, takes, sh, tslot))
+        if (threadIdx.x == 0 && t == N - 1) write_final(a.final, 0, R.status, a.epoch);
+    return false;
+}
+
+// The whole pipeline of one wave (W0: wave 0's role) from pipe_start on.
 template <bool W0, int W, bool FEAT, class M = TileB32T8>
 __device__ __forceinline__ void pipe2_run(const CompressArgs &a, const Resolved &R, CompressShared<W> &sh,
-                                          uint32_t *qb, uint32_t *pb, int w)
+                                          uint32_t *qb, uint32_t *pb, int w, uint64_t A, int tslot)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t N = a.nchunks;
     const uint64_t takes = N + gridDim.x;
-    int tslot = 0;
-    const uint64_t A = next_ticket(a.ticket, takes, sh, tslot);
-    if (A >= N) return;
-    chunk_fetch<W>(a, A, qb, w, lane);
     uint64_t B = next_ticket(a.ticket, takes, sh, tslot);
     int x[32], y[32];
     chunk_read(qb, lane, x);
@@ -1608,7 +1628,8 @@ __device__ __forceinline__ uint64_t ctrl_step(const CompressArgs &a, const Resol
 }
 
 template <int WD>
-__device__ __forceinline__ void ctrl_run(const CompressArgs &a, const Resolved &R, CompressShared<WD> &sh)
+__device__ __forceinline__ void ctrl_run(const CompressArgs &a, const Resolved &R, CompressShared<WD> &sh, uint64_t A,
+                                         int tslot)
 {
     const uint64_t N = a.nchunks;
     const uint64_t takes = N + gridDim.x;
@@ -1616,9 +1637,6 @@ __device__ __forceinline__ void ctrl_run(const CompressArgs &a, const Resolved &
     // data waves in their rate pass, and its short lookback bursts gate the
     // step's second barrier
     __builtin_amdgcn_s_setprio(3);
-    int tslot = 0;
-    uint64_t A = next_ticket(a.ticket, takes, sh, tslot);
-    if (A >= N) return;
     uint64_t B = next_ticket(a.ticket, takes, sh, tslot);
     lds_barrier();  // the rate pass of A
     uint64_t C = N;
@@ -1648,20 +1666,14 @@ __global__ __launch_bounds__((WD + 1) * 64) void compress_ctrl_kernel(CompressAr
     __shared__ __attribute__((aligned(16))) uint32_t inbuf[WD * kPipeInDwords];
     __shared__ __attribute__((aligned(16))) uint32_t stbuf[WD * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const Resolved R = resolve_call<(WD + 1) * 64>(a);
-    if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
-        const uint64_t takes = a.nchunks + gridDim.x;
-        int tslot = 0;
-        for (;;) {
-            const uint64_t t = next_ticket(a.ticket, takes, sh, tslot);
-            if (t >= a.nchunks) return;
-            if (threadIdx.x == 0 && t == a.nchunks - 1) write_final(a.final, 0, R.status, a.epoch);
-        }
-    }
+    Resolved R;
+    uint64_t A;
+    int tslot;
+    if (!pipe_start<(WD + 1) * 64, WD>(a, sh, inbuf + w * kPipeInDwords, w, R, A, tslot)) return;
     if (w < WD)
-        pipe2_run<false, WD, false>(a, R, sh, inbuf + w * kPipeInDwords, stbuf + w * kPipeOutDwords, w);
+        pipe2_run<false, WD, false>(a, R, sh, inbuf + w * kPipeInDwords, stbuf + w * kPipeOutDwords, w, A, tslot);
     else
-        ctrl_run<WD>(a, R, sh);
+        ctrl_run<WD>(a, R, sh, A, tslot);
 }
 
 // The wave-0 form, for the feature switches (a.features).  W waves per
@@ -1677,20 +1689,14 @@ __global__ __launch_bounds__(W * 64) void compress_pipe2_kernel(CompressArgs a)
     uint32_t *qb = inbuf + w * kPipeInDwords;
     uint32_t *pb = stbuf + w * kPipeOutDwords;
 
-    const Resolved R = resolve_call<W * 64>(a);
-    if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
-        const uint64_t takes = a.nchunks + gridDim.x;
-        int tslot = 0;
-        for (;;) {
-            const uint64_t t = next_ticket(a.ticket, takes, sh, tslot);
-            if (t >= a.nchunks) return;
-            if (threadIdx.x == 0 && t == a.nchunks - 1) write_final(a.final, 0, R.status, a.epoch);
-        }
-    }
+    Resolved R;
+    uint64_t A;
+    int tslot;
+    if (!pipe_start<W * 64, W>(a, sh, qb, w, R, A, tslot)) return;
     if (w == 0)
-        pipe2_run<true, W, true>(a, R, sh, qb, pb, w);
+        pipe2_run<true, W, true>(a, R, sh, qb, pb, w, A, tslot);
     else
-        pipe2_run<false, W, true>(a, R, sh, qb, pb, w);
+        pipe2_run<false, W, true>(a, R, sh, qb, pb, w, A, tslot);
 }
 
 // ------------------------------------------------------------------ decompress
@@ -3007,21 +3013,15 @@ __global__ __launch_bounds__(9 * 64) void compress_cfg_pipe_kernel(CompressArgs 
     __shared__ __attribute__((aligned(16))) uint32_t inbuf[8 * kPipeInDwords];
     __shared__ __attribute__((aligned(16))) uint32_t stbuf[8 * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const Resolved R = resolve_call<9 * 64>(a);
-    if (R.status != FSZ_OK) {  // no data work: hand out the tickets, the last chunk reports
-        const uint64_t takes = a.nchunks + gridDim.x;
-        int tslot = 0;
-        for (;;) {
-            const uint64_t t = next_ticket(a.ticket, takes, sh, tslot);
-            if (t >= a.nchunks) return;
-            if (threadIdx.x == 0 && t == a.nchunks - 1) write_final(a.final, 0, R.status, a.epoch);
-        }
-    }
+    Resolved R;
+    uint64_t A;
+    int tslot;
+    if (!pipe_start<9 * 64, 8>(a, sh, inbuf + w * kPipeInDwords, w, R, A, tslot)) return;
     if (w < 8)
         pipe2_run<false, 8, false, TileCfg<HB, L>>(a, R, sh, inbuf + w * kPipeInDwords,
-                                                    stbuf + w * kPipeOutDwords, w);
+                                                    stbuf + w * kPipeOutDwords, w, A, tslot);
     else
-        ctrl_run<8>(a, R, sh);
+        ctrl_run<8>(a, R, sh, A, tslot);
 }
 
 // WV waves per workgroup, chunks of 64 WV segments (4 waves: a wider grid,
