@@ -96,8 +96,8 @@ struct Workspace {
     uint64_t b_flags_cap = 0;
     StatsPartial *b_partials = nullptr;
     uint64_t b_partials_cap = 0;
-    fsz_stats *b_stats = nullptr;
-    uint64_t b_stats_cap = 0;
+    Resolved *b_bounds = nullptr;
+    uint64_t b_bounds_cap = 0;
     unsigned long long *b_ticket = nullptr;
     unsigned long long *b_words = nullptr;  // decompress jobs: group totals, chunk offsets
     uint64_t b_words_cap = 0;
@@ -446,10 +446,10 @@ struct BatchLayout {
 
 // Data waves per workgroup of the batched compressor, for the elements of all
 // its jobs: wide workgroups once there are enough items for the chip, narrow
-// ones where the spread counts (4 / 8 / 10 waves in us per call: 0.1 M elements
-// in 2 jobs 26 / 28 / 29, 3.0 M in 8 33.5 / 33.2 / 34, 7.0 M in 32 47 / 43 / 43,
-// 17 M in 16 - / 62 / 62, 125 M in 64 - / 266 / 252).
-int compress_batch_waves(uint64_t elems) { return elems >= (1ull << 23) ? 10 : elems >= (1ull << 21) ? 8 : 4; }
+// ones where the spread counts (us per call: 0.1 M elements in 2 jobs with 4
+// waves 26, with 8 28; 3.0 M in 8 33.5 and 33.2; 7.0 M in 32 47 and 43, with 10
+// 43; 125 M in 64 with 8 266, with 10 252).
+int compress_batch_waves(uint64_t elems) { return elems >= (1ull << 23) ? 11 : elems >= (1ull << 21) ? 8 : 4; }
 
 // Validates every job (nothing is enqueued unless all pass) and lays out
 // global chunk and segment (or tile group) ranges of each kind in job order.
@@ -638,7 +638,7 @@ fsz_status resolve_tuning(const fsz_job *jobs, size_t njobs, const fsz_tuning *t
 }
 
 BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigned long long *flags,
-                     unsigned long long *ticket, fsz_stats *stats, StatsPartial *partials, unsigned long long *words)
+                     unsigned long long *ticket, Resolved *bounds, StatsPartial *partials, unsigned long long *words)
 {
     BatchArgs b{};
     const KindLayout &C = L.k[FSZ_OP_COMPRESS], &D = L.k[FSZ_OP_DECOMPRESS];
@@ -660,7 +660,7 @@ BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigne
     b.nflags = L.flag_words();
     b.flags = flags;
     b.ticket = ticket;
-    b.stats = stats;
+    b.bounds = bounds;
     b.partials = partials;
     b.dec.njobs = (uint32_t)D.jobs.size();
     b.dec.tpc_log2 = (uint32_t)__builtin_ctz((unsigned)(kTilesPerWave * L.waves));
@@ -706,7 +706,7 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
     if (st != FSZ_OK || njobs == 0) return st;
     if (!grow(&ws->b_flags, &ws->b_flags_cap, L.flag_words(), ws->stream) ||
         !grow(&ws->b_partials, &ws->b_partials_cap, L.k[FSZ_OP_COMPRESS].total_segs, ws->stream) ||
-        !grow(&ws->b_stats, &ws->b_stats_cap, njobs, ws->stream) ||
+        !grow(&ws->b_bounds, &ws->b_bounds_cap, njobs, ws->stream) ||
         !grow(&ws->b_words, &ws->b_words_cap, L.dec_words(), ws->stream))
         return FSZ_ERR_DEVICE;
     DescSlot &slot = ws->ring[ws->ring_next++ % ws->ring.size()];
@@ -716,7 +716,7 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
     L.pack(slot.h);
     if (!ok(hipMemcpyAsync(slot.d, slot.h, bytes, hipMemcpyHostToDevice, ws->stream))) return FSZ_ERR_DEVICE;
     if (++ws->call == 0) ++ws->call;
-    BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_stats, ws->b_partials,
+    BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_bounds, ws->b_partials,
                                    ws->b_words);
     b.h_done = slot.h_done;
     slot.epoch = ws->call;
@@ -735,7 +735,7 @@ bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t 
     std::lock_guard<std::mutex> g(ws->mu);
     if (!grow(&ws->b_flags, &ws->b_flags_cap, std::max<uint64_t>(chunks, 1) * kFlagStride, ws->stream) ||
         !grow(&ws->b_partials, &ws->b_partials_cap, std::max<uint64_t>(segs, 1), ws->stream) ||
-        !grow(&ws->b_stats, &ws->b_stats_cap, std::max<uint64_t>(jobs, 1), ws->stream) ||
+        !grow(&ws->b_bounds, &ws->b_bounds_cap, std::max<uint64_t>(jobs, 1), ws->stream) ||
         !grow(&ws->b_words, &ws->b_words_cap, chunks + segs, ws->stream))  // a tile group holds several segments
         return false;
     const size_t bytes = jobs * (sizeof(BatchJob) + 2 * sizeof(uint64_t));
@@ -757,7 +757,7 @@ struct fsz_plan {
     unsigned long long *d_flags = nullptr;
     unsigned long long *d_ticket = nullptr;
     StatsPartial *d_partials = nullptr;
-    fsz_stats *d_stats = nullptr;
+    Resolved *d_bounds = nullptr;
     unsigned long long *d_words = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -774,7 +774,7 @@ void free_plan(fsz_plan *p)
     (void)hipFree(p->d_flags);
     (void)hipFree(p->d_ticket);
     (void)hipFree(p->d_partials);
-    (void)hipFree(p->d_stats);
+    (void)hipFree(p->d_bounds);
     (void)hipFree(p->d_words);
     delete p;
 }
@@ -1071,12 +1071,12 @@ fsz_status fsz_plan_create(const fsz_job *jobs, size_t njobs, const fsz_tuning *
                ok(hipMalloc(&p->d_ticket, sizeof(unsigned long long))) &&
                ok(hipMalloc(&p->d_partials,
                             std::max<uint64_t>(L.k[FSZ_OP_COMPRESS].total_segs, 1) * sizeof(StatsPartial))) &&
-               ok(hipMalloc(&p->d_stats, njobs * sizeof(fsz_stats))) &&
+               ok(hipMalloc(&p->d_bounds, njobs * sizeof(Resolved))) &&
                ok(hipMemcpy(p->d_desc, host.data(), host.size(), hipMemcpyHostToDevice)) &&
                ok(hipMemset(p->d_ticket, 0, sizeof(unsigned long long))) && ok(hipDeviceSynchronize()) &&
                ok(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
         if (good) {
-            const BatchArgs b = batch_args(L, p->d_desc, g_plan_ids++, p->d_flags, p->d_ticket, p->d_stats,
+            const BatchArgs b = batch_args(L, p->d_desc, g_plan_ids++, p->d_flags, p->d_ticket, p->d_bounds,
                                            p->d_partials, p->d_words);
             good = ok(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
             if (good) {

@@ -56,6 +56,14 @@ struct StatsPartial {
     uint32_t flags;
 };
 
+// A call's error bound (Sec. V-A) as the kernels use it: the step, its inverse,
+// the stream header's flag bit 0 and the status.
+struct Resolved {
+    float E, inv;
+    uint32_t flags;
+    int status;
+};
+
 struct StatsArgs {
     const float *x;
     uint64_t n;
@@ -168,7 +176,7 @@ struct BatchArgs {
     uint64_t total_chunks, total_segs, nflags;  // nflags: flag words (kFlagStride per chunk)
     unsigned long long *flags;  // cleared by the batch's range pass
     unsigned long long *ticket; // zero between launches (self-resetting)
-    fsz_stats *stats;           // one per job
+    Resolved *bounds;           // one per job
     StatsPartial *partials;     // one per segment
     // decompress jobs
     struct {

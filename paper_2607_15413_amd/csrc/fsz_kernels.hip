@@ -251,12 +251,6 @@ __device__ __forceinline__ void write_final(fsz_result *final, uint64_t size, ui
 
 // ------------------------------------------------------------------ bound
 
-struct Resolved {
-    float E, inv;
-    uint32_t flags;
-    int status;
-};
-
 // binary32 spacing at magnitude m, from its exponent field
 __device__ __forceinline__ double spacing32(float m)
 {
@@ -2402,7 +2396,8 @@ __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
     }
 }
 
-// Per-job fold of the batched range pass (one workgroup per job).
+// Per-job fold of the batched range pass (one workgroup per job) and the job's
+// bound.
 template <int THREADS>
 __device__ __forceinline__ void fold_job_stats(const BatchArgs &b, uint32_t job)
 {
@@ -2412,7 +2407,8 @@ __device__ __forceinline__ void fold_job_stats(const BatchArgs &b, uint32_t job)
     for (uint64_t i = threadIdx.x; i < J.nsegs; i += THREADS)
         stats_combine(mn, mx, ma, nf, b.partials[J.seg_base + i]);
     const StatsPartial p = stats_block_reduce<THREADS>(mn, mx, ma, nf);
-    if (threadIdx.x == 0) b.stats[job] = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+    if (threadIdx.x == 0)
+        b.bounds[job] = resolve_bound(fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags}, J.mode, J.value, J.n);
 }
 
 __global__ __launch_bounds__(kStatsThreads) void batch_stats_final_kernel(BatchArgs b)
@@ -2495,101 +2491,84 @@ struct BItem {
     uint64_t c;    // chunk index inside the job
 };
 
-// Up to kPipeLdsJobs job records and their resolved bounds are copied to LDS
-// when the kernel starts, so that no step waits on global memory for its
-// items' arguments; larger batches read the job table and resolve per use.
-constexpr uint32_t kPipeLdsJobs = 96;
+// An item's job is the same in every lane and nothing writes the tables while
+// the kernel runs: read through the constant address space, a job's record
+// and bound come by scalar loads, into scalar registers and from the scalar
+// cache.  (Copies of the records in LDS went through vector registers and took
+// the room of an eleventh data wave.)
+typedef __attribute__((address_space(4))) BatchJob c_job;
+typedef __attribute__((address_space(4))) Resolved c_resolved;
 
-// A job's fields are the same in every lane: taken out of LDS into scalar
-// registers, they leave the vector registers to the data.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ uint64_t uniform(uint64_t v)
 {
     return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
 }
-template <typename T>
-__device__ __forceinline__ T *uniform(T *p)
-{
-    return reinterpret_cast<T *>(uniform((uint64_t)p));
-}
 
-struct JobView {
-    const BatchJob *jobs;       // LDS copy or the global table
-    const Resolved *bound;      // LDS (null: resolve from the job's stats)
-    const uint64_t *chunk_end;  // LDS copy or the global table
-};
-
-__device__ __forceinline__ Resolved job_bound(const BatchArgs &b, const JobView &v, uint32_t job)
+__device__ __forceinline__ Resolved job_bound(const BatchArgs &b, uint32_t job)
 {
-    Resolved r;
-    if (v.bound) {
-        r = v.bound[job];
-    } else {
-        const BatchJob &J = v.jobs[job];
-        r = resolve_bound(b.stats[job], J.mode, J.value, J.n);
-    }
-    return Resolved{__uint_as_float(uniform(__float_as_uint(r.E))), __uint_as_float(uniform(__float_as_uint(r.inv))),
-                    uniform(r.flags), (int)uniform((uint32_t)r.status)};
+    const c_resolved *r = (const c_resolved *)(b.bounds + job);
+    return Resolved{r->E, r->inv, r->flags, r->status};
 }
 
 // The arguments of a job's chunks, as the whole-field kernels take them.
-__device__ __forceinline__ CompressArgs batch_compress_args(const BatchArgs &b, const JobView &v, uint32_t job)
+__device__ __forceinline__ CompressArgs batch_compress_args(const BatchArgs &b, uint32_t job)
 {
-    const BatchJob &J = v.jobs[job];
+    const c_job *J = (const c_job *)(b.jobs + job);
     CompressArgs a;
-    a.x = static_cast<const float *>(uniform(J.src));
-    a.n = uniform(J.n);
-    a.ntiles = uniform(J.ntiles);
-    a.nblocks = uniform(J.nblocks);
-    a.nchunks = uniform(J.nchunks);
-    a.data0 = uniform(J.data0);
-    a.out = static_cast<uint8_t *>(uniform(J.dst));
-    a.capacity = uniform(J.dst_capacity);
+    a.x = static_cast<const float *>(J->src);
+    a.n = J->n;
+    a.ntiles = J->ntiles;
+    a.nblocks = J->nblocks;
+    a.nchunks = J->nchunks;
+    a.data0 = J->data0;
+    a.out = static_cast<uint8_t *>(J->dst);
+    a.capacity = J->dst_capacity;
     a.stats = nullptr;
     a.partials = nullptr;
     a.nparts = 0;
-    a.value = J.value;
-    a.mode = J.mode;
+    a.value = J->value;
+    a.mode = J->mode;
     a.features = kFeaturesAll;
     a.cfg_flags = 0;
     a.epoch = b.epoch;
     a.flag_epoch = 1;
-    a.flags = b.flags + uniform(J.chunk_base) * kFlagStride;
+    a.flags = b.flags + J->chunk_base * kFlagStride;
     a.ticket = nullptr;
-    a.final = uniform(J.final);
+    a.final = J->final;
     return a;
 }
 
-__device__ __forceinline__ BItem batch_item(const BatchArgs &b, const JobView &v, uint64_t t, uint32_t job)
+__device__ __forceinline__ BItem batch_item(const BatchArgs &b, uint64_t t, uint32_t job)
 {
     BItem it;
     it.t = uniform(t);
     it.job = uniform(t < b.total_chunks && job < b.njobs ? job : b.njobs);
-    it.c = it.job < b.njobs ? it.t - uniform(v.jobs[it.job].chunk_base) : 0;
+    it.c = it.job < b.njobs ? it.t - ((const c_job *)(b.jobs + it.job))->chunk_base : 0;
     return it;
 }
 
-__device__ __forceinline__ BItem batch_item_of(const BatchArgs &b, const JobView &v, uint64_t t)
+__device__ __forceinline__ BItem batch_item_of(const BatchArgs &b, const uint64_t *chunk_end, uint64_t t)
 {
-    return batch_item(b, v, t, t < b.total_chunks ? find_job(v.chunk_end, b.njobs, t) : b.njobs);
+    return batch_item(b, t, t < b.total_chunks ? find_job(chunk_end, b.njobs, t) : b.njobs);
 }
 
 template <int W>
-__device__ __forceinline__ void batch_fetch(const BatchArgs &b, const JobView &v, const BItem &it, uint32_t *qb,
+__device__ __forceinline__ void batch_fetch(const BatchArgs &b, const BItem &it, uint32_t *qb,
                                             int w, int lane)
 {
-    chunk_fetch<W>(batch_compress_args(b, v, it.job), it.c, qb, w, lane);
+    chunk_fetch<W>(batch_compress_args(b, it.job), it.c, qb, w, lane);
 }
 
 // Rate pass of item B (as compress_rates with DEFER), or an empty state and
 // the same barrier for an item whose job has no valid bound.
 template <int W>
-__device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const JobView &v, const BItem &it,
+__device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const BItem &it,
                                                   int (&x)[32], int slot, CompressShared<W> &sh)
 {
-    const Resolved R = job_bound(b, v, it.job);
+    const Resolved R = job_bound(b, it.job);
     if (R.status == FSZ_OK) {
-        ChunkState cs = compress_rates<W, true>(batch_compress_args(b, v, it.job), R, it.c, x, slot, sh);
+        ChunkState cs = compress_rates<W, true>(batch_compress_args(b, it.job), R, it.c, x, slot, sh);
         cs.chunk = it.c;
         return cs;
     }
@@ -2603,7 +2582,7 @@ __device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const JobV
 // A data wave's step of the batched pipeline: as pipe2_step, with A, B, C and
 // the new item each in its own job.
 template <int W>
-__device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobView &v, const BItem &iA,
+__device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const BItem &iA,
                                                  const ChunkState &ca, int (&xa)[32], int sa, const BItem &iB,
                                                  int (&yb)[32], ChunkState &cb, const BItem &iC, uint32_t *qb,
                                                  uint32_t *pb, CompressShared<W> &sh, const uint32_t &s_job, int w)
@@ -2611,10 +2590,10 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobVi
     const uint64_t N = b.total_chunks;
     const int lane = threadIdx.x & 63;
     const int j = lane & 7;
-    if (iB.t < N) cb = batch_rates<W>(b, v, iB, yb, sa ^ 1, sh);
+    if (iB.t < N) cb = batch_rates<W>(b, iB, yb, sa ^ 1, sh);
     lds_barrier();  // the control wave has A's offset and the new ticket
     const uint64_t base = sh.base;
-    const BItem iD = batch_item(b, v, sh.ticket[0], s_job);
+    const BItem iD = batch_item(b, sh.ticket[0], s_job);
 
     uint32_t chunk_total = 0, wave_base = 0;
 #pragma unroll
@@ -2622,8 +2601,8 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobVi
         if (k < w) wave_base += sh.wave_total[sa][k];
         chunk_total += sh.wave_total[sa][k];
     }
-    const CompressArgs aA = batch_compress_args(b, v, iA.job);
-    const bool liveA = job_bound(b, v, iA.job).status == FSZ_OK;
+    const CompressArgs aA = batch_compress_args(b, iA.job);
+    const bool liveA = job_bound(b, iA.job).status == FSZ_OK;
     const uint64_t tile0 = iA.c * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
     const bool ok = liveA && aA.data0 + base + chunk_total <= aA.capacity && tile0 < aA.ntiles;
     uint32_t *wave_out = reinterpret_cast<uint32_t *>(aA.out + aA.data0 + base + wave_base);
@@ -2632,7 +2611,7 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobVi
     if (iC.t < N) chunk_read(qb, lane, xa);
     if (iD.t < N) {
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the read of qb is done before it is overwritten
-        batch_fetch<W>(b, v, iD, qb, w, lane);
+        batch_fetch<W>(b, iD, qb, w, lane);
     }
     if (liveA && ca.vm != 0)
         ((g_u8 *)aA.out)[kHeaderBytes + (tile0 + (lane >> 3)) * kBlocksPerTile + j] = (uint8_t)ca.rbyte;
@@ -2647,39 +2626,39 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const JobVi
 }
 
 template <int W>
-__device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const JobView &v, CompressShared<W> &sh,
+__device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const uint64_t *chunk_end, CompressShared<W> &sh,
                                                const uint32_t &s_job, uint32_t *qb, uint32_t *pb, int w)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t N = b.total_chunks;
     const uint64_t takes = N + gridDim.x;
     int tslot = 0;
-    BItem iA = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    BItem iA = batch_item_of(b, chunk_end, next_ticket(b.ticket, takes, sh, tslot));
     if (iA.t >= N) return;
-    batch_fetch<W>(b, v, iA, qb, w, lane);
-    BItem iB = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    batch_fetch<W>(b, iA, qb, w, lane);
+    BItem iB = batch_item_of(b, chunk_end, next_ticket(b.ticket, takes, sh, tslot));
     int x[32], y[32];
     chunk_read(qb, lane, x);
     if (iB.t < N) {
         __builtin_amdgcn_s_waitcnt(0xC07F);
-        batch_fetch<W>(b, v, iB, qb, w, lane);
+        batch_fetch<W>(b, iB, qb, w, lane);
     }
-    ChunkState ca = batch_rates<W>(b, v, iA, x, 0, sh);
+    ChunkState ca = batch_rates<W>(b, iA, x, 0, sh);
     ChunkState cb = ca;
-    BItem iC = batch_item(b, v, N, b.njobs);
+    BItem iC = batch_item(b, N, b.njobs);
     if (iB.t < N) {
-        iC = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+        iC = batch_item_of(b, chunk_end, next_ticket(b.ticket, takes, sh, tslot));
         chunk_read(qb, lane, y);
         if (iC.t < N) {
             __builtin_amdgcn_s_waitcnt(0xC07F);
-            batch_fetch<W>(b, v, iC, qb, w, lane);
+            batch_fetch<W>(b, iC, qb, w, lane);
         }
     }
     // loop invariant: A rate-passed in x (slot 0), B read into y, C in flight
     for (;;) {
-        const BItem iD = batch_pipe_step<W>(b, v, iA, ca, x, 0, iB, y, cb, iC, qb, pb, sh, s_job, w);
+        const BItem iD = batch_pipe_step<W>(b, iA, ca, x, 0, iB, y, cb, iC, qb, pb, sh, s_job, w);
         if (iB.t >= N) return;
-        const BItem iE = batch_pipe_step<W>(b, v, iB, cb, y, 1, iC, x, ca, iD, qb, pb, sh, s_job, w);
+        const BItem iE = batch_pipe_step<W>(b, iB, cb, y, 1, iC, x, ca, iD, qb, pb, sh, s_job, w);
         if (iC.t >= N) return;
         iA = iC;
         iB = iD;
@@ -2691,7 +2670,7 @@ __device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const JobView
 // item rate-passed in the previous step.  Passes every barrier of the data
 // waves.
 template <int W>
-__device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const JobView &v, CompressShared<W> &sh,
+__device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const uint64_t *chunk_end, CompressShared<W> &sh,
                                                uint32_t &s_job)
 {
     const uint64_t N = b.total_chunks;
@@ -2699,12 +2678,12 @@ __device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const JobView
     const int lane = __lane_id();
     __builtin_amdgcn_s_setprio(3);  // as ctrl_run
     int tslot = 0;
-    BItem iA = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    BItem iA = batch_item_of(b, chunk_end, next_ticket(b.ticket, takes, sh, tslot));
     if (iA.t >= N) return;
-    BItem iB = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    BItem iB = batch_item_of(b, chunk_end, next_ticket(b.ticket, takes, sh, tslot));
     lds_barrier();  // the rate pass of A
-    BItem iC = batch_item(b, v, N, b.njobs);
-    if (iB.t < N) iC = batch_item_of(b, v, next_ticket(b.ticket, takes, sh, tslot));
+    BItem iC = batch_item(b, N, b.njobs);
+    if (iB.t < N) iC = batch_item_of(b, chunk_end, next_ticket(b.ticket, takes, sh, tslot));
     for (int sa = 0;; sa ^= 1) {
         const bool take = iC.t < N;
         unsigned long long traw = 0;
@@ -2712,12 +2691,12 @@ __device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const JobView
         uint32_t chunk_total = 0;
 #pragma unroll
         for (int k = 0; k < W; k++) chunk_total += sh.wave_total[sa][k];  // A's, from the previous step
-        const CompressArgs aA = batch_compress_args(b, v, iA.job);
-        const Resolved RA = job_bound(b, v, iA.job);
+        const CompressArgs aA = batch_compress_args(b, iA.job);
+        const Resolved RA = job_bound(b, iA.job);
         Prefix pre{0, false};
         if (RA.status == FSZ_OK) pre = lookback_wait(aA.flags, iA.c, aA.flag_epoch, chunk_total, false);
         const unsigned long long tk = take ? uniform((uint64_t)traw) : N;
-        const uint32_t jobD = tk < N ? find_job(v.chunk_end, b.njobs, tk) : b.njobs;
+        const uint32_t jobD = tk < N ? find_job(chunk_end, b.njobs, tk) : b.njobs;
         if (iB.t < N) lds_barrier();  // the data waves' rate pass of B
         if (lane == 0) {
             if (take && tk == takes - 1)
@@ -2736,18 +2715,17 @@ __device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const JobView
         if (iB.t >= N) return;
         iA = iB;
         iB = iC;
-        iC = batch_item(b, v, tk, jobD);
+        iC = batch_item(b, tk, jobD);
     }
 }
 
 // W data waves (8 tiles each per item) and a control wave, one workgroup per
-// CU.  LDSJOBS (njobs <= kPipeLdsJobs): the job records, their resolved bounds
-// and chunk ends are copied to LDS at the start; the view's address space is
-// then fixed at compile time, so job fields are read with LDS instructions.
-// 10 data waves and the job records fill the LDS (the narrower forms:
-// compress_batch_waves).  64 fields of 125 M elements: 251 us per call with the
-// range pass, where groups of 4 waves whose wave 0 walked the lookback beside
-// its data took 309 and such groups of 8 waves 266.
+// CU (compress_batch_waves).  LDSJOBS (njobs <= kPipeLdsJobs): the jobs' chunk
+// ends are copied to LDS at the start for the control wave's searches.  64
+// fields of 125 M elements: 222 us per call with the range pass, where groups of 4
+// waves whose wave 0 walked the lookback beside its data took 309 and such
+// groups of 8 waves 266.
+constexpr uint32_t kPipeLdsJobs = 512;
 template <int W, bool LDSJOBS>
 __global__ __launch_bounds__((W + 1) * 64) void batch_pipe_kernel(BatchArgs b)
 {
@@ -2759,28 +2737,18 @@ __global__ __launch_bounds__((W + 1) * 64) void batch_pipe_kernel(BatchArgs b)
     uint32_t *qb = inbuf + w * kPipeInDwords;
     uint32_t *pb = stbuf + w * kPipeOutDwords;
     if (LDSJOBS) {
-        __shared__ __attribute__((aligned(16))) BatchJob ljobs[kPipeLdsJobs];
-        __shared__ Resolved lbound[kPipeLdsJobs];
         __shared__ uint64_t lend[kPipeLdsJobs];
-        for (uint32_t k = threadIdx.x; k < b.njobs * (uint32_t)(sizeof(BatchJob) / 16); k += blockDim.x)
-            reinterpret_cast<u32x4 *>(ljobs)[k] = reinterpret_cast<const u32x4 *>(b.jobs)[k];
-        for (uint32_t k = threadIdx.x; k < b.njobs; k += blockDim.x) {
-            const BatchJob &J = b.jobs[k];
-            lbound[k] = resolve_bound(b.stats[k], J.mode, J.value, J.n);
-            lend[k] = b.chunk_end[k];
-        }
+        for (uint32_t k = threadIdx.x; k < b.njobs; k += blockDim.x) lend[k] = b.chunk_end[k];
         lds_barrier();
-        const JobView v{ljobs, lbound, lend};
         if (w < W)
-            batch_pipe_run<W>(b, v, sh, s_job, qb, pb, w);
+            batch_pipe_run<W>(b, lend, sh, s_job, qb, pb, w);
         else
-            batch_ctrl_run<W>(b, v, sh, s_job);
+            batch_ctrl_run<W>(b, lend, sh, s_job);
     } else {
-        const JobView v{b.jobs, nullptr, b.chunk_end};
         if (w < W)
-            batch_pipe_run<W>(b, v, sh, s_job, qb, pb, w);
+            batch_pipe_run<W>(b, b.chunk_end, sh, s_job, qb, pb, w);
         else
-            batch_ctrl_run<W>(b, v, sh, s_job);
+            batch_ctrl_run<W>(b, b.chunk_end, sh, s_job);
     }
 }
 
@@ -3521,7 +3489,7 @@ static hipError_t launch_batch_pipe(const BatchArgs &b, hipStream_t s)
 static hipError_t launch_batch_compress(const BatchArgs &b, hipStream_t s)
 {
     const bool lds = b.njobs <= kPipeLdsJobs;
-    if (b.waves == 10) return lds ? launch_batch_pipe<10, true>(b, s) : launch_batch_pipe<10, false>(b, s);
+    if (b.waves == 11) return lds ? launch_batch_pipe<11, true>(b, s) : launch_batch_pipe<11, false>(b, s);
     if (b.waves == 4) return lds ? launch_batch_pipe<4, true>(b, s) : launch_batch_pipe<4, false>(b, s);
     return lds ? launch_batch_pipe<8, true>(b, s) : launch_batch_pipe<8, false>(b, s);
 }

@@ -527,10 +527,10 @@ def test_batches_back_to_back(count):
 
 
 @pytest.mark.parametrize("total", [(1 << 21) - 1, 1 << 21, (1 << 23) - 1, 1 << 23])
-@pytest.mark.parametrize("njobs", [3, 97])
+@pytest.mark.parametrize("njobs", [3, 97, 513])
 def test_batch_compress_widths(total, njobs):
-    """The compressing workgroups of a batch are 4, 8 or 10 data waves wide by
-    its elements, with the job records in LDS up to 96 jobs: sizes on both
+    """The compressing workgroups of a batch are 4, 8 or 11 data waves wide by
+    its elements, with the jobs' chunk ends in LDS up to 512 jobs: sizes on both
     sides of each line, a job without a valid bound among the others."""
     base = workloads.sinusoid_field(1 << 22, 77)
     sizes = [int(s) for s in np.random.default_rng(total + njobs).multinomial(total - njobs, [1 / njobs] * njobs) + 1]
