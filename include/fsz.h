@@ -126,7 +126,7 @@ fsz_status fsz_decompress(const void *d_cmp, size_t cmp_size, float *d_out, size
  * is read back to the host, so these calls can be chained on a stream and
  * issued from a tight loop.  fsz_compress_async runs the value-range pass
  * first when d_stats is NULL, otherwise it reuses *d_stats.  Each call is
- * one kernel launch (two with the range pass). */
+ * one kernel launch (two with the range pass of a field above 16384 elements). */
 fsz_status fsz_compress_async(const float *d_in, size_t n, fsz_eb_mode mode, double value,
                               const fsz_stats *d_stats, void *d_out, size_t out_capacity,
                               fsz_result *d_result, void *stream);

@@ -200,7 +200,9 @@ fsz_status enqueue_compress(Workspace *ws, const float *d_in, uint64_t n, int mo
                             uint32_t *epoch_out, uint32_t features = kFeaturesAll)
 {
     CompressArgs a{};
-    if (!d_stats) {
+    if (!d_stats && n > 0 && n <= kSelfRangeMax && features == kFeaturesAll) {
+        a.self_range = 1;
+    } else if (!d_stats) {
         StatsArgs sa{d_in, n, ws->d_stats, ws->d_partials};
         if (!ok(launch_stats_partials(sa, &a.nparts, ws->stream))) return FSZ_ERR_DEVICE;
         a.partials = ws->d_partials;

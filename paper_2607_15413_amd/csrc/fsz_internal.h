@@ -21,6 +21,12 @@ constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
 constexpr int kTilesPerWave = 8;
 constexpr int kTilesPerChunk = kTilesPerWave * kWaves;
+constexpr uint64_t kWaveElems = (uint64_t)kTilesPerWave * kTile;
+// Fields up to this size are one chunk of a compressor of 4 or 8 data waves and
+// are compressed without a range pass, in one launch instead of two (us per
+// call, one / two: 8192 elements 7.0 / 9.6, 16384 8.7 / 9.7; with 11 waves 22528
+// elements would take 10.9 / 10.2).
+constexpr uint64_t kSelfRangeMax = 8 * kWaveElems;
 constexpr int kStatsThreads = 256;
 constexpr int kStatsMaxBlocks = 1024;
 constexpr int kRangeMaxBlocks = 256;  // workgroups (and partials) of the single-field range pass
@@ -79,6 +85,7 @@ struct CompressArgs {
     const fsz_stats *stats;        // the caller's, or
     const StatsPartial *partials;  // of the call's own range pass (null: stats)
     uint32_t nparts;
+    uint32_t self_range;  // no stats and no partials: the field is one chunk, which gives its range itself
     double value;
     int mode;
     uint32_t features;    // FSZ_FEAT_* switches (kFeaturesAll = the full method)

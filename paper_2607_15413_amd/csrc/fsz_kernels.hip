@@ -1517,7 +1517,9 @@ __device__ __forceinline__ uint64_t pipe2_step(const CompressArgs &a, const Reso
 // every workgroup from the partials of the call's own range pass (at most one
 // per thread; a launch of its own for that took 4.6 us on large fields and 2 us
 // on small ones).  The partials' loads go out first, so neither the ticket's
-// round trip nor the chunk's copy waits on them.  False: no chunk is left, or
+// round trip nor the chunk's copy waits on them.  A field of one chunk needs no
+// range pass (a.self_range): its workgroup takes the range from the copy in
+// LDS.  False: no chunk is left, or
 // the bound does not resolve (the tickets are then handed out without data
 // work, and the last chunk's taker reports).
 template <int THREADS, int W>
@@ -1534,7 +1536,21 @@ __device__ __forceinline__ bool pipe_start(const CompressArgs &a, CompressShared
     if (A >= N) return false;
     if (w < W) chunk_fetch<W>(a, A, qb, w, threadIdx.x & 63);
     fsz_stats s;
-    if (a.partials) {
+    if (a.self_range) {
+        RangeAcc acc;
+        if (w < W) {
+            const int lane = threadIdx.x & 63;
+            int v[32];
+            chunk_read(qb, lane, v);
+            const uint64_t e = (uint64_t)(w * 64 + lane) * kBlock;
+            const int cnt = e >= a.n ? 0 : (a.n - e >= kBlock ? kBlock : (int)(a.n - e));
+#pragma unroll
+            for (int i = 0; i < 32; i++)
+                if (i < cnt) acc.take(__int_as_float(v[i]));
+        }
+        const StatsPartial p = acc.template reduce<THREADS>();
+        s = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
+    } else if (a.partials) {
         const StatsPartial p = stats_block_reduce<THREADS>(part.xmin, part.xmax, part.maxabs, part.flags);
         s = fsz_stats{p.xmin, p.xmax, p.maxabs, p.flags};
     } else {
@@ -3335,8 +3351,9 @@ hipError_t launch_compress(const CompressArgs &a, hipStream_t s)
     // per call, range pass included: 2^14 9.8 / 10.5 / -, 2^18 10.8 / 12.1 / -,
     // 2^20 13.3 / 13.6 / 16.0, 2^21 17.6 / 15.3 / -, 2^22 - / 22.3 / 22.7, 6 M
     // - / 26.5 / 26.9, 2^23 - / 30.9 / 30.3, 2^25 - / 76.9 / 74.5)
+    // A field without a range pass (self_range) takes the least that holds it.
     if (a.n >= (1ull << 23)) FSZ_LAUNCH_PIPE(compress_ctrl_kernel<11>, 12, 11)
-    if (a.n <= (1ull << 20)) FSZ_LAUNCH_PIPE(compress_ctrl_kernel<4>, 5, 4)
+    if (a.n <= (a.self_range ? 4 * kWaveElems : 1ull << 20)) FSZ_LAUNCH_PIPE(compress_ctrl_kernel<4>, 5, 4)
     FSZ_LAUNCH_PIPE(compress_ctrl_kernel<8>, 9, 8)
 }
 

@@ -672,3 +672,27 @@ def test_range_pass_rounds(n):
             s = stats.tolist()
             assert s[k] == v and s[2] == abs(v)
         xd[at] = keep
+
+
+@pytest.mark.parametrize("offset", [0, 3])
+@pytest.mark.parametrize("n", [1, 31, 33, 2047, 2048, 2049, 8191, 8192, 8193, 16383, 16384, 16385])
+def test_one_chunk_takes_its_own_range(n, offset):
+    """A field of one chunk is compressed without a range pass: extremes at its
+    ends and in the last whole block count, larger values and NaN just outside
+    the field and in the slots past its end do not, NaN inside it is reported."""
+    base = np.linspace(-1.0, 1.0, n).astype(np.float32)
+    for at in sorted({0, n - 1, (n - 1) // 32 * 32, n // 2}):
+        for v in (-40.0, 55.0, np.nan):
+            x = base.copy()
+            x[at] = v
+            xd = torch.full((n + offset + 64,), 1e9, dtype=torch.float32, device=_dev())
+            xd[offset + n] = float("nan")
+            xd[offset:offset + n] = torch.from_numpy(x).to(_dev())
+            announce(f"own range n={n} offset={offset} value {v} at {at}")
+            out = torch.zeros(fsz.fsz_compressed_bound(n), dtype=torch.uint8, device=_dev())
+            want, ref = oracle.compress_status(x, oracle.REL, 1e-3)
+            st, size = fsz.fsz_compress(xd.data_ptr() + 4 * offset, n, fsz.FSZ_REL, 1e-3, out.data_ptr(),
+                                        out.numel(), _stream())
+            assert st == want
+            if st == fsz.FSZ_OK:
+                assert out[:size].cpu().numpy().tobytes() == ref
