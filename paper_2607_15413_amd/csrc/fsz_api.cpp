@@ -720,8 +720,18 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
     if (++ws->call == 0) ++ws->call;
     BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_bounds, ws->b_partials,
                                    ws->b_words);
-    b.h_done = slot.h_done;
-    slot.epoch = ws->call;
+    // A batch captured into a graph reads its table again at every replay: its
+    // buffers leave the ring for good.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!ok(hipStreamIsCapturing(ws->stream, &cap))) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) {
+        slot.h = slot.d = nullptr;
+        slot.cap = 0;
+        slot.epoch = 0;
+    } else {
+        b.h_done = slot.h_done;
+        slot.epoch = ws->call;
+    }
     return ok(launch_batch(b, L.aligned_out, shape, ws->stream)) ? FSZ_OK : FSZ_ERR_DEVICE;
 }
 

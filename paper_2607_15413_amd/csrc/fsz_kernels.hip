@@ -1665,9 +1665,10 @@ __device__ __forceinline__ void ctrl_run(const CompressArgs &a, const Resolved &
 // One workgroup per CU; what bounds it are the data waves' latencies (its VALU
 // is busy half of the time, HBM at 60%), so the more waves the better: 11 data
 // waves and the control wave are three per SIMD, which 168 VGPRs allow, and
-// fill 154 of the 160 KB of LDS.  512^3 GRF, REL 1e-2 / 1e-3 / 1e-4, with the
-// range pass: 11 waves 228 / 236 / 247 us, 10 232 / 240 / 251, 9 239 / 246 /
-// 258, 8 242 / 250 / 259.  A field too small to give every workgroup two
+// fill 154 of the 160 KB of LDS.  512^3 GRF, REL 1e-2 / 1e-3 / 1e-4, with a
+// range pass and fold of 97 us: 11 waves 228 / 236 / 247 us, 10 232 / 240 / 251,
+// 9 239 / 246 / 258, 8 242 / 250 / 259 (at REL 1e-3 the kernel moves 663 MB in
+// 140 us, 4.7 TB/s; a large copy reaches 5.0).  A field too small to give every workgroup two
 // chunks takes 8 (launch_compress).
 template <int WD>
 __global__ __launch_bounds__((WD + 1) * 64) void compress_ctrl_kernel(CompressArgs a)
@@ -3348,7 +3349,7 @@ hipError_t launch_compress(const CompressArgs &a, hipStream_t s)
         FSZ_LAUNCH_PIPE(compress_pipe2_kernel<8>, 8, 8)
     // 11 data waves and a control wave; fewer where the smaller workgroup's
     // start and the finer spread count for more (4 / 8 / 11 data waves in us
-    // per call, range pass included: 2^14 9.8 / 10.5 / -, 2^18 10.8 / 12.1 / -,
+    // per call, each with the same range pass: 2^14 9.8 / 10.5 / -, 2^18 10.8 / 12.1 / -,
     // 2^20 13.3 / 13.6 / 16.0, 2^21 17.6 / 15.3 / -, 2^22 - / 22.3 / 22.7, 6 M
     // - / 26.5 / 26.9, 2^23 - / 30.9 / 30.3, 2^25 - / 76.9 / 74.5)
     // A field without a range pass (self_range) takes the least that holds it.

@@ -546,3 +546,36 @@ def test_batch_compress_widths(total, njobs):
     b = DeviceBatch(specs, offset=njobs % 2, out_offset=1)
     b.run()
     check_against_oracle(b, refs, f"{njobs} jobs, {total} elements")
+
+
+def test_captured_batch_keeps_its_jobs():
+    """A batch captured into a graph runs its own jobs at every replay, also
+    after more eager batches on the same stream than there are staging slots."""
+    fields = small_fields(6, 33, hi=1 << 18)
+    specs = [("c", f.data, fsz.FSZ_REL, f.rel) for f in fields[:3]]
+    _, data = oracle.compress_status(fields[0].data, fsz.FSZ_REL, 1e-2)
+    specs.append(("d", data, fields[0].data.size))
+    others = [("c", f.data, fsz.FSZ_REL, f.rel) for f in fields[3:]] + specs[3:]
+    refs, other_refs = oracle_refs(specs), oracle_refs(others)
+    a, b = DeviceBatch(specs), DeviceBatch(others)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for batch in (a, b, a, b):  # the stream's workspace, staging slots included, grows before the capture
+        assert fsz.fsz_batch_async(batch.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    announce("captured batch")
+    with torch.cuda.graph(graph, stream=side):
+        assert fsz.fsz_batch_async(a.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+    for rep in range(4):
+        for _ in range(6):
+            assert fsz.fsz_batch_async(b.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+        torch.cuda.synchronize()
+        a.clear_outputs()
+        torch.cuda.synchronize()
+        announce(f"replay {rep}")
+        with torch.cuda.stream(side):
+            graph.replay()
+        torch.cuda.synchronize()
+        check_against_oracle(a, refs, f"replay {rep}")
+        check_against_oracle(b, other_refs, f"eager {rep}")
