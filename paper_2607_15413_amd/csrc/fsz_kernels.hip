@@ -1852,6 +1852,25 @@ __device__ __forceinline__ uint32_t dec_prefix_share(const DecompressArgs &a, ui
     return 4u * units + 4u * cents;
 }
 
+// Bytes of the groups before the chunk's, this wave's share of them (all
+// threads of the workgroup read at once), and whether one holds a reserved bit.
+template <int THREADS>
+__device__ __forceinline__ unsigned long long groups_share(const DecompressArgs &a, uint32_t g, bool &bad)
+{
+    unsigned long long v = 0, flags = 0;
+    for (uint32_t k = threadIdx.x; k < g; k += THREADS) {
+        const unsigned long long t = a.groups[k];
+        v += t & ~kGroupBad;
+        flags |= t;
+    }
+    bad = (flags & kGroupBad) != 0;
+    // block sizes of up to 2^29 elements cannot add up to 2^32 bytes (at most
+    // 132 per block and 4 per tile), and a 32-bit sum takes a sixth of the
+    // instructions, which every chunk's workgroup pays
+    if (a.n <= (1ull << 29)) return (uint32_t)__builtin_amdgcn_readlane(wave_incl_scan((int)(uint32_t)v), 63);
+    return wave_sum_u64(v);
+}
+
 // rb: the lane's rate byte from dec_rate_byte (loaded ahead by the caller).
 // kByGroups: the offsets pre-pass has summed the groups of chunks and placed
 // every chunk inside its group; wave 0 brings its group cursor up to the
@@ -1903,14 +1922,7 @@ __device__ __forceinline__ DecChunk dec_sizes(const DecompressArgs &a, uint64_t 
             seen = bad || pbad != 0;
         } else {
             const uint32_t g = (uint32_t)(chunk >> a.group_shift);
-            unsigned long long v = 0, flags = 0;
-            for (uint32_t k = tid; k < g; k += W * 64) {
-                const unsigned long long t = a.groups[k];
-                v += t & ~kGroupBad;
-                flags |= t;
-            }
-            psum = wave_sum_u64(v);
-            seen = (flags & kGroupBad) != 0;
+            psum = groups_share<W * 64>(a, g, seen);
             d.base = a.offsets[chunk];
             gc.next = g;
         }
@@ -3073,9 +3085,17 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
         sh.wave_total[0][w] = wave_total;
         sh.wave_total[1][w] = wave_bad ? 1u : 0u;
     }
-    if (PRESCAN && w == 0) {
-        groups_advance(a.groups, chunk >> a.group_shift, gc);
-        if (lane == 0) sh.base = gc.sum + a.offsets[chunk];
+    uint64_t base = 0;
+    if (PRESCAN) {
+        bool seen;
+        gc.next = chunk >> a.group_shift;
+        const unsigned long long share = groups_share<WV * 64>(a, (uint32_t)gc.next, seen);
+        const bool wave_seen = __ballot(seen) != 0;
+        base = a.offsets[chunk];
+        if (lane == 0) {
+            sh.wave_prefix[w] = share;
+            sh.wave_bad[w] = wave_seen ? 1u : 0u;
+        }
     }
     lds_barrier();
     uint32_t chunk_total = 0, wave_base = 0;
@@ -3086,9 +3106,12 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
         chunk_total += sh.wave_total[0][k];
         any_bad = any_bad || sh.wave_total[1][k] != 0;
     }
-    uint64_t base;
     if (PRESCAN) {
-        base = sh.base;
+#pragma unroll
+        for (int k = 0; k < WV; k++) {
+            base += sh.wave_prefix[k];
+            gc.bad = gc.bad || sh.wave_bad[k] != 0;
+        }
         if (w == 0 && chunk == a.nchunks - 1) 
             finish_decode<false>(a, gc.bad || (a.groups[gc.next] & kGroupBad) != 0, base + chunk_total, total);
     } else {
