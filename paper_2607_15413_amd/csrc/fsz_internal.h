@@ -115,6 +115,7 @@ struct DecompressArgs {
     const unsigned long long *groups;
     const unsigned long long *offsets;
     uint32_t group_shift;
+    uint32_t groups_scanned;  // nonzero: the bytes before each group instead
     uint32_t epoch, flag_epoch;
     unsigned long long *flags;
     unsigned long long *ticket;  // zero between launches (self-resetting)

@@ -450,3 +450,37 @@ def test_config_stream_beyond_4gib():
             i = k + int(bad[0])
             raise AssertionError(f"{bad.numel()} of the elements [{k}, {k + a.numel()}) differ; first at {i}: "
                                  f"decoded {float(y[i])} expected {float(expect[i])} (x = {float(x[i])})")
+
+
+@pytest.mark.parametrize("n", [(1 << 26) - 1, 1 << 26, (1 << 27) + 3 * 1024 * 256 + 5])
+def test_config_decode_offsets_at_scan_edge(n):
+    """From 2^26 elements the pre-pass's group totals become running sums before
+    the decoder reads them (above 512 x 1024 tiles a group takes several
+    rounds): decoded bits, and a reserved rate bit in the first and the last
+    block."""
+    x = workloads.sparse_field(n, 12, spacing=700)
+    old = oracle.set_threads(8)
+    try:
+        y_ref = oracle.decompress(oracle.compress(x, oracle.REL, 1e-3), n)
+    finally:
+        oracle.set_threads(old)
+    xd = torch.from_numpy(x).to("cuda:0")
+    for block, tiles in ((32, 4), (64, 16)):
+        out = torch.zeros(fsz.fsz_compressed_bound_config(n, block, tiles), dtype=torch.uint8, device="cuda:0")
+        y = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda:0")
+        res = torch.zeros(4, dtype=torch.int32, device="cuda:0")
+        stream = torch.cuda.current_stream().cuda_stream
+        assert fsz.fsz_compress_config_async(xd.data_ptr(), n, fsz.FSZ_REL, 1e-3, None, block, tiles, out.data_ptr(),
+                                             out.numel(), res.data_ptr(), stream) == fsz.FSZ_OK
+        size, status, _ = fsz.read_result(res)
+        assert status == fsz.FSZ_OK
+        for bad_block, want in ((None, fsz.FSZ_OK), (0, fsz.FSZ_ERR_CORRUPT), ((n - 1) // block, fsz.FSZ_ERR_CORRUPT)):
+            s = out[:size].clone()
+            if bad_block is not None:
+                s[32 + bad_block] |= 0x20
+            print(f"\n[case] config {block}/{tiles} n={n} bad block {bad_block}", flush=True)
+            assert fsz.fsz_decompress_config_async(s.data_ptr(), size, y.data_ptr(), n, block, tiles, res.data_ptr(),
+                                                   stream) == fsz.FSZ_OK
+            assert fsz.read_result(res)[1] == want
+            if bad_block is None:
+                assert np.array_equal(y.cpu().numpy().view(np.uint32), y_ref.view(np.uint32))
