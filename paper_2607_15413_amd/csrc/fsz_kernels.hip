@@ -773,11 +773,16 @@ struct ChunkState {
     uint32_t rbyte;  // the block's rate byte (Sec. III-A)
 };
 
+// All of it is double-buffered.  A pipeline's step may pass a single barrier (its
+// last one has no rate pass), and one wave may be a step ahead of another, so a
+// step never writes the slot that the step before it reads: step k uses slot
+// k % 2 of base and ticket, and is separated from step k + 2 by the barrier of
+// step k + 1.
 template <int W>
 struct CompressShared {
     uint32_t wave_total[2][W];
-    unsigned long long base;
-    unsigned long long ticket[2];  // alternating broadcast slots
+    unsigned long long base[2];
+    unsigned long long ticket[2];
 };
 
 // Rate pass of one chunk (8 tiles per wave), Sec. III-A steps 1-3:
@@ -1010,12 +1015,12 @@ __device__ __forceinline__ void compress_encode(const CompressArgs &a, const Res
     if (w == 0) {
         const Prefix pre = lookback_wait(a.flags, cs.chunk, a.flag_epoch, chunk_total, false);
         if (lane == 0) {
-            sh.base = pre.excl;
+            sh.base[slot] = pre.excl;
             if (cs.chunk == a.nchunks - 1) finish_stream(a, R, pre, chunk_total);
         }
     }
     lds_barrier();
-    const uint64_t base = sh.base;
+    const uint64_t base = sh.base[slot];
     const uint64_t tile0 = cs.chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
     if (a.data0 + base + chunk_total > a.capacity || tile0 >= a.ntiles) return;
 
@@ -1397,14 +1402,14 @@ __device__ __forceinline__ uint64_t pipe2_lookback(const CompressArgs &a, const 
         if (lane == 0) {
             if (took && tk == takes - 1)
                 __hip_atomic_store(a.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh.base = pre.excl;
-            sh.ticket[0] = tk;
+            sh.base[slot] = pre.excl;
+            sh.ticket[slot] = tk;
             if (cs.chunk == a.nchunks - 1) finish_stream(a, R, pre, chunk_total);
         }
     }
     lds_barrier();
-    *next = sh.ticket[0];
-    return sh.base;
+    *next = sh.ticket[slot];
+    return sh.base[slot];
 }
 
 // Residual codes and bit planes of one wave's blocks into its staging area
@@ -1629,8 +1634,8 @@ __device__ __forceinline__ uint64_t ctrl_step(const CompressArgs &a, const Resol
              : N;
     if (lane == 0) {
         if (take && tk == takes - 1) __hip_atomic_store(a.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh.base = pre.excl;
-        sh.ticket[0] = tk;
+        sh.base[sa] = pre.excl;
+        sh.ticket[sa] = tk;
         if (A == N - 1) finish_stream(a, R, pre, chunk_total);
     }
     lds_barrier();  // the offset and the ticket go out
@@ -2647,15 +2652,15 @@ template <int W>
 __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const BItem &iA,
                                                  const ChunkState &ca, int (&xa)[32], int sa, const BItem &iB,
                                                  int (&yb)[32], ChunkState &cb, const BItem &iC, uint32_t *qb,
-                                                 uint32_t *pb, CompressShared<W> &sh, const uint32_t &s_job, int w)
+                                                 uint32_t *pb, CompressShared<W> &sh, const uint32_t (&s_job)[2], int w)
 {
     const uint64_t N = b.total_chunks;
     const int lane = threadIdx.x & 63;
     const int j = lane & 7;
     if (iB.t < N) cb = batch_rates<W>(b, iB, yb, sa ^ 1, sh);
     lds_barrier();  // the control wave has A's offset and the new ticket
-    const uint64_t base = sh.base;
-    const BItem iD = batch_item(b, sh.ticket[0], s_job);
+    const uint64_t base = sh.base[sa];
+    const BItem iD = batch_item(b, sh.ticket[sa], s_job[sa]);
 
     uint32_t chunk_total = 0, wave_base = 0;
 #pragma unroll
@@ -2689,7 +2694,7 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const BItem
 
 template <int W>
 __device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const uint64_t *chunk_end, CompressShared<W> &sh,
-                                               const uint32_t &s_job, uint32_t *qb, uint32_t *pb, int w)
+                                               const uint32_t (&s_job)[2], uint32_t *qb, uint32_t *pb, int w)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t N = b.total_chunks;
@@ -2733,7 +2738,7 @@ __device__ __forceinline__ void batch_pipe_run(const BatchArgs &b, const uint64_
 // waves.
 template <int W>
 __device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const uint64_t *chunk_end, CompressShared<W> &sh,
-                                               uint32_t &s_job)
+                                               uint32_t (&s_job)[2])
 {
     const uint64_t N = b.total_chunks;
     const uint64_t takes = N + gridDim.x;
@@ -2763,9 +2768,9 @@ __device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const uint64_
         if (lane == 0) {
             if (take && tk == takes - 1)
                 __hip_atomic_store(b.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh.base = pre.excl;
-            sh.ticket[0] = tk;
-            s_job = jobD;
+            sh.base[sa] = pre.excl;
+            sh.ticket[sa] = tk;
+            s_job[sa] = jobD;
             if (iA.c == aA.nchunks - 1) {
                 if (RA.status == FSZ_OK)
                     finish_stream(aA, RA, pre, chunk_total);
@@ -2792,7 +2797,7 @@ template <int W, bool LDSJOBS>
 __global__ __launch_bounds__((W + 1) * 64) void batch_pipe_kernel(BatchArgs b)
 {
     __shared__ CompressShared<W> sh;
-    __shared__ uint32_t s_job;
+    __shared__ uint32_t s_job[2];  // the job of the ticket in the same slot of sh
     __shared__ __attribute__((aligned(16))) uint32_t inbuf[W * kPipeInDwords];
     __shared__ __attribute__((aligned(16))) uint32_t stbuf[W * kPipeOutDwords];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform

@@ -579,3 +579,24 @@ def test_captured_batch_keeps_its_jobs():
         torch.cuda.synchronize()
         check_against_oracle(a, refs, f"replay {rep}")
         check_against_oracle(b, other_refs, f"eager {rep}")
+
+
+@pytest.mark.parametrize("n", [9_000, 17_000, 50_000])
+def test_batch_last_items_without_a_wait(n):
+    """Items whose offset the control wave has at once (chunk 0 of a job, or a
+    job whose bound does not resolve) right behind later chunks of another job,
+    more items than workgroups, at each width of the compressor: every stream
+    is its own, wherever a workgroup's last item falls."""
+    base = workloads.sinusoid_field(n + 170 * 64, 41)
+    specs = []
+    for k in range(170):
+        x = base[64 * k:64 * k + n]
+        specs += [("c", x, fsz.FSZ_REL, (1e-2, 1e-3, 1e-4)[k % 3]), ("c", x[:100], fsz.FSZ_REL, 1e-3),
+                  ("c", x[:100], fsz.FSZ_ABS, 1e-12)]
+    refs = oracle_refs(specs)
+    b = DeviceBatch(specs)
+    for rep in range(3):
+        announce(f"170 jobs of {n} elements, each before a one-chunk job and one without a bound, run {rep}")
+        b.clear_outputs()
+        b.run()
+        check_against_oracle(b, refs, f"run {rep}")
