@@ -1467,6 +1467,22 @@ struct TileB32T8 {
     }
 };
 
+// The wave totals of a chunk (slot of CompressShared): the chunk's bytes, and
+// those before wave w's.  Read before the step's second barrier: a wave that is
+// ahead writes the same slot in the rate pass of the next step, which only that
+// barrier separates from this read.
+template <int W>
+__device__ __forceinline__ void chunk_totals(const CompressShared<W> &sh, int slot, int w, uint32_t &wave_base,
+                                             uint32_t &chunk_total)
+{
+    wave_base = chunk_total = 0;
+#pragma unroll
+    for (int k = 0; k < W; k++) {
+        if (k < w) wave_base += sh.wave_total[slot][k];
+        chunk_total += sh.wave_total[slot][k];
+    }
+}
+
 // One step with chunk A rate-passed (registers xa, wave totals in slot sa),
 // chunk B read (registers yb) and chunk C being copied into qb: rate pass of
 // B, lookback + staging of A, read C into xa, start the copy of the ticket
@@ -1488,15 +1504,11 @@ __device__ __forceinline__ uint64_t pipe2_step(const CompressArgs &a, const Reso
         probe = lookback_probe(a.flags, ca.chunk, a.flag_epoch);
     }
     if (B < a.nchunks) cb = M::template rates<W, FEAT>(a, R, B, yb, sa ^ 1, sh);
+    uint32_t wave_base, chunk_total;
+    chunk_totals<W>(sh, sa, w, wave_base, chunk_total);
     uint64_t D;
     const uint64_t base = pipe2_lookback<W0, W>(a, R, ca, sa, sh, probe, take, traw, takes, &D);
 
-    uint32_t chunk_total = 0, wave_base = 0;
-#pragma unroll
-    for (int k = 0; k < W; k++) {
-        if (k < w) wave_base += sh.wave_total[sa][k];
-        chunk_total += sh.wave_total[sa][k];
-    }
     const bool ok = a.data0 + base + chunk_total <= a.capacity && M::template wave_live<W>(a, ca.chunk, w);
     uint32_t *wave_out = reinterpret_cast<uint32_t *>(a.out + a.data0 + base + wave_base);
     uint32_t *ps = pb + (((uint32_t)(uintptr_t)wave_out >> 2) & 3u);  // staging at the output's 16-byte phase
@@ -2658,16 +2670,12 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const BItem
     const int lane = threadIdx.x & 63;
     const int j = lane & 7;
     if (iB.t < N) cb = batch_rates<W>(b, iB, yb, sa ^ 1, sh);
+    uint32_t wave_base, chunk_total;
+    chunk_totals<W>(sh, sa, w, wave_base, chunk_total);
     lds_barrier();  // the control wave has A's offset and the new ticket
     const uint64_t base = sh.base[sa];
     const BItem iD = batch_item(b, sh.ticket[sa], s_job[sa]);
 
-    uint32_t chunk_total = 0, wave_base = 0;
-#pragma unroll
-    for (int k = 0; k < W; k++) {
-        if (k < w) wave_base += sh.wave_total[sa][k];
-        chunk_total += sh.wave_total[sa][k];
-    }
     const CompressArgs aA = batch_compress_args(b, iA.job);
     const bool liveA = job_bound(b, iA.job).status == FSZ_OK;
     const uint64_t tile0 = iA.c * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;

@@ -217,3 +217,36 @@ def test_base_features_stream_beyond_4gib():
             i = k + int(bad[0])
             raise AssertionError(f"{bad.numel()} of the elements [{k}, {k + a.numel()}) differ; first at {i}: "
                                  f"decoded {float(y[i])} expected {float(expect[i])} (x = {float(x[i])})")
+
+
+@pytest.mark.parametrize("path", ["default", "features", "config"])
+def test_many_steps_with_uneven_waves(path):
+    """Several chunks per workgroup whose waves write very different numbers of
+    bytes: every wave's place follows from its own chunk's totals."""
+    n = 18_000_007
+    rng = np.random.default_rng(17)
+    x = rng.standard_normal(n, dtype=np.float32)
+    x *= np.repeat(np.float32(10) ** rng.integers(-6, 2, n // 2048 + 1).astype(np.float32), 2048)[:n]
+    xd = torch.from_numpy(x).to(_dev())
+    res = torch.zeros(2, dtype=torch.int64, device=_dev())
+    stream = torch.cuda.current_stream(_dev()).cuda_stream
+    features, config = (5, (32, 8)) if path == "features" else (7, (64, 8) if path == "config" else (32, 8))
+    old = oracle.set_threads(8)
+    try:
+        exp = oracle.compress(x, oracle.REL, 1e-4, features=features, config=config)
+    finally:
+        oracle.set_threads(old)
+    out = torch.zeros(len(exp) + 64, dtype=torch.uint8, device=_dev())
+    for rep in range(3):
+        announce(f"{path}, n={n}, run {rep}")
+        out.zero_()
+        head = xd.data_ptr(), n, oracle.REL, 1e-4, None
+        tail = out.data_ptr(), out.numel(), res.data_ptr(), stream
+        st = (fsz.fsz_compress_features_async(*head, features, *tail) if path == "features" else
+              fsz.fsz_compress_config_async(*head, *config, *tail) if path == "config" else
+              fsz.fsz_compress_async(*head, *tail))
+        assert st == fsz.FSZ_OK
+        torch.cuda.synchronize()
+        assert int(res[1]) & 0xFFFFFFFF == fsz.FSZ_OK
+        got = out[:int(res[0])].cpu().numpy().tobytes()
+        assert got == exp, first_diff(got, exp)
