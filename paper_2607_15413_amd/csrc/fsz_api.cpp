@@ -234,9 +234,9 @@ template <typename T>
 bool grow(T **p, uint64_t *cap, uint64_t want, hipStream_t s);
 
 // Room for the offsets pre-pass of a decode, if it has one.
-bool ensure_words(Workspace *ws, const DecompressArgs &a, bool prezero)
+bool ensure_words(Workspace *ws, const DecompressArgs &a)
 {
-    if (!prezero && decode_by_prefix(a.tile_begin, a.tile_end)) return true;
+    if (decode_by_prefix(a.tile_begin, a.tile_end)) return true;
     return grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + ceil_div(a.tile_end, (uint64_t)kTilesPerChunk) + 1,
                 ws->stream);
 }
@@ -296,7 +296,7 @@ fsz_status enqueue_decompress(Workspace *ws, const void *d_cmp, uint64_t cmp_siz
     a.tile_end = a.ntiles;
     a.elem_begin = 0;
     a.elem_end = n;
-    if (!ensure_words(ws, a, prezero)) return FSZ_ERR_DEVICE;
+    if (!ensure_words(ws, a)) return FSZ_ERR_DEVICE;
     if (!next_epoch(ws, &a.epoch, &a.flag_epoch)) return FSZ_ERR_DEVICE;
     a.final = d_final;
     const hipError_t e = prezero ? launch_decompress_prezero(a, ws->d_offs, aligned(d_out, 16), ws->stream)
@@ -403,7 +403,7 @@ fsz_status enqueue_decompress_range(Workspace *ws, const void *d_cmp, uint64_t c
     a.tile_end = end > begin ? ceil_div(end, kTile) : a.tile_begin;
     a.elem_begin = begin;
     a.elem_end = end;
-    if (!ensure_words(ws, a, false)) return FSZ_ERR_DEVICE;
+    if (!ensure_words(ws, a)) return FSZ_ERR_DEVICE;
     if (!next_epoch(ws, &a.epoch, &a.flag_epoch)) return FSZ_ERR_DEVICE;
     a.final = d_final;
     // 16-byte stores need the field's element 0 (d_out - begin) 16-byte aligned

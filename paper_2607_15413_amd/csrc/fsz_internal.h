@@ -220,8 +220,9 @@ hipError_t launch_compress_naive(const CompressArgs &a, const NaiveTables &t, bo
 // tile_end.
 hipError_t launch_decompress(const DecompressArgs &a, unsigned long long *words, bool out_aligned16, bool range,
                              hipStream_t s);
-// Pre-zeroed decompression (Sec. III-A): a fill of out[0, n) with +0.0, the
-// offsets pre-pass, then the decoder that skips waves whose tiles are all zero.
+// Pre-zeroed decompression (Sec. III-A): a fill of out[0, n) with +0.0, then the
+// same launches with a decoder that skips waves whose tiles are all zero
+// (persistent behind the pre-pass at every size).
 hipError_t launch_decompress_prezero(const DecompressArgs &a, unsigned long long *words, bool out_aligned16,
                                      hipStream_t s);
 // Tile configurations (Sec. VI-C), block in {32, 64}, tile_blocks in {4, 8, 16}:

@@ -2330,7 +2330,7 @@ __global__ __launch_bounds__(kGroupThreads) void dec_groups_kernel(DecompressArg
 // 2^16 6.6 -> 4.8, a range of 300 elements at 10^6 13.8 -> 6.5).
 // The size pass needs nothing of the stream header but the room for the rate
 // bytes, so its loads go out before the header's have come back.
-template <bool ALIGNED, int W, bool RANGE, int OFF>
+template <bool ALIGNED, int W, bool RANGE, int OFF, bool PREZERO = false>
 __device__ __forceinline__ void decompress_one(const DecompressArgs &a, uint64_t chunk, DecompressShared<W> &sh,
                                                uint32_t *st)
 {
@@ -2346,17 +2346,17 @@ __device__ __forceinline__ void decompress_one(const DecompressArgs &a, uint64_t
         if (threadIdx.x == 0 && chunk == a.chunk_begin) write_final(a.final, 0, hst, a.epoch);
         return;
     }
-    const DecPlace pl = dec_place<W, RANGE, false, OFF>(a, dc, 0, total, sh, gc);
+    const DecPlace pl = dec_place<W, RANGE, PREZERO, OFF>(a, dc, 0, total, sh, gc);
     if (pl.live) dec_decode<ALIGNED, W, RANGE>(a, dc, pl, E, indep, st);
 }
 
-template <bool ALIGNED, int W, bool RANGE, int OFF>
+template <bool ALIGNED, int W, bool RANGE, int OFF, bool PREZERO>
 __global__ __launch_bounds__(W * 64) void decompress_direct_kernel(DecompressArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint32_t stage[W * kStageWaveDwords];
     __shared__ DecompressShared<W> sh;
-    decompress_one<ALIGNED, W, RANGE, OFF>(a, a.chunk_begin + blockIdx.x, sh,
-                                           stage + (threadIdx.x >> 6) * kStageWaveDwords);
+    decompress_one<ALIGNED, W, RANGE, OFF, PREZERO>(a, a.chunk_begin + blockIdx.x, sh,
+                                                    stage + (threadIdx.x >> 6) * kStageWaveDwords);
 }
 
 // ------------------------------------------------------------------ batched form
@@ -3334,46 +3334,45 @@ static void chunk_span(DecompressArgs &a, uint64_t tpc, bool from_begin)
     a.nchunks = t1 > t0 ? ceil_div(t1, tpc) : a.chunk_begin + 1;
 }
 
-template <bool ALIGNED, int W, bool RANGE, int OFF>
+template <bool ALIGNED, int W, bool RANGE, int OFF, bool PREZERO = false>
 static hipError_t launch_decompress_direct(const DecompressArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL((decompress_direct_kernel<ALIGNED, W, RANGE, OFF>), dim3((unsigned)(a.nchunks - a.chunk_begin)),
-                       dim3(W * 64), 0, s, a);
+    hipLaunchKernelGGL((decompress_direct_kernel<ALIGNED, W, RANGE, OFF, PREZERO>),
+                       dim3((unsigned)(a.nchunks - a.chunk_begin)), dim3(W * 64), 0, s, a);
     return hipGetLastError();
 }
 
-template <bool ALIGNED, bool RANGE>
-static hipError_t launch_decompress_t(const DecompressArgs &a, unsigned long long *words, bool prezero, hipStream_t s)
+template <bool ALIGNED, bool RANGE, bool PREZERO = false>
+static hipError_t launch_decompress_t(const DecompressArgs &a, unsigned long long *words, hipStream_t s)
 {
     DecompressArgs p = a;
     const uint64_t tiles = a.tile_end - a.tile_begin;
-    if (!prezero && decode_by_prefix(a.tile_begin, a.tile_end)) {
+    if (decode_by_prefix(a.tile_begin, a.tile_end)) {
         // chunks of 4 waves spread small decodes wider; from 2^21 elements
         // on 8 waves halve the reads of the rate bytes (2^21 GRF 7.4 against
         // 7.9 us, 2^22 9.9 against 9.0)
         const bool wide = tiles * kTile > (1ull << 21);
         chunk_span(p, (uint64_t)kTilesPerWave * (wide ? 8 : 4), true);
-        return wide ? launch_decompress_direct<ALIGNED, 8, RANGE, kByPrefix>(p, s)
-                    : launch_decompress_direct<ALIGNED, 4, RANGE, kByPrefix>(p, s);
+        return wide ? launch_decompress_direct<ALIGNED, 8, RANGE, kByPrefix, PREZERO>(p, s)
+                    : launch_decompress_direct<ALIGNED, 4, RANGE, kByPrefix, PREZERO>(p, s);
     }
-    const bool direct = !prezero && tiles * kTile < tuning().dec_direct_below;
+    const bool direct = !PREZERO && tiles * kTile < tuning().dec_direct_below;
     const hipError_t e = direct ? launch_dec_groups<kTilesPerWave * 4>(p, words, false, s)
                                 : launch_dec_groups<kTilesPerWave * 8>(p, words, false, s);
     if (e != hipSuccess) return e;
     chunk_span(p, (uint64_t)kTilesPerWave * (direct ? 4 : 8), false);
     if (direct) return launch_decompress_direct<ALIGNED, 4, RANGE, kByGroupsOnce>(p, s);
-    if (!RANGE && prezero) return launch_decompress_persistent<ALIGNED, false, true>(p, s);
-    return launch_decompress_persistent<ALIGNED, RANGE, false>(p, s);
+    return launch_decompress_persistent<ALIGNED, RANGE, PREZERO>(p, s);
 }
 
 hipError_t launch_decompress(const DecompressArgs &a, unsigned long long *words, bool out_aligned16, bool range,
                              hipStream_t s)
 {
     if (range)
-        return out_aligned16 ? launch_decompress_t<true, true>(a, words, false, s)
-                             : launch_decompress_t<false, true>(a, words, false, s);
-    return out_aligned16 ? launch_decompress_t<true, false>(a, words, false, s)
-                         : launch_decompress_t<false, false>(a, words, false, s);
+        return out_aligned16 ? launch_decompress_t<true, true>(a, words, s)
+                             : launch_decompress_t<false, true>(a, words, s);
+    return out_aligned16 ? launch_decompress_t<true, false>(a, words, s)
+                         : launch_decompress_t<false, false>(a, words, s);
 }
 
 // +0.0 into out[0, n): 16-byte nontemporal stores from the first 16-byte
@@ -3402,8 +3401,8 @@ hipError_t launch_decompress_prezero(const DecompressArgs &a, unsigned long long
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return out_aligned16 ? launch_decompress_t<true, false>(a, words, true, s)
-                         : launch_decompress_t<false, false>(a, words, true, s);
+    return out_aligned16 ? launch_decompress_t<true, false, true>(a, words, s)
+                         : launch_decompress_t<false, false, true>(a, words, s);
 }
 
 template <typename K>

@@ -5,6 +5,8 @@ partly zero and ordinary fields, ragged sizes and unaligned outputs (the
 output is pre-filled with NaN so that an element the fill or the decoder
 misses shows).  Every case prints its name before touching the GPU.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -75,3 +77,34 @@ def test_prezero_decode_empty_and_corrupt():
     good = oracle.compress(x, oracle.REL, 1e-3)
     st, _ = gpu_decode(fsz.fsz_decompress_prezero_async, good, x.size + 1)
     assert st == fsz.FSZ_ERR_SIZE_MISMATCH
+
+
+def _captured_kernels(call):
+    """Nodes that `call(stream)` records when captured on a side stream."""
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    side = torch.cuda.Stream()
+    s, graph, count = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    assert call(side.cuda_stream) == fsz.FSZ_OK  # the stream's workspace
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(s, 1) == 0
+    st = call(side.cuda_stream)
+    assert hip.hipStreamEndCapture(s, ctypes.byref(graph)) == 0 and st == fsz.FSZ_OK
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("n", [1, 5001, 1 << 20, 1 << 22])
+def test_small_decodes_need_no_offsets_launch(n):
+    """Small decodes find their offsets themselves: one kernel, and with the
+    output cleared first two."""
+    x = workloads.sparse_field(n, 9, spacing=max(2, min(n, 2000)))
+    s = oracle.compress(x, oracle.REL, 1e-3)
+    buf = torch.from_numpy(np.frombuffer(s, dtype=np.uint8).copy()).to(_dev())
+    out = torch.zeros(n, dtype=torch.float32, device=_dev())
+    res = torch.zeros(2, dtype=torch.int64, device=_dev())
+    announce(f"launches of a decode, n = {n}")
+    args = buf.data_ptr(), len(s), out.data_ptr(), n, res.data_ptr()
+    assert _captured_kernels(lambda st: fsz.fsz_decompress_async(*args, st)) == 1
+    assert _captured_kernels(lambda st: fsz.fsz_decompress_prezero_async(*args, st)) == 2
