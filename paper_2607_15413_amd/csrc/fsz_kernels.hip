@@ -601,13 +601,17 @@ __device__ __forceinline__ uint32_t align_head(const void *x)
 // whose loads in flight lay a grid apart took 92 us, 5.8 TB/s) and leaves 256
 // partials to fold.  The last, partial round goes to all threads one vector at
 // a time, the elements before the first and after the last 16-byte boundary
-// singly.  KEEP: loads without the nontemporal hint, which leave the field in
-// the memory-side cache for the compressor's read.
+// singly.  The loads are nontemporal at every size.  Without the hint a field of
+// 2^23 to 2^25 elements stays in the memory-side cache for the compressor's
+// read, but the lines it displaces cost as much again once a program compresses
+// field after field: rotating over 805 MB of fields, us per compression with /
+// without the hint, GRF 2^24 at REL 1e-2 43.3 / 43.3, at 1e-4 46.1 / 48.5, 25 M
+// 54.5 / 53.5 and 58.0 / 61.9, 2^25 68.4 / 66.4 and 71.4 / 76.7, piecewise
+// quadratic 25 M at 1e-4 56.0 / 55.7; one field again and again 54.1 / 55.0.
 constexpr int kRangeUnroll = 4;
-template <int THREADS, bool KEEP>
+template <int THREADS>
 __global__ __launch_bounds__(THREADS) void stats_partial_kernel(StatsArgs a)
 {
-    auto load = [](const f4 *p) { return KEEP ? *p : __builtin_nontemporal_load(p); };
     RangeAcc acc;
     const uint64_t tid = (uint64_t)blockIdx.x * THREADS + threadIdx.x;
     const uint64_t nthreads = (uint64_t)gridDim.x * THREADS;
@@ -619,7 +623,7 @@ __global__ __launch_bounds__(THREADS) void stats_partial_kernel(StatsArgs a)
          i += kRangeUnroll * nthreads) {
         f4 f[kRangeUnroll];
 #pragma unroll
-        for (int u = 0; u < kRangeUnroll; u++) f[u] = load(x4 + i + u * THREADS);
+        for (int u = 0; u < kRangeUnroll; u++) f[u] = __builtin_nontemporal_load(x4 + i + u * THREADS);
 #pragma unroll
         for (int u = 0; u < kRangeUnroll; u++) acc.take4(f[u]);
     }
@@ -628,7 +632,7 @@ __global__ __launch_bounds__(THREADS) void stats_partial_kernel(StatsArgs a)
 #pragma unroll
         for (int u = 0; u < kRangeUnroll; u++) {
             const uint64_t i = whole + tid + u * nthreads;
-            if (i < nvec) f[u] = load(x4 + i);
+            if (i < nvec) f[u] = __builtin_nontemporal_load(x4 + i);
         }
 #pragma unroll
         for (int u = 0; u < kRangeUnroll; u++)
@@ -2528,19 +2532,10 @@ hipError_t launch_stats_partials(const StatsArgs &a, uint32_t *nparts, hipStream
     const bool small = a.n <= (1ull << 21);
     const uint64_t want = ceil_div(a.n, (small ? 256ull : 512ull) * 16);
     *nparts = (uint32_t)(want < 1 ? 1 : (want > kRangeMaxBlocks ? kRangeMaxBlocks : want));
-    // A field that fits half of the memory-side cache (256 MB) beside what the
-    // compressor writes is kept there: GRF at REL 1e-2 / 1e-4, us per compression
-    // kept / not: 2^23 26.6 / 26.7, 28.7 / 29.4; 2^24 43.3 / 44.1, 46.3 / 47.0; 2^25
-    // 66.7 / 68.4, 72.7 / 72.6; but 2^25.25 75.1 / 77.5, 89.1 / 82.5 and 2^26
-    // 116.3 / 116.2, 130.1 / 124.6, and below 2^23 it gains nothing (2^22
-    // 20.3 / 19.9, 21.6 / 21.0).
-    const bool keep = a.n >= (1ull << 23) && a.n <= (1ull << 25);
     if (small)
-        hipLaunchKernelGGL((stats_partial_kernel<256, false>), dim3(*nparts), dim3(256), 0, s, a);
-    else if (keep)
-        hipLaunchKernelGGL((stats_partial_kernel<512, true>), dim3(*nparts), dim3(512), 0, s, a);
+        hipLaunchKernelGGL(stats_partial_kernel<256>, dim3(*nparts), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL((stats_partial_kernel<512, false>), dim3(*nparts), dim3(512), 0, s, a);
+        hipLaunchKernelGGL(stats_partial_kernel<512>, dim3(*nparts), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 
