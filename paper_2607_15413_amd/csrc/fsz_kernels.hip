@@ -21,6 +21,7 @@
 #include <float.h>
 
 #include <mutex>
+#include <utility>
 
 namespace fsz {
 namespace {
@@ -113,6 +114,13 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, 63);
     const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), 63);
     return (unsigned long long)hi << 32 | lo;
+}
+
+// a value that every lane holds, in scalar registers
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v)
+{
+    return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
 }
 
 // Workgroup barrier that orders LDS only: the waves of a workgroup exchange
@@ -1060,7 +1068,7 @@ __device__ __forceinline__ uint64_t next_ticket(unsigned long long *ticket, uint
 {
     if (threadIdx.x == 0) sh.ticket[slot] = take_ticket(ticket, takes);
     lds_barrier();
-    const uint64_t t = sh.ticket[slot];
+    const uint64_t t = uniform((uint64_t)sh.ticket[slot]);
     slot ^= 1;
     return t;
 }
@@ -1288,34 +1296,55 @@ constexpr int kPipeInDwords = 2048;
 constexpr int kPipeOutDwords = 64 * 24 + 4;
 typedef __attribute__((address_space(3))) void lds_void;
 
+template <int SIZE, int STEP, int... K>
+__device__ __forceinline__ void lds_copies(const float *src, uint32_t *dst, std::integer_sequence<int, K...>)
+{
+    static_assert(SIZE == 16 || SIZE == 4, "the builtin takes a literal size");
+    if constexpr (SIZE == 16)
+        (__builtin_amdgcn_global_load_lds((const void *)src, (lds_void *)dst, 16, K * STEP, kCachePolicyNT), ...);
+    else
+        (__builtin_amdgcn_global_load_lds((const void *)src, (lds_void *)dst, 4, K * STEP, kCachePolicyNT), ...);
+}
+
+// N copies of SIZE bytes per lane, each STEP bytes further in both memories: the
+// instruction's offset, which counts for both, does the stepping.  (An address
+// for every copy of the 4-byte form took registers that compress_ctrl_kernel<11>
+// and the configuration compressors did not have: they spilled up to 12, and
+// the reloads waited for everything in flight.  2^27 elements at offset 1, us per
+// call before / after: 64/8 280 / 252, 64/16 294 / 256, default 234 / 233.)
+template <int SIZE, int STEP, int N>
+__device__ __forceinline__ void copy_to_lds(const float *src, uint32_t *dst)
+{
+    if constexpr (N > 0) {
+        constexpr int kPerBase = 4096 / STEP < N ? 4096 / STEP : N;  // a 13-bit signed offset
+        lds_copies<SIZE, STEP>(src, dst, std::make_integer_sequence<int, kPerBase>{});
+        copy_to_lds<SIZE, STEP, N - kPerBase>(src + kPerBase * STEP / 4, dst + kPerBase * STEP / 4);
+    }
+}
+
 // Input of the wave's 8 tiles (element e0 onward, all in bounds) -> LDS.
 // The copies carry the nontemporal hint: the input is read once, and without
 // the hint it displaces cached data, among it the stream just written.
 __device__ __forceinline__ void chunk_copy_async(const float *__restrict__ x, uint64_t e0, uint32_t *wbuf, int lane)
 {
-#pragma unroll
-    for (int k = 0; k < 8; k++) {
-        const int b = 8 * k + (lane >> 3);
-        const int m = ((lane & 7) - b) & 7;
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(x + e0 + 32 * b + 4 * m),
-                                         (lds_void *)(wbuf + 256 * k), 16, 0, kCachePolicyNT);
-    }
+    const int m = ((lane & 7) - (lane >> 3)) & 7;
+    copy_to_lds<16, 1024, 8>(x + e0 + 32 * (lane >> 3) + 4 * m, wbuf);
 }
 
-// Same image from an input off the 16-byte grid, 4 bytes per lane: instruction
+// Same image from an input off the 16-byte grid, 4 bytes per lane: copy
 // k brings blocks 2k and 2k + 1 (a lane's dword d = 64 k + lane is element d & 3
 // of the piece at slot d >> 2).  Four times the instructions, and lines that
-// straddle are fetched by two of them, but the pipeline hides it: 2^27 elements
-// at offset 1 265 us per call with the range pass, 248 aligned (the kernel with
-// one chunk per workgroup that such inputs had before: 673); 3.1 M 21.4 (32.1).
+// straddle are fetched by two of them, but the pipeline hides most of it: 2^27
+// elements at offset 1 233 us per call with the range pass, 216 aligned (a kernel
+// with one chunk per workgroup: 673); 3.1 M 17.1 and 16.7 (32.1).
 __device__ __forceinline__ void chunk_copy_async4(const float *__restrict__ x, uint64_t e0, uint32_t *wbuf, int lane)
 {
     const int half = lane >> 5;
+    const float *src = x + e0 + 32 * half + (lane & 3);
 #pragma unroll
-    for (int k = 0; k < 32; k++) {
+    for (int k = 0; k < 4; k++) {  // the rotation is the same every four copies
         const int m = (((lane >> 2) & 7) - 2 * k - half) & 7;
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(x + e0 + 64 * k + 32 * half + 4 * m + (lane & 3)),
-                                         (lds_void *)(wbuf + 64 * k), 4, 0, kCachePolicyNT);
+        copy_to_lds<4, 1024, 8>(src + 64 * k + 4 * m, wbuf + 64 * k);
     }
 }
 
@@ -1412,7 +1441,7 @@ __device__ __forceinline__ uint64_t pipe2_lookback(const CompressArgs &a, const 
         }
     }
     lds_barrier();
-    *next = sh.ticket[slot];
+    *next = uniform((uint64_t)sh.ticket[slot]);
     return sh.base[slot];
 }
 
@@ -2572,12 +2601,6 @@ struct BItem {
 // the room of an eleventh data wave.)
 typedef __attribute__((address_space(4))) BatchJob c_job;
 typedef __attribute__((address_space(4))) Resolved c_resolved;
-
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ uint64_t uniform(uint64_t v)
-{
-    return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
-}
 
 __device__ __forceinline__ Resolved job_bound(const BatchArgs &b, uint32_t job)
 {

@@ -2,6 +2,7 @@
 import ctypes
 import os
 import re
+import struct
 import subprocess
 import sys
 
@@ -137,3 +138,49 @@ def test_bench_refuses_more_than_one_gpu():
         assert r.returncode == 2, (n, r.returncode, r.stderr)
         assert "exactly one GPU" in r.stderr and f"--gpus {n}" in r.stderr
         assert r.stdout == ""
+
+
+def _kernel_resources(path):
+    """The compiler's own record of every kernel in the library's code object: {name: metadata}."""
+    msgpack = pytest.importorskip("msgpack")
+    with open(path, "rb") as f:
+        lib = f.read()
+    kernels = {}
+    at = lib.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while at >= 0:
+        p = at + 32
+        for _ in range(struct.unpack_from("<Q", lib, at + 24)[0]):
+            off, size, name_len = struct.unpack_from("<QQQ", lib, p)
+            target = lib[p + 24:p + 24 + name_len]
+            p += 24 + name_len
+            if b"gfx" not in target:
+                continue
+            elf = lib[at + off:at + off + size]
+            phoff, = struct.unpack_from("<Q", elf, 32)
+            phsize, phcount = struct.unpack_from("<HH", elf, 54)
+            for k in range(phcount):
+                kind, _, q, _, _, length = struct.unpack_from("<IIQQQQ", elf, phoff + k * phsize)
+                end = q + length
+                while kind == 4 and q < end:  # PT_NOTE
+                    nlen, dlen, note = struct.unpack_from("<III", elf, q)
+                    desc = q + 12 + (nlen + 3) // 4 * 4
+                    if note == 32:  # NT_AMDGPU_METADATA
+                        for rec in msgpack.unpackb(elf[desc:desc + dlen])["amdhsa.kernels"]:
+                            kernels[rec[".name"]] = rec
+                    q = desc + (dlen + 3) // 4 * 4
+        at = lib.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 24)
+    return kernels
+
+
+def test_kernels_keep_their_registers():
+    """No kernel spills vector registers: in the pipelined compressors a reload
+    from scratch waits for the prefetch and the stores in flight.  The
+    compressors of the default format and of the tile configurations spill no
+    scalar registers either."""
+    kernels = _kernel_resources(fsz.LIB_PATH)
+    pipelined = [k for k in kernels if "compress_ctrl_kernel" in k or "compress_cfg_pipe_kernel" in k]
+    assert len(pipelined) == 9 and any("batch_pipe_kernel" in k for k in kernels)
+    spilled = {k: r[".vgpr_spill_count"] for k, r in kernels.items()
+               if r[".vgpr_spill_count"] or r[".private_segment_fixed_size"]}
+    assert not spilled, spilled
+    assert not [k for k in pipelined if kernels[k][".sgpr_spill_count"]]
