@@ -105,7 +105,11 @@ fsz_status fsz_compress(const float *d_in, size_t n, fsz_eb_mode mode, double va
 
 /* As fsz_compress but with field statistics already computed by
  * fsz_field_stats on the same stream (one HBM read of d_in instead of
- * two; lets several bounds reuse one range pass). */
+ * two; lets several bounds reuse one range pass).  Here and in every call
+ * that takes d_stats, *d_stats must cover d_in (min, max and max|x| at least
+ * as wide, the flag set if a value is not finite): narrower statistics still
+ * give FSZ_OK and write only d_out[0..out_capacity), but the values may then
+ * lie outside the bound. */
 fsz_status fsz_compress_ex(const float *d_in, size_t n, fsz_eb_mode mode, double value,
                            const fsz_stats *d_stats, void *d_out, size_t out_capacity,
                            size_t *out_size, void *stream);

@@ -1287,17 +1287,23 @@ __global__ __launch_bounds__(kThreads) void naive_encode_kernel(CompressArgs a, 
 // conflicts.
 
 constexpr int kCachePolicyNT = 2;  // cache-policy operand of the LDS copies: nontemporal
-// A wave's LDS: 8 tiles of input, and its output at a 16-byte phase.  The output
-// is at most 64 x 96 bytes: |q| <= 2^21 + 1 bounds every LZ1 residual by
-// 2^22 + 2, i.e. 23 bits and 4 + 4 x 23 bytes a block, LZ1 without centring may
-// always be selected, and a tile takes its cheapest variant (a 64-element
-// block: twice that for two lanes).
+// A wave's LDS: 8 tiles of input, and its output at a 16-byte phase.  With
+// statistics that cover the field the output is at most 64 x 96 bytes:
+// |q| <= 2^21 + 1 bounds every LZ1 residual by 2^22 + 2, i.e. 23 bits and
+// 4 + 4 x 23 bytes a block, LZ1 without centring may always be selected, and a
+// tile takes its cheapest variant (a 64-element block: twice that for two
+// lanes).  A caller's statistics may understate max |x|: a wave whose output is
+// larger stores it without staging (store_oversize).  Room for 31 planes would
+// leave 8 data waves per workgroup instead of 11.
 constexpr int kPipeInDwords = 2048;
-constexpr int kPipeOutDwords = 64 * 24 + 4;
+constexpr uint32_t kPipeOutBytes = 64 * 96;
+constexpr int kPipeOutDwords = kPipeOutBytes / 4 + 4;
 typedef __attribute__((address_space(3))) void lds_void;
 
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+
 template <int SIZE, int STEP, int... K>
-__device__ __forceinline__ void lds_copies(const float *src, uint32_t *dst, std::integer_sequence<int, K...>)
+__device__ __forceinline__ void lds_copies(const float *src, lds_u32 *dst, std::integer_sequence<int, K...>)
 {
     static_assert(SIZE == 16 || SIZE == 4, "the builtin takes a literal size");
     if constexpr (SIZE == 16)
@@ -1313,7 +1319,7 @@ __device__ __forceinline__ void lds_copies(const float *src, uint32_t *dst, std:
 // the reloads waited for everything in flight.  2^27 elements at offset 1, us per
 // call before / after: 64/8 280 / 252, 64/16 294 / 256, default 234 / 233.)
 template <int SIZE, int STEP, int N>
-__device__ __forceinline__ void copy_to_lds(const float *src, uint32_t *dst)
+__device__ __forceinline__ void copy_to_lds(const float *src, lds_u32 *dst)
 {
     if constexpr (N > 0) {
         constexpr int kPerBase = 4096 / STEP < N ? 4096 / STEP : N;  // a 13-bit signed offset
@@ -1328,7 +1334,7 @@ __device__ __forceinline__ void copy_to_lds(const float *src, uint32_t *dst)
 __device__ __forceinline__ void chunk_copy_async(const float *__restrict__ x, uint64_t e0, uint32_t *wbuf, int lane)
 {
     const int m = ((lane & 7) - (lane >> 3)) & 7;
-    copy_to_lds<16, 1024, 8>(x + e0 + 32 * (lane >> 3) + 4 * m, wbuf);
+    copy_to_lds<16, 1024, 8>(x + e0 + 32 * (lane >> 3) + 4 * m, (lds_u32 *)wbuf);
 }
 
 // Same image from an input off the 16-byte grid, 4 bytes per lane: copy
@@ -1339,12 +1345,15 @@ __device__ __forceinline__ void chunk_copy_async(const float *__restrict__ x, ui
 // with one chunk per workgroup: 673); 3.1 M 17.1 and 16.7 (32.1).
 __device__ __forceinline__ void chunk_copy_async4(const float *__restrict__ x, uint64_t e0, uint32_t *wbuf, int lane)
 {
+    lds_u32 *dst = (lds_u32 *)wbuf;
+    // the four rotations and their LDS addresses stay out of the pipeline loop's registers
+    asm volatile("; %0 %1" : "+v"(lane), "+s"(dst));
     const int half = lane >> 5;
     const float *src = x + e0 + 32 * half + (lane & 3);
 #pragma unroll
     for (int k = 0; k < 4; k++) {  // the rotation is the same every four copies
         const int m = (((lane >> 2) & 7) - 2 * k - half) & 7;
-        copy_to_lds<4, 1024, 8>(src + 64 * k + 4 * m, wbuf + 64 * k);
+        copy_to_lds<4, 1024, 8>(src + 64 * k + 4 * m, dst + 64 * k);
     }
 }
 
@@ -1442,7 +1451,7 @@ __device__ __forceinline__ uint64_t pipe2_lookback(const CompressArgs &a, const 
     }
     lds_barrier();
     *next = uniform((uint64_t)sh.ticket[slot]);
-    return sh.base[slot];
+    return uniform((uint64_t)sh.base[slot]);
 }
 
 // Residual codes and bit planes of one wave's blocks into its staging area
@@ -1469,12 +1478,56 @@ __device__ __forceinline__ void pipe2_stage(const ChunkState &cs, int (&B)[32], 
     }
 }
 
+// The words of a wave whose output does not fit its staging area, straight to
+// global memory (at wave_out), each lane's block from the input (seg0: the
+// wave's first 32-element segment; LANES per tile, STRIDE dwords from one word of
+// a block to the next).  Only wrong statistics bring such waves about, so this is
+// written for few registers and little code beside the staging it stands in for:
+// staging in two halves cost 512^3 at REL 1e-3 10% (218 -> 240 us), unrolled
+// stores to global memory spilled 26 registers.
+template <int LANES, int STRIDE, bool FEAT>
+__device__ __forceinline__ void store_oversize(const CompressArgs &a, const Resolved &R, const ChunkState &cs,
+                                               uint64_t seg0, uint32_t *wave_out)
+{
+    int lane = __lane_id();
+    asm volatile("; %0" : "+v"(lane));  // keeps what follows from it out of the registers of the pipeline's loop
+    // slots past the end of the field (the second half of a 64-element block may
+    // lie there as a whole) read a valid one; their bits are cleared
+    const bool live = cs.vm != 0;
+    const g_f32 *x = (const g_f32 *)a.x + (live ? (seg0 + lane) * kBlock : 0);
+    g_u32 *out = (g_u32 *)wave_out;
+    const bool tile_start = lane % LANES == 0, first = FEAT ? cs.first != 0 : tile_start;
+    if (live && tile_start && cs.cent) out[cs.tile_excl >> 2] = (uint32_t)cs.mu;
+    if (cs.r == 0) return;
+    auto quantized = [&](int i) { return __float_as_int(x[i] * R.inv + kQMagic); };
+    const int before = quantized(first || !live ? 0 : -1);
+#pragma unroll 1
+    for (uint32_t b = 0; b <= cs.r; b++) {
+        int pb = first ? kQBias : before, pl = cs.carry_l1;
+        uint32_t word = 0;
+#pragma unroll 1
+        for (int i = 0; i < kBlock; i++) {
+            const uint32_t valid = (cs.vm >> i) & 1u;
+            const int q = quantized(valid ? i : 0);
+            int d = q - pb;
+            if (i == 0 && first && cs.cent) d -= cs.mu;
+            const int e = mad_i24(pl, -cs.order2, d);  // as block_codes
+            const uint64_t code = __builtin_amdgcn_alignbit((uint32_t)max(e, -e), (uint32_t)e, 31);
+            word |= ((uint32_t)(code >> b) & valid) << (i ^ 7);
+            pb = q;
+            pl = d;
+        }
+        out[(cs.blk_off >> 2) + STRIDE * b] = word;
+    }
+}
+
 // The tile geometry a compression pipeline runs: its rate pass (one
 // workgroup barrier), its staging of the codes, whether a wave's first tile
 // exists, and where a lane's rate byte goes.  TileB32T8 is the default format
 // (blocks of 32 elements, tiles of 8 blocks); the tile-configuration sweep
 // has its own.
 struct TileB32T8 {
+    static constexpr int kLanes = 8, kWordStride = 1;  // lanes per tile, dwords from one word of a block to the next
     template <int W, bool FEAT>
     static __device__ __forceinline__ ChunkState rates(const CompressArgs &a, const Resolved &R, uint64_t chunk,
                                                        int (&x)[32], int slot, CompressShared<W> &sh)
@@ -1514,6 +1567,8 @@ __device__ __forceinline__ void chunk_totals(const CompressShared<W> &sh, int sl
         if (k < w) wave_base += sh.wave_total[slot][k];
         chunk_total += sh.wave_total[slot][k];
     }
+    wave_base = uniform(wave_base);
+    chunk_total = uniform(chunk_total);
 }
 
 // One step with chunk A rate-passed (registers xa, wave totals in slot sa),
@@ -1545,17 +1600,22 @@ __device__ __forceinline__ uint64_t pipe2_step(const CompressArgs &a, const Reso
     const bool ok = a.data0 + base + chunk_total <= a.capacity && M::template wave_live<W>(a, ca.chunk, w);
     uint32_t *wave_out = reinterpret_cast<uint32_t *>(a.out + a.data0 + base + wave_base);
     uint32_t *ps = pb + (((uint32_t)(uintptr_t)wave_out >> 2) & 3u);  // staging at the output's 16-byte phase
-    if (ok) M::template stage<FEAT>(ca, xa, ps);
+    uint32_t staged = ok ? ca.wave_total : 0;  // bytes
+    if (staged > kPipeOutBytes) {
+        store_oversize<M::kLanes, M::kWordStride, FEAT>(a, R, ca, (ca.chunk * W + (uint64_t)w) * 64, wave_out);
+        staged = 0;
+    }
+    if (staged) M::template stage<FEAT>(ca, xa, ps);
     if (C < a.nchunks) chunk_read(qb, lane, xa);
     if (D < a.nchunks) {
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the read of qb is done before it is overwritten
         chunk_fetch<W>(a, D, qb, w, lane);
     }
     M::template store_rate<W>(a, ca, w, lane);
-    if (ok) {
+    if (staged) {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        wave_store_staged_phased(wave_out, ps, ca.wave_total >> 2, lane);
+        wave_store_staged_phased(wave_out, ps, staged >> 2, lane);
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
@@ -2691,7 +2751,7 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const BItem
     uint32_t wave_base, chunk_total;
     chunk_totals<W>(sh, sa, w, wave_base, chunk_total);
     lds_barrier();  // the control wave has A's offset and the new ticket
-    const uint64_t base = sh.base[sa];
+    const uint64_t base = uniform((uint64_t)sh.base[sa]);
     const BItem iD = batch_item(b, sh.ticket[sa], s_job[sa]);
 
     const CompressArgs aA = batch_compress_args(b, iA.job);
@@ -2700,7 +2760,7 @@ __device__ __forceinline__ BItem batch_pipe_step(const BatchArgs &b, const BItem
     const bool ok = liveA && aA.data0 + base + chunk_total <= aA.capacity && tile0 < aA.ntiles;
     uint32_t *wave_out = reinterpret_cast<uint32_t *>(aA.out + aA.data0 + base + wave_base);
     uint32_t *ps = pb + (((uint32_t)(uintptr_t)wave_out >> 2) & 3u);  // staging at the output's 16-byte phase
-    if (ok) pipe2_stage<false>(ca, xa, ps);
+    if (ok) pipe2_stage<false>(ca, xa, ps);  // fits: a batch computes its own statistics
     if (iC.t < N) chunk_read(qb, lane, xa);
     if (iD.t < N) {
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the read of qb is done before it is overwritten
@@ -3038,6 +3098,7 @@ __device__ __forceinline__ void cfg_stage(const ChunkState &cs, int (&B)[32], ui
 // per block, L lanes per tile (a wave's 64 segments hold 64 / L tiles).
 template <int HB, int L>
 struct TileCfg {
+    static constexpr int kLanes = L, kWordStride = HB;
     template <int W, bool FEAT>
     static __device__ __forceinline__ ChunkState rates(const CompressArgs &a, const Resolved &R, uint64_t chunk,
                                                        int (&x)[32], int slot, CompressShared<W> &sh)

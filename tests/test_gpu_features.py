@@ -250,3 +250,50 @@ def test_many_steps_with_uneven_waves(path):
         assert int(res[1]) & 0xFFFFFFFF == fsz.FSZ_OK
         got = out[:int(res[0])].cpu().numpy().tobytes()
         assert got == exp, first_diff(got, exp)
+
+
+@pytest.mark.parametrize("n", [2048, 40_000, 2_201_546, 9_000_011])
+@pytest.mark.parametrize("entry", ["default", "config", "wide blocks"])
+def test_statistics_that_understate_the_field(n, entry):
+    """Statistics of a smaller field let blocks reach rates that no bound of
+    their own allows (24 to 31 planes, more than a wave stages at once): the
+    stream stays the five-read form's, whose waves stage 31 planes."""
+    rng = np.random.default_rng(n)
+    q = rng.integers(-(1 << 22) + 1, 1 << 22, n).astype(np.float32)
+    wave = rng.integers(0, 4, n // 2048 + 1)  # ordinary waves and three sizes of excess
+    wave[0] = wave[-1] = 3  # the last one, if ragged, ends inside the first half of a 64-element block
+    x = q * np.repeat(np.array([1e-3, 1.4, 1.9, 2.9], np.float32)[wave], 2048)[:n]
+    xd = torch.from_numpy(x).to(_dev())
+    stats = torch.tensor([-1.0, 1.0, 1.0, 0.0], device=_dev())  # max |x| = 1; flags 0
+    cap = fsz.fsz_compressed_bound(n)
+    stream = torch.cuda.current_stream(_dev()).cuda_stream
+    announce(f"{entry}, n={n}, understated statistics")
+
+    def call(fn, *extra):
+        out = torch.full((cap,), 0xA5, dtype=torch.uint8, device=_dev())
+        res = torch.zeros(2, dtype=torch.int64, device=_dev())
+        assert fn(xd.data_ptr(), n, oracle.ABS, 0.5, stats.data_ptr(), *extra, out.data_ptr(), cap, res.data_ptr(),
+                  stream) == fsz.FSZ_OK
+        torch.cuda.synchronize()
+        assert int(res[1]) & 0xFFFFFFFF == fsz.FSZ_OK
+        return out[:int(res[0])].cpu().numpy().tobytes()
+
+    exp = call(fsz.fsz_compress_five_read_async)
+    rates = np.frombuffer(exp, np.uint8, -(-n // 32), 32) & 31
+    assert 25 <= rates.max() <= 31
+    if entry == "wide blocks":  # another stream of the same quantized values
+        got = call(fsz.fsz_compress_config_async, 64, 16)
+        y = torch.zeros(2, n, dtype=torch.float32, device=_dev())
+        res = torch.zeros(2, 2, dtype=torch.int64, device=_dev())
+        for k, data in enumerate((exp, got)):
+            buf = torch.from_numpy(np.frombuffer(data, np.uint8).copy()).to(_dev())
+            args = buf.data_ptr(), len(data), y[k].data_ptr(), n
+            st = (fsz.fsz_decompress_config_async(*args, 64, 16, res[k].data_ptr(), stream) if k else
+                  fsz.fsz_decompress_async(*args, res[k].data_ptr(), stream))
+            assert st == fsz.FSZ_OK
+            torch.cuda.synchronize()
+            assert int(res[k, 1]) & 0xFFFFFFFF == fsz.FSZ_OK
+        assert torch.equal(y[0].view(torch.int32), y[1].view(torch.int32))
+        return
+    got = call(fsz.fsz_compress_config_async, 32, 8) if entry == "config" else call(fsz.fsz_compress_async)
+    assert got == exp, first_diff(got, exp)
