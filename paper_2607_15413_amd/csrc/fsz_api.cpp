@@ -10,6 +10,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -690,14 +691,25 @@ bool grow_slot(DescSlot &slot, size_t bytes)
     return true;
 }
 
-// Waits until the slot's last batch has read its staging: a short spin, then
-// the stream.
+// Waits until the slot's last batch has read its staging, i.e. has started:
+// polls the slot's word and no more, since the stream may hold other batches and
+// the caller's own work behind that one.  Every few ms the stream is looked at
+// too: if nothing is left on it, the batch is done or was lost with an error.
+// Rounds of 16 slices one behind the other, us per round: 40.8; 45.4 with a look
+// every 4096 polls, which costs the GPU time; 42.8 with a wait for the whole
+// stream after 4096 polls, which stopped the host for up to 210 us (64 fields of
+// 125 M elements: 1.03 ms) and left the GPU idle meanwhile.
 bool wait_slot(Workspace *ws, DescSlot &slot)
 {
     if (!slot.epoch) return true;
-    for (int k = 0; k < 4096; k++)
-        if (__atomic_load_n(slot.h_done, __ATOMIC_ACQUIRE) == slot.epoch) return true;
-    return ok(hipStreamSynchronize(ws->stream));
+    for (uint32_t k = 1; __atomic_load_n(slot.h_done, __ATOMIC_ACQUIRE) != slot.epoch; k++) {
+        if (k % (1u << 12) == 0) std::this_thread::yield();
+        if (k % (1u << 22)) continue;
+        const hipError_t e = hipStreamQuery(ws->stream);
+        if (e != hipErrorNotReady) return ok(e);
+        if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
+    }
+    return true;
 }
 
 // Enqueue one batch on the workspace's stream (caller holds ws->mu).

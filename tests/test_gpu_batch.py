@@ -600,3 +600,37 @@ def test_batch_last_items_without_a_wait(n):
         b.clear_outputs()
         b.run()
         check_against_oracle(b, refs, f"run {rep}")
+
+
+def test_batch_waits_for_its_slot_alone():
+    """With every staging slot taken, a batch waits until the oldest one has
+    started and not for what the stream holds behind it."""
+    fields = small_fields(4, 51, hi=1 << 14)
+    batches = [DeviceBatch([("c", f.data, fsz.FSZ_REL, f.rel)]) for f in fields] + \
+        [DeviceBatch([("c", fields[0].data, fsz.FSZ_REL, 1e-3)])]
+    refs = [oracle_refs(b.specs) for b in batches]
+    side = torch.cuda.Stream()
+    for b in batches:  # the stream's workspace
+        assert fsz.fsz_batch_async(b.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+        b.clear_outputs()
+    torch.cuda.synchronize()
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(1000)
+        t0.record()
+        torch.cuda._sleep(1_000_000)
+        t1.record()
+        torch.cuda.synchronize()
+        per_ms = 1_000_000 / max(t0.elapsed_time(t1), 0.01)
+        announce(f"4 batches behind a busy stream, a fifth behind 400 ms of other work ({per_ms:.0f} cycles per ms)")
+        torch.cuda._sleep(int(30 * per_ms))
+        for b in batches[:4]:
+            assert fsz.fsz_batch_async(b.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+        torch.cuda._sleep(int(400 * per_ms))
+        done = torch.cuda.Event()
+        done.record()
+        assert fsz.fsz_batch_async(batches[4].jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+        assert not done.query()
+    torch.cuda.synchronize()
+    for k, b in enumerate(batches):
+        check_against_oracle(b, refs[k], f"batch {k}")
