@@ -93,6 +93,7 @@ struct Workspace {
     // batched form
     std::array<DescSlot, 4> ring;
     unsigned ring_next = 0;
+    std::vector<DescSlot> captured;  // tables of batches captured into graphs
     unsigned long long *b_flags = nullptr;
     uint64_t b_flags_cap = 0;
     StatsPartial *b_partials = nullptr;
@@ -674,6 +675,16 @@ BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigne
     return b;
 }
 
+// While it lives, allocations are allowed on this thread although a stream is
+// being captured.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+};
+
 // Make a job-table slot hold `bytes` (the slot is idle).  Freeing device
 // memory synchronizes the device, so long-running callers reserve up front
 // (reserve_batch).
@@ -723,24 +734,27 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
         !grow(&ws->b_bounds, &ws->b_bounds_cap, njobs, ws->stream) ||
         !grow(&ws->b_words, &ws->b_words_cap, L.dec_words(), ws->stream))
         return FSZ_ERR_DEVICE;
-    DescSlot &slot = ws->ring[ws->ring_next++ % ws->ring.size()];
+    // A batch captured into a graph reads its table again at every replay, when
+    // nobody knows how often or until when: it gets buffers of its own, which
+    // stay, and leaves the ring alone.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!ok(hipStreamIsCapturing(ws->stream, &cap))) (void)hipGetLastError();
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    if (capturing) ws->captured.emplace_back();
+    DescSlot &slot = capturing ? ws->captured.back() : ws->ring[ws->ring_next++ % ws->ring.size()];
     if (!wait_slot(ws, slot)) return FSZ_ERR_DEVICE;
     const size_t bytes = L.desc_bytes();
-    if (!grow_slot(slot, bytes)) return FSZ_ERR_DEVICE;
+    if (capturing) {
+        RelaxedCapture relaxed;
+        if (!grow_slot(slot, bytes)) return FSZ_ERR_DEVICE;
+    } else if (!grow_slot(slot, bytes)) {
+        return FSZ_ERR_DEVICE;
+    }
     L.pack(slot.h);
     if (!ok(hipMemcpyAsync(slot.d, slot.h, bytes, hipMemcpyHostToDevice, ws->stream))) return FSZ_ERR_DEVICE;
     if (++ws->call == 0) ++ws->call;
-    BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_bounds, ws->b_partials,
-                                   ws->b_words);
-    // A batch captured into a graph reads its table again at every replay: its
-    // buffers leave the ring for good.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!ok(hipStreamIsCapturing(ws->stream, &cap))) (void)hipGetLastError();
-    if (cap != hipStreamCaptureStatusNone) {
-        slot.h = slot.d = nullptr;
-        slot.cap = 0;
-        slot.epoch = 0;
-    } else {
+    BatchArgs b = batch_args(L, slot.d, ws->call, ws->b_flags, ws->b_ticket, ws->b_bounds, ws->b_partials, ws->b_words);
+    if (!capturing) {
         b.h_done = slot.h_done;
         slot.epoch = ws->call;
     }

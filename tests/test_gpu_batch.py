@@ -634,3 +634,35 @@ def test_batch_waits_for_its_slot_alone():
     torch.cuda.synchronize()
     for k, b in enumerate(batches):
         check_against_oracle(b, refs[k], f"batch {k}")
+
+
+def test_many_batches_in_one_capture():
+    """More batches captured into one graph than there are staging slots, each
+    with jobs of its own, behind a single eager batch: no slot is used up and
+    every replay runs every batch's own jobs, with eager batches between."""
+    fields = small_fields(8, 57, hi=1 << 16)
+    batches = [DeviceBatch([("c", f.data, fsz.FSZ_REL, f.rel)]) for f in fields[:7]]
+    other = DeviceBatch([("c", f.data, fsz.FSZ_REL, f.rel) for f in fields])
+    refs, other_refs = [oracle_refs(b.specs) for b in batches], oracle_refs(other.specs)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert fsz.fsz_batch_async(other.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    announce("7 batches in one capture")
+    with torch.cuda.graph(graph, stream=side):
+        for b in batches:
+            assert fsz.fsz_batch_async(b.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+    for rep in range(3):
+        for b in batches + [other]:
+            b.clear_outputs()
+        torch.cuda.synchronize()
+        announce(f"replay {rep}")
+        for _ in range(6):
+            assert fsz.fsz_batch_async(other.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+        with torch.cuda.stream(side):
+            graph.replay()
+        torch.cuda.synchronize()
+        for k, b in enumerate(batches):
+            check_against_oracle(b, refs[k], f"batch {k}, replay {rep}")
+        check_against_oracle(other, other_refs, f"eager {rep}")
