@@ -23,8 +23,9 @@
  *     several host threads are serialized by an internal lock.
  *   - The library allocates its workspace (chunk flags, tickets, result
  *     words, batch job tables) on first use per (device, stream) and grows
- *     it when a larger field or batch arrives; plans own their buffers; it
- *     never allocates on the device otherwise.
+ *     it when a larger field or batch arrives (the buffers it outgrows stay,
+ *     for work enqueued or captured with them; each is at most half the next
+ *     one); plans own their buffers; it never allocates on the device otherwise.
  *   - Errors are returned as fsz_status values; nothing is thrown across
  *     the ABI.  Device-detected errors (non-finite input, bound too small,
  *     capacity, corrupt stream) arrive through the final status read.

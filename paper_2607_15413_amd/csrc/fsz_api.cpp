@@ -154,21 +154,22 @@ Workspace *get_workspace(hipStream_t s, fsz_status *st)
     return raw;
 }
 
-// Make room for nchunks flag words.  Growing waits for the stream, since an
-// earlier launch may still use the old array.
+// Make room for nchunks flag words.  The array that a larger one replaces stays
+// allocated, here and in grow: an earlier launch may still use it, and a call
+// captured into a graph names it at every replay.  Sizes double, so what stays
+// is less than what is in use.
 bool ensure_flags(Workspace *ws, uint64_t nchunks)
 {
     if (nchunks <= ws->flags_cap) return true;
     uint64_t cap = ws->flags_cap ? ws->flags_cap : 1024;
     while (cap < nchunks) cap *= 2;
-    if (ws->d_flags) {
-        if (!ok(hipStreamSynchronize(ws->stream))) return false;
-        if (!ok(hipFree(ws->d_flags))) return false;
-        ws->d_flags = nullptr;
-        ws->flags_cap = 0;
+    unsigned long long *d = nullptr;
+    if (!ok(hipMalloc(&d, cap * kFlagStride * sizeof(unsigned long long)))) return false;
+    if (!ok(hipMemsetAsync(d, 0, cap * kFlagStride * sizeof(unsigned long long), ws->stream))) {
+        (void)hipFree(d);
+        return false;
     }
-    if (!ok(hipMalloc(&ws->d_flags, cap * kFlagStride * sizeof(unsigned long long)))) return false;
-    if (!ok(hipMemsetAsync(ws->d_flags, 0, cap * kFlagStride * sizeof(unsigned long long), ws->stream))) return false;
+    ws->d_flags = d;
     ws->flags_cap = cap;
     return true;
 }
@@ -233,14 +234,13 @@ fsz_status enqueue_compress(Workspace *ws, const float *d_in, uint64_t n, int mo
 }
 
 template <typename T>
-bool grow(T **p, uint64_t *cap, uint64_t want, hipStream_t s);
+bool grow(T **p, uint64_t *cap, uint64_t want);
 
 // Room for the offsets pre-pass of a decode, if it has one.
 bool ensure_words(Workspace *ws, const DecompressArgs &a)
 {
     if (decode_by_prefix(a.tile_begin, a.tile_end)) return true;
-    return grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + ceil_div(a.tile_end, (uint64_t)kTilesPerChunk) + 1,
-                ws->stream);
+    return grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + ceil_div(a.tile_end, (uint64_t)kTilesPerChunk) + 1);
 }
 
 // The five-read baseline (Sec. V-C, Fig. 6): the same stream as
@@ -268,7 +268,7 @@ fsz_status enqueue_compress_naive(Workspace *ws, const float *d_in, uint64_t n, 
     a.features = kFeaturesAll;
     const uint64_t nt = std::max<uint64_t>(a.ntiles, 1);
     const uint64_t off_rates = 16 * nt, off_mu = off_rates + 32 * nt, off_ok = off_mu + 4 * nt;
-    if (!grow(&ws->d_naive, &ws->naive_cap, off_ok + nt, ws->stream)) return FSZ_ERR_DEVICE;
+    if (!grow(&ws->d_naive, &ws->naive_cap, off_ok + nt)) return FSZ_ERR_DEVICE;
     NaiveTables t;
     t.cost = reinterpret_cast<uint32_t *>(ws->d_naive);
     t.rates = ws->d_naive + off_rates;
@@ -379,7 +379,7 @@ fsz_status enqueue_decompress_config(Workspace *ws, const void *d_cmp, uint64_t 
     hipError_t e;
     if (prescan) {
         // chunk offsets from the rate header first, as for the default format
-        if (!grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + a.nchunks, ws->stream)) return FSZ_ERR_DEVICE;
+        if (!grow(&ws->d_offs, &ws->offs_cap, kMaxGroupWords + a.nchunks)) return FSZ_ERR_DEVICE;
         e = launch_decompress_cfg_prescan(a, ws->d_offs, block, tile_blocks, aligned(d_out, 16), ws->stream);
     } else {
         e = launch_decompress_cfg(a, block, tile_blocks, aligned(d_out, 16), ws->stream);
@@ -519,17 +519,14 @@ fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayou
 }
 
 template <typename T>
-bool grow(T **p, uint64_t *cap, uint64_t want, hipStream_t s)
+bool grow(T **p, uint64_t *cap, uint64_t want)
 {
     if (want <= *cap) return true;
     uint64_t c = *cap ? *cap : 256;
     while (c < want) c *= 2;
-    if (*p) {
-        if (!ok(hipStreamSynchronize(s)) || !ok(hipFree(*p))) return false;
-        *p = nullptr;
-        *cap = 0;
-    }
-    if (!ok(hipMalloc(p, c * sizeof(T)))) return false;
+    T *d = nullptr;
+    if (!ok(hipMalloc(&d, c * sizeof(T)))) return false;
+    *p = d;
     *cap = c;
     return true;
 }
@@ -729,10 +726,10 @@ fsz_status enqueue_batch(Workspace *ws, const fsz_job *jobs, size_t njobs, const
     BatchLayout L;
     fsz_status st = layout_batch(jobs, njobs, shape.waves, &L);
     if (st != FSZ_OK || njobs == 0) return st;
-    if (!grow(&ws->b_flags, &ws->b_flags_cap, L.flag_words(), ws->stream) ||
-        !grow(&ws->b_partials, &ws->b_partials_cap, L.k[FSZ_OP_COMPRESS].total_segs, ws->stream) ||
-        !grow(&ws->b_bounds, &ws->b_bounds_cap, njobs, ws->stream) ||
-        !grow(&ws->b_words, &ws->b_words_cap, L.dec_words(), ws->stream))
+    if (!grow(&ws->b_flags, &ws->b_flags_cap, L.flag_words()) ||
+        !grow(&ws->b_partials, &ws->b_partials_cap, L.k[FSZ_OP_COMPRESS].total_segs) ||
+        !grow(&ws->b_bounds, &ws->b_bounds_cap, njobs) ||
+        !grow(&ws->b_words, &ws->b_words_cap, L.dec_words()))
         return FSZ_ERR_DEVICE;
     // A batch captured into a graph reads its table again at every replay, when
     // nobody knows how often or until when: it gets buffers of its own, which
@@ -771,10 +768,10 @@ bool reserve_batch(hipStream_t stream, uint64_t jobs, uint64_t chunks, uint64_t 
     Workspace *ws = get_workspace(stream, &st);
     if (!ws) return false;
     std::lock_guard<std::mutex> g(ws->mu);
-    if (!grow(&ws->b_flags, &ws->b_flags_cap, std::max<uint64_t>(chunks, 1) * kFlagStride, ws->stream) ||
-        !grow(&ws->b_partials, &ws->b_partials_cap, std::max<uint64_t>(segs, 1), ws->stream) ||
-        !grow(&ws->b_bounds, &ws->b_bounds_cap, std::max<uint64_t>(jobs, 1), ws->stream) ||
-        !grow(&ws->b_words, &ws->b_words_cap, chunks + segs, ws->stream))  // a tile group holds several segments
+    if (!grow(&ws->b_flags, &ws->b_flags_cap, std::max<uint64_t>(chunks, 1) * kFlagStride) ||
+        !grow(&ws->b_partials, &ws->b_partials_cap, std::max<uint64_t>(segs, 1)) ||
+        !grow(&ws->b_bounds, &ws->b_bounds_cap, std::max<uint64_t>(jobs, 1)) ||
+        !grow(&ws->b_words, &ws->b_words_cap, chunks + segs))  // a tile group holds several segments
         return false;
     const size_t bytes = jobs * (sizeof(BatchJob) + 2 * sizeof(uint64_t));
     for (auto &slot : ws->ring) {

@@ -666,3 +666,65 @@ def test_many_batches_in_one_capture():
         for k, b in enumerate(batches):
             check_against_oracle(b, refs[k], f"batch {k}, replay {rep}")
         check_against_oracle(other, other_refs, f"eager {rep}")
+
+
+def test_captured_calls_outlive_workspace_growth():
+    """A captured batch and a captured decode (offsets pre-pass) replay
+    correctly after eager calls on the stream have outgrown every buffer of the
+    workspace that they were captured with."""
+    fields = small_fields(4, 61, hi=1 << 17)
+    _, data = oracle.compress_status(fields[0].data, fsz.FSZ_REL, 1e-3)
+    specs = [("c", f.data, fsz.FSZ_REL, f.rel) for f in fields] + [("d", data, fields[0].data.size)]
+    refs = oracle_refs(specs)
+    a = DeviceBatch(specs)
+    n = 5_000_003
+    x = workloads.sinusoid_field(4 * n, 63)
+    old = oracle.set_threads(8)
+    try:
+        small, big = oracle.compress(x[:n], oracle.REL, 1e-3), oracle.compress(x, oracle.REL, 1e-3)
+        y_small, y_big = oracle.decompress(small, n), oracle.decompress(big, 4 * n)
+    finally:
+        oracle.set_threads(old)
+    d = [torch.from_numpy(np.frombuffer(s, np.uint8).copy()).to(_dev()) for s in (small, big)]
+    y = [torch.zeros(k * n, dtype=torch.float32, device=_dev()) for k in (1, 4)]
+    res = torch.zeros(2, 4, dtype=torch.int32, device=_dev())
+    large = [("c", x[k * 70_000:(k + 1) * 70_000], fsz.FSZ_REL, 1e-3) for k in range(280)]
+    large += [("d", data, fields[0].data.size)] * 300
+    large_refs = oracle_refs(large[:281])
+    b = DeviceBatch(large)
+    side = torch.cuda.Stream()
+
+    def decode(k):
+        assert fsz.fsz_decompress_async(d[k].data_ptr(), d[k].numel(), y[k].data_ptr(), y[k].numel(),
+                                        res[k].data_ptr(), side.cuda_stream) == fsz.FSZ_OK
+
+    def batch(s):
+        assert fsz.fsz_batch_async(s.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+
+    torch.cuda.synchronize()
+    batch(a)
+    decode(0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    announce("capture of a batch and a decode")
+    with torch.cuda.graph(graph, stream=side):
+        batch(a)
+        decode(0)
+    for rep in range(3):
+        a.clear_outputs()
+        y[0].fill_(float("nan"))
+        torch.cuda.synchronize()
+        announce(f"larger eager calls, then replay {rep}")
+        batch(b)
+        decode(1)
+        torch.cuda.synchronize()
+        keep = [torch.full((1 << 18,), 7, dtype=torch.int64, device=_dev()) for _ in range(8)]
+        with torch.cuda.stream(side):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert all(bool((k == 7).all()) for k in keep)
+        check_against_oracle(a, refs, f"replay {rep}")
+        assert np.array_equal(y[0].cpu().numpy().view(np.uint32), y_small.view(np.uint32))
+    check_against_oracle(b, large_refs[:280] + [large_refs[280]] * 300, "larger batch")
+    assert np.array_equal(y[1].cpu().numpy().view(np.uint32), y_big.view(np.uint32))
+    assert res[:, 2].tolist() == [0, 0]
