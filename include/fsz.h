@@ -291,8 +291,8 @@ fsz_status fsz_decompress_config_async(const void *d_cmp, size_t cmp_size, float
  * capacity, corrupt stream) arrive in that job's *d_result and do not affect
  * the other jobs.
  *
- * A batch may be captured into a graph, behind an eager batch as large on the
- * same stream (which allocates the workspace); its replays are work of that
+ * A batch may be captured into a graph, behind an eager call on the same
+ * stream (which creates the workspace); its replays are work of that
  * stream like the calls on it.  Every captured batch keeps its job table (144
  * bytes per job, 4 KB at least, on the device and as much of pinned memory)
  * until the process ends: a program that captures again and again takes plans,

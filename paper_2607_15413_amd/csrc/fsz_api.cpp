@@ -154,6 +154,16 @@ Workspace *get_workspace(hipStream_t s, fsz_status *st)
     return raw;
 }
 
+// While it lives, allocations are allowed on this thread although a stream is
+// being captured.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+};
+
 // Make room for nchunks flag words.  The array that a larger one replaces stays
 // allocated, here and in grow: an earlier launch may still use it, and a call
 // captured into a graph names it at every replay.  Sizes double, so what stays
@@ -518,6 +528,8 @@ fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayou
     return FSZ_OK;
 }
 
+// As ensure_flags for buffers whose contents a call writes itself before it reads
+// them: these may grow inside a capture, too.
 template <typename T>
 bool grow(T **p, uint64_t *cap, uint64_t want)
 {
@@ -525,6 +537,7 @@ bool grow(T **p, uint64_t *cap, uint64_t want)
     uint64_t c = *cap ? *cap : 256;
     while (c < want) c *= 2;
     T *d = nullptr;
+    RelaxedCapture relaxed;
     if (!ok(hipMalloc(&d, c * sizeof(T)))) return false;
     *p = d;
     *cap = c;
@@ -671,16 +684,6 @@ BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigne
     b.dec.offsets = words + D.total_segs;
     return b;
 }
-
-// While it lives, allocations are allowed on this thread although a stream is
-// being captured.
-struct RelaxedCapture {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    RelaxedCapture(const RelaxedCapture &) = delete;
-    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
-};
 
 // Make a job-table slot hold `bytes` (the slot is idle).  Freeing device
 // memory synchronizes the device, so long-running callers reserve up front

@@ -209,3 +209,45 @@ def test_range_offsets_at_edges(begin, end):
             bad[32 + 8 * tile] |= 0x20
             announce(f"range offsets [{begin}, {end}): reserved bit in tile {tile}")
             assert gpu_decompress_range(bytes(bad), _N, begin, end)[0] == want
+
+
+def test_capture_behind_a_small_call():
+    """Range and whole-field decodes that need the offsets pre-pass, captured
+    behind a range read of a small field alone: the pre-pass's buffers grow inside
+    the capture, and every replay decodes."""
+    n, lo, hi = 12_000_017, 11_000_001, 11_400_000
+    x = workloads.sinusoid_field(n, 81)
+    old = oracle.set_threads(8)
+    try:
+        s = oracle.compress(x, oracle.REL, 1e-3)
+        ref = oracle.decompress(s, n)
+    finally:
+        oracle.set_threads(old)
+    buf = torch.from_numpy(np.frombuffer(s, np.uint8).copy()).to(_dev())
+    tiny = torch.from_numpy(np.frombuffer(oracle.compress(x[:1000], oracle.REL, 1e-3), np.uint8).copy()).to(_dev())
+    y = torch.zeros(n, dtype=torch.float32, device=_dev())
+    part = torch.zeros(hi - lo, dtype=torch.float32, device=_dev())
+    res = torch.zeros(2, 4, dtype=torch.int32, device=_dev())
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert fsz.fsz_decompress_range_async(tiny.data_ptr(), tiny.numel(), 1000, 0, 10, part.data_ptr(),
+                                          res[0].data_ptr(), side.cuda_stream) == fsz.FSZ_OK
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    announce(f"capture of a range read and a decode, n={n}")
+    with torch.cuda.graph(graph, stream=side):
+        assert fsz.fsz_decompress_range_async(buf.data_ptr(), buf.numel(), n, lo, hi, part.data_ptr(),
+                                              res[0].data_ptr(), side.cuda_stream) == fsz.FSZ_OK
+        assert fsz.fsz_decompress_async(buf.data_ptr(), buf.numel(), y.data_ptr(), n, res[1].data_ptr(),
+                                        side.cuda_stream) == fsz.FSZ_OK
+    for rep in range(3):
+        y.fill_(float("nan"))
+        part.fill_(float("nan"))
+        torch.cuda.synchronize()
+        announce(f"replay {rep}")
+        with torch.cuda.stream(side):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(part.cpu().numpy().view(np.uint32), ref[lo:hi].view(np.uint32))
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+        assert res[:, 2].tolist() == [0, 0]
