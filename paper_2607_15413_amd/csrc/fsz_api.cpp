@@ -685,19 +685,22 @@ BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigne
     return b;
 }
 
-// Make a job-table slot hold `bytes` (the slot is idle).  Freeing device
-// memory synchronizes the device, so long-running callers reserve up front
-// (reserve_batch).
+// Make a job-table slot hold `bytes` (its staging is idle).  As in grow the
+// buffers that larger ones replace stay: the slot's last batch may still read
+// the device copy, and freeing would wait for the whole device.
 bool grow_slot(DescSlot &slot, size_t bytes)
 {
     if (bytes <= slot.cap) return true;
-    if (slot.h && !ok(hipHostFree(slot.h))) return false;
-    if (slot.d && !ok(hipFree(slot.d))) return false;
-    slot.h = slot.d = nullptr;
-    slot.cap = 0;
     size_t c = 4096;
     while (c < bytes) c *= 2;
-    if (!ok(hipHostMalloc(&slot.h, c, hipHostMallocDefault)) || !ok(hipMalloc(&slot.d, c))) return false;
+    void *h = nullptr, *d = nullptr;
+    if (!ok(hipHostMalloc(&h, c, hipHostMallocDefault))) return false;
+    if (!ok(hipMalloc(&d, c))) {
+        (void)hipHostFree(h);
+        return false;
+    }
+    slot.h = h;
+    slot.d = d;
     slot.cap = c;
     return true;
 }

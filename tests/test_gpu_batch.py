@@ -728,3 +728,21 @@ def test_captured_calls_outlive_workspace_growth():
     check_against_oracle(b, large_refs[:280] + [large_refs[280]] * 300, "larger batch")
     assert np.array_equal(y[1].cpu().numpy().view(np.uint32), y_big.view(np.uint32))
     assert res[:, 2].tolist() == [0, 0]
+
+
+def test_growing_batches_back_to_back():
+    """Batches whose job tables outgrow their staging slot again and again,
+    enqueued while the batches before them wait or run."""
+    fields = small_fields(6, 71, hi=1 << 16)
+    specs = [[("c", fields[(k + j) % 6].data, fsz.FSZ_REL, 1e-3) for j in range(3 << k)] for k in range(8)]
+    batches = [DeviceBatch(s) for s in specs]
+    refs = {k: (st, data) for k, (st, data) in enumerate(oracle_refs([("c", f.data, fsz.FSZ_REL, 1e-3) for f in fields]))}
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    announce("8 batches of 3 to 384 jobs, each twice")
+    for b in batches:
+        for _ in range(2):
+            assert fsz.fsz_batch_async(b.jobs, (4, 0), side.cuda_stream) == fsz.FSZ_OK
+    torch.cuda.synchronize()
+    for k, b in enumerate(batches):
+        check_against_oracle(b, [refs[(k + j) % 6] for j in range(3 << k)], f"batch {k}")
