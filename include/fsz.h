@@ -335,8 +335,9 @@ typedef struct {
  * so `jobs` may be reused when the call returns. */
 fsz_status fsz_batch_async(const fsz_job *jobs, size_t njobs, const fsz_tuning *tuning, void *stream);
 
-/* Autotuner: runs the batch under every supported shape (`reps` timed runs
- * each, HIP events on `stream`), stores the fastest in the process-wide
+/* Autotuner: runs the batch under every supported shape that makes a
+ * difference (`reps` timed runs each, HIP events on `stream`; a batch without
+ * decompress jobs has the default one alone), stores the fastest in the process-wide
  * cache for the batch's size class (and in the file named by the
  * FSZ_TUNE_CACHE environment variable, if set), and returns it in *best.
  * The jobs' outputs are written (identically) by every run.  Blocks. */

@@ -1059,6 +1059,8 @@ fsz_status fsz_autotune(const fsz_job *jobs, size_t njobs, int reps, void *strea
     for (int w : waves) {
         for (int gcu : groups) {
             const fsz_tuning cand{w, gcu};
+            // only decompress jobs are shaped: without them every shape runs the same kernels
+            if (L.k[FSZ_OP_DECOMPRESS].jobs.empty() && (w != 4 || gcu != 0)) continue;
             if (!batch_shape_supported(to_shape(cand))) continue;
             std::lock_guard<std::mutex> g(ws->mu);
             st = enqueue_batch(ws, jobs, njobs, to_shape(cand));  // warm-up

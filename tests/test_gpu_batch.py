@@ -746,3 +746,18 @@ def test_growing_batches_back_to_back():
     torch.cuda.synchronize()
     for k, b in enumerate(batches):
         check_against_oracle(b, [refs[(k + j) % 6] for j in range(3 << k)], f"batch {k}")
+
+
+def test_autotune_has_no_choice_for_compression():
+    """The launch shape is the decompress kernel's: a batch that only compresses
+    gets the default one, whatever the timings, and runs."""
+    fields = small_fields(5, 83, hi=1 << 15)
+    specs = [("c", f.data, fsz.FSZ_REL, f.rel) for f in fields]
+    refs = oracle_refs(specs)
+    for rep in range(4):
+        announce(f"autotune of a compress-only batch, {rep}")
+        b = DeviceBatch(specs[rep:])
+        st, best = fsz.fsz_autotune(b.jobs, 1, _stream())
+        assert st == fsz.FSZ_OK and best == (4, 0)
+        torch.cuda.synchronize()
+        check_against_oracle(b, refs[rep:], "after autotune")
