@@ -523,7 +523,7 @@ fsz_status layout_batch(const fsz_job *jobs, size_t njobs, int waves, BatchLayou
     }
     // one work item per workgroup: grid x times workgroup size must fit 32 bits
     if ((L->k[0].total_chunks + L->k[1].total_chunks) * (uint64_t)(waves * 64) >= (1ull << 32) ||
-        (L->k[0].total_segs + L->k[1].total_segs) * kStatsThreads >= (1ull << 32))
+        L->k[FSZ_OP_COMPRESS].total_segs * kStatsThreads >= (1ull << 32))
         return FSZ_ERR_INVALID_ARG;
     return FSZ_OK;
 }
@@ -680,6 +680,7 @@ BatchArgs batch_args(const BatchLayout &L, void *d_desc, uint32_t epoch, unsigne
     b.dec.tpc_log2 = (uint32_t)__builtin_ctz((unsigned)(kTilesPerWave * L.waves));
     b.dec.total_chunks = D.total_chunks;
     b.dec.total_groups = D.total_segs;
+    b.dec.group_wgs = (uint32_t)std::min(D.total_segs, kMaxGroupWgs);
     b.dec.groups = words;
     b.dec.offsets = words + D.total_segs;
     return b;

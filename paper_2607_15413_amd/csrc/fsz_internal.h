@@ -138,6 +138,7 @@ constexpr int kGroupThreads = 256;
 constexpr int kGroupTilesPerThread = 4;
 constexpr int kGroupTiles = kGroupThreads * kGroupTilesPerThread;
 constexpr uint64_t kMaxGroupWords = 512;
+constexpr uint64_t kMaxGroupWgs = 65536;  // of a batch's pre-pass (256 per CU)
 // Rounds of kGroupTiles tiles per group: the least power of two that leaves at
 // most kMaxGroupWords groups.
 inline uint32_t group_passes(uint64_t ntiles)
@@ -191,6 +192,7 @@ struct BatchArgs {
         const BatchJob *jobs;
         const uint64_t *chunk_end, *group_end;
         uint32_t njobs, tpc_log2;         // log2 of the tiles per chunk
+        uint32_t group_wgs;               // workgroups that sum them: one each, up to kMaxGroupWgs
         uint64_t total_chunks, total_groups;
         unsigned long long *groups, *offsets;  // one word per group / per chunk
     } dec;

@@ -2496,9 +2496,9 @@ __device__ __forceinline__ DecompressArgs batch_decompress_args(const BatchArgs 
     return a;
 }
 
-// Batched range pass and offsets pre-pass.  The first b.dec.total_groups
-// workgroups each sum one group of tiles of a decompress job (as
-// dec_groups_kernel).  The others reduce segments (kSegElems elements of one
+// Batched range pass and offsets pre-pass.  The first b.dec.group_wgs
+// workgroups each sum a group of tiles of a decompress job (as
+// dec_groups_kernel), or several one after the other.  The others reduce segments (kSegElems elements of one
 // compress job, a partial each) and clear the batch's chunk flags for the
 // kernel that follows.
 __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
@@ -2506,16 +2506,19 @@ __global__ __launch_bounds__(kStatsThreads) void batch_stats_kernel(BatchArgs b)
     static_assert(kStatsThreads == kGroupThreads, "both parts of the launch");
     if (blockIdx.x == 0 && threadIdx.x == 0 && b.h_done)  // the job table's copy is done with its staging
         __hip_atomic_store(b.h_done, b.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (blockIdx.x < b.dec.total_groups) {
-        const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.dec.group_end, b.dec.njobs, blockIdx.x));
-        if (job >= b.dec.njobs) return;
-        const BatchJob &J = b.dec.jobs[job];
-        DecompressArgs a = batch_decompress_args(b, J);
-        group_sums<kBlocksPerTile, 1>(a, blockIdx.x - J.seg_base, J.group_passes, b.dec.tpc_log2,
-                                      b.dec.offsets + J.chunk_base, b.dec.groups + J.seg_base);
+    if (blockIdx.x < b.dec.group_wgs) {
+        for (uint64_t g = blockIdx.x; g < b.dec.total_groups; g += b.dec.group_wgs) {
+            const uint32_t job = __builtin_amdgcn_readfirstlane(find_job(b.dec.group_end, b.dec.njobs, g));
+            if (job >= b.dec.njobs) return;
+            const BatchJob &J = b.dec.jobs[job];
+            DecompressArgs a = batch_decompress_args(b, J);
+            group_sums<kBlocksPerTile, 1>(a, g - J.seg_base, J.group_passes, b.dec.tpc_log2,
+                                          b.dec.offsets + J.chunk_base, b.dec.groups + J.seg_base);
+            lds_barrier();  // its shared slots are reused by the next group
+        }
         return;
     }
-    const uint64_t wg = blockIdx.x - b.dec.total_groups, nwg = gridDim.x - b.dec.total_groups;
+    const uint64_t wg = blockIdx.x - b.dec.group_wgs, nwg = gridDim.x - b.dec.group_wgs;
     for (uint64_t i = wg * kStatsThreads + threadIdx.x; i < b.nflags; i += nwg * kStatsThreads) b.flags[i] = 0;
     // workgroups loop over segments (one partial each), so the job search and
     // the workgroup start are paid once per several segments
@@ -3717,7 +3720,7 @@ hipError_t launch_batch(const BatchArgs &b, bool aligned_out, const BatchShape &
     uint64_t grid = b.total_segs < 2048 ? b.total_segs : 2048;
     const uint64_t clear = ceil_div(b.nflags, kStatsThreads);
     if (grid < clear) grid = clear < kStatsMaxBlocks ? clear : kStatsMaxBlocks;
-    grid += b.dec.total_groups;
+    grid += b.dec.group_wgs;
     hipLaunchKernelGGL(batch_stats_kernel, dim3((unsigned)grid), dim3(kStatsThreads), 0, s, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

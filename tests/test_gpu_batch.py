@@ -761,3 +761,31 @@ def test_autotune_has_no_choice_for_compression():
         assert st == fsz.FSZ_OK and best == (4, 0)
         torch.cuda.synchronize()
         check_against_oracle(b, refs[rep:], "after autotune")
+
+
+def test_batch_of_many_small_decodes():
+    """More decompress jobs than workgroups of the offsets pre-pass, a corrupt
+    one and a compress job among them."""
+    count = 70_001
+    x = workloads.sinusoid_field(600, 91)
+    streams = [oracle.compress(x[:n], oracle.REL, 1e-3) for n in (1, 300, 600)]
+    refs = [oracle.decompress(s, n) for s, n in zip(streams, (1, 300, 600))]
+    bad = bytearray(streams[2])
+    bad[32] |= 0x20
+    src = [torch.from_numpy(np.frombuffer(bytes(s), np.uint8).copy()).to(_dev()) for s in streams + [bad]]
+    out = torch.full((count, 600), float("nan"), dtype=torch.float32, device=_dev())
+    res = torch.full((count, 4), -1, dtype=torch.int32, device=_dev())
+    kind = np.random.default_rng(5).integers(0, 4, count)
+    jobs = [fsz.decompress_job(src[q].data_ptr(), src[q].numel(), out.data_ptr() + 2400 * k, (1, 300, 600, 600)[q],
+                               res.data_ptr() + 16 * k) for k, q in enumerate(kind)]
+    b = DeviceBatch([("c", x, fsz.FSZ_REL, 1e-3)])
+    announce(f"{count} decompress jobs and a compress job")
+    assert fsz.fsz_batch_async(jobs[:1000] + b.jobs + jobs[1000:], (2, 0), _stream()) == fsz.FSZ_OK
+    torch.cuda.synchronize()
+    check_against_oracle(b, oracle_refs(b.specs), "compress job")
+    assert np.array_equal(res[:, 2].cpu().numpy() == fsz.FSZ_ERR_CORRUPT, kind == 3)
+    assert np.array_equal(res[:, 2].cpu().numpy() == fsz.FSZ_OK, kind != 3)
+    y = out.cpu().numpy()
+    for q, n in enumerate((1, 300, 600)):
+        assert np.array_equal(y[kind == q][:, :n].view(np.uint32), np.tile(refs[q].view(np.uint32), ((kind == q).sum(), 1)))
+        assert np.isnan(y[kind == q][:, n:]).all()
