@@ -3,15 +3,20 @@
 // Data layout on the GPU (the format itself is fixed by Sec. III-A / IV-C):
 //   - one lane owns one 32-element block; lanes 8t..8t+7 of a wave own the
 //     8 blocks of one 256-element tile, so a wave64 holds 8 tiles;
-//   - a workgroup of kWaves waves owns a chunk of 8*kWaves consecutive
-//     tiles; chunk ids come from an atomic ticket so that the decoupled
-//     lookback (Sec. IV-D) only ever waits on chunks already running;
-//   - HBM is read once with coalesced 16-byte loads, transposed through LDS
-//     into the lane-per-block layout, and kept in VGPRs across the lookback
-//     (the paper's kernel re-reads its input for the encode pass instead);
 //   - the cross-block prediction state (Sec. IV-A, Eq. (2)) moves between
 //     the lanes of a tile with one DPP row shift per block;
 //   - per-tile reductions (mean, costs) use DPP within 8-lane groups.
+// Compression is a persistent pipeline: a workgroup of 4, 8 or 11 data waves
+// and a control wave takes chunks of 8 tiles per data wave by an atomic ticket,
+// so that the decoupled lookback (Sec. IV-D), which the control wave walks, only
+// ever waits on chunks already running; input is read once, by asynchronous
+// copies to LDS a chunk ahead, and stays in VGPRs from the rate pass to the
+// encode (the paper's kernel re-reads it instead).
+// Decompression knows every chunk's offset before it starts, from the rate
+// header alone (a sum in each workgroup for small fields, a pre-pass otherwise),
+// so its workgroups wait on nobody.  The tile configurations' decoder for small
+// fields and the five-read baseline keep one chunk per workgroup with a ticket
+// and a lookback.
 //
 // Floating point: compiled with -ffp-contract=off; the quantizer is one
 // binary32 multiply and a round-half-even (v_mul_f32, v_rndne_f32), the
@@ -804,12 +809,12 @@ struct CompressShared {
 //   3 adaptive select (strict minimum in the order LZ1, LZ2, LZ1c, LZ2c),
 //     rate header; the chunk's byte count is published for the lookback.
 // On return x holds the blocks' LZ1 residuals (block_extrema).
-// DEFER: leave the rate byte in cs.rbyte for the caller to store, and publish
-// the aggregate from wave 1 (whose memory queue the lookback does not wait on).
+// The rate byte is left in cs.rbyte for the caller to store; wave 1 publishes the
+// aggregate (wave 0's memory queue is the one a lookback may wait on).
 // FEAT: honour a.features (the ablation's switches, Sec. VI-B): without the
 // cross-block state every block restarts prediction and is re-rated per
 // variant like block 0; switched-off variants are never selected.
-template <int W, bool DEFER = false, bool FEAT = false>
+template <int W, bool FEAT = false>
 __device__ __forceinline__ ChunkState compress_rates(const CompressArgs &a, const Resolved &R, uint64_t chunk,
                                                      int (&x)[32], int slot, CompressShared<W> &sh)
 {
@@ -963,7 +968,6 @@ __device__ __forceinline__ ChunkState compress_rates(const CompressArgs &a, cons
     cs.r = j == 0 ? (uint32_t)(dec & 31) : (cs.order2 ? r2 : r1);
     cs.rbyte = j == 0 ? (uint32_t)(dec & 0xFF) : cs.r;
     }
-    if (!DEFER && cnt > 0) ((g_u8 *)a.out)[kHeaderBytes + tile * kBlocksPerTile + j] = (uint8_t)cs.rbyte;
     const uint32_t S = block_bytes(cs.r);
 
     // ---- offsets inside the wave / chunk, aggregate for the lookback
@@ -973,7 +977,7 @@ __device__ __forceinline__ ChunkState compress_rates(const CompressArgs &a, cons
     cs.blk_off = cs.tile_excl + group_excl_scan(S, j) + 4u * cs.cent;
     if (lane == 0) sh.wave_total[slot][w] = cs.wave_total;
     lds_barrier();
-    if (tid == (DEFER && W > 1 ? 64 : 0)) {
+    if (tid == 64) {
         uint32_t chunk_total = 0;
 #pragma unroll
         for (int k = 0; k < W; k++) chunk_total += sh.wave_total[slot][k];
@@ -1005,59 +1009,6 @@ __device__ __forceinline__ void finish_stream(const CompressArgs &a, const Resol
         for (uint64_t k = kHeaderBytes + a.nblocks; k < a.data0; k++) a.out[k] = 0;
     }
     write_final(a.final, total, status, a.epoch);
-}
-
-// Steps 4-5 of one chunk whose rate pass is done: wait for the chunk's output
-// offset (decoupled lookback, Sec. IV-D), then the sign / bit-plane encoding
-// (Sec. IV-C) through the wave's LDS staging area.  B holds the LZ1 residuals.
-template <int W>
-__device__ __forceinline__ void compress_encode(const CompressArgs &a, const Resolved &R, const ChunkState &cs,
-                                                int (&B)[32], int slot, CompressShared<W> &sh, uint32_t *st)
-{
-    const int tid = threadIdx.x;
-    const int w = tid >> 6;
-    const int lane = tid & 63;
-    const int j = lane & 7;
-    uint32_t chunk_total = 0, wave_base = 0;
-#pragma unroll
-    for (int k = 0; k < W; k++) {
-        if (k < w) wave_base += sh.wave_total[slot][k];
-        chunk_total += sh.wave_total[slot][k];
-    }
-    if (w == 0) {
-        const Prefix pre = lookback_wait(a.flags, cs.chunk, a.flag_epoch, chunk_total, false);
-        if (lane == 0) {
-            sh.base[slot] = pre.excl;
-            if (cs.chunk == a.nchunks - 1) finish_stream(a, R, pre, chunk_total);
-        }
-    }
-    lds_barrier();
-    const uint64_t base = sh.base[slot];
-    const uint64_t tile0 = cs.chunk * (kTilesPerWave * W) + (uint64_t)w * kTilesPerWave;
-    if (a.data0 + base + chunk_total > a.capacity || tile0 >= a.ntiles) return;
-
-    uint8_t *wave_out = a.out + a.data0 + base + wave_base;
-    if (cs.vm != 0 && j == 0 && cs.cent) st[cs.tile_excl >> 2] = (uint32_t)cs.mu;
-    block_codes(B, cs.carry_l1, j, cs.order2, cs.cent, cs.mu);
-    // valid slots in stored bit order (element i at bit i ^ 7)
-    const uint32_t keep = __builtin_bswap32(__builtin_bitreverse32(cs.vm));
-    const uint32_t nwords = cs.r ? cs.r + 1 : 0;  // sign word + r planes
-    uint32_t *words = st + (cs.blk_off >> 2);
-    for (uint32_t g = 0; __ballot(8 * g < nwords) != 0; g++) {
-        uint32_t Rg[8];
-#pragma unroll
-        for (int rho = 0; rho < 8; rho++)
-            Rg[rho] = pack_byte_g((uint32_t)B[7 - rho], (uint32_t)B[15 - rho], (uint32_t)B[23 - rho],
-                                  (uint32_t)B[31 - rho], g);
-        transpose8(Rg);
-#pragma unroll
-        for (int p = 0; p < 8; p++)
-            if (8 * g + p < nwords) words[8 * g + p] = Rg[p] & keep;
-    }
-    // coalesced copy of the wave's contiguous output
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    wave_store_staged(reinterpret_cast<uint32_t *>(wave_out), st, cs.wave_total >> 2, lane);
 }
 
 // Thread 0 takes the next ticket and broadcasts it.  Consecutive calls use
@@ -1239,6 +1190,58 @@ __device__ __forceinline__ ChunkState naive_select(const CompressArgs &a, const 
     return cs;
 }
 
+// Steps 4-5 of one chunk whose rate pass is done: wait for the chunk's output
+// offset (decoupled lookback, Sec. IV-D), then the sign / bit-plane encoding
+// (Sec. IV-C) through the wave's LDS staging area.  B holds the LZ1 residuals.
+__device__ __forceinline__ void naive_encode(const CompressArgs &a, const Resolved &R, const ChunkState &cs,
+                                             int (&B)[32], CompressShared<kWaves> &sh, uint32_t *st)
+{
+    const int tid = threadIdx.x;
+    const int w = tid >> 6;
+    const int lane = tid & 63;
+    const int j = lane & 7;
+    uint32_t chunk_total = 0, wave_base = 0;
+#pragma unroll
+    for (int k = 0; k < kWaves; k++) {
+        if (k < w) wave_base += sh.wave_total[0][k];
+        chunk_total += sh.wave_total[0][k];
+    }
+    if (w == 0) {
+        const Prefix pre = lookback_wait(a.flags, cs.chunk, a.flag_epoch, chunk_total, false);
+        if (lane == 0) {
+            sh.base[0] = pre.excl;
+            if (cs.chunk == a.nchunks - 1) finish_stream(a, R, pre, chunk_total);
+        }
+    }
+    lds_barrier();
+    const uint64_t base = sh.base[0];
+    const uint64_t tile0 = cs.chunk * kTilesPerChunk + (uint64_t)w * kTilesPerWave;
+    if (a.data0 + base + chunk_total > a.capacity || tile0 >= a.ntiles) return;
+
+    uint8_t *wave_out = a.out + a.data0 + base + wave_base;
+    if (cs.vm != 0 && j == 0 && cs.cent) st[cs.tile_excl >> 2] = (uint32_t)cs.mu;
+    block_codes(B, cs.carry_l1, j, cs.order2, cs.cent, cs.mu);
+    // valid slots in stored bit order (element i at bit i ^ 7)
+    const uint32_t keep = __builtin_bswap32(__builtin_bitreverse32(cs.vm));
+    const uint32_t nwords = cs.r ? cs.r + 1 : 0;  // sign word + r planes
+    uint32_t *words = st + (cs.blk_off >> 2);
+    for (uint32_t g = 0; __ballot(8 * g < nwords) != 0; g++) {
+        uint32_t Rg[8];
+#pragma unroll
+        for (int rho = 0; rho < 8; rho++)
+            Rg[rho] = pack_byte_g((uint32_t)B[7 - rho], (uint32_t)B[15 - rho], (uint32_t)B[23 - rho],
+                                  (uint32_t)B[31 - rho], g);
+        transpose8(Rg);
+#pragma unroll
+        for (int p = 0; p < 8; p++)
+            if (8 * g + p < nwords) words[8 * g + p] = Rg[p] & keep;
+    }
+    // coalesced copy of the wave's contiguous output
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wave_store_staged(reinterpret_cast<uint32_t *>(wave_out), st, cs.wave_total >> 2, lane);
+}
+
 // Encode pass: one chunk per workgroup from the ticket counter (the fifth
 // read of the input), the tables' choice, lookback, the single pass's encoder.
 template <bool ALIGNED>
@@ -1272,7 +1275,7 @@ __global__ __launch_bounds__(kThreads) void naive_encode_kernel(CompressArgs a, 
         for (int i = 0; i < 32; i++) x[i] = __float_as_int(f[i]);
     }
     const ChunkState cs = naive_select(a, R, t, chunk, x, sh);
-    compress_encode<kWaves>(a, R, cs, x, 0, sh, st);
+    naive_encode(a, R, cs, x, sh, st);
 }
 
 // ------------------------------------------------------------------ pipelined compress
@@ -1532,7 +1535,7 @@ struct TileB32T8 {
     static __device__ __forceinline__ ChunkState rates(const CompressArgs &a, const Resolved &R, uint64_t chunk,
                                                        int (&x)[32], int slot, CompressShared<W> &sh)
     {
-        return compress_rates<W, true, FEAT>(a, R, chunk, x, slot, sh);
+        return compress_rates<W, FEAT>(a, R, chunk, x, slot, sh);
     }
     template <bool FEAT>
     static __device__ __forceinline__ void stage(const ChunkState &cs, int (&B)[32], uint32_t *st)
@@ -1628,11 +1631,11 @@ __device__ __forceinline__ uint64_t pipe2_step(const CompressArgs &a, const Reso
 // per thread; a launch of its own for that took 4.6 us on large fields and 2 us
 // on small ones).  The partials' loads go out first, so neither the ticket's
 // round trip nor the chunk's copy waits on them.  A field of one chunk needs no
-// range pass (a.self_range): its workgroup takes the range from the copy in
+// range pass (SELF, a.self_range): its workgroup takes the range from the copy in
 // LDS.  False: no chunk is left, or
 // the bound does not resolve (the tickets are then handed out without data
 // work, and the last chunk's taker reports).
-template <int THREADS, int W>
+template <int THREADS, int W, bool SELF = false>
 __device__ __forceinline__ bool pipe_start(const CompressArgs &a, CompressShared<W> &sh, uint32_t *qb, int w,
                                            Resolved &R, uint64_t &A, int &tslot)
 {
@@ -1646,7 +1649,7 @@ __device__ __forceinline__ bool pipe_start(const CompressArgs &a, CompressShared
     if (A >= N) return false;
     if (w < W) chunk_fetch<W>(a, A, qb, w, threadIdx.x & 63);
     fsz_stats s;
-    if (a.self_range) {
+    if (SELF && a.self_range) {
         RangeAcc acc;
         if (w < W) {
             const int lane = threadIdx.x & 63;
@@ -1790,7 +1793,7 @@ __global__ __launch_bounds__((WD + 1) * 64) void compress_ctrl_kernel(CompressAr
     Resolved R;
     uint64_t A;
     int tslot;
-    if (!pipe_start<(WD + 1) * 64, WD>(a, sh, inbuf + w * kPipeInDwords, w, R, A, tslot)) return;
+    if (!pipe_start<(WD + 1) * 64, WD, WD * kWaveElems <= kSelfRangeMax>(a, sh, inbuf + w * kPipeInDwords, w, R, A, tslot)) return;
     if (w < WD)
         pipe2_run<false, WD, false>(a, R, sh, inbuf + w * kPipeInDwords, stbuf + w * kPipeOutDwords, w, A, tslot);
     else
@@ -2720,7 +2723,7 @@ __device__ __forceinline__ void batch_fetch(const BatchArgs &b, const BItem &it,
     chunk_fetch<W>(batch_compress_args(b, it.job), it.c, qb, w, lane);
 }
 
-// Rate pass of item B (as compress_rates with DEFER), or an empty state and
+// Rate pass of item B (as compress_rates), or an empty state and
 // the same barrier for an item whose job has no valid bound.
 template <int W>
 __device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const BItem &it,
@@ -2728,7 +2731,7 @@ __device__ __forceinline__ ChunkState batch_rates(const BatchArgs &b, const BIte
 {
     const Resolved R = job_bound(b, it.job);
     if (R.status == FSZ_OK) {
-        ChunkState cs = compress_rates<W, true>(batch_compress_args(b, it.job), R, it.c, x, slot, sh);
+        ChunkState cs = compress_rates<W>(batch_compress_args(b, it.job), R, it.c, x, slot, sh);
         cs.chunk = it.c;
         return cs;
     }
@@ -3065,7 +3068,7 @@ __device__ __forceinline__ ChunkState cfg_rates(const CompressArgs &a, const Res
     cs.blk_off = cs.tile_excl + 4u * (uint32_t)cs.cent + pre - (uint32_t)h * S + 4u * (uint32_t)h;
     if (lane == 0) sh.wave_total[slot][w] = cs.wave_total;
     lds_barrier();
-    if (tid == (W > 1 ? 64 : 0)) {
+    if (tid == 64) {
         uint32_t chunk_total = 0;
 #pragma unroll
         for (int k = 0; k < W; k++) chunk_total += sh.wave_total[slot][k];
@@ -3378,7 +3381,7 @@ static unsigned persistent_grid(K kernel, uint64_t nchunks, int threads = kThrea
 }
 
 // Enqueues the offsets pre-pass for chunks of TPC tiles and names its results
-// in a: `words` holds kMaxGroups group totals, then an offset per chunk.
+// in a: `words` holds kMaxGroupWords group totals, then an offset per chunk.
 template <int TPC, int T = kBlocksPerTile, int HB = 1>
 static hipError_t launch_dec_groups(DecompressArgs &a, unsigned long long *words, bool scan, hipStream_t s)
 {
