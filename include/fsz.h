@@ -14,7 +14,7 @@
  *     tensor's data pointer) on the current HIP device.  The caller owns
  *     them; the library never frees or retains them after the call.
  *   - d_in / d_out float arrays need 4-byte alignment; 16-byte aligned ones
- *     are a little faster (compression 0-7%).  Compressed buffers need 4-byte alignment.
+ *     are a little faster (compression 0-8%).  Compressed buffers need 4-byte alignment.
  *   - `stream` is a hipStream_t (NULL = the default stream).  Calls that
  *     return a size block the host until the stream has executed them.
  *     Calls on the same stream are ordered; the library keeps one
@@ -116,7 +116,8 @@ fsz_status fsz_compress_ex(const float *d_in, size_t n, fsz_eb_mode mode, double
                            size_t *out_size, void *stream);
 
 /* Decompress a stream of cmp_size bytes into d_out[0..n) (Sec. III-A,
- * decompression steps 1-5, in one kernel).  n must equal the stream's
+ * decompression steps 1-5, in one kernel, from about 4.4 M elements behind a
+ * small one that finds the chunks' offsets).  n must equal the stream's
  * element count (else FSZ_ERR_SIZE_MISMATCH).  Corrupt streams return
  * FSZ_ERR_CORRUPT; d_out contents are then unspecified.  Blocks until the
  * stream finished. */
@@ -131,7 +132,8 @@ fsz_status fsz_decompress(const void *d_cmp, size_t cmp_size, float *d_out, size
  * is read back to the host, so these calls can be chained on a stream and
  * issued from a tight loop.  fsz_compress_async runs the value-range pass
  * first when d_stats is NULL, otherwise it reuses *d_stats.  Each call is
- * one kernel launch (two with the range pass of a field above 16384 elements). */
+ * one kernel launch; two with the range pass of a field above 16384 elements,
+ * and for decompression from about 4.4 M elements. */
 fsz_status fsz_compress_async(const float *d_in, size_t n, fsz_eb_mode mode, double value,
                               const fsz_stats *d_stats, void *d_out, size_t out_capacity,
                               fsz_result *d_result, void *stream);

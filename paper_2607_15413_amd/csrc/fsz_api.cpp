@@ -1,5 +1,5 @@
 // C ABI of libfsz.so: argument validation, per-(device, stream) workspace,
-// kernel launches and the single device->host status read per call.
+// kernel launches, and the outcome of blocking calls from pinned memory.
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -462,7 +462,7 @@ struct BatchLayout {
 // its jobs: wide workgroups once there are enough items for the chip, narrow
 // ones where the spread counts (us per call: 0.1 M elements in 2 jobs with 4
 // waves 26, with 8 28; 3.0 M in 8 33.5 and 33.2; 7.0 M in 32 47 and 43, with 10
-// 43; 125 M in 64 with 8 266, with 10 252).
+// 43; 125 M in 64 with 8 266, with 10 252, with 11 222).
 int compress_batch_waves(uint64_t elems) { return elems >= (1ull << 23) ? 11 : elems >= (1ull << 21) ? 8 : 4; }
 
 // Validates every job (nothing is enqueued unless all pass) and lays out

@@ -2881,7 +2881,7 @@ __device__ __forceinline__ void batch_ctrl_run(const BatchArgs &b, const uint64_
 // W data waves (8 tiles each per item) and a control wave, one workgroup per
 // CU (compress_batch_waves).  LDSJOBS (njobs <= kPipeLdsJobs): the jobs' chunk
 // ends are copied to LDS at the start for the control wave's searches.  64
-// fields of 125 M elements: 222 us per call with the range pass, where groups of 4
+// fields of 125 M elements: 219 us per call with the range pass, where groups of 4
 // waves whose wave 0 walked the lookback beside its data took 309 and such
 // groups of 8 waves 266.
 constexpr uint32_t kPipeLdsJobs = 512;
@@ -3606,7 +3606,8 @@ static hipError_t launch_decompress_cfg_prescan_t(const DecompressArgs &a, unsig
     // From 2^26 elements on a small launch turns the group totals into running
     // sums, so that no workgroup adds them up (512^3 from a cold cache, REL 1e-3,
     // 32/4 138 against 156 us, 64/16 147 / 157; 25 M elements 37.3 / 37.0, 40.9 /
-    // 40.7).
+    // 40.7).  That brings large fields back to where a pre-pass with tickets and
+    // a lookback over the totals had them (135 us), which cost smaller ones more.
     const hipError_t e = launch_dec_groups<kCfgDecChunkSegs / L, L / HB, HB>(p, words, a.n >= (1ull << 26), s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decompress_cfg_kernel<ALIGNED, HB, L, true>), dim3((unsigned)a.nchunks),
