@@ -3354,11 +3354,26 @@ __global__ __launch_bounds__(WV * 64) void decompress_cfg_kernel(DecompressArgs 
             }
         }
     } else {
-#pragma unroll 8
-        for (int k = 0; k < 32; k++) {
-            const int p = k * 64 + lane;
-            const uint64_t e = w0 + p;
-            if (fullw || e < a.n) a.out[e] = __uint_as_float(st[(p >> 5) * kStageRowDwords + (p & 31)]);
+        // 16-byte stores between the output's 16-byte boundaries, the elements
+        // before the first and after the last one singly.  32 stores of 4 bytes
+        // kept the workgroup's end waiting for their issue, and every addition
+        // before them showed: 512^3 at offset 1, us per call, 32/4 150 with a
+        // ticketed pre-pass, 164 with the group totals, 119 with these stores (115
+        // aligned); 64/16 158, 173 and 125 (121).
+        const uint32_t cnt = fullw ? 2048u : (uint32_t)(a.n - w0);
+        const uint32_t head = min(align_head(a.out), cnt), nq = (cnt - head) / 4;  // w0 is a multiple of 2048
+        const uint32_t tail = head + 4 * nq;
+        g_f32 *out = (g_f32 *)a.out + w0;
+        auto staged = [&](uint32_t p) { return __uint_as_float(st[(p >> 5) * kStageRowDwords + (p & 31)]); };
+        if ((uint32_t)lane < head) out[lane] = staged(lane);
+        if ((uint32_t)lane < cnt - tail) out[tail + lane] = staged(tail + lane);
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const uint32_t q = k * 64 + lane, p = head + 4 * q;
+            if (q < nq) {
+                const f4 f = {staged(p), staged(p + 1), staged(p + 2), staged(p + 3)};
+                __builtin_nontemporal_store(f, (g_f4 *)(out + p));
+            }
         }
     }
 }

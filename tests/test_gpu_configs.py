@@ -484,3 +484,22 @@ def test_config_decode_offsets_at_scan_edge(n):
             assert fsz.read_result(res)[1] == want
             if bad_block is None:
                 assert np.array_equal(y.cpu().numpy().view(np.uint32), y_ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("config", [(32, 4), (32, 16), (64, 8), (64, 16)])
+@pytest.mark.parametrize("out_offset", [0, 1, 2, 3])
+def test_config_decode_output_phases(config, out_offset):
+    """Outputs at every 4-byte phase of a 16-byte line, at the edges of a
+    thread's 16 bytes, a wave's 2048 elements and a chunk, in the lookback and
+    the pre-pass form: each element once and nothing outside."""
+    base = workloads.sinusoid_field((1 << 23) + 5, 27)
+    old = oracle.set_threads(8)
+    try:
+        for n in (1, 2, 3, 4, 5, 2047, 2048, 2049, 2051, 8191, 8193, 12_346, (1 << 23) + 1, (1 << 23) + 4):
+            announce(f"config {config}, n={n}, output at word {out_offset}")
+            s = oracle.compress(base[:n], oracle.ABS, 1e-3, config=config)
+            st, y = gpu_decompress_config(s, n, config, out_offset=out_offset)
+            assert st == fsz.FSZ_OK
+            assert np.array_equal(y.view(np.uint32), oracle.decompress(s, n).view(np.uint32)), n
+    finally:
+        oracle.set_threads(old)
